@@ -212,7 +212,9 @@ int nbody_kick_drift(void *pos_mass, void *vel, const void *acc_pot, int64_t n, 
  * (offsets_host as above) in one persistent launch over a longest-first
  * work list of (system, target tile) units.  eps_per_sys: device float[nsys]
  * or NULL to use `eps` for all.  Each system's result is bitwise the result
- * of nbody_accel on that system alone with the same tuning.
+ * of nbody_accel on that system alone with the same tuning: the batch's shape
+ * pinned for nbody_accel too (nbody_set_tuning; unpinned, nbody_accel chooses
+ * a shape, and for a few thousand bodies a kernel, for one system alone).
  */
 int nbody_batched_accel(const void *pos_mass, const int64_t *offsets_host, int32_t nsys,
                         int32_t prec, double G, const float *eps_per_sys, double eps,

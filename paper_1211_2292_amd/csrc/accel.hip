@@ -412,6 +412,141 @@ __global__ __launch_bounds__(kBlock) void k_accel_f64(const double4 *__restrict_
     }
 }
 
+// ---- small problems: sources over the lanes and waves of one workgroup ---------
+// A few thousand bodies are too few targets for 64 per wave to reach all 256
+// CUs, and a source split costs a second launch.  Here a workgroup of 1024
+// threads takes kSliceT targets and kSlices slices of the sources (slice s
+// takes sources s, s + kSlices, ...), which it stages in LDS in chunks; a wave
+// holds 64 / kSliceT slices, whose lanes read neighbouring records.  The
+// slices' sums meet in LDS in a fixed order, so an evaluation is one launch:
+// at 4096 FP64 bodies 256 workgroups, one per CU.  Only the steps that meet
+// the workgroup's own targets run the masked pair.  FP32 partial sums hold at
+// most 32 sources and are added in FP64 in every mode.  What bounds it: up to
+// about 4000 FP32 bodies the call itself (12.5 us from Python); above, the
+// pair arithmetic at 4 to 8 waves per SIMD.
+constexpr int kSliceThreads = 1024;
+constexpr int kSliceT = 16;
+constexpr int kSlices = kSliceThreads / kSliceT;
+
+template <typename T>
+struct SliceRec;
+template <>
+struct SliceRec<float> {
+    using V = float4;
+    static constexpr int kChunk = 2048;
+};
+template <>
+struct SliceRec<double> {
+    using V = double4;
+    static constexpr int kChunk = 1024;
+};
+
+template <bool MASK>
+__device__ __forceinline__ void slice_pair(const float4 b, int j, const Targets<float, 1> &T, float eps2,
+                                           Sums<float, 1> &S)
+{
+    pair_f32<1, MASK>(b, j, T, eps2, S);
+}
+template <bool MASK>
+__device__ __forceinline__ void slice_pair(const double4 b, int j, const Targets<double, 1> &T, double eps2,
+                                           Sums<double, 1> &S)
+{
+    pair_f64<1, MASK>(b, j, T, eps2, S);
+}
+
+// Steps [k0, k1) of slice sl over the chunk that starts at source c0.
+template <bool MASK, typename T, typename V>
+__device__ __forceinline__ void slice_sweep(const V *buf, int c0, int sl, int k0, int k1, const Targets<T, 1> &TT,
+                                            T eps2, Sums<T, 1> &S)
+{
+    constexpr int U = 4;
+    int k = k0;
+    for (; k + U <= k1; k += U) {
+        V b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) b[u] = buf[kSlices * (k + u) + sl];
+#pragma unroll
+        for (int u = 0; u < U; ++u) slice_pair<MASK>(b[u], c0 + kSlices * (k + u) + sl, TT, eps2, S);
+    }
+    for (; k < k1; ++k) slice_pair<MASK>(buf[kSlices * k + sl], c0 + kSlices * k + sl, TT, eps2, S);
+}
+
+template <typename T, int MODE>
+__global__ __launch_bounds__(kSliceThreads) void k_accel_slice(const typename SliceRec<T>::V *__restrict__ src, int n,
+                                                              T eps2_in, double G, int tbeg, int tcount,
+                                                              typename SliceRec<T>::V *__restrict__ out)
+{
+    using V = typename SliceRec<T>::V;
+    constexpr int C = SliceRec<T>::kChunk;
+    static_assert(C % kSlices == 0 && sizeof(V) * C >= sizeof(double) * 4 * kSliceThreads, "the sums reuse the chunk");
+    __shared__ V buf[C];
+    const int tid = threadIdx.x, tg = tid % kSliceT, sl = tid / kSliceT;
+    const int t0 = tbeg + blockIdx.x * kSliceT, i = t0 + tg;
+    T eps2;
+    if constexpr (sizeof(T) == 4)
+        eps2 = lane_copy(eps2_in);
+    else
+        eps2 = eps2_in;
+    Targets<T, 1> TT;
+    {
+        const V p = src[min(i, n - 1)];
+        TT.x[0] = p.x;
+        TT.y[0] = p.y;
+        TT.z[0] = p.z;
+        TT.i[0] = i;
+    }
+    double R[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int c0 = 0; c0 < n; c0 += C) {
+        const int cnt = min(C, n - c0);
+        __syncthreads();
+        for (int k = tid; k < cnt; k += kSliceThreads) buf[k] = src[c0 + k];
+        __syncthreads();
+        Sums<T, 1> S;
+        S.zero();
+        const int kf = cnt / kSlices;  // steps that every slice has
+        // steps that meet targets [t0, t0 + kSliceT)
+        const int lo = min(max(t0 - c0, 0) / kSlices, kf);
+        const int hi = min((max(t0 + kSliceT - c0, 0) + kSlices - 1) / kSlices, kf);
+        slice_sweep<false>(buf, c0, sl, 0, lo, TT, eps2, S);
+        slice_sweep<true>(buf, c0, sl, lo, hi, TT, eps2, S);
+        slice_sweep<false>(buf, c0, sl, hi, kf, TT, eps2, S);
+        if (kSlices * kf + sl < cnt) slice_sweep<true>(buf, c0, sl, kf, kf + 1, TT, eps2, S);
+        R[0] += S.ax[0];
+        R[1] += S.ay[0];
+        R[2] += S.az[0];
+        R[3] += S.ph[0];
+    }
+    // Sum over the slices: red[slice][4][target], one (component, target) and
+    // kPart slices per thread, then the parts in order.
+    constexpr int kOut = 4 * kSliceT, kParts = kSliceThreads / kOut, kPart = kSlices / kParts;
+    double *red = reinterpret_cast<double *>(buf);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) red[(sl * 4 + c) * kSliceT + tg] = R[c];
+    __syncthreads();
+    const int o = tid % kOut, part = tid / kOut;
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < kPart; ++q) v += red[(part * kPart + q) * kOut + o];
+    __syncthreads();
+    red[part * kOut + o] = v;
+    __syncthreads();
+    if (tid < kSliceT && i < tbeg + tcount) {
+        double r[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            double w = 0.0;
+#pragma unroll
+            for (int q = 0; q < kParts; ++q) w += red[q * kOut + c * kSliceT + tg];
+            r[c] = w;
+        }
+        if constexpr (MODE == M_F32)
+            put_f32(out, i - tbeg, r, (float)G);
+        else
+            put(out, i - tbeg, r, G);
+    }
+}
+
 // Fixed-order reduction of the per-split records.
 template <typename OUT>
 __global__ __launch_bounds__(kBlock) void k_split_reduce(const double4 *__restrict__ partial,
@@ -628,6 +763,7 @@ bool tune_valid(const Tune &t)
 
 size_t accel_partial_bytes(int prec, int tcount, const Tune &t)
 {
+    if (t.path == kPathSlice) return 0;
     if (t.jsplit <= 1) return 0;
     const size_t rec = (prec == NBODY_F32) ? sizeof(float4) : sizeof(double4);
     return rec * (size_t)t.jsplit * (size_t)tcount;
@@ -635,9 +771,28 @@ size_t accel_partial_bytes(int prec, int tcount, const Tune &t)
 
 static float eps2_f32(double eps) { return (float)((double)eps * (double)eps); }
 
+namespace {
+hipError_t go_slice(int prec, const void *pm, int n, double G, double eps, void *out, int tbeg, int tcount,
+                    hipStream_t s)
+{
+    const dim3 grid((tcount + kSliceT - 1) / kSliceT), blk(kSliceThreads);
+    if (prec == NBODY_F64)
+        hipLaunchKernelGGL((k_accel_slice<double, M_F64ACC>), grid, blk, 0, s, (const double4 *)pm, n, eps * eps, G,
+                           tbeg, tcount, (double4 *)out);
+    else if (prec == NBODY_F32)
+        hipLaunchKernelGGL((k_accel_slice<float, M_F32>), grid, blk, 0, s, (const float4 *)pm, n, eps2_f32(eps), G,
+                           tbeg, tcount, (float4 *)out);
+    else
+        hipLaunchKernelGGL((k_accel_slice<float, M_F64ACC>), grid, blk, 0, s, (const float4 *)pm, n, eps2_f32(eps), G,
+                           tbeg, tcount, (float4 *)out);
+    return hipGetLastError();
+}
+}  // namespace
+
 hipError_t launch_accel(int prec, const void *pm, int n, double G, double eps, void *out, int tbeg,
                         int tcount, const Tune &t, void *partial, hipStream_t s, bool reduce)
 {
+    if (t.path == kPathSlice) return go_slice(prec, pm, n, G, eps, out, tbeg, tcount, s);
     if (prec == NBODY_F64) {
         const double4 *p = (const double4 *)pm;
         double4 *o = (double4 *)out;

@@ -24,7 +24,11 @@ struct Tune {
     int jsplit = 1;
     int jtile = 512;
     int variant = 0;
+    // Which force kernels run the shape: the sweep above (every pinned or
+    // measured shape), or one of the library's own choices for a whole call.
+    int path = 0;
 };
+enum { kPathSweep = 0, kPathSlice = 1 };
 
 constexpr int kBlock = 256;  // threads per workgroup: four independent waves
 constexpr int kUnroll = 8;   // sources per unrolled step of the sweep

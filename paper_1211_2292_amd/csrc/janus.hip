@@ -148,6 +148,7 @@ Tune janus_tune(const Tune &vjp_default)
     Tune t = vjp_default;
     t.tpl = 1;
     t.variant = 0;
+    t.path = kPathSweep;
     return t;
 }
 

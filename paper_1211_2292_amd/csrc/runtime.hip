@@ -259,6 +259,14 @@ static void save_cache_locked()
     rename(tmp.c_str(), path);
 }
 
+// Sources up to which a whole call runs the one-launch slice kernel.  Measured
+// against the split sweep and its reduction (us per call, both sides):
+// FP32 300: 14.3 / 12.6, 1000: 25.5 / 12.7, 4096: 16.4 / 12.7, 8192: 28.6 /
+// 24.3; above 8192 the workgroups no longer fit the chip at once (10007: 42.0
+// / 42.1).  FP64 300: 19.8 / 12.5, 2000: 34.9 / 12.6, 4096: 21.4 / 17.5; above
+// 4096 the sweep is as fast or faster (5003: 39.4 / 39.1, 8000: 56 / 61).
+constexpr int64_t kSliceMaxF32 = 8192, kSliceMaxF64 = 4096;
+
 // Heuristic shape from measured sweeps on MI355X (force kernel, FP32 modes).
 // n sources, ntarg targets (fewer than n for a target range, e.g. one GPU's
 // share of the targets).
@@ -287,6 +295,7 @@ static Tune default_tune(int kernel, int prec, int64_t n, int64_t ntarg)
     // 256 sources and the FP64 split records stay within 1 GiB.
     if (kernel == 0 && js < 8 && n / 8 >= 256 && ntarg * 8 * 32 <= ((int64_t)1 << 30)) js = 8;
     t.jsplit = js;
+    if (kernel == 0 && n <= (prec == NBODY_F64 ? kSliceMaxF64 : kSliceMaxF32)) t.path = kPathSlice;
     return t;
 }
 
@@ -784,7 +793,7 @@ int nbody_leapfrog_kdk(void *pos_mass, void *vel, void *acc_pot, int64_t n,
     {
         Tune t = lookup_tune(0, prec, n), bt = lookup_tune(1, prec, n);
         key.v.insert(key.v.end(), {(uint64_t)t.tpl, (uint64_t)t.jsplit, (uint64_t)t.jtile,
-                                   (uint64_t)t.variant, (uint64_t)bt.tpl, (uint64_t)bt.jtile});
+                                   (uint64_t)t.variant, (uint64_t)t.path, (uint64_t)bt.tpl, (uint64_t)bt.jtile});
     }
     GraphEntry *ge = nullptr;
     {

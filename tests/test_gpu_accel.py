@@ -334,3 +334,25 @@ def test_scratch_growth_does_not_wait():
     finally:
         nb.set_tuning(0, mode)
         nb.release()
+
+
+@pytest.mark.parametrize("n,tb,tc", [(2, 0, 2), (15, 0, 15), (16, 0, 16), (17, 0, 17), (65, 0, 65), (1023, 0, 1023),
+                                     (1025, 0, 1025), (2047, 0, 2047), (2049, 0, 2049), (2113, 2040, 73),
+                                     (4096, 0, 4096), (4097, 4090, 7), (8192, 0, 8192), (8193, 0, 8193)])
+@pytest.mark.parametrize("mode", ["F64"] + MODES32)
+def test_small_problem_kernel_edges(orc, mode, n, tb, tc):
+    """Sizes at the edges of the small-problem kernel's target blocks (16),
+    slices (64), LDS chunks (1024 and 2048 records) and range (4096 bodies in
+    FP64, 8192 in FP32), unequal masses, and target ranges across a chunk
+    edge.  Bars as for the other ragged sizes: FP32 pair terms carry a few
+    2^-24 of relative error each and are summed over at most 32 sources."""
+    torch, nb = gpu()
+    pm, _ = ics.plummer(n, 4000 + n)
+    pm[:, 3] *= np.linspace(0.5, 1.5, n)
+    dtype = torch.float64 if mode == "F64" else torch.float32
+    src = pm if mode == "F64" else widen32(pm)
+    out = _run(nb, torch, src, 0.02, mode, dtype, target_begin=tb, target_count=tc)
+    k = ics.sample_targets(tc, min(tc, 700), n)
+    acc, pot = orc.accel(src, 0.02, targets=tb + k)
+    bar = 1e-12 if mode == "F64" else 2e-6
+    assert rms_rel(out[k, :3], acc) <= bar and rms_rel(out[k, 3], pot) <= bar
