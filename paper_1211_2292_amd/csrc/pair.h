@@ -72,7 +72,7 @@ __device__ __forceinline__ void pair_f32(const float4 b, const int j, const Targ
         const float dy = b.y - T.y[t];
         const float dz = b.z - T.z[t];
         const float r2 = __builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, __builtin_fmaf(dx, dx, eps2)));
-        float rho = __builtin_amdgcn_rsqf(r2);
+        float rho = rsq_prio(r2);
         if (MASK) rho = (j == T.i[t]) ? 0.0f : rho;
         const float mr = b.w * rho;
         const float s = mr * (rho * rho);

@@ -68,7 +68,7 @@ __device__ __forceinline__ T rsq_t(T q);
 template <>
 __device__ __forceinline__ float rsq_t<float>(float q)
 {
-    return __builtin_amdgcn_rsqf(q);
+    return rsq_prio(q);
 }
 template <>
 __device__ __forceinline__ double rsq_t<double>(double q)
