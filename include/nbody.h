@@ -129,6 +129,12 @@ int nbody_permute(const void *src, void *dst, const int32_t *perm, int64_t n,
  * acc_pot_out: target_count records, entry t for target target_begin + t;
  * it must not overlap pos_mass.  Deterministic: the same inputs and tuning
  * give bitwise the same output.
+ * Unless a shape is pinned (nbody_set_tuning), all of 45056 to 2^24 bodies as
+ * targets in an FP32 mode evaluate every unordered pair once and add the sums
+ * across tiles in FP64 in every mode; this takes up to 1 GiB of library
+ * scratch (where that cannot be allocated, the split sweep runs instead), and
+ * the record of a target then differs from its record in a call for fewer
+ * targets within the mode's error bound, not bit for bit.
  */
 int nbody_accel(const void *pos_mass, int64_t n, int32_t prec, double G, double eps,
                 void *acc_pot_out, int64_t target_begin, int64_t target_count, void *stream);
@@ -145,9 +151,9 @@ int nbody_accel(const void *pos_mass, int64_t n, int32_t prec, double G, double 
  *   - If the partials of nbody_accel's shape fit, the same shape runs and the
  *     result equals nbody_accel's bit for bit.
  *   - If they do not fit and the shape was chosen by the library (default or
- *     autotuned), the split count is halved until they fit (one split needs
- *     no scratch): the partial sums are then grouped differently, within the
- *     same error bound.
+ *     autotuned), the split sweep runs, its split count halved until they fit
+ *     (one split needs no scratch): the partial sums are then grouped
+ *     differently, within the same error bound.
  *   - If they do not fit and the shape was pinned with nbody_set_tuning, the
  *     call returns NBODY_E_INVAL before anything is enqueued, with the sizes
  *     in nbody_last_error().

@@ -761,12 +761,17 @@ bool tune_valid(const Tune &t)
            (t.variant == 0 || (t.variant == 1 && t.jtile % kLdsTile == 0));
 }
 
-size_t accel_partial_bytes(int prec, int tcount, const Tune &t)
+int accel_partial_records(int tcount, const Tune &t)
 {
     if (t.path == kPathSlice) return 0;
-    if (t.jsplit <= 1) return 0;
-    const size_t rec = (prec == NBODY_F32) ? sizeof(float4) : sizeof(double4);
-    return rec * (size_t)t.jsplit * (size_t)tcount;
+    if (t.path == kPathSym) return sym_plan(tcount).slots();
+    return t.jsplit > 1 ? t.jsplit : 0;
+}
+
+size_t accel_partial_bytes(int prec, int tcount, const Tune &t)
+{
+    const size_t rec = (prec == NBODY_F32 && t.path == kPathSweep) ? sizeof(float4) : sizeof(double4);
+    return rec * (size_t)accel_partial_records(tcount, t) * (size_t)tcount;
 }
 
 static float eps2_f32(double eps) { return (float)((double)eps * (double)eps); }
@@ -793,6 +798,13 @@ hipError_t launch_accel(int prec, const void *pm, int n, double G, double eps, v
                         int tcount, const Tune &t, void *partial, hipStream_t s, bool reduce)
 {
     if (t.path == kPathSlice) return go_slice(prec, pm, n, G, eps, out, tbeg, tcount, s);
+    if (t.path == kPathSym) {  // all bodies
+        const hipError_t e = launch_sym(pm, n, eps, partial, s);
+        if (e != hipSuccess || !reduce) return e;
+        hipLaunchKernelGGL(k_split_reduce<float4>, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
+                           (const double4 *)partial, accel_partial_records(n, t), n, G, (float4 *)out);
+        return hipGetLastError();
+    }
     if (prec == NBODY_F64) {
         const double4 *p = (const double4 *)pm;
         double4 *o = (double4 *)out;

@@ -28,7 +28,7 @@ struct Tune {
     // measured shape), or one of the library's own choices for a whole call.
     int path = 0;
 };
-enum { kPathSweep = 0, kPathSlice = 1 };
+enum { kPathSweep = 0, kPathSlice = 1, kPathSym = 2 };
 
 constexpr int kBlock = 256;  // threads per workgroup: four independent waves
 constexpr int kUnroll = 8;   // sources per unrolled step of the sweep
@@ -75,6 +75,20 @@ hipError_t launch_accel(int prec, const void *pm, int n, double G, double eps, v
                         int tbeg, int tcount, const Tune &t, void *partial, hipStream_t s,
                         bool reduce = true);
 size_t accel_partial_bytes(int prec, int tcount, const Tune &t);
+int accel_partial_records(int tcount, const Tune &t);
+
+// ---- force on all bodies, each unordered pair once (sym.hip) -----------------
+// M blocks; each launch takes `runs` runs of `len` block distances.  The sums
+// meet in `slots` = runs (1 + len) records per body, kSymScratch bytes at most
+// (two records per body if that is more), to be added per body in slot order.
+constexpr int kSymBlock = 1024;
+constexpr size_t kSymScratch = size_t(1) << 30;
+struct SymPlan {
+    int blocks = 0, len = 0, runs = 0, launches = 0;
+    int slots() const { return runs * (1 + len); }
+};
+SymPlan sym_plan(int n);
+hipError_t launch_sym(const void *pm, int n, double eps, void *slots, hipStream_t s);
 
 // Split partials of nbody_accel_noalloc: a file-scope device array in
 // accel.hip of kStaticScratchBytes.  static_split_scratch() returns its

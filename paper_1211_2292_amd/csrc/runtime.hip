@@ -267,6 +267,22 @@ static void save_cache_locked()
 // 4096 the sweep is as fast or faster (5003: 39.4 / 39.1, 8000: 56 / 61).
 constexpr int64_t kSliceMaxF32 = 8192, kSliceMaxF64 = 4096;
 
+// Bodies from which a force on all of them evaluates every unordered pair once
+// (sym.hip).  Its tiles of 1024 x 1024 bodies have to fill 256 CUs evenly: with
+// 44 blocks (990 tiles) it takes 454 us against 530 for the split sweep, with
+// 40 it was 5-9% slower.  65536 bodies: 927 / 1085 us, 2^18: 13.3 / 16.7 ms,
+// 2^20: 212.8 / 256.6 ms.  Above kSymMax its sums no longer fit kSymScratch.
+constexpr int64_t kSymMin = 44 * kSymBlock, kSymMax = int64_t(1) << 24;
+
+// Kernels of a call whose shape is not pinned.
+static int default_path(int kernel, int prec, int64_t n, int64_t ntarg)
+{
+    if (kernel != 0) return kPathSweep;
+    if (n <= (prec == NBODY_F64 ? kSliceMaxF64 : kSliceMaxF32)) return kPathSlice;
+    if (prec != NBODY_F64 && ntarg == n && n >= kSymMin && n <= kSymMax) return kPathSym;
+    return kPathSweep;
+}
+
 // Heuristic shape from measured sweeps on MI355X (force kernel, FP32 modes).
 // n sources, ntarg targets (fewer than n for a target range, e.g. one GPU's
 // share of the targets).
@@ -295,7 +311,7 @@ static Tune default_tune(int kernel, int prec, int64_t n, int64_t ntarg)
     // 256 sources and the FP64 split records stay within 1 GiB.
     if (kernel == 0 && js < 8 && n / 8 >= 256 && ntarg * 8 * 32 <= ((int64_t)1 << 30)) js = 8;
     t.jsplit = js;
-    if (kernel == 0 && n <= (prec == NBODY_F64 ? kSliceMaxF64 : kSliceMaxF32)) t.path = kPathSlice;
+    t.path = default_path(kernel, prec, n, ntarg);
     return t;
 }
 
@@ -306,27 +322,41 @@ static Tune lookup_tune(int kernel, int prec, int64_t n, int64_t ntarg = -1, boo
     auto p = g_pinned.find({kernel, prec});
     if (pinned) *pinned = p != g_pinned.end();
     if (p != g_pinned.end()) return p->second;
+    if (ntarg < 0) ntarg = n;
     auto it = g_tuned.find(TuneKey(kernel, prec, log2ceil(n)));
-    if (it != g_tuned.end()) return it->second;
-    return default_tune(kernel, prec, n, ntarg < 0 ? n : ntarg);
+    if (it == g_tuned.end()) return default_tune(kernel, prec, n, ntarg);
+    Tune t = it->second;  // a measured shape of the sweep, for the calls that run it
+    t.path = default_path(kernel, prec, n, ntarg);
+    return t;
 }
 
 // ---------------------------------------------------------------------------
 // Force dispatch shared by the entry points
 // ---------------------------------------------------------------------------
+// Scratch of one force evaluation (unless the caller has it already).  Where
+// the pairwise path's does not fit the device, the sweep runs instead.
+static int force_scratch(int prec, int tcount, Tune &t, void *&partial)
+{
+    size_t pb = accel_partial_bytes(prec, tcount, t);
+    if (!pb || partial) return NBODY_OK;
+    partial = scratch(kSlotPartial, pb);
+    if (!partial && t.path == kPathSym) {
+        t.path = kPathSweep;
+        pb = accel_partial_bytes(prec, tcount, t);
+        if (!pb) return NBODY_OK;
+        partial = scratch(kSlotPartial, pb);
+    }
+    if (partial) return NBODY_OK;
+    set_error("cannot allocate %zu bytes of split scratch", pb);
+    return NBODY_E_NOMEM;
+}
+
 static int force(int prec, const void *pm, int n, double G, double eps, void *out, int tbeg,
                  int tcount, hipStream_t s, void *partial_override = nullptr)
 {
     Tune t = lookup_tune(0, prec, n, tcount);
-    void *partial = nullptr;
-    const size_t pb = accel_partial_bytes(prec, tcount, t);
-    if (pb) {
-        partial = partial_override ? partial_override : scratch(kSlotPartial, pb);
-        if (!partial) {
-            set_error("cannot allocate %zu bytes of split scratch", pb);
-            return NBODY_E_NOMEM;
-        }
-    }
+    void *partial = partial_override;
+    NB_CHECK(force_scratch(prec, tcount, t, partial));
     NB_TRY(launch_accel(prec, pm, n, G, eps, out, tbeg, tcount, t, partial, s), "force kernel");
     return NBODY_OK;
 }
@@ -449,16 +479,14 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
     // scratch and the step pass reduces them itself (one launch fewer).
     auto eval_step = [&](bool step, bool close, bool open) -> int {
         if (!plan) {
-            const Tune t = lookup_tune(0, prec, n);
-            const size_t pb = accel_partial_bytes(prec, n, t);
-            if (pb && step) {
-                void *partial = buf.partial ? buf.partial : scratch(kSlotPartial, pb);
-                if (!partial) {
-                    set_error("cannot allocate %zu bytes of split scratch", pb);
-                    return NBODY_E_NOMEM;
-                }
+            Tune t = lookup_tune(0, prec, n);
+            void *partial = buf.partial;
+            NB_CHECK(force_scratch(prec, n, t, partial));
+            if (const int records = accel_partial_records(n, t); records && step) {
                 NB_TRY(launch_accel(prec, pm, n, G, eps, acc, 0, n, t, partial, s, false), "force kernel");
-                NB_TRY(launch_reduce_step(prec, partial, t.jsplit, G, pm, vel, acc, n, h, dt, close, open,
+                // the pairwise path keeps FP64 records in every mode
+                const int rprec = t.path == kPathSym ? NBODY_F32_F64ACC : prec;
+                NB_TRY(launch_reduce_step(rprec, partial, records, G, pm, vel, acc, n, h, dt, close, open,
                                           ep, &eb, s),
                        "reduce + step kernel");
                 return NBODY_OK;
@@ -578,6 +606,10 @@ int nbody_accel_noalloc(const void *pos_mass, int64_t n, int32_t prec, double G,
                   "bytes of split scratch, above the static buffer's %zu",
                   t.jsplit, (long long)target_count, pb, kStaticScratchBytes);
         return NBODY_E_INVAL;
+    }
+    if (pb > kStaticScratchBytes && t.path == kPathSym) {
+        t.path = kPathSweep;
+        pb = accel_partial_bytes(prec, (int)target_count, t);
     }
     while (pb > kStaticScratchBytes) {
         t.jsplit = t.jsplit / 2 > 1 ? t.jsplit / 2 : 1;

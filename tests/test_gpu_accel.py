@@ -356,3 +356,56 @@ def test_small_problem_kernel_edges(orc, mode, n, tb, tc):
     acc, pot = orc.accel(src, 0.02, targets=tb + k)
     bar = 1e-12 if mode == "F64" else 2e-6
     assert rms_rel(out[k, :3], acc) <= bar and rms_rel(out[k, 3], pot) <= bar
+
+
+# 44 blocks of 1024 is the smallest count the pairwise kernels take: full, one
+# body in the last block, one short of full, an odd count, and a size whose
+# sums take two launches (the slots of 2^18 + 1 bodies pass 1 GiB)
+@pytest.mark.parametrize("n", [45056, 45057, 46079, 47104, (1 << 18) + 1])
+@pytest.mark.parametrize("mode,eps", [("F32_KAHAN", 0.01), ("F32_F64ACC", 0.0), ("F32", 0.02)])
+def test_pairwise_kernel_edges(orc, mode, eps, n):
+    """Force on all bodies where every unordered pair is evaluated once, with
+    unequal masses, on targets at the block edges and random ones; eps = 0
+    takes the masked form of the last block.  Bars as for the sampled Plummer
+    sphere; the same call twice gives the same bits."""
+    torch, nb = gpu()
+    pm, _ = ics.plummer(n, 5000 + n % 997)
+    pm[:, 3] *= np.linspace(0.5, 1.5, n)
+    src = widen32(pm)
+    out = _run(nb, torch, src, eps, mode, torch.float32)
+    assert np.array_equal(out, _run(nb, torch, src, eps, mode, torch.float32))
+    tg = np.unique(np.concatenate([[0, 63, 64, 255, 256, 1023, 1024, n - 1025, n - 2, n - 1],
+                                   ics.sample_targets(n, 400, n)]))
+    acc, pot = orc.accel(src, eps, targets=tg)
+    bar = 1e-4 if mode == "F32" else 2e-6
+    assert rms_rel(out[tg, :3], acc) <= bar and rms_rel(out[tg, 3], pot) <= bar
+
+
+@pytest.mark.parametrize("n", [45056, 46081])
+def test_pairwise_kernel_leapfrog_and_graph(n):
+    """The fused reduction and step after the pairwise kernels: one call of
+    three steps equals force and kick_drift by hand, and graph replays equal
+    eager calls with other work in between."""
+    torch, nb = gpu()
+    pm, v = ics.plummer(n, 61)
+    prec, eps, dt = nb.F32_KAHAN, 0.01, 1e-3
+    p0, v0 = to_dev(torch, pm, torch.float32), to_dev(torch, v, torch.float32)
+    pe, ve, ae = p0.clone(), v0.clone(), torch.empty_like(p0)
+    nb.leapfrog_kdk(pe, ve, ae, eps, dt, 3, prec=prec)
+    ph, vh = p0.clone(), v0.clone()
+    ah = nb.accel(ph, eps, prec=prec)
+    for k in range(3):
+        nb.kick_drift(ph, vh, ah, dt / 2, dt, close=k > 0, open=True, prec=prec)
+        ah = nb.accel(ph, eps, prec=prec)
+    nb.kick_drift(ph, vh, ah, dt / 2, dt, close=True, open=False, prec=prec)
+    torch.cuda.synchronize()
+    assert torch.equal(pe, ph) and torch.equal(ve, vh) and torch.equal(ae, ah)
+    pg, vg, ag = p0.clone(), v0.clone(), torch.empty_like(p0)
+    for rep in range(3):
+        pg.copy_(p0)
+        vg.copy_(v0)
+        nb.leapfrog_kdk(pg, vg, ag, eps, dt, 3, prec=prec, graph=True)
+        torch.cuda.synchronize()
+        junk = nb.accel(p0, eps, prec=prec).sum()
+        assert torch.equal(pg, pe) and torch.equal(vg, ve) and torch.equal(ag, ae), rep
+        del junk
