@@ -216,7 +216,7 @@ int nbody_kick_drift(void *pos_mass, void *vel, const void *acc_pot, int64_t n, 
 /*
  * Force and potential of nsys independent systems stored back to back
  * (offsets_host as above) in one persistent launch over a longest-first
- * work list of (system, target tile) units.  eps_per_sys: device float[nsys]
+ * work list of (system, target block) units.  eps_per_sys: device float[nsys]
  * or NULL to use `eps` for all.  Each system's result is bitwise the result
  * of nbody_accel on that system alone with the same tuning: the batch's shape
  * pinned for nbody_accel too (nbody_set_tuning; unpinned, nbody_accel chooses

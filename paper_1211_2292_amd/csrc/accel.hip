@@ -584,95 +584,141 @@ __global__ __launch_bounds__(kBlock) void k_split_reduce_f32(const float4 *__res
 }
 
 // ---- batched persistent kernel -------------------------------------------------
-// Each wave pops (system, first target) units from a longest-first list with
-// one integer atomic; a unit is one wave's worth of targets of one system
-// swept over that system's sources with the same tiles as k_accel_f32 with
-// one split, so each system's result equals its standalone evaluation
-// bit for bit.  The wave that finishes last returns both counters to zero,
-// which keeps repeated launches and graph replays self-contained.
-template <int TPL, int MODE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_batched_f32(const float4 *__restrict__ pm,
-                                                        const int64_t *__restrict__ offsets,
-                                                        const int2 *__restrict__ units, int nunits,
-                                                        const float *__restrict__ eps_sys,
-                                                        float eps2_all, double G, int jtile,
-                                                        float4 *__restrict__ out,
-                                                        unsigned *__restrict__ counter)
+// Workgroups of 4 waves pop units from a longest-first list with one integer
+// atomic.  A unit is 256 TPL / q targets of one system, q waves to each 64
+// TPL targets: the q waves take the source tiles in turn, leave their FP32 (or
+// FP64) tile sums in LDS, and fold them in tile order into running sums kept
+// one component per wave.  The sums are those of k_accel_f32 with one split
+// over the same tiles, folded in the same order, so each system's result
+// equals its standalone evaluation bit for bit; but the longest system no
+// longer takes one wave's time for all its sources, which had bound batches
+// whose units all fit the chip at once: 128 systems of 256 to 8192 bodies ran
+// 655 us with one wave per 64 targets, 361 us now (the pairs
+// alone need about 290 at the force kernel's rate).  The workgroup that
+// finishes last returns both counters to zero, which keeps repeated launches
+// and graph replays self-contained.
+template <int TPL, bool SEQ>
+__device__ __forceinline__ void tile_sums(const float4 *__restrict__ src, int jc, int ce, int d0, int d1,
+                                          const Targets<float, TPL> &T, float eps2, Sums<float, TPL> &S)
 {
-    constexpr int WT = 64 * TPL;
-    const int lane = threadIdx.x & 63;
-    const unsigned nwaves = gridDim.x * (kBlock / 64);
-    for (;;) {
-        unsigned u = 0;
-        if (lane == 0) u = atomicAdd(&counter[0], 1u);
-        u = __builtin_amdgcn_readfirstlane(u);
-        if (u >= (unsigned)nunits) break;
-        const int2 w = units[u];
-        const int64_t base = offsets[w.x];
-        const int n = (int)(offsets[w.x + 1] - base);
-        const float4 *src = pm + base;
-        float eps2 = eps2_all;
-        if (eps_sys) {
-            const double e = eps_sys[w.x];
-            eps2 = (float)(e * e);
-        }
-        double res[TPL][4];
-        wave_f32<TPL, MODE>(src, n, w.y, 0, n, jtile, eps2, res);
-#pragma unroll
-        for (int t = 0; t < TPL; ++t) {
-            const int i = w.y + t * 64 + lane;
-            if (i >= n) continue;
-            if constexpr (MODE == M_F32)
-                put_f32(out + base, i, res[t], (float)G);
-            else
-                put(out + base, i, res[t], G);
-        }
-    }
-    (void)WT;
-    if (lane == 0) {
-        const unsigned done = atomicAdd(&counter[1], 1u);
-        if (done == nwaves - 1) {
-            atomicExch(&counter[0], 0u);
-            atomicExch(&counter[1], 0u);
-        }
-    }
+    range_f32<TPL, SEQ>(src, jc, ce, d0, d1, T, eps2, S);
+}
+template <int TPL, bool SEQ>
+__device__ __forceinline__ void tile_sums(const double4 *__restrict__ src, int jc, int ce, int d0, int d1,
+                                          const Targets<double, TPL> &T, double eps2, Sums<double, TPL> &S)
+{
+    const int lo = min(max(d0, jc), ce);
+    const int hi = min(max(d1, jc), ce);
+    sweep_f64<TPL, false>(src, jc, lo, T, eps2, S);
+    sweep_f64<TPL, true>(src, lo, hi, T, eps2, S);
+    sweep_f64<TPL, false>(src, hi, ce, T, eps2, S);
 }
 
-template <int TPL>
-__global__ __launch_bounds__(kBlock) void k_batched_f64(const double4 *__restrict__ pm,
-                                                        const int64_t *__restrict__ offsets,
-                                                        const int2 *__restrict__ units, int nunits,
-                                                        const float *__restrict__ eps_sys,
-                                                        double eps2_all, double G, int jtile,
-                                                        double4 *__restrict__ out,
-                                                        unsigned *__restrict__ counter)
+template <typename T, int TPL, int MODE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 8 : 4))) void k_batched(
+    const typename SliceRec<T>::V *__restrict__ pm, const int64_t *__restrict__ offsets,
+    const int2 *__restrict__ units, int nunits, const float *__restrict__ eps_sys, T eps2_all, double G, int jtile,
+    typename SliceRec<T>::V *__restrict__ out, unsigned *__restrict__ counter)
 {
+    using V = typename SliceRec<T>::V;
+    constexpr int K = 4 * TPL;  // sums per lane
+    constexpr int kWaves = kBlock / 64;
+    __shared__ T part[2][kWaves][K][64];
+    __shared__ unsigned next;
+    static_assert(sizeof(part) >= sizeof(double) * (kWaves / 2) * K * 64, "the results reuse the tile sums");
     const int lane = threadIdx.x & 63;
-    const unsigned nwaves = gridDim.x * (kBlock / 64);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (;;) {
-        unsigned u = 0;
-        if (lane == 0) u = atomicAdd(&counter[0], 1u);
-        u = __builtin_amdgcn_readfirstlane(u);
+        __syncthreads();  // the previous unit's results have been read
+        if (threadIdx.x == 0) next = atomicAdd(&counter[0], 1u);
+        __syncthreads();
+        const unsigned u = __builtin_amdgcn_readfirstlane(next);
         if (u >= (unsigned)nunits) break;
-        const int2 w = units[u];
-        const int64_t base = offsets[w.x];
-        const int n = (int)(offsets[w.x + 1] - base);
-        double eps2 = eps2_all;
+        const int2 un = units[u];
+        const int64_t base = offsets[un.x];
+        const int n = (int)(offsets[un.x + 1] - base);
+        const V *src = pm + base;
+        T eps2 = eps2_all;
         if (eps_sys) {
-            const double e = eps_sys[w.x];
-            eps2 = e * e;
+            const double e = eps_sys[un.x];
+            eps2 = (T)(e * e);
         }
-        double res[TPL][4];
-        wave_f64<TPL>(pm + base, n, w.y, 0, n, jtile, eps2, res);
+        if constexpr (sizeof(T) == 4) eps2 = lane_copy(eps2);
+        const int q = batch_split(n, jtile);
+        const int sub = wave & (q - 1), grp = wave / q;
+        const int nt = (int)(((long)n + jtile - 1) / jtile);
+        const int t0 = un.y + grp * 64 * TPL;
+        Targets<T, TPL> TT;
 #pragma unroll
         for (int t = 0; t < TPL; ++t) {
-            const int i = w.y + t * 64 + lane;
-            if (i < n) put(out + base, i, res[t], G);
+            const int i = t0 + t * 64 + lane;
+            TT.i[t] = i;
+            const V p = src[min(i, n - 1)];
+            TT.x[t] = p.x;
+            TT.y[t] = p.y;
+            TT.z[t] = p.z;
+        }
+        Run<MODE> R[K];  // of the components this wave folds: k mod q == sub
+#pragma unroll
+        for (int k = 0; k < K; ++k) R[k].zero();
+        int buf = 0;
+        for (int k0 = 0; k0 < nt; k0 += q) {
+            Sums<T, TPL> S;
+            S.zero();
+            if (k0 + sub < nt && t0 < n) {
+                const int jc = (k0 + sub) * jtile;
+                tile_sums<TPL, MODE == M_F32>(src, jc, n - jc > jtile ? jc + jtile : n, t0, t0 + 64 * TPL, TT, eps2, S);
+            }
+            if (q == 1) {
+#pragma unroll
+                for (int t = 0; t < TPL; ++t) {
+                    R[4 * t].fold(S.ax[t]);
+                    R[4 * t + 1].fold(S.ay[t]);
+                    R[4 * t + 2].fold(S.az[t]);
+                    R[4 * t + 3].fold(S.ph[t]);
+                }
+                continue;
+            }
+#pragma unroll
+            for (int t = 0; t < TPL; ++t) {
+                part[buf][wave][4 * t][lane] = S.ax[t];
+                part[buf][wave][4 * t + 1][lane] = S.ay[t];
+                part[buf][wave][4 * t + 2][lane] = S.az[t];
+                part[buf][wave][4 * t + 3][lane] = S.ph[t];
+            }
+            __syncthreads();
+            const int m = min(q, nt - k0);
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if ((k & (q - 1)) == sub)
+                    for (int r = 0; r < m; ++r) R[k].fold(part[buf][grp * q + r][k][lane]);
+            buf ^= 1;  // the other buffer's sums were read before this round's barrier
+        }
+        double *fin = reinterpret_cast<double *>(part);  // [group][K][64]
+        if (q > 1) {
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if ((k & (q - 1)) == sub) fin[(grp * K + k) * 64 + lane] = R[k].get();
+            __syncthreads();
+            if (sub > 0) continue;
+        }
+#pragma unroll
+        for (int t = 0; t < TPL; ++t) {
+            const int i = t0 + t * 64 + lane;
+            if (i >= n) continue;
+            double r[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) r[c] = q > 1 ? fin[(grp * K + 4 * t + c) * 64 + lane] : R[4 * t + c].get();
+            if constexpr (MODE == M_F32)
+                put_f32(out + base, i, r, (float)G);
+            else
+                put(out + base, i, r, G);
         }
     }
-    if (lane == 0) {
+    if (threadIdx.x == 0) {
         const unsigned done = atomicAdd(&counter[1], 1u);
-        if (done == nwaves - 1) {
+        if (done == gridDim.x - 1) {
             atomicExch(&counter[0], 0u);
             atomicExch(&counter[1], 0u);
         }
@@ -735,7 +781,7 @@ hipError_t go_batched_f32(const float4 *pm, const int64_t *off, const int2 *unit
                           const float *eps_sys, float eps2, double G, float4 *out, const Tune &t,
                           unsigned *counter, int grid, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_batched_f32<TPL, MODE>), dim3(grid), dim3(kBlock), 0, s, pm, off, units,
+    hipLaunchKernelGGL((k_batched<float, TPL, MODE>), dim3(grid), dim3(kBlock), 0, s, pm, off, units,
                        nunits, eps_sys, eps2, G, t.jtile, out, counter);
     return hipGetLastError();
 }
@@ -832,10 +878,10 @@ hipError_t launch_batched(int prec, const void *pm, const int64_t *offsets, cons
         const double4 *p = (const double4 *)pm;
         double4 *o = (double4 *)out;
         if (t.tpl == 1)
-            hipLaunchKernelGGL((k_batched_f64<1>), dim3(grid), dim3(kBlock), 0, s, p, offsets, units,
+            hipLaunchKernelGGL((k_batched<double, 1, M_F64ACC>), dim3(grid), dim3(kBlock), 0, s, p, offsets, units,
                                nunits, eps_sys, eps * eps, G, t.jtile, o, counter);
         else
-            hipLaunchKernelGGL((k_batched_f64<2>), dim3(grid), dim3(kBlock), 0, s, p, offsets, units,
+            hipLaunchKernelGGL((k_batched<double, 2, M_F64ACC>), dim3(grid), dim3(kBlock), 0, s, p, offsets, units,
                                nunits, eps_sys, eps * eps, G, t.jtile, o, counter);
         return hipGetLastError();
     }

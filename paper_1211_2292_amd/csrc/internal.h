@@ -98,8 +98,11 @@ constexpr size_t kStaticScratchBytes = NBODY_NOALLOC_SCRATCH;
 void *static_split_scratch();
 
 // Batched force over a work list of (system, first target) units sorted
-// longest first.  units: int2[nunits] = (system, target offset within the
-// system); offsets: int64 device copy [nsys+1]; counter: one zeroed uint32
+// longest first.  Waves that share each 64 tpl targets of a system of n bodies:
+// 4, or as many as it has source tiles (a power of two); a unit of 4 waves
+// then holds 256 tpl / batch_split targets.
+__host__ __device__ inline int batch_split(int64_t n, int jtile) { return n > 3 * (int64_t)jtile ? 4 : (n > jtile ? 2 : 1); }
+// units: int2[nunits] = (system, target offset within the system); offsets: int64 device copy [nsys+1]; counter: one zeroed uint32
 // pair, left zeroed again by the kernel on exit.
 hipError_t launch_batched(int prec, const void *pm, const int64_t *offsets, const int2 *units,
                           int nunits, double G, const float *eps_sys, double eps, void *out,

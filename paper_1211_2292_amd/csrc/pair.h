@@ -41,7 +41,7 @@ template <>
 struct Run<M_F64ACC> {
     double s;
     __device__ void zero() { s = 0.0; }
-    __device__ void fold(float p) { s += (double)p; }
+    __device__ void fold(double p) { s += p; }
     __device__ double get() const { return s; }
 };
 

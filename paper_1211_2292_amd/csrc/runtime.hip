@@ -400,6 +400,7 @@ static int get_plan(const int64_t *off, int32_t nsys, const Tune &t, BatchPlan *
 {
     std::vector<int64_t> key(off, off + nsys + 1);
     key.push_back(t.tpl);
+    key.push_back(t.jtile);
     int dev = 0;
     (void)hipGetDevice(&dev);
     key.push_back(dev);
@@ -409,9 +410,7 @@ static int get_plan(const int64_t *off, int32_t nsys, const Tune &t, BatchPlan *
         *out = &it->second;
         return NBODY_OK;
     }
-    // (system, first target) units of one wave each, longest system first:
-    // the cost of a unit is proportional to its system's body count.
-    const int wt = 64 * t.tpl;
+    // (system, first target) units of one workgroup each, longest system first
     std::vector<int> order(nsys);
     for (int s = 0; s < nsys; ++s) order[s] = s;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
@@ -420,6 +419,7 @@ static int get_plan(const int64_t *off, int32_t nsys, const Tune &t, BatchPlan *
     std::vector<int2> units;
     for (int s : order) {
         const int64_t ns = off[s + 1] - off[s];
+        const int wt = kBlock * t.tpl / batch_split(ns, t.jtile);
         for (int64_t t0 = 0; t0 < ns; t0 += wt) units.push_back(make_int2(s, (int)t0));
     }
     BatchPlan p;
@@ -441,9 +441,8 @@ static int get_plan(const int64_t *off, int32_t nsys, const Tune &t, BatchPlan *
     int cus = 256;
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, dev) == hipSuccess) cus = prop.multiProcessorCount;
-    // Persistent grid: eight workgroups (32 waves) per CU, never more waves
-    // than units.
-    p.grid = std::max(1, std::min(cus * 8, (p.nunits + 3) / 4));
+    // Persistent grid: eight workgroups (32 waves) per CU, never more than units.
+    p.grid = std::max(1, std::min(cus * 8, p.nunits));
     auto ins = g_plans.emplace(key, p);
     *out = &ins.first->second;
     return NBODY_OK;

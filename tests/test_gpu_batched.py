@@ -170,3 +170,31 @@ def test_empty_target_range():
     nb.accel(p, 0.01, target_begin=100, target_count=0, out=sentinel[:0])
     torch.cuda.synchronize()
     assert torch.all(sentinel == 7.0)
+
+
+@pytest.mark.parametrize("mode,tpl,jtile", [("F64", 1, 512), ("F32", 1, 512), ("F32_KAHAN", 1, 512), ("F32_KAHAN", 2, 64),
+                                            ("F32_F64ACC", 4, 256), ("F64", 2, 128)])
+def test_batched_tile_sharing_edges(mode, tpl, jtile):
+    """Systems of one to five source tiles and one body more, which 1, 2 or 4
+    waves share, with target counts around the waves' groups: every system is
+    bit for bit its standalone evaluation in the batch's shape."""
+    torch, nb = gpu()
+    prec = getattr(nb, mode)
+    dtype = torch.float64 if mode == "F64" else torch.float32
+    sizes = [k * jtile + e for k in (1, 2, 3, 4, 5) for e in (-1, 0, 1)] + [1, 63, 65, 129, 257]
+    pm, _, off = _batch(sizes, 93)
+    p = to_dev(torch, pm, dtype)
+    nb.set_tuning(1, prec, tpl, 1, jtile)
+    nb.set_tuning(0, prec, tpl, 1, jtile)
+    try:
+        for _ in range(2):
+            out = nb.batched_accel(p, off, 0.01, prec=prec)
+        torch.cuda.synchronize()
+        for s in range(len(sizes)):
+            a, b = off[s], off[s + 1]
+            ref = nb.accel(p[a:b].contiguous(), 0.01, prec=prec)
+            torch.cuda.synchronize()
+            assert torch.equal(out[a:b], ref), sizes[s]
+    finally:
+        nb.set_tuning(0, prec)
+        nb.set_tuning(1, prec)
