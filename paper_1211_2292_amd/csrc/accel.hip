@@ -81,19 +81,6 @@ __device__ __forceinline__ void wave_f32(const float4 *__restrict__ src, int n, 
 }
 
 // ---- FP64 pair ---------------------------------------------------------------
-// 1/sqrt(q) from the hardware estimate and two Newton-Raphson steps
-// y <- y + y (1 - q y^2) / 2.
-__device__ __forceinline__ double rsqrt_f64(double q)
-{
-    double y = __builtin_amdgcn_rsq(q);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const double e = __builtin_fma(-q, y * y, 1.0);
-        y = __builtin_fma(0.5 * y, e, y);
-    }
-    return y;
-}
-
 template <int TPL, bool MASK>
 __device__ __forceinline__ void pair_f64(const double4 b, const int j, const Targets<double, TPL> &T,
                                          const double eps2, Sums<double, TPL> &S)
@@ -104,7 +91,7 @@ __device__ __forceinline__ void pair_f64(const double4 b, const int j, const Tar
         const double dy = b.y - T.y[t];
         const double dz = b.z - T.z[t];
         const double r2 = __builtin_fma(dz, dz, __builtin_fma(dy, dy, __builtin_fma(dx, dx, eps2)));
-        double rho = rsqrt_f64(r2);
+        double rho = rsq_f64(r2);
         if (MASK) rho = (j == T.i[t]) ? 0.0 : rho;
         const double mr = b.w * rho;
         const double s = mr * (rho * rho);

@@ -73,13 +73,7 @@ __device__ __forceinline__ float rsq_t<float>(float q)
 template <>
 __device__ __forceinline__ double rsq_t<double>(double q)
 {
-    double y = __builtin_amdgcn_rsq(q);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const double e = __builtin_fma(-q, y * y, 1.0);
-        y = __builtin_fma(0.5 * y, e, y);
-    }
-    return y;
+    return rsq_f64(q);
 }
 
 template <typename T, typename V, int TPL, bool PHI, bool MASK>
