@@ -148,7 +148,8 @@ int step_blocks(int n);
 hipError_t launch_reduce_step(int prec, const void *partial, int js, double G, void *pm, void *vel,
                               void *acc, int n, double h, double dt, bool close, bool open,
                               double *epart, int *eblocks, hipStream_t s);
-hipError_t launch_energy_final(const double *epart, int nblocks, double *out, hipStream_t s);
+// Energies of `states` states whose partials follow one another, nblocks each.
+hipError_t launch_energy_final(const double *epart, int nblocks, int states, double *out, hipStream_t s);
 hipError_t launch_permute(const void *src, void *dst, const int32_t *perm, int n, int rec_bytes,
                           bool inverse, hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t s);

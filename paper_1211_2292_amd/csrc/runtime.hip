@@ -461,9 +461,18 @@ static int batched_force(int prec, const void *pm, const BatchPlan &p, double G,
 // Leapfrog driver
 // ---------------------------------------------------------------------------
 struct StepBuffers {
-    double *epart = nullptr;  // energy block partials
+    double *epart = nullptr;  // energy block partials of kEnergySteps states
     void *partial = nullptr;  // split scratch of the force kernel
+    bool sweep = false;       // partial holds the sweep's records only
 };
+
+// States whose energy partials wait for one final launch (a launch per step
+// took 3.5 of 24 us at 4096 FP64 bodies).
+constexpr int kEnergySteps = 64;
+static size_t energy_bytes(int nb, int nsteps)
+{
+    return sizeof(double) * 2 * (size_t)nb * (size_t)std::min(kEnergySteps, nsteps + 1);
+}
 
 static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPlan *plan, int prec,
                             double G, double eps, double dt, int nsteps, uint32_t flags,
@@ -473,12 +482,26 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
     Tune bt = lookup_tune(1, prec, n);
     double *ep = energy ? buf.epart : nullptr;
     int eb = 0;
+    int waiting = 0;  // states whose partials are in buf.epart, the last one state `seen` - 1
+    int seen = 0;
+    auto energies = [&](bool last) -> int {
+        if (!energy) return NBODY_OK;
+        ++waiting;
+        ++seen;
+        if (waiting == kEnergySteps || last) {
+            NB_TRY(launch_energy_final(buf.epart, eb, waiting, energy + 2 * (seen - waiting), s), "energy kernel");
+            waiting = 0;
+        }
+        ep = buf.epart + 2 * (size_t)eb * waiting;
+        return NBODY_OK;
+    };
     // A force evaluation followed by the step pass (close, open, energy).
     // A direct force with a source split leaves its per-split records in
     // scratch and the step pass reduces them itself (one launch fewer).
     auto eval_step = [&](bool step, bool close, bool open) -> int {
         if (!plan) {
             Tune t = lookup_tune(0, prec, n);
+            if (buf.sweep) t.path = kPathSweep;
             void *partial = buf.partial;
             NB_CHECK(force_scratch(prec, n, t, partial));
             if (const int records = accel_partial_records(n, t); records && step) {
@@ -490,7 +513,7 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
                        "reduce + step kernel");
                 return NBODY_OK;
             }
-            NB_CHECK(force(prec, pm, n, G, eps, acc, 0, n, s, buf.partial));
+            NB_TRY(launch_accel(prec, pm, n, G, eps, acc, 0, n, t, partial, s), "force kernel");
         } else {
             NB_CHECK(batched_force(prec, pm, *plan, G, nullptr, eps, acc, bt, s));
         }
@@ -506,16 +529,15 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
         // a(x_0) and, on request, the energies at t_0
         if (!have_acc) NB_CHECK(eval_step(energy != nullptr, false, false));
         else if (energy) NB_CHECK(step_only(false, false));
-        if (energy) NB_TRY(launch_energy_final(ep, eb, energy, s), "energy kernel");
-        return NBODY_OK;
+        return energies(true);
     }
     if (!have_acc) NB_CHECK(eval_step(true, false, true));
     else NB_CHECK(step_only(false, true));
-    if (energy) NB_TRY(launch_energy_final(ep, eb, energy, s), "energy kernel");
+    NB_CHECK(energies(false));
     for (int k = 0; k < nsteps; ++k) {
         const bool last = (k == nsteps - 1);
         NB_CHECK(eval_step(true, true, !last));
-        if (energy) NB_TRY(launch_energy_final(ep, eb, energy + 2 * (k + 1), s), "energy kernel");
+        NB_CHECK(energies(last));
     }
     return NBODY_OK;
 }
@@ -757,7 +779,7 @@ int nbody_energy(const void *pos_mass, const void *vel, const void *acc_pot, int
     NB_TRY(launch_step(prec, const_cast<void *>(pos_mass), const_cast<void *>(vel), acc_pot, (int)n,
                        0.0, 0.0, false, false, ep, nullptr, s),
            "energy kernel");
-    NB_TRY(launch_energy_final(ep, nb, energy_out, s), "energy kernel");
+    NB_TRY(launch_energy_final(ep, nb, 1, energy_out, s), "energy kernel");
     return NBODY_OK;
 }
 
@@ -804,7 +826,7 @@ int nbody_leapfrog_kdk(void *pos_mass, void *vel, void *acc_pot, int64_t n,
     if (!(flags & NBODY_GRAPH)) {
         StepBuffers buf;
         if (en) {
-            buf.epart = (double *)scratch(kSlotEnergy, sizeof(double) * 2 * nb);
+            buf.epart = (double *)scratch(kSlotEnergy, energy_bytes(nb, nsteps));
             if (!buf.epart) {
                 set_error("cannot allocate energy scratch");
                 return NBODY_E_NOMEM;
@@ -848,9 +870,17 @@ int nbody_leapfrog_kdk(void *pos_mass, void *vel, void *acc_pot, int64_t n,
             }
         } undo{e};
         Tune t = lookup_tune(0, prec, n);
-        const size_t pb = plan ? 0 : accel_partial_bytes(prec, (int)n, t);
-        if (pb) NB_TRY(hipMalloc(&e.partial, pb), "graph scratch");
-        if (en) NB_TRY(hipMalloc((void **)&e.epart, sizeof(double) * 2 * nb), "graph scratch");
+        size_t pb = plan ? 0 : accel_partial_bytes(prec, (int)n, t);
+        StepBuffers buf;
+        if (pb && t.path == kPathSym && hipMalloc(&e.partial, pb) != hipSuccess) {
+            (void)hipGetLastError();
+            e.partial = nullptr;
+            buf.sweep = true;
+            t.path = kPathSweep;
+            pb = accel_partial_bytes(prec, (int)n, t);
+        }
+        if (pb && !e.partial) NB_TRY(hipMalloc(&e.partial, pb), "graph scratch");
+        if (en) NB_TRY(hipMalloc((void **)&e.epart, energy_bytes(nb, nsteps)), "graph scratch");
         hipStream_t cs;
         {
             std::lock_guard<std::mutex> lk(g_mu);
@@ -866,7 +896,6 @@ int nbody_leapfrog_kdk(void *pos_mass, void *vel, void *acc_pot, int64_t n,
             cs = it->second;
         }
         NB_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal), "begin capture");
-        StepBuffers buf;
         buf.epart = e.epart;
         buf.partial = e.partial;
         int rc = leapfrog_enqueue(pos_mass, vel, acc_pot, (int)n, plan, prec, G, eps, dt, nsteps, flags,

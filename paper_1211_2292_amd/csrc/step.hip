@@ -120,12 +120,14 @@ __global__ __launch_bounds__(kBlock) void k_reduce_step(const P *__restrict__ pa
     }
 }
 
-// One workgroup: each lane sums a strided subset of the block partials in
-// order, then a fixed-order tree.
+// One workgroup per state: each lane sums a strided subset of the block
+// partials in order, then a fixed-order tree.
 __global__ __launch_bounds__(kBlock) void k_energy_final(const double *__restrict__ epart,
                                                          int nblocks, double *__restrict__ out)
 {
     double a = 0.0, b = 0.0;
+    epart += 2 * (size_t)nblocks * blockIdx.x;
+    out += 2 * blockIdx.x;
     for (int k = threadIdx.x; k < nblocks; k += kBlock) {
         a += epart[2 * k];
         b += epart[2 * k + 1];
@@ -218,9 +220,9 @@ hipError_t launch_reduce_step(int prec, const void *partial, int js, double G, v
     return hipGetLastError();
 }
 
-hipError_t launch_energy_final(const double *epart, int nblocks, double *out, hipStream_t s)
+hipError_t launch_energy_final(const double *epart, int nblocks, int states, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(kBlock), 0, s, epart, nblocks, out);
+    hipLaunchKernelGGL(k_energy_final, dim3(states), dim3(kBlock), 0, s, epart, nblocks, out);
     return hipGetLastError();
 }
 

@@ -98,3 +98,24 @@ def test_acc_valid_flag_skips_first_evaluation():
     nb.leapfrog_kdk(p2, v2, a2, 0.01, 1e-3, 3, acc_valid=True)
     torch.cuda.synchronize()
     assert torch.equal(p1, p2) and torch.equal(v1, v2) and torch.equal(a1, a2)
+
+
+@pytest.mark.parametrize("steps", [0, 1, 62, 63, 64, 130])
+def test_energies_of_many_steps(steps):
+    """The energies of up to 64 states wait for one reduction launch: around
+    that count, each equals nbody_energy on the state that steps taken one at
+    a time reach, bit for bit."""
+    torch, nb = gpu()
+    pm, v = ics.plummer(700, 53)
+    p1, v1 = to_dev(torch, pm, torch.float32), to_dev(torch, v, torch.float32)
+    p2, v2 = p1.clone(), v1.clone()
+    a1, a2 = torch.empty_like(p1), torch.empty_like(p1)
+    en = nb.leapfrog_kdk(p1, v1, a1, 0.01, 1e-3, steps, energy=True)
+    nb.leapfrog_kdk(p2, v2, a2, 0.01, 1e-3, 0)
+    ref = [nb.energy(p2, v2, a2)]
+    for _ in range(steps):
+        nb.leapfrog_kdk(p2, v2, a2, 0.01, 1e-3, 1, acc_valid=True)
+        ref.append(nb.energy(p2, v2, a2))
+    torch.cuda.synchronize()
+    assert torch.equal(p1, p2) and torch.equal(v1, v2)
+    assert torch.equal(en, torch.stack(ref))
