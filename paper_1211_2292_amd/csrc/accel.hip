@@ -65,7 +65,7 @@ __device__ __forceinline__ void wave_f32(const float4 *__restrict__ src, int n, 
         ce = je - jc > jtile ? jc + jtile : je;  // no jc + jtile past je (int range)
         S.zero();
         // pure FP32 pins the per-source schedule (see sweep_f32)
-        range_f32<TPL, MODE == M_F32>(src, jc, ce, d0, d1, T, eps2, S);
+        range_f32<TPL, MODE == M_F32, 2 * kUnroll>(src, jc, ce, d0, d1, T, eps2, S);
 #pragma unroll
         for (int t = 0; t < TPL; ++t) {
             R[t][0].fold(S.ax[t]);
@@ -317,10 +317,10 @@ __global__ __launch_bounds__(kBlock) void k_accel_f32(const float4 *__restrict__
             else
                 put(out, k, res[t], G);
         } else if constexpr (MODE == M_F32) {
-            reinterpret_cast<float4 *>(partial)[(long)by * tcount + k] =
+            reinterpret_cast<float4 *>(partial)[split_at(k, by, gridDim.y, tcount)] =
                 make_float4((float)res[t][0], (float)res[t][1], (float)res[t][2], (float)res[t][3]);
         } else {
-            reinterpret_cast<double4 *>(partial)[(long)by * tcount + k] =
+            reinterpret_cast<double4 *>(partial)[split_at(k, by, gridDim.y, tcount)] =
                 make_double4(res[t][0], res[t][1], res[t][2], res[t][3]);
         }
     }
@@ -360,10 +360,10 @@ __global__ __launch_bounds__(kBlock) void k_accel_lds_f32(const float4 *__restri
             else
                 put(out, k, res[t], G);
         } else if constexpr (MODE == M_F32) {
-            reinterpret_cast<float4 *>(partial)[(long)by * tcount + k] =
+            reinterpret_cast<float4 *>(partial)[split_at(k, by, gridDim.y, tcount)] =
                 make_float4((float)res[t][0], (float)res[t][1], (float)res[t][2], (float)res[t][3]);
         } else {
-            reinterpret_cast<double4 *>(partial)[(long)by * tcount + k] =
+            reinterpret_cast<double4 *>(partial)[split_at(k, by, gridDim.y, tcount)] =
                 make_double4(res[t][0], res[t][1], res[t][2], res[t][3]);
         }
     }
@@ -395,7 +395,7 @@ __global__ __launch_bounds__(kBlock) void k_accel_f64(const double4 *__restrict_
         if (gridDim.y == 1)
             put(out, k, res[t], G);
         else
-            partial[(long)by * tcount + k] = make_double4(res[t][0], res[t][1], res[t][2], res[t][3]);
+            partial[split_at(k, by, gridDim.y, tcount)] = make_double4(res[t][0], res[t][1], res[t][2], res[t][3]);
     }
 }
 
@@ -540,34 +540,20 @@ __global__ __launch_bounds__(kBlock) void k_split_reduce(const double4 *__restri
                                                          int js, int tcount, double G,
                                                          OUT *__restrict__ out)
 {
-    const long k = (long)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= tcount) return;
-    double r[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int s = 0; s < js; ++s) {
-        const double4 p = partial[(long)s * tcount + k];
-        r[0] += p.x;
-        r[1] += p.y;
-        r[2] += p.z;
-        r[3] += p.w;
-    }
-    put(out, k, r, G);
+    const long k = ((long)blockIdx.x * kBlock + threadIdx.x) / kSumLanes;
+    double r[4];
+    split_sum<kSumLanes>(reinterpret_cast<const double *>(partial), js, tcount, min(k, (long)tcount - 1), r);
+    if (threadIdx.x % kSumLanes == 0 && k < tcount) put(out, k, r, G);
 }
 
 __global__ __launch_bounds__(kBlock) void k_split_reduce_f32(const float4 *__restrict__ partial,
                                                              int js, int tcount, float G,
                                                              float4 *__restrict__ out)
 {
-    const long k = (long)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= tcount) return;
-    float r[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int s = 0; s < js; ++s) {
-        const float4 p = partial[(long)s * tcount + k];
-        r[0] += p.x;
-        r[1] += p.y;
-        r[2] += p.z;
-        r[3] += p.w;
-    }
-    out[k] = make_float4(G * r[0], G * r[1], G * r[2], -G * r[3]);
+    const long k = ((long)blockIdx.x * kBlock + threadIdx.x) / kSumLanes;
+    float r[4];
+    split_sum<kSumLanes>(reinterpret_cast<const float *>(partial), js, tcount, min(k, (long)tcount - 1), r);
+    if (threadIdx.x % kSumLanes == 0 && k < tcount) out[k] = make_float4(G * r[0], G * r[1], G * r[2], -G * r[3]);
 }
 
 // ---- batched persistent kernel -------------------------------------------------
@@ -712,6 +698,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
     }
 }
 
+unsigned split_reduce_blocks(int tcount)
+{
+    return (unsigned)(((long)tcount * kSumLanes + kBlock - 1) / kBlock);
+}
+
 template <int TPL, int MODE>
 hipError_t go_f32(const float4 *pm, int n, float eps2, double G, float4 *out, int tbeg, int tcount,
                   const Tune &t, void *partial, bool reduce, hipStream_t s)
@@ -726,7 +717,7 @@ hipError_t go_f32(const float4 *pm, int n, float eps2, double G, float4 *out, in
                            tcount, t.jtile, out, partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || t.jsplit == 1 || !reduce) return e;
-    const int rb = (tcount + kBlock - 1) / kBlock;
+    const unsigned rb = split_reduce_blocks(tcount);
     if constexpr (MODE == M_F32)
         hipLaunchKernelGGL(k_split_reduce_f32, dim3(rb), dim3(kBlock), 0, s,
                            (const float4 *)partial, t.jsplit, tcount, (float)G, out);
@@ -746,7 +737,7 @@ hipError_t go_f64(const double4 *pm, int n, double eps2, double G, double4 *out,
                        t.jtile, out, (double4 *)partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || t.jsplit == 1 || !reduce) return e;
-    const int rb = (tcount + kBlock - 1) / kBlock;
+    const unsigned rb = split_reduce_blocks(tcount);
     hipLaunchKernelGGL(k_split_reduce<double4>, dim3(rb), dim3(kBlock), 0, s,
                        (const double4 *)partial, t.jsplit, tcount, G, out);
     return hipGetLastError();
@@ -834,7 +825,7 @@ hipError_t launch_accel(int prec, const void *pm, int n, double G, double eps, v
     if (t.path == kPathSym) {  // all bodies
         const hipError_t e = launch_sym(pm, n, eps, partial, s);
         if (e != hipSuccess || !reduce) return e;
-        hipLaunchKernelGGL(k_split_reduce<float4>, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
+        hipLaunchKernelGGL(k_split_reduce<float4>, dim3(split_reduce_blocks(n)), dim3(kBlock), 0, s,
                            (const double4 *)partial, accel_partial_records(n, t), n, G, (float4 *)out);
         return hipGetLastError();
     }

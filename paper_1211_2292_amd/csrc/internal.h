@@ -79,6 +79,43 @@ __device__ __forceinline__ double rsq_f64(double q)
 
 bool tune_valid(const Tune &t);
 
+// Place of target k's record of split s among js splits of tcount targets:
+// 64 targets' records of one split side by side, the splits of those targets
+// after one another.  (With all records of a split side by side, a power of two
+// of targets puts every split of a target on the same memory channels.)
+__device__ __forceinline__ long split_at(long k, int s, int js, long tcount)
+{
+    const long g = k & ~63L;
+    return g * js + s * min(64L, tcount - g) + (k - g);
+}
+
+// Fixed-order sum of the js split records (L values of type E each) of target
+// k by L neighbouring lanes, one value each with 8 splits in flight; every lane
+// of the L receives all sums.  (One lane per target was bound by the latency
+// of its loads: 23457 bodies and 32 splits 10.6 us, 4.9 now; with the order of
+// split_at, pairwise sums of 65536 bodies 926 against 897 us per force.)
+constexpr int kSumLanes = 4;
+template <int L, typename E, typename R>
+__device__ __forceinline__ void split_sum(const E *__restrict__ partial, int js, long tcount, long k, R (&r)[L])
+{
+    const int c = threadIdx.x % L;
+    const E *src = partial + L * split_at(k, 0, js, tcount) + c;
+    const long stride = L * min(64L, tcount - (k & ~63L));
+    R v = R(0);
+    int s = 0;
+    for (; s + 8 <= js; s += 8) {
+        E a[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a[u] = src[(s + u) * stride];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += a[u];
+    }
+    for (; s < js; ++s) v += src[s * stride];
+    const int first = (threadIdx.x & 63) - c;
+#pragma unroll
+    for (int q = 0; q < L; ++q) r[q] = __shfl(v, first + q);
+}
+
 // ---- force (accel.hip) -----------------------------------------------------
 // pm: float4/double4 records; out: target_count records; partial: scratch of
 // jsplit * target_count double4 (F32 mode: float4) records when jsplit > 1.

@@ -12,12 +12,15 @@
 namespace nbi {
 namespace {
 
-// Fixed-order block reduction of two doubles; thread 0 holds the result.
-__device__ __forceinline__ void block_sum2(double &a, double &b)
+// Fixed-order sum over kBlock slots of two doubles, slot k set by one thread
+// of the workgroup (owner); thread 0 holds the result.
+__device__ __forceinline__ void block_sum2(double &a, double &b, int slot, bool owner)
 {
     __shared__ double sa[kBlock], sb[kBlock];
-    sa[threadIdx.x] = a;
-    sb[threadIdx.x] = b;
+    if (owner) {
+        sa[slot] = a;
+        sb[slot] = b;
+    }
     __syncthreads();
     for (int w = kBlock / 2; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w) {
@@ -70,7 +73,7 @@ __global__ __launch_bounds__(kBlock) void k_step(V *__restrict__ pm, V *__restri
     double ek = 0.0, eu = 0.0;
     if (i < n) step_one(pm, vel, i, acc[i], h, dt, close, open, epart != nullptr, ek, eu);
     if (epart) {
-        block_sum2(ek, eu);
+        block_sum2(ek, eu, threadIdx.x, true);
         if (threadIdx.x == 0) {
             epart[2 * blockIdx.x] = ek;
             epart[2 * blockIdx.x + 1] = eu;
@@ -79,30 +82,28 @@ __global__ __launch_bounds__(kBlock) void k_step(V *__restrict__ pm, V *__restri
 }
 
 // The force kernel's source-split reduction and the step in one pass: the
-// js partial records of body i are summed in split order and scaled exactly
-// as the stand-alone reduction does (R = the partials' type, GT = the type G
-// is applied in), the record is stored to acc, and the same value drives the
-// kick, drift and energy partials.  Results equal reduce-then-step bit for
-// bit; one launch and one pass over acc fewer.
+// js partial records of body i are summed in split order (4 lanes per body, see
+// split_sum) and scaled exactly as the stand-alone reduction does (R = the type
+// of the sums, GT = the type G is applied in); the first of the 4 lanes stores
+// the record to acc and applies the kick, drift and energy partials to the same
+// value.  Results equal reduce-then-step bit for bit; one launch and one pass
+// over acc fewer.  A workgroup holds kBlock bodies, as k_step's.
+constexpr int kReduceThreads = kBlock * kSumLanes;
 template <typename V, typename S, typename P, typename R, typename GT>
-__global__ __launch_bounds__(kBlock) void k_reduce_step(const P *__restrict__ partial, int js, GT G,
-                                                        V *__restrict__ pm, V *__restrict__ vel,
-                                                        V *__restrict__ acc, int n, S h, S dt,
-                                                        int close, int open,
-                                                        double *__restrict__ epart)
+__global__ __launch_bounds__(kReduceThreads) void k_reduce_step(const P *__restrict__ partial, int js, GT G,
+                                                                V *__restrict__ pm, V *__restrict__ vel,
+                                                                V *__restrict__ acc, int n, S h, S dt, int close,
+                                                                int open, double *__restrict__ epart)
 {
     using E = typename std::conditional<sizeof(V) == 16, float, double>::type;
-    const int i = blockIdx.x * kBlock + threadIdx.x;
+    using PE = typename std::conditional<sizeof(P) == 16, float, double>::type;
+    const int slot = threadIdx.x / kSumLanes;
+    const int i = blockIdx.x * kBlock + slot;
+    const bool owner = threadIdx.x % kSumLanes == 0;
     double ek = 0.0, eu = 0.0;
-    if (i < n) {
-        R r[4] = {R(0), R(0), R(0), R(0)};
-        for (int k = 0; k < js; ++k) {
-            const P q = partial[(long)k * n + i];
-            r[0] += q.x;
-            r[1] += q.y;
-            r[2] += q.z;
-            r[3] += q.w;
-        }
+    R r[4];
+    split_sum<kSumLanes>(reinterpret_cast<const PE *>(partial), js, n, min(i, n - 1), r);
+    if (owner && i < n) {
         V a;
         a.x = (E)(G * r[0]);
         a.y = (E)(G * r[1]);
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_step(const P *__restrict__ pa
         step_one(pm, vel, i, a, h, dt, close, open, epart != nullptr, ek, eu);
     }
     if (epart) {
-        block_sum2(ek, eu);
+        block_sum2(ek, eu, slot, owner);
         if (threadIdx.x == 0) {
             epart[2 * blockIdx.x] = ek;
             epart[2 * blockIdx.x + 1] = eu;
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_final(const double *__restric
         a += epart[2 * k];
         b += epart[2 * k + 1];
     }
-    block_sum2(a, b);
+    block_sum2(a, b, threadIdx.x, true);
     if (threadIdx.x == 0) {
         out[0] = a;
         out[1] = b;
@@ -205,16 +206,16 @@ hipError_t launch_reduce_step(int prec, const void *partial, int js, double G, v
     if (eblocks) *eblocks = nb;
     if (prec == NBODY_F64)
         hipLaunchKernelGGL((k_reduce_step<double4, double, double4, double, double>), dim3(nb),
-                           dim3(kBlock), 0, s, (const double4 *)partial, js, G, (double4 *)pm,
+                           dim3(kReduceThreads), 0, s, (const double4 *)partial, js, G, (double4 *)pm,
                            (double4 *)vel, (double4 *)acc, n, h, dt, (int)close, (int)open, epart);
     else if (prec == NBODY_F32)
         hipLaunchKernelGGL((k_reduce_step<float4, float, float4, float, float>), dim3(nb),
-                           dim3(kBlock), 0, s, (const float4 *)partial, js, (float)G, (float4 *)pm,
+                           dim3(kReduceThreads), 0, s, (const float4 *)partial, js, (float)G, (float4 *)pm,
                            (float4 *)vel, (float4 *)acc, n, (float)h, (float)dt, (int)close,
                            (int)open, epart);
     else
         hipLaunchKernelGGL((k_reduce_step<float4, float, double4, double, double>), dim3(nb),
-                           dim3(kBlock), 0, s, (const double4 *)partial, js, G, (float4 *)pm,
+                           dim3(kReduceThreads), 0, s, (const double4 *)partial, js, G, (float4 *)pm,
                            (float4 *)vel, (float4 *)acc, n, (float)h, (float)dt, (int)close,
                            (int)open, epart);
     return hipGetLastError();

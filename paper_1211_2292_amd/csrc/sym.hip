@@ -357,8 +357,8 @@ __device__ __forceinline__ void sym_store(double4 *p, double4 v, int add)
 }
 
 // grid.x = M * runs: workgroup (run, I) takes d = d0 + run * len .. + len - 1.
-// slots: [runs + runs * len][n] records: first the runs' sums of I, then the
-// sums of J per d of the launch.
+// slots: runs (1 + len) records per body, placed as split records (split_at):
+// first the runs' sums of I, then the sums of J per d of the launch.
 template <int TPL>
 __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_sym(
     const float4 *__restrict__ src, int n, int M, int d0, int len, int runs, float eps2_in, int add,
@@ -369,6 +369,7 @@ __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(4, 
     __shared__ float4 jp[kSymWaves][128];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int run = blockIdx.x / M, I = blockIdx.x % M;
+    const int total = runs * (1 + len);  // slots per body
     const float eps2 = lane_copy(eps2_in);
     SymTargets<TPL> T;
     double R[TPL][4];
@@ -415,17 +416,16 @@ __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(4, 
                 __syncthreads();
             }
         }
-        double4 *o = slots + (long)(runs + e) * n;
         for (int k = threadIdx.x; k < B; k += kSymThreads) {
             const long j = (long)J * B + k;
-            if (j < n) sym_store(o + j, jacc[k], add);
+            if (j < n) sym_store(slots + split_at(j, runs + e, total, n), jacc[k], add);
         }
         __syncthreads();  // jacc is cleared for the next tile
     }
 #pragma unroll
     for (int t = 0; t < TPL; ++t)
         if (const int i = T.i0 + 64 * t + lane; i < n)
-            sym_store(slots + (long)run * n + i, make_double4(R[t][0], R[t][1], R[t][2], R[t][3]), add);
+            sym_store(slots + split_at(i, run, total, n), make_double4(R[t][0], R[t][1], R[t][2], R[t][3]), add);
 }
 
 }  // namespace
