@@ -274,6 +274,17 @@ constexpr int64_t kSliceMaxF32 = 8192, kSliceMaxF64 = 4096;
 // 2^20: 212.8 / 256.6 ms.  Above kSymMax its sums no longer fit kSymScratch.
 constexpr int64_t kSymMin = 44 * kSymBlock, kSymMax = int64_t(1) << 24;
 
+// Sources per split that the force + VJP sweep keeps: a few thousand bodies
+// leave most of the chip idle otherwise (256 / 128 / 64 sources: 1000 bodies 48
+// / 27 / 19 us, 3001 bodies 40 / 27 / 26 us, an adjoint run of 20 steps at 4001
+// bodies 1441 / 994 / 876 us).  The fixed-point leapfrog keeps 256: its states
+// depend on the shape bit for bit.
+constexpr int64_t kVjpMinSources = 64;
+// Sources per FP32 partial sum of that sweep.  Tiles of 128 instead of 512 cost
+// under 1% and cut the errors by a third (10007 bodies, against FP64: xbar
+// 4.8e-7 to 3.3e-7, mbar 3.2e-7 to 2.3e-7).
+constexpr int kVjpTile = 128;
+
 // Kernels of a call whose shape is not pinned.
 static int default_path(int kernel, int prec, int64_t n, int64_t ntarg)
 {
@@ -286,7 +297,7 @@ static int default_path(int kernel, int prec, int64_t n, int64_t ntarg)
 // Heuristic shape from measured sweeps on MI355X (force kernel, FP32 modes).
 // n sources, ntarg targets (fewer than n for a target range, e.g. one GPU's
 // share of the targets).
-static Tune default_tune(int kernel, int prec, int64_t n, int64_t ntarg)
+static Tune default_tune(int kernel, int prec, int64_t n, int64_t ntarg, int64_t min_sources = 256)
 {
     Tune t;
     t.jtile = 512;
@@ -302,7 +313,7 @@ static Tune default_tune(int kernel, int prec, int64_t n, int64_t ntarg)
     }
     const int64_t waves = (ntarg + 63) / 64;
     int js = 1;
-    while (js < 32 && waves * js < 65536 && n / (js * 2) >= 256) js *= 2;
+    while (js < 32 && waves * js < 65536 && n / (js * 2) >= min_sources) js *= 2;
     // A multiple of 8 splits gives each XCD its own source segments, read
     // from its own L2 (the force kernels' workgroup mapping).  At 2^20
     // sources, 8 splits of 2 MiB fit that 4 MiB cache: the bytes fetched past
@@ -324,6 +335,11 @@ static Tune lookup_tune(int kernel, int prec, int64_t n, int64_t ntarg = -1, boo
     if (p != g_pinned.end()) return p->second;
     if (ntarg < 0) ntarg = n;
     auto it = g_tuned.find(TuneKey(kernel, prec, log2ceil(n)));
+    if (it == g_tuned.end() && kernel == 2) {
+        Tune t = default_tune(kernel, prec, n, ntarg, kVjpMinSources);
+        t.jtile = kVjpTile;
+        return t;
+    }
     if (it == g_tuned.end()) return default_tune(kernel, prec, n, ntarg);
     Tune t = it->second;  // a measured shape of the sweep, for the calls that run it
     t.path = default_path(kernel, prec, n, ntarg);

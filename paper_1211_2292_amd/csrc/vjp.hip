@@ -12,11 +12,11 @@
 // Per wave: 64*TPL targets in VGPRs; each source brings its position/mass
 // and its cotangent record through wave-uniform scalar loads.  Per pair the
 // sweep accumulates
-//     P  += w e                 e = m_k abar_j - m_j abar_k
-//     Q  += (w rho^2)(d . e) d  -> xbar = G (P - 3 Q) + ...
-//     M  += w (d . abar_j)      -> mbar = -G M + ...
-//     A  += m_j w d, F += m_j rho        (forward force and potential)
-//     B  += phibar_j w d, H += phibar_j rho   (only with phibar)
+//     X  += w e - w (3 rho^2 (d . e) + m_k phibar_j) d   e = m_k abar_j - m_j abar_k
+//                                -> xbar = G X - phibar_k a_k
+//     M  += w (d . abar_j), H += phibar_j rho  -> mbar = -G (M + H)
+//     A  += m_j w d, F += m_j rho              (forward force and potential)
+// (the phibar_j terms only with phibar): 37 VALU and a reciprocal square root.
 // FP32 tile partials are folded into FP64 running sums for the FP32 modes;
 // the FP64 mode runs the same sweep in FP64.
 //
@@ -29,7 +29,9 @@
 namespace nbi {
 namespace {
 
-constexpr int kVjpUnroll = 2;  // sources per unrolled step (measured: 2 beats 1, 3 and 4)
+// Sources per unrolled step.  Measured with the reciprocal square root at
+// raised priority: 1, 2, 4, 8 take 106, 99, 96, 90 us for 10007 bodies.
+constexpr int kVjpUnroll = 8;
 
 // eps^2 is kept in a vector register in FP32 (see lane_copy); FP64 keeps the
 // compiler's choice.
@@ -38,16 +40,15 @@ __device__ __forceinline__ T lane_copy_t(T x) { return x; }
 template <>
 __device__ __forceinline__ float lane_copy_t<float>(float x) { return lane_copy(x); }
 
-template <typename T, int TPL, bool PHI>
+template <typename T, int TPL>
 struct VAcc {
-    T P[TPL][3], Q[TPL][3], M[TPL], A[TPL][3], F[TPL];
-    T B[TPL][3], H[TPL];
+    T X[TPL][3], M[TPL], A[TPL][3], F[TPL], H[TPL];
     __device__ void zero()
     {
 #pragma unroll
         for (int t = 0; t < TPL; ++t) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) P[t][c] = Q[t][c] = A[t][c] = B[t][c] = T(0);
+            for (int c = 0; c < 3; ++c) X[t][c] = A[t][c] = T(0);
             M[t] = F[t] = H[t] = T(0);
         }
     }
@@ -78,7 +79,7 @@ __device__ __forceinline__ double rsq_t<double>(double q)
 
 template <typename T, typename V, int TPL, bool PHI, bool MASK>
 __device__ __forceinline__ void vpair(const V p, const V c, const int j, const VTgt<T, TPL> &K,
-                                      const T eps2, VAcc<T, TPL, PHI> &S)
+                                      const T eps2, VAcc<T, TPL> &S)
 {
 #pragma unroll
     for (int t = 0; t < TPL; ++t) {
@@ -95,33 +96,25 @@ __device__ __forceinline__ void vpair(const V p, const V c, const int j, const V
         const T e2 = fmat(-p.w, K.ab[t][2], K.m[t] * c.z);
         const T de = fmat(d2, e2, fmat(d1, e1, d0 * e0));
         const T da = fmat(d2, c.z, fmat(d1, c.y, d0 * c.x));
-        const T uq = (w * r2) * de;
-        S.P[t][0] = fmat(w, e0, S.P[t][0]);
-        S.P[t][1] = fmat(w, e1, S.P[t][1]);
-        S.P[t][2] = fmat(w, e2, S.P[t][2]);
-        S.Q[t][0] = fmat(uq, d0, S.Q[t][0]);
-        S.Q[t][1] = fmat(uq, d1, S.Q[t][1]);
-        S.Q[t][2] = fmat(uq, d2, S.Q[t][2]);
+        const T r3 = T(3) * r2;
+        const T g = -w * (PHI ? fmat(r3, de, K.m[t] * c.w) : r3 * de);
+        S.X[t][0] = fmat(g, d0, fmat(w, e0, S.X[t][0]));
+        S.X[t][1] = fmat(g, d1, fmat(w, e1, S.X[t][1]));
+        S.X[t][2] = fmat(g, d2, fmat(w, e2, S.X[t][2]));
         S.M[t] = fmat(w, da, S.M[t]);
+        if (PHI) S.H[t] = fmat(c.w, rho, S.H[t]);
         const T mw = p.w * w;
         S.A[t][0] = fmat(mw, d0, S.A[t][0]);
         S.A[t][1] = fmat(mw, d1, S.A[t][1]);
         S.A[t][2] = fmat(mw, d2, S.A[t][2]);
         S.F[t] = fmat(p.w, rho, S.F[t]);
-        if (PHI) {
-            const T pw = c.w * w;
-            S.B[t][0] = fmat(pw, d0, S.B[t][0]);
-            S.B[t][1] = fmat(pw, d1, S.B[t][1]);
-            S.B[t][2] = fmat(pw, d2, S.B[t][2]);
-            S.H[t] = fmat(c.w, rho, S.H[t]);
-        }
     }
 }
 
 template <typename T, typename V, int TPL, bool PHI, bool MASK>
 __device__ __forceinline__ void vsweep(const V *__restrict__ pm, const V *__restrict__ cot, int j0,
                                        int j1, const VTgt<T, TPL> &K, T eps2,
-                                       VAcc<T, TPL, PHI> &S)
+                                       VAcc<T, TPL> &S)
 {
     int j = j0;
     for (; j + kVjpUnroll <= j1; j += kVjpUnroll) {
@@ -135,22 +128,6 @@ __device__ __forceinline__ void vsweep(const V *__restrict__ pm, const V *__rest
         for (int u = 0; u < kVjpUnroll; ++u) vpair<T, V, TPL, PHI, MASK>(p[u], c[u], j + u, K, eps2, S);
     }
     for (; j < j1; ++j) vpair<T, V, TPL, PHI, MASK>(pm[j], cot[j], j, K, eps2, S);
-}
-
-// Number of accumulated scalars per target.
-constexpr int kVN = 17;
-
-template <typename T, int TPL, bool PHI>
-__device__ __forceinline__ void vflatten(const VAcc<T, TPL, PHI> &S, int t, T (&f)[kVN])
-{
-    f[0] = S.P[t][0]; f[1] = S.P[t][1]; f[2] = S.P[t][2];
-    f[3] = S.Q[t][0]; f[4] = S.Q[t][1]; f[5] = S.Q[t][2];
-    f[6] = S.M[t];
-    f[7] = S.A[t][0]; f[8] = S.A[t][1]; f[9] = S.A[t][2];
-    f[10] = S.F[t];
-    f[11] = S.B[t][0]; f[12] = S.B[t][1]; f[13] = S.B[t][2];
-    f[14] = S.H[t];
-    f[15] = 0; f[16] = 0;
 }
 
 // Output of one target: xbar (3), mbar, a (3), phi, all linear in the sums,
@@ -217,12 +194,12 @@ __device__ __forceinline__ void vjp_general(const V *__restrict__ pm, const V *_
         K.pb[t] = c.w;
     }
     const int d0 = t0, d1 = t0 + WT;
-    double R[TPL][kVN];
+    double R[TPL][9];  // X, M, A, F, H
 #pragma unroll
     for (int t = 0; t < TPL; ++t)
 #pragma unroll
-        for (int c = 0; c < kVN; ++c) R[t][c] = 0.0;
-    VAcc<T, TPL, PHI> S;
+        for (int c = 0; c < 9; ++c) R[t][c] = 0.0;
+    VAcc<T, TPL> S;
     for (int jc = jb, ce; jc < je; jc = ce) {
         ce = je - jc > jtile ? jc + jtile : je;  // no jc + jtile past je (int range)
         const int lo = min(max(d0, jc), ce);
@@ -233,37 +210,40 @@ __device__ __forceinline__ void vjp_general(const V *__restrict__ pm, const V *_
         vsweep<T, V, TPL, PHI, false>(pm, cot, hi, ce, K, eps2, S);
 #pragma unroll
         for (int t = 0; t < TPL; ++t) {
-            T f[kVN];
-            vflatten(S, t, f);
 #pragma unroll
-            for (int c = 0; c < 15; ++c) R[t][c] += (double)f[c];
+            for (int c = 0; c < 3; ++c) {
+                R[t][c] += (double)S.X[t][c];
+                R[t][4 + c] += (double)S.A[t][c];
+            }
+            R[t][3] += (double)S.M[t];
+            R[t][7] += (double)S.F[t];
+            if (PHI) R[t][8] += (double)S.H[t];
         }
     }
 #pragma unroll
     for (int t = 0; t < TPL; ++t) {
         const int i = t0 + t * 64 + lane;
         if (i >= n) continue;
-        const double mk = K.m[t];
         const double pbk = PHI ? (double)K.pb[t] : 0.0;
         double o[8];
-        o[4] = G * R[t][7];
-        o[5] = G * R[t][8];
-        o[6] = G * R[t][9];
-        o[7] = -G * R[t][10];
-        o[0] = G * (R[t][0] - 3.0 * R[t][3]);
-        o[1] = G * (R[t][1] - 3.0 * R[t][4]);
-        o[2] = G * (R[t][2] - 3.0 * R[t][5]);
-        o[3] = -G * R[t][6];
+        o[4] = G * R[t][4];
+        o[5] = G * R[t][5];
+        o[6] = G * R[t][6];
+        o[7] = -G * R[t][7];
+        o[0] = G * R[t][0];
+        o[1] = G * R[t][1];
+        o[2] = G * R[t][2];
+        o[3] = -G * R[t][3];
         if (PHI) {
-            o[0] += -G * mk * R[t][11] - pbk * o[4];
-            o[1] += -G * mk * R[t][12] - pbk * o[5];
-            o[2] += -G * mk * R[t][13] - pbk * o[6];
-            o[3] += -G * R[t][14];
+            o[0] -= pbk * o[4];
+            o[1] -= pbk * o[5];
+            o[2] -= pbk * o[6];
+            o[3] -= G * R[t][8];
         }
         if (gridDim.y == 1) {
             apply_out(o, scale, accumulate, i, pos_cot, mass_cot, acc_out);
         } else {
-            double4 *dst = partial + 2 * ((long)blockIdx.y * n + i);
+            double4 *dst = partial + 2 * split_at(i, blockIdx.y, gridDim.y, n);
             dst[0] = make_double4(o[0], o[1], o[2], o[3]);
             dst[1] = make_double4(o[4], o[5], o[6], o[7]);
         }
@@ -285,7 +265,7 @@ __global__ __launch_bounds__(kBlock) void k_vjp(const V *__restrict__ pm, const 
 // With at = abar / m per body, e = at_j - at_k and s1 = m_j w:
 //   xbar_k = G m_k [sum s1 e - 3 sum (s1 rho^2)(d . e) d]
 //   mbar_k = -G [sum s1 (d . e) + at_k . sum s1 d],   a_k = G sum s1 d
-// 28 VALU per pair (no potential), against 34 for the general form.
+// 28 VALU per pair (no potential), against 35 for the general form.
 template <typename T, int TPL>
 struct SAcc {
     T P[TPL][3], Q[TPL][3], M[TPL], F[TPL][3];
@@ -423,7 +403,7 @@ __device__ __forceinline__ void vjp_scaled(const V *__restrict__ pm, const V *__
         if (gridDim.y == 1) {
             apply_out(o, scale, accumulate, i, pos_cot, mass_cot, acc_out);
         } else {
-            double4 *dst = partial + 2 * ((long)blockIdx.y * n + i);
+            double4 *dst = partial + 2 * split_at(i, blockIdx.y, gridDim.y, n);
             dst[0] = make_double4(o[0], o[1], o[2], o[3]);
             dst[1] = make_double4(o[4], o[5], o[6], o[7]);
         }
@@ -469,7 +449,10 @@ __global__ __launch_bounds__(kBlock) void k_prescale(const V *__restrict__ cot,
     if (!(p.w > 0)) atomicOr(nonpos, 1);
 }
 
-// Fixed-order sum of the per-split records, then the same output step.
+// Fixed-order sum of the per-split records (8 lanes per target, see split_sum:
+// 8.9 us at 16384 bodies and 32 splits, 13.1 with one lane per target), then
+// the same output step.
+constexpr int kVjpLanes = 8;
 template <typename V, typename MT>
 __global__ __launch_bounds__(kBlock) void k_vjp_reduce(const double4 *__restrict__ partial, int js,
                                                        int n, double scale, int accumulate,
@@ -477,15 +460,10 @@ __global__ __launch_bounds__(kBlock) void k_vjp_reduce(const double4 *__restrict
                                                        MT *__restrict__ mass_cot,
                                                        V *__restrict__ acc_out)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    double o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int s = 0; s < js; ++s) {
-        const double4 *src = partial + 2 * ((long)s * n + i);
-        const double4 a = src[0], b = src[1];
-        o[0] += a.x; o[1] += a.y; o[2] += a.z; o[3] += a.w;
-        o[4] += b.x; o[5] += b.y; o[6] += b.z; o[7] += b.w;
-    }
+    const int i = (int)(((long)blockIdx.x * kBlock + threadIdx.x) / kVjpLanes);
+    double o[8];
+    split_sum<kVjpLanes>(reinterpret_cast<const double *>(partial), js, n, min(i, n - 1), o);
+    if (threadIdx.x % kVjpLanes || i >= n) return;
     apply_out(o, scale, accumulate, i, pos_cot, mass_cot, acc_out);
 }
 
@@ -526,15 +504,10 @@ __global__ __launch_bounds__(kBlock) void k_vjp_reduce_post(
     MT *__restrict__ mass_cot, V *__restrict__ x, V *__restrict__ vh, V *__restrict__ vbar,
     V *__restrict__ vsc, S hk, S dt)
 {
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    double o[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int s = 0; s < js; ++s) {
-        const double4 *src = partial + 2 * ((long)s * n + i);
-        const double4 a = src[0], b = src[1];
-        o[0] += a.x; o[1] += a.y; o[2] += a.z; o[3] += a.w;
-        o[4] += b.x; o[5] += b.y; o[6] += b.z; o[7] += b.w;
-    }
+    const int i = (int)(((long)blockIdx.x * kBlock + threadIdx.x) / kVjpLanes);
+    double o[8];
+    split_sum<kVjpLanes>(reinterpret_cast<const double *>(partial), js, n, min(i, n - 1), o);
+    if (threadIdx.x % kVjpLanes || i >= n) return;
     V g = pos_cot[i];
     g.x = (S)(o[0] * scale + (double)g.x);
     g.y = (S)(o[1] * scale + (double)g.y);
@@ -612,6 +585,8 @@ __global__ __launch_bounds__(kBlock) void k_reverse(V *__restrict__ x, V *__rest
     vsc[i] = o;
 }
 
+dim3 vjp_reduce_grid(int n) { return dim3((unsigned)(((long)n * kVjpLanes + kBlock - 1) / kBlock)); }
+
 template <typename T, typename V, typename MT, int TPL>
 hipError_t go_vjp(const void *pm, const void *cot, int n, T eps2, double G, const Tune &t, double scale,
                   int accumulate, bool phi, void *pos_cot, void *mass_cot, void *acc_out,
@@ -629,7 +604,7 @@ hipError_t go_vjp(const void *pm, const void *cot, int n, T eps2, double G, cons
                            (MT *)mass_cot, (V *)acc_out, (double4 *)partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || t.jsplit == 1) return e;
-    hipLaunchKernelGGL((k_vjp_reduce<V, MT>), dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL((k_vjp_reduce<V, MT>), vjp_reduce_grid(n), dim3(kBlock), 0, s,
                        (const double4 *)partial, t.jsplit, n, scale, accumulate, (V *)pos_cot,
                        (MT *)mass_cot, (V *)acc_out);
     return hipGetLastError();
@@ -749,7 +724,7 @@ hipError_t go_vjp_adj(const void *pm, const void *raw, const void *sc, const int
                        (V *)pos_cot, (MT *)mass_cot, (V *)acc_out, (double4 *)partial);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || t.jsplit == 1) return e;
-    hipLaunchKernelGGL((k_vjp_reduce<V, MT>), dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
+    hipLaunchKernelGGL((k_vjp_reduce<V, MT>), vjp_reduce_grid(n), dim3(kBlock), 0, s,
                        (const double4 *)partial, t.jsplit, n, scale, 1, (V *)pos_cot,
                        (MT *)mass_cot, (V *)acc_out);
     return hipGetLastError();
@@ -789,7 +764,7 @@ hipError_t launch_vjp_adj_step(int prec, int post, void *pm, void *raw, void *sc
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const dim3 rg((n + kBlock - 1) / kBlock);
+    const dim3 rg = vjp_reduce_grid(n);
     if (prec == NBODY_F64) {
         if (post == 2)
             hipLaunchKernelGGL((k_vjp_reduce_post<double4, double, double, 2>), rg, dim3(kBlock), 0, s,
