@@ -129,7 +129,7 @@ int nbody_permute(const void *src, void *dst, const int32_t *perm, int64_t n,
  * acc_pot_out: target_count records, entry t for target target_begin + t;
  * it must not overlap pos_mass.  Deterministic: the same inputs and tuning
  * give bitwise the same output.
- * Unless a shape is pinned (nbody_set_tuning), all of 45056 to 2^24 bodies as
+ * Unless a shape is pinned (nbody_set_tuning), all of 22528 to 2^24 bodies as
  * targets in an FP32 mode evaluate every unordered pair once and add the sums
  * across tiles in FP64 in every mode; this takes up to 1 GiB of library
  * scratch (where that cannot be allocated, the split sweep runs instead), and

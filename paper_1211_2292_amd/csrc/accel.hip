@@ -535,14 +535,14 @@ __global__ __launch_bounds__(kSliceThreads) void k_accel_slice(const typename Sl
 }
 
 // Fixed-order reduction of the per-split records.
-template <typename OUT>
-__global__ __launch_bounds__(kBlock) void k_split_reduce(const double4 *__restrict__ partial,
+template <typename OUT, typename E = double>
+__global__ __launch_bounds__(kBlock) void k_split_reduce(const void *__restrict__ partial,
                                                          int js, int tcount, double G,
                                                          OUT *__restrict__ out)
 {
     const long k = ((long)blockIdx.x * kBlock + threadIdx.x) / kSumLanes;
     double r[4];
-    split_sum<kSumLanes>(reinterpret_cast<const double *>(partial), js, tcount, min(k, (long)tcount - 1), r);
+    split_sum<kSumLanes>(reinterpret_cast<const E *>(partial), js, tcount, min(k, (long)tcount - 1), r);
     if (threadIdx.x % kSumLanes == 0 && k < tcount) put(out, k, r, G);
 }
 
@@ -722,8 +722,8 @@ hipError_t go_f32(const float4 *pm, int n, float eps2, double G, float4 *out, in
         hipLaunchKernelGGL(k_split_reduce_f32, dim3(rb), dim3(kBlock), 0, s,
                            (const float4 *)partial, t.jsplit, tcount, (float)G, out);
     else
-        hipLaunchKernelGGL(k_split_reduce<float4>, dim3(rb), dim3(kBlock), 0, s,
-                           (const double4 *)partial, t.jsplit, tcount, G, out);
+        hipLaunchKernelGGL((k_split_reduce<float4, double>), dim3(rb), dim3(kBlock), 0, s,
+                           partial, t.jsplit, tcount, G, out);
     return hipGetLastError();
 }
 
@@ -738,8 +738,8 @@ hipError_t go_f64(const double4 *pm, int n, double eps2, double G, double4 *out,
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || t.jsplit == 1 || !reduce) return e;
     const unsigned rb = split_reduce_blocks(tcount);
-    hipLaunchKernelGGL(k_split_reduce<double4>, dim3(rb), dim3(kBlock), 0, s,
-                       (const double4 *)partial, t.jsplit, tcount, G, out);
+    hipLaunchKernelGGL((k_split_reduce<double4, double>), dim3(rb), dim3(kBlock), 0, s,
+                       partial, t.jsplit, tcount, G, out);
     return hipGetLastError();
 }
 
@@ -792,9 +792,15 @@ int accel_partial_records(int tcount, const Tune &t)
     return t.jsplit > 1 ? t.jsplit : 0;
 }
 
+RecordKind accel_record_kind(int prec, int tcount, const Tune &t)
+{
+    if (t.path == kPathSym) return sym_plan(tcount).tpl == 2 ? kRecTile : kRecF64;
+    return prec == NBODY_F32 ? kRecF32 : kRecF64;
+}
+
 size_t accel_partial_bytes(int prec, int tcount, const Tune &t)
 {
-    const size_t rec = (prec == NBODY_F32 && t.path == kPathSweep) ? sizeof(float4) : sizeof(double4);
+    const size_t rec = accel_record_kind(prec, tcount, t) == kRecF64 ? sizeof(double4) : sizeof(float4);
     return rec * (size_t)accel_partial_records(tcount, t) * (size_t)tcount;
 }
 
@@ -825,8 +831,10 @@ hipError_t launch_accel(int prec, const void *pm, int n, double G, double eps, v
     if (t.path == kPathSym) {  // all bodies
         const hipError_t e = launch_sym(pm, n, eps, partial, s);
         if (e != hipSuccess || !reduce) return e;
-        hipLaunchKernelGGL(k_split_reduce<float4>, dim3(split_reduce_blocks(n)), dim3(kBlock), 0, s,
-                           (const double4 *)partial, accel_partial_records(n, t), n, G, (float4 *)out);
+        const auto kernel = accel_record_kind(prec, n, t) == kRecTile ? k_split_reduce<float4, float>
+                                                                      : k_split_reduce<float4, double>;
+        hipLaunchKernelGGL(kernel, dim3(split_reduce_blocks(n)), dim3(kBlock), 0, s, (const void *)partial,
+                           accel_partial_records(n, t), n, G, (float4 *)out);
         return hipGetLastError();
     }
     if (prec == NBODY_F64) {

@@ -126,16 +126,27 @@ hipError_t launch_accel(int prec, const void *pm, int n, double G, double eps, v
                         bool reduce = true);
 size_t accel_partial_bytes(int prec, int tcount, const Tune &t);
 int accel_partial_records(int tcount, const Tune &t);
+// What those records hold: FP64 sums, FP32 sums to be added in FP32, or FP32
+// tile sums to be added in FP64.
+enum RecordKind { kRecF64 = 0, kRecF32 = 1, kRecTile = 2 };
+RecordKind accel_record_kind(int prec, int tcount, const Tune &t);
 
 // ---- force on all bodies, each unordered pair once (sym.hip) -----------------
-// M blocks; each launch takes `runs` runs of `len` block distances.  The sums
-// meet in `slots` = runs (1 + len) records per body, kSymScratch bytes at most
-// (two records per body if that is more), to be added per body in slot order.
-constexpr int kSymBlock = 1024;
+// M blocks of 256 tpl bodies; each launch takes `runs` runs of `len` block
+// distances.  The sums meet in `slots` = runs (1 + len) records per body,
+// kSymScratch bytes at most (two records per body if that is more), to be added
+// per body in slot order in FP64.  With blocks of 512 bodies every record is one
+// tile's partial sum, in FP32 as the modes define it (len is 1 then).
+// Blocks of 512 bodies (2 targets per lane) below kSymWide: there the tiles of
+// 1024 x 1024 are too few to fill 256 CUs evenly (40001 bodies 356 / 458 us,
+// 65536 885 / 904); above, 4 targets per lane need half the rotations per pair
+// (100000 bodies 2081 / 1954 us).
+constexpr int kSymWide = 72 * 1024;
 constexpr size_t kSymScratch = size_t(1) << 30;
 struct SymPlan {
-    int blocks = 0, len = 0, runs = 0, launches = 0;
+    int tpl = 0, blocks = 0, len = 0, runs = 0, launches = 0;
     int slots() const { return runs * (1 + len); }
+    size_t record() const { return tpl == 2 ? sizeof(float4) : sizeof(double4); }
 };
 SymPlan sym_plan(int n);
 hipError_t launch_sym(const void *pm, int n, double eps, void *slots, hipStream_t s);
@@ -182,7 +193,7 @@ int step_blocks(int n);
 // Split reduction of the force (js partial records per body, as left by
 // launch_accel(..., reduce = false) for all n targets) fused with the step:
 // acc receives the reduced force, then the kick/drift of launch_step runs.
-hipError_t launch_reduce_step(int prec, const void *partial, int js, double G, void *pm, void *vel,
+hipError_t launch_reduce_step(int prec, RecordKind kind, const void *partial, int js, double G, void *pm, void *vel,
                               void *acc, int n, double h, double dt, bool close, bool open,
                               double *epart, int *eblocks, hipStream_t s);
 // Energies of `states` states whose partials follow one another, nblocks each.

@@ -268,11 +268,12 @@ static void save_cache_locked()
 constexpr int64_t kSliceMaxF32 = 8192, kSliceMaxF64 = 4096;
 
 // Bodies from which a force on all of them evaluates every unordered pair once
-// (sym.hip).  Its tiles of 1024 x 1024 bodies have to fill 256 CUs evenly: with
-// 44 blocks (990 tiles) it takes 454 us against 530 for the split sweep, with
-// 40 it was 5-9% slower.  65536 bodies: 927 / 1085 us, 2^18: 13.3 / 16.7 ms,
-// 2^20: 212.8 / 256.6 ms.  Above kSymMax its sums no longer fit kSymScratch.
-constexpr int64_t kSymMin = 44 * kSymBlock, kSymMax = int64_t(1) << 24;
+// (sym.hip).  Its tiles have to fill 256 CUs evenly: with 46 blocks of 512
+// bodies (23457) it takes 148 us against 160 for the split sweep, with 51 169 /
+// 186, but with 40 122 / 116.  40001 bodies 356 / 420 us, 65536 885 / 1085, 2^18
+// 13.3 / 16.7 ms, 2^20 207.5 / 256.6 ms.  Above kSymMax its sums no longer fit
+// kSymScratch.
+constexpr int64_t kSymMin = 44 * 512, kSymMax = int64_t(1) << 24;
 
 // Sources per split that the force + VJP sweep keeps: a few thousand bodies
 // leave most of the chip idle otherwise (256 / 128 / 64 sources: 1000 bodies 48
@@ -522,9 +523,7 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
             NB_CHECK(force_scratch(prec, n, t, partial));
             if (const int records = accel_partial_records(n, t); records && step) {
                 NB_TRY(launch_accel(prec, pm, n, G, eps, acc, 0, n, t, partial, s, false), "force kernel");
-                // the pairwise path keeps FP64 records in every mode
-                const int rprec = t.path == kPathSym ? NBODY_F32_F64ACC : prec;
-                NB_TRY(launch_reduce_step(rprec, partial, records, G, pm, vel, acc, n, h, dt, close, open,
+                NB_TRY(launch_reduce_step(prec, accel_record_kind(prec, n, t), partial, records, G, pm, vel, acc, n, h, dt, close, open,
                                           ep, &eb, s),
                        "reduce + step kernel");
                 return NBODY_OK;

@@ -198,7 +198,7 @@ hipError_t launch_step(int prec, void *pm, void *vel, const void *acc, int n, do
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_step(int prec, const void *partial, int js, double G, void *pm, void *vel,
+hipError_t launch_reduce_step(int prec, RecordKind kind, const void *partial, int js, double G, void *pm, void *vel,
                               void *acc, int n, double h, double dt, bool close, bool open,
                               double *epart, int *eblocks, hipStream_t s)
 {
@@ -208,7 +208,12 @@ hipError_t launch_reduce_step(int prec, const void *partial, int js, double G, v
         hipLaunchKernelGGL((k_reduce_step<double4, double, double4, double, double>), dim3(nb),
                            dim3(kReduceThreads), 0, s, (const double4 *)partial, js, G, (double4 *)pm,
                            (double4 *)vel, (double4 *)acc, n, h, dt, (int)close, (int)open, epart);
-    else if (prec == NBODY_F32)
+    else if (kind == kRecTile)
+        hipLaunchKernelGGL((k_reduce_step<float4, float, float4, double, double>), dim3(nb),
+                           dim3(kReduceThreads), 0, s, (const float4 *)partial, js, G, (float4 *)pm,
+                           (float4 *)vel, (float4 *)acc, n, (float)h, (float)dt, (int)close,
+                           (int)open, epart);
+    else if (kind == kRecF32)
         hipLaunchKernelGGL((k_reduce_step<float4, float, float4, float, float>), dim3(nb),
                            dim3(kReduceThreads), 0, s, (const float4 *)partial, js, (float)G, (float4 *)pm,
                            (float4 *)vel, (float4 *)acc, n, (float)h, (float)dt, (int)close,

@@ -5,7 +5,8 @@
 // reciprocal square root and rho^2 serve both bodies: 19 FP32 instructions
 // and one v_rsq_f32 for two interactions, against 2 x (13 + 1).
 //
-// * The bodies form M blocks of B = 256 TPL (the last one may be short).
+// * The bodies form M blocks of B = 256 TPL, TPL 2 or 4 (the last one may be
+//   short).
 //   Every pair of blocks (I, J = I + d mod M), d = 0 .. M/2, is one tile (for
 //   even M and d = M/2 only the first half of the I).  A workgroup of 4 waves
 //   takes block I and a run of consecutive d.
@@ -32,13 +33,14 @@
 // at the rates measured in isolation (1.75 instructions per clock and CU, 2.1
 // clocks per v_rsq_f32, 1.1 per DPP move) take 56 clocks for 512 interactions
 // of a wave; it runs at 60 (1.41 instructions per clock, 2.36 GHz).  A step of
-// 2^20 bodies takes 212.8 ms, 5.17e12 interactions per second, against 256.6
-// for the one-sided sweep with 8 source splits.  The reciprocal square roots and the DPP
-// moves, which issue alone, stand together at raised wave priority (see
-// rsq_prio).  TPL = 4 and 4 waves per SIMD (99 VGPRs, 40 KB of LDS) measured
-// best: with 2 targets per lane the rotation costs twice as much per pair.
+// 2^20 bodies takes 207.5 ms, 5.3e12 interactions per second, against 256.6
+// for the one-sided sweep with 8 source splits.  The reciprocal square roots
+// and the DPP moves, which issue alone, stand together at raised wave priority
+// (see rsq_prio).  4 targets per lane and 4 waves per SIMD (128 VGPRs, 40 KB of
+// LDS) measured best for many tiles, 2 targets and 6 waves for few (kSymWide).
 #include <algorithm>
 #include <cfloat>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -147,116 +149,76 @@ __device__ __forceinline__ void sym_chunk(const float4 *jp, int j0, int n, int s
     }
 }
 
-// The unmasked two-sided 64 steps of 4 targets, with the registers laid out
-// by hand: an FMA whose accumulator lies in the register bank (number mod 4)
-// of a multiplicand issues at half the rate, so dx, dy, dz sit in banks 0, 1,
-// 2, the weights and eps2 in bank 3, and the x, y, z sums in banks 1, 2, 0
-// (the compiler's own allocation put a third of the FMAs in conflict: 215.4 ms
-// per step of 2^20 bodies against 213.7).  Each step reads the next step's
-// record before it uses its own; the DPP moves and the reciprocal square roots,
-// which issue alone, stand together at raised priority.
-//   v16-31 targets (x, y, z, m) x 4     v32-47 their sums (az, ax, ay, ph) x 4
-//   v48-51 sources' sums (az, ax, ay, ph)      v55 eps2
-//   v56-59, v60-63 source records       v64-95 temporaries, 8 per target
-#define NB_SYM_STEP(NEXT, OFF, QX, QY, QZ, QM) \
-    "s_waitcnt lgkmcnt(0)\n" \
-    "ds_read_b128 v[" NEXT "], %[addr] offset:" OFF "\n" \
-    "v_sub_f32 v64, v" QX ", v16\n" \
-    "v_sub_f32 v72, v" QX ", v20\n" \
-    "v_sub_f32 v80, v" QX ", v24\n" \
-    "v_sub_f32 v88, v" QX ", v28\n" \
-    "v_sub_f32 v65, v" QY ", v17\n" \
-    "v_sub_f32 v73, v" QY ", v21\n" \
-    "v_sub_f32 v81, v" QY ", v25\n" \
-    "v_sub_f32 v89, v" QY ", v29\n" \
-    "v_sub_f32 v66, v" QZ ", v18\n" \
-    "v_sub_f32 v74, v" QZ ", v22\n" \
-    "v_sub_f32 v82, v" QZ ", v26\n" \
-    "v_sub_f32 v90, v" QZ ", v30\n" \
-    "v_fma_f32 v67, v64, v64, v55\n" \
-    "v_fma_f32 v75, v72, v72, v55\n" \
-    "v_fma_f32 v83, v80, v80, v55\n" \
-    "v_fma_f32 v91, v88, v88, v55\n" \
-    "v_fmac_f32 v67, v65, v65\n" \
-    "v_fmac_f32 v75, v73, v73\n" \
-    "v_fmac_f32 v83, v81, v81\n" \
-    "v_fmac_f32 v91, v89, v89\n" \
-    "v_fmac_f32 v67, v66, v66\n" \
-    "v_fmac_f32 v75, v74, v74\n" \
-    "v_fmac_f32 v83, v82, v82\n" \
-    "v_fmac_f32 v91, v90, v90\n" \
-    "s_setprio 1\n" \
-    "v_mov_b32_dpp v49, v49 wave_rol:1 row_mask:0xf bank_mask:0xf\n" \
-    "v_mov_b32_dpp v50, v50 wave_rol:1 row_mask:0xf bank_mask:0xf\n" \
-    "v_mov_b32_dpp v48, v48 wave_rol:1 row_mask:0xf bank_mask:0xf\n" \
-    "v_rsq_f32 v67, v67\n" \
-    "v_rsq_f32 v75, v75\n" \
-    "v_rsq_f32 v83, v83\n" \
-    "v_rsq_f32 v91, v91\n" \
-    "s_setprio 0\n" \
-    "v_mul_f32 v68, v67, v67\n" \
-    "v_mul_f32 v76, v75, v75\n" \
-    "v_mul_f32 v84, v83, v83\n" \
-    "v_mul_f32 v92, v91, v91\n" \
-    "v_mul_f32 v69, v" QM ", v67\n" \
-    "v_mul_f32 v77, v" QM ", v75\n" \
-    "v_mul_f32 v85, v" QM ", v83\n" \
-    "v_mul_f32 v93, v" QM ", v91\n" \
-    "v_mul_f32 v70, v19, v67\n" \
-    "v_mul_f32 v78, v23, v75\n" \
-    "v_mul_f32 v86, v27, v83\n" \
-    "v_mul_f32 v94, v31, v91\n" \
-    "v_mul_f32 v67, v69, v68\n" \
-    "v_mul_f32 v75, v77, v76\n" \
-    "v_mul_f32 v83, v85, v84\n" \
-    "v_mul_f32 v91, v93, v92\n" \
-    "v_mul_f32 v71, -v70, v68\n" \
-    "v_mul_f32 v79, -v78, v76\n" \
-    "v_mul_f32 v87, -v86, v84\n" \
-    "v_mul_f32 v95, -v94, v92\n" \
-    "v_add_f32_dpp v51, v51, v70 wave_rol:1 row_mask:0xf bank_mask:0xf\n" \
-    "v_add_f32 v35, v35, v69\n" \
-    "v_fmac_f32 v33, v67, v64\n" \
-    "v_fmac_f32 v34, v67, v65\n" \
-    "v_fmac_f32 v32, v67, v66\n" \
-    "v_fmac_f32 v49, v71, v64\n" \
-    "v_fmac_f32 v50, v71, v65\n" \
-    "v_fmac_f32 v48, v71, v66\n" \
-    "v_add_f32 v51, v51, v78\n" \
-    "v_add_f32 v39, v39, v77\n" \
-    "v_fmac_f32 v37, v75, v72\n" \
-    "v_fmac_f32 v38, v75, v73\n" \
-    "v_fmac_f32 v36, v75, v74\n" \
-    "v_fmac_f32 v49, v79, v72\n" \
-    "v_fmac_f32 v50, v79, v73\n" \
-    "v_fmac_f32 v48, v79, v74\n" \
-    "v_add_f32 v51, v51, v86\n" \
-    "v_add_f32 v43, v43, v85\n" \
-    "v_fmac_f32 v41, v83, v80\n" \
-    "v_fmac_f32 v42, v83, v81\n" \
-    "v_fmac_f32 v40, v83, v82\n" \
-    "v_fmac_f32 v49, v87, v80\n" \
-    "v_fmac_f32 v50, v87, v81\n" \
-    "v_fmac_f32 v48, v87, v82\n" \
-    "v_add_f32 v51, v51, v94\n" \
-    "v_add_f32 v47, v47, v93\n" \
-    "v_fmac_f32 v45, v91, v88\n" \
-    "v_fmac_f32 v46, v91, v89\n" \
-    "v_fmac_f32 v44, v91, v90\n" \
-    "v_fmac_f32 v49, v95, v88\n" \
-    "v_fmac_f32 v50, v95, v89\n" \
-    "v_fmac_f32 v48, v95, v90\n"
+// The unmasked two-sided 64 steps, with the registers laid out by hand: an FMA
+// whose accumulator lies in the register bank (number mod 4) of a multiplicand
+// issues at half the rate, so a pair's dx, dy, dz sit in banks 0, 1, 2, the
+// weights and eps2 in bank 3, and the x, y, z sums in banks 1, 2, 0 (the
+// compiler's own allocation put a third of the FMAs in conflict: 215.4 ms per
+// step of 2^20 bodies against 213.7).  Each step reads the next step's record
+// before it uses its own; the DPP moves and the reciprocal square roots, which
+// issue alone, stand together at raised priority.  Base registers (multiples
+// of 4): T targets (x, y, z, m), S their sums (az, ax, ay, ph), J the sources'
+// sums (az, ax, ay, ph), E + 3 eps2, Q the step's record, D temporaries, 8 per
+// target: dx, dy, dz, r2 then rho then the weight of the target's sums, rho^2,
+// m_j rho, m_i rho, minus the weight of the sources' sums.
+#define NB_EACH(LIST, INS) ".irp t," LIST "\n" INS "\n.endr\n"
+#define NB_SYM_ADD(S, J, D)                                                                                       \
+    "v_add_f32 v[" S "+4*\\t+3], v[" S "+4*\\t+3], v[" D "+8*\\t+5]\n"                                            \
+    "v_fmac_f32 v[" S "+4*\\t+1], v[" D "+8*\\t+3], v[" D "+8*\\t]\n"                                             \
+    "v_fmac_f32 v[" S "+4*\\t+2], v[" D "+8*\\t+3], v[" D "+8*\\t+1]\n"                                           \
+    "v_fmac_f32 v[" S "+4*\\t], v[" D "+8*\\t+3], v[" D "+8*\\t+2]\n"                                             \
+    "v_fmac_f32 v[" J "+1], v[" D "+8*\\t+7], v[" D "+8*\\t]\n"                                                    \
+    "v_fmac_f32 v[" J "+2], v[" D "+8*\\t+7], v[" D "+8*\\t+1]\n"                                                  \
+    "v_fmac_f32 v[" J "], v[" D "+8*\\t+7], v[" D "+8*\\t+2]"
+#define NB_SYM_STEP(LIST, LIST1, T, S, J, E, Q, NEXT, D, OFF)                                                     \
+    "s_waitcnt lgkmcnt(0)\n"                                                                                      \
+    "ds_read_b128 v[" NEXT ":" NEXT "+3], %[addr] offset:" OFF "\n"                                               \
+    NB_EACH(LIST, "v_sub_f32 v[" D "+8*\\t], v[" Q "], v[" T "+4*\\t]")                                           \
+    NB_EACH(LIST, "v_sub_f32 v[" D "+8*\\t+1], v[" Q "+1], v[" T "+4*\\t+1]")                                     \
+    NB_EACH(LIST, "v_sub_f32 v[" D "+8*\\t+2], v[" Q "+2], v[" T "+4*\\t+2]")                                     \
+    NB_EACH(LIST, "v_fma_f32 v[" D "+8*\\t+3], v[" D "+8*\\t], v[" D "+8*\\t], v[" E "+3]")                      \
+    NB_EACH(LIST, "v_fmac_f32 v[" D "+8*\\t+3], v[" D "+8*\\t+1], v[" D "+8*\\t+1]")                             \
+    NB_EACH(LIST, "v_fmac_f32 v[" D "+8*\\t+3], v[" D "+8*\\t+2], v[" D "+8*\\t+2]")                             \
+    "s_setprio 1\n"                                                                                               \
+    "v_mov_b32_dpp v[" J "+1], v[" J "+1] wave_rol:1 row_mask:0xf bank_mask:0xf\n"                                \
+    "v_mov_b32_dpp v[" J "+2], v[" J "+2] wave_rol:1 row_mask:0xf bank_mask:0xf\n"                                \
+    "v_mov_b32_dpp v[" J "], v[" J "] wave_rol:1 row_mask:0xf bank_mask:0xf\n"                                    \
+    NB_EACH(LIST, "v_rsq_f32 v[" D "+8*\\t+3], v[" D "+8*\\t+3]")                                                 \
+    "s_setprio 0\n"                                                                                               \
+    NB_EACH(LIST, "v_mul_f32 v[" D "+8*\\t+4], v[" D "+8*\\t+3], v[" D "+8*\\t+3]")                              \
+    NB_EACH(LIST, "v_mul_f32 v[" D "+8*\\t+5], v[" Q "+3], v[" D "+8*\\t+3]")                                     \
+    NB_EACH(LIST, "v_mul_f32 v[" D "+8*\\t+6], v[" T "+4*\\t+3], v[" D "+8*\\t+3]")                              \
+    NB_EACH(LIST, "v_mul_f32 v[" D "+8*\\t+3], v[" D "+8*\\t+5], v[" D "+8*\\t+4]")                              \
+    NB_EACH(LIST, "v_mul_f32 v[" D "+8*\\t+7], -v[" D "+8*\\t+6], v[" D "+8*\\t+4]")                             \
+    "v_add_f32_dpp v[" J "+3], v[" J "+3], v[" D "+6] wave_rol:1 row_mask:0xf bank_mask:0xf\n"                    \
+    NB_EACH("0", NB_SYM_ADD(S, J, D))                                                                             \
+    NB_EACH(LIST1, "v_add_f32 v[" J "+3], v[" J "+3], v[" D "+8*\\t+6]\n" NB_SYM_ADD(S, J, D))
+// 64 steps, 8 per turn of the loop, the records alternating between Q and P.
+#define NB_SYM_LOOP(LIST, LIST1, T, S, J, E, Q, P, D)                                                             \
+    "ds_read_b128 v[" Q ":" Q "+3], %[addr]\n"                                                                    \
+    ".Lsym%=:\n"                                                                                                  \
+    NB_SYM_STEP(LIST, LIST1, T, S, J, E, Q, P, D, "16") NB_SYM_STEP(LIST, LIST1, T, S, J, E, P, Q, D, "32")       \
+    NB_SYM_STEP(LIST, LIST1, T, S, J, E, Q, P, D, "48") NB_SYM_STEP(LIST, LIST1, T, S, J, E, P, Q, D, "64")       \
+    NB_SYM_STEP(LIST, LIST1, T, S, J, E, Q, P, D, "80") NB_SYM_STEP(LIST, LIST1, T, S, J, E, P, Q, D, "96")       \
+    NB_SYM_STEP(LIST, LIST1, T, S, J, E, Q, P, D, "112") NB_SYM_STEP(LIST, LIST1, T, S, J, E, P, Q, D, "128")     \
+    "v_add_u32 %[addr], 0x80, %[addr]\n"                                                                          \
+    "s_sub_i32 %[cnt], %[cnt], 1\n"                                                                               \
+    "s_cmp_lg_u32 %[cnt], 0\n"                                                                                    \
+    "s_cbranch_scc1 .Lsym%=\n"                                                                                    \
+    "s_waitcnt lgkmcnt(0)\n"                                                                                      \
+    "s_nop 1\n"
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-__device__ __forceinline__ void sym_chunk4(const float4 *jp, SymTargets<4> &T, float eps2,
-                                           float (&s)[4])
+template <int TPL>
+__device__ __forceinline__ void sym_chunk_asm(const float4 *jp, SymTargets<TPL> &T, float eps2, float (&s)[4])
 {
-    f32x16 tg, sum;
+    typename std::conditional<TPL == 4, f32x16, f32x8>::type tg, sum;
     f32x4 js = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < TPL; ++t) {
         tg[4 * t] = T.x[t];
         tg[4 * t + 1] = T.y[t];
         tg[4 * t + 2] = T.z[t];
@@ -268,29 +230,22 @@ __device__ __forceinline__ void sym_chunk4(const float4 *jp, SymTargets<4> &T, f
     }
     unsigned addr = (unsigned)(size_t)(__attribute__((address_space(3))) const float4 *)(jp + (threadIdx.x & 63));
     int cnt = 8;
-    asm volatile("ds_read_b128 v[56:59], %[addr]\n"
-                 ".Lsym%=:\n"
-                 NB_SYM_STEP("60:63", "16", "56", "57", "58", "59")
-                 NB_SYM_STEP("56:59", "32", "60", "61", "62", "63")
-                 NB_SYM_STEP("60:63", "48", "56", "57", "58", "59")
-                 NB_SYM_STEP("56:59", "64", "60", "61", "62", "63")
-                 NB_SYM_STEP("60:63", "80", "56", "57", "58", "59")
-                 NB_SYM_STEP("56:59", "96", "60", "61", "62", "63")
-                 NB_SYM_STEP("60:63", "112", "56", "57", "58", "59")
-                 NB_SYM_STEP("56:59", "128", "60", "61", "62", "63")
-                 "v_add_u32 %[addr], 0x80, %[addr]\n"
-                 "s_sub_i32 %[cnt], %[cnt], 1\n"
-                 "s_cmp_lg_u32 %[cnt], 0\n"
-                 "s_cbranch_scc1 .Lsym%=\n"
-                 "s_waitcnt lgkmcnt(0)\n"
-                 "s_nop 1\n"
-                 : "+{v[32:47]}"(sum), "+{v[48:51]}"(js), [addr] "+v"(addr), [cnt] "+s"(cnt)
-                 : "{v[16:31]}"(tg), "{v55}"(eps2)
-                 : "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63", "v64", "v65", "v66", "v67", "v68", "v69",
-                   "v70", "v71", "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v80", "v81", "v82", "v83",
-                   "v84", "v85", "v86", "v87", "v88", "v89", "v90", "v91", "v92", "v93", "v94", "v95", "scc", "memory");
+    if constexpr (TPL == 4)
+        asm volatile(NB_SYM_LOOP("0,1,2,3", "1,2,3", "16", "32", "48", "52", "56", "60", "64")
+                     : "+{v[32:47]}"(sum), "+{v[48:51]}"(js), [addr] "+v"(addr), [cnt] "+s"(cnt)
+                     : "{v[16:31]}"(tg), "{v55}"(eps2)
+                     : "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63", "v64", "v65", "v66", "v67", "v68",
+                       "v69", "v70", "v71", "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v80", "v81",
+                       "v82", "v83", "v84", "v85", "v86", "v87", "v88", "v89", "v90", "v91", "v92", "v93", "v94",
+                       "v95", "scc", "memory");
+    else
+        asm volatile(NB_SYM_LOOP("0,1", "1", "16", "24", "32", "36", "40", "44", "48")
+                     : "+{v[24:31]}"(sum), "+{v[32:35]}"(js), [addr] "+v"(addr), [cnt] "+s"(cnt)
+                     : "{v[16:23]}"(tg), "{v39}"(eps2)
+                     : "v40", "v41", "v42", "v43", "v44", "v45", "v46", "v47", "v48", "v49", "v50", "v51", "v52",
+                       "v53", "v54", "v55", "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63", "scc", "memory");
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < TPL; ++t) {
         T.az[t] = sum[4 * t];
         T.ax[t] = sum[4 * t + 1];
         T.ay[t] = sum[4 * t + 2];
@@ -321,8 +276,8 @@ __device__ __forceinline__ void sym_phase(const float4 *__restrict__ src, int n,
         q = sym_record(src, (c + 1 < TPL ? jc + 64 : jnext) + lane, n);
         __builtin_amdgcn_wave_barrier();
         float s[4];
-        if constexpr (TPL == 4 && !MASK && BOTH)
-            sym_chunk4(jp, T, eps2, s);
+        if constexpr (!MASK && BOTH)
+            sym_chunk_asm<TPL>(jp, T, eps2, s);
         else
             sym_chunk<TPL, MASK, BOTH>(jp, jc, n, c, T, eps2, s);
         __builtin_amdgcn_wave_barrier();
@@ -355,14 +310,19 @@ __device__ __forceinline__ void sym_store(double4 *p, double4 v, int add)
     }
     *p = v;
 }
+__device__ __forceinline__ void sym_store(float4 *p, double4 v, int)
+{
+    *p = make_float4((float)v.x, (float)v.y, (float)v.z, (float)v.w);
+}
 
 // grid.x = M * runs: workgroup (run, I) takes d = d0 + run * len .. + len - 1.
 // slots: runs (1 + len) records per body, placed as split records (split_at):
 // first the runs' sums of I, then the sums of J per d of the launch.
-template <int TPL>
-__global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_sym(
+// REC float4: one launch and runs of one tile, so that no record is added to.
+template <int TPL, typename REC>
+__global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(TPL == 4 ? 4 : 6))) void k_sym(
     const float4 *__restrict__ src, int n, int M, int d0, int len, int runs, float eps2_in, int add,
-    double4 *__restrict__ slots)
+    REC *__restrict__ slots)
 {
     constexpr int W = 64 * TPL, B = kSymWaves * W;
     __shared__ double4 jacc[B];
@@ -433,12 +393,13 @@ __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(4, 
 SymPlan sym_plan(int n)
 {
     SymPlan p;
-    p.blocks = (int)(((long)n + kSymBlock - 1) / kSymBlock);
+    p.tpl = n < kSymWide ? 2 : 4;
+    p.blocks = (int)(((long)n + kSymThreads * p.tpl - 1) / (kSymThreads * p.tpl));
     const int dist = p.blocks / 2 + 1;  // distances 0 .. M/2
-    const long room = std::max(2L, (long)(kSymScratch / sizeof(double4) / n));  // slots that fit
+    const long room = std::max(2L, (long)(kSymScratch / p.record() / n));  // slots that fit
     // runs of up to 8 tiles: fewer sums of I to store; shorter ones while the
     // tiles are few, so that the launch still fills the chip evenly
-    p.len = (int)std::min(std::min(8L, room - 1), std::max(1L, (long)p.blocks / 64));
+    p.len = p.tpl == 2 ? 1 : (int)std::min(std::min(8L, room - 1), std::max(1L, (long)p.blocks / 64));
     const int all = (dist + p.len - 1) / p.len;
     p.runs = (int)std::min((long)all, std::max(1L, room / (p.len + 1)));
     p.launches = (all + p.runs - 1) / p.runs;
@@ -449,9 +410,14 @@ hipError_t launch_sym(const void *pm, int n, double eps, void *slots, hipStream_
 {
     const SymPlan p = sym_plan(n);
     const float e2 = (float)(eps * eps);
+    if (p.tpl == 2) {
+        hipLaunchKernelGGL((k_sym<2, float4>), dim3((unsigned)p.blocks * p.runs), dim3(kSymThreads), 0, s,
+                           (const float4 *)pm, n, p.blocks, 0, 1, p.runs, e2, 0, (float4 *)slots);
+        return hipGetLastError();
+    }
     hipError_t e = hipSuccess;
     for (int l = 0; l < p.launches && e == hipSuccess; ++l) {
-        hipLaunchKernelGGL(k_sym<kSymBlock / kSymThreads>, dim3((unsigned)p.blocks * p.runs), dim3(kSymThreads), 0, s,
+        hipLaunchKernelGGL((k_sym<4, double4>), dim3((unsigned)p.blocks * p.runs), dim3(kSymThreads), 0, s,
                            (const float4 *)pm, n, p.blocks, l * p.runs * p.len, p.len, p.runs, e2, l > 0 ? 1 : 0,
                            (double4 *)slots);
         e = hipGetLastError();

@@ -358,10 +358,11 @@ def test_small_problem_kernel_edges(orc, mode, n, tb, tc):
     assert rms_rel(out[k, :3], acc) <= bar and rms_rel(out[k, 3], pot) <= bar
 
 
-# 44 blocks of 1024 is the smallest count the pairwise kernels take: full, one
-# body in the last block, one short of full, an odd count, and a size whose
-# sums take two launches (the slots of 2^18 + 1 bodies pass 1 GiB)
-@pytest.mark.parametrize("n", [45056, 45057, 46079, 47104, (1 << 18) + 1])
+# 44 blocks of 512 is the smallest count the pairwise kernels take: full, one
+# body in the last block, one short of full, an odd count; the same around the
+# first size with blocks of 1024; and a size whose sums take two launches (the
+# slots of 2^18 + 1 bodies pass 1 GiB)
+@pytest.mark.parametrize("n", [22528, 22529, 23551, 24064, 73727, 73728, 73729, 74752, (1 << 18) + 1])
 @pytest.mark.parametrize("mode,eps", [("F32_KAHAN", 0.01), ("F32_F64ACC", 0.0), ("F32", 0.02)])
 def test_pairwise_kernel_edges(orc, mode, eps, n):
     """Force on all bodies where every unordered pair is evaluated once, with
@@ -381,7 +382,7 @@ def test_pairwise_kernel_edges(orc, mode, eps, n):
     assert rms_rel(out[tg, :3], acc) <= bar and rms_rel(out[tg, 3], pot) <= bar
 
 
-@pytest.mark.parametrize("n", [45056, 46081])
+@pytest.mark.parametrize("n", [22528, 23041, 74753])
 def test_pairwise_kernel_leapfrog_and_graph(n):
     """The fused reduction and step after the pairwise kernels: one call of
     three steps equals force and kick_drift by hand, and graph replays equal
