@@ -23,9 +23,8 @@
 //   it, so the size-to-distance ratio is below theta for every target.
 //
 // Kernels:
-// * k_tree_leaves, then k_tree_inner once per node height (children are
-//   always lower than their parent): one thread per node, left + right.  The
-//   kernel boundaries order the levels, so no fences or counters are needed.
+// * k_tree_moments: whole subtrees per workgroup, bottom-up through LDS, two or
+//   three launches in all (see there).
 // * k_tree_walk: one wave per group.  The walk starts from the siblings of
 //   the group's ancestors (every cell disjoint from the group) and pops up to
 //   64 cells per step from a 512-entry stack in LDS, one cell per lane: the acceptance
@@ -76,6 +75,7 @@
 // The remaining cells go through the quadrupole path or are opened, with
 // the same tests as above; every decision is the FP64 expression of the
 // definitions, so the lists equal the FP64 definition's.
+#include <algorithm>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -97,113 +97,238 @@ constexpr int kBuf = 128;      // LDS batch entries (cells, near ranges)
 constexpr int kPseudo = 12;    // pseudo-particles per cell (pseudo-particle cells)
 
 
-__device__ __forceinline__ void finish_node(const TreeDev &T, int c, double M, double sx, double sy,
-                                            double sz, float4 lo, float4 hi, double &cx, double &cy,
-                                            double &cz)
+// Moments of a node, as they pass from children to parent.
+template <bool Q2>
+struct Moments {
+    double M, sx, sy, sz;           // sums of m and m x
+    double cx, cy, cz;              // centre of mass
+    float lo[3], hi[3];             // box
+    double s2[Q2 ? 6 : 1];          // second moment about the centre of mass: xx yy zz xy xz yz
+};
+
+// Centre of mass from the sums; the box centre without mass.
+template <bool Q2>
+__device__ __forceinline__ void node_centre(Moments<Q2> &m)
 {
-    if (M > 0.0) {
-        cx = sx / M;
-        cy = sy / M;
-        cz = sz / M;
+    if (m.M > 0.0) {
+        m.cx = m.sx / m.M;
+        m.cy = m.sy / m.M;
+        m.cz = m.sz / m.M;
     } else {
-        cx = 0.5 * ((double)lo.x + (double)hi.x);
-        cy = 0.5 * ((double)lo.y + (double)hi.y);
-        cz = 0.5 * ((double)lo.z + (double)hi.z);
+        m.cx = 0.5 * ((double)m.lo[0] + (double)m.hi[0]);
+        m.cy = 0.5 * ((double)m.lo[1] + (double)m.hi[1]);
+        m.cz = 0.5 * ((double)m.lo[2] + (double)m.hi[2]);
     }
-    const double ex = (double)hi.x - (double)lo.x;
-    const double ey = (double)hi.y - (double)lo.y;
-    const double ez = (double)hi.z - (double)lo.z;
+}
+
+// Stores node c's records (quad: its quadrupole record too).
+template <bool Q2>
+__device__ __forceinline__ void node_store(const TreeDev &T, int c, const Moments<Q2> &m, bool quad)
+{
+    const double ex = (double)m.hi[0] - (double)m.lo[0];
+    const double ey = (double)m.hi[1] - (double)m.lo[1];
+    const double ez = (double)m.hi[2] - (double)m.lo[2];
     double d2 = 0.0;
     d2 = d2 + ex * ex;
     d2 = d2 + ey * ey;
     d2 = d2 + ez * ez;
-    T.sums[c] = make_double4(M, sx, sy, sz);
-    T.comd[c] = make_double4(cx, cy, cz, d2);
-    T.rec[c] = make_float4((float)cx, (float)cy, (float)cz, (float)M);
-    T.lo[c] = lo;
-    T.hi[c] = hi;
+    const float4 rec = make_float4((float)m.cx, (float)m.cy, (float)m.cz, (float)m.M);
+    T.sums[c] = make_double4(m.M, m.sx, m.sy, m.sz);
+    T.comd[c] = make_double4(m.cx, m.cy, m.cz, d2);
+    T.rec[c] = rec;
+    T.lo[c] = make_float4(m.lo[0], m.lo[1], m.lo[2], 0.0f);
+    T.hi[c] = make_float4(m.hi[0], m.hi[1], m.hi[2], 0.0f);
+    if constexpr (Q2) {
+        T.s2a[c] = make_double4(m.s2[0], m.s2[1], m.s2[2], m.s2[3]);
+        T.s2b[c] = make_double4(m.s2[4], m.s2[5], 0.0, 0.0);
+        if (quad) {  // Q = 3 S - trace(S) I in FP64, rounded to FP32
+            const double tr = (m.s2[0] + m.s2[1]) + m.s2[2];
+            float4 *o = T.qr + (long)kQuadRec * c;
+            o[0] = rec;
+            o[1] = make_float4((float)(3.0 * m.s2[0] - tr), (float)(3.0 * m.s2[1] - tr), (float)(3.0 * m.s2[2] - tr),
+                               (float)(3.0 * m.s2[3]));
+            o[2] = make_float4((float)(3.0 * m.s2[4]), (float)(3.0 * m.s2[5]), 0.0f, 0.0f);
+        }
+    }
 }
 
-// Leaves: one thread per leaf sums its bodies in position order (Q2: then
-// the second moment about the centre of mass).
+// A leaf sums its bodies in position order (Q2: then the second moment about
+// the centre of mass).
 template <bool Q2>
-__global__ __launch_bounds__(256) void k_tree_leaves(const float4 *__restrict__ pm, TreeDev T, int nleaves)
+__device__ __forceinline__ void leaf_moments(const float4 *__restrict__ pm, int4 nd, Moments<Q2> &o)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nleaves) return;
-    const int c = T.by_height[t];
-    const int4 nd = T.node[c];
     const float4 p0 = pm[nd.x];
-    float4 lo = make_float4(p0.x, p0.y, p0.z, 0.0f), hi = lo;
-    double M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
+    o.lo[0] = o.hi[0] = p0.x;
+    o.lo[1] = o.hi[1] = p0.y;
+    o.lo[2] = o.hi[2] = p0.z;
+    o.M = o.sx = o.sy = o.sz = 0.0;
     for (int p = nd.x; p < nd.y; ++p) {
         const float4 b = pm[p];
         const double m = b.w;
-        M = M + m;
+        o.M = o.M + m;
         const double mx = m * (double)b.x, my = m * (double)b.y, mz = m * (double)b.z;
-        sx = sx + mx;
-        sy = sy + my;
-        sz = sz + mz;
-        if (b.x < lo.x) lo.x = b.x;
-        if (b.x > hi.x) hi.x = b.x;
-        if (b.y < lo.y) lo.y = b.y;
-        if (b.y > hi.y) hi.y = b.y;
-        if (b.z < lo.z) lo.z = b.z;
-        if (b.z > hi.z) hi.z = b.z;
+        o.sx = o.sx + mx;
+        o.sy = o.sy + my;
+        o.sz = o.sz + mz;
+        if (b.x < o.lo[0]) o.lo[0] = b.x;
+        if (b.x > o.hi[0]) o.hi[0] = b.x;
+        if (b.y < o.lo[1]) o.lo[1] = b.y;
+        if (b.y > o.hi[1]) o.hi[1] = b.y;
+        if (b.z < o.lo[2]) o.lo[2] = b.z;
+        if (b.z > o.hi[2]) o.hi[2] = b.z;
     }
-    double cx, cy, cz;
-    finish_node(T, c, M, sx, sy, sz, lo, hi, cx, cy, cz);
+    node_centre(o);
     if constexpr (Q2) {
-        double xx = 0.0, yy = 0.0, zz = 0.0, xy = 0.0, xz = 0.0, yz = 0.0;
+        for (int k = 0; k < 6; ++k) o.s2[k] = 0.0;
         for (int p = nd.x; p < nd.y; ++p) {
             const float4 b = pm[p];
             const double m = b.w;
-            const double dx = (double)b.x - cx, dy = (double)b.y - cy, dz = (double)b.z - cz;
+            const double dx = (double)b.x - o.cx, dy = (double)b.y - o.cy, dz = (double)b.z - o.cz;
             const double mx = m * dx, my = m * dy, mz = m * dz;
-            xx = xx + mx * dx;
-            yy = yy + my * dy;
-            zz = zz + mz * dz;
-            xy = xy + mx * dy;
-            xz = xz + mx * dz;
-            yz = yz + my * dz;
+            o.s2[0] = o.s2[0] + mx * dx;
+            o.s2[1] = o.s2[1] + my * dy;
+            o.s2[2] = o.s2[2] + mz * dz;
+            o.s2[3] = o.s2[3] + mx * dy;
+            o.s2[4] = o.s2[4] + mx * dz;
+            o.s2[5] = o.s2[5] + my * dz;
         }
-        T.s2a[c] = make_double4(xx, yy, zz, xy);
-        T.s2b[c] = make_double4(xz, yz, 0.0, 0.0);
     }
 }
 
-// Inner nodes of one height (their children are all lower, so finished by
-// the previous launches): left + right (Q2: second moments moved to the
-// parent's centre of mass).
+// An inner node: left + right (Q2: second moments moved to the parent's
+// centre of mass).
 template <bool Q2>
-__global__ __launch_bounds__(256) void k_tree_inner(TreeDev T, int first, int count)
+__device__ __forceinline__ void merge_moments(const Moments<Q2> &a, const Moments<Q2> &b, Moments<Q2> &o)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= count) return;
-    const int c = T.by_height[first + t];
-    const int4 nd = T.node[c];
-    const double4 a = T.sums[nd.z], b = T.sums[nd.w];
-    const float4 la = T.lo[nd.z], lb = T.lo[nd.w], ha = T.hi[nd.z], hb = T.hi[nd.w];
-    const float4 lo = make_float4(la.x < lb.x ? la.x : lb.x, la.y < lb.y ? la.y : lb.y,
-                                  la.z < lb.z ? la.z : lb.z, 0.0f);
-    const float4 hi = make_float4(ha.x > hb.x ? ha.x : hb.x, ha.y > hb.y ? ha.y : hb.y,
-                                  ha.z > hb.z ? ha.z : hb.z, 0.0f);
-    double cx, cy, cz;
-    finish_node(T, c, a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w, lo, hi, cx, cy, cz);
+    for (int k = 0; k < 3; ++k) {
+        o.lo[k] = a.lo[k] < b.lo[k] ? a.lo[k] : b.lo[k];
+        o.hi[k] = a.hi[k] > b.hi[k] ? a.hi[k] : b.hi[k];
+    }
+    o.M = a.M + b.M;
+    o.sx = a.sx + b.sx;
+    o.sy = a.sy + b.sy;
+    o.sz = a.sz + b.sz;
+    node_centre(o);
     if constexpr (Q2) {
-        const double4 ca = T.comd[nd.z], cb = T.comd[nd.w];
-        const double4 pa = T.s2a[nd.z], pb = T.s2a[nd.w], qa = T.s2b[nd.z], qb = T.s2b[nd.w];
-        const double ax = ca.x - cx, ay = ca.y - cy, az = ca.z - cz;
-        const double bx = cb.x - cx, by = cb.y - cy, bz = cb.z - cz;
-        const double ma = a.x, mb = b.x;
-        const double xx = (pa.x + ma * ax * ax) + (pb.x + mb * bx * bx);
-        const double yy = (pa.y + ma * ay * ay) + (pb.y + mb * by * by);
-        const double zz = (pa.z + ma * az * az) + (pb.z + mb * bz * bz);
-        const double xy = (pa.w + ma * ax * ay) + (pb.w + mb * bx * by);
-        const double xz = (qa.x + ma * ax * az) + (qb.x + mb * bx * bz);
-        const double yz = (qa.y + ma * ay * az) + (qb.y + mb * by * bz);
-        T.s2a[c] = make_double4(xx, yy, zz, xy);
-        T.s2b[c] = make_double4(xz, yz, 0.0, 0.0);
+        const double ax = a.cx - o.cx, ay = a.cy - o.cy, az = a.cz - o.cz;
+        const double bx = b.cx - o.cx, by = b.cy - o.cy, bz = b.cz - o.cz;
+        const double ma = a.M, mb = b.M;
+        o.s2[0] = (a.s2[0] + ma * ax * ax) + (b.s2[0] + mb * bx * bx);
+        o.s2[1] = (a.s2[1] + ma * ay * ay) + (b.s2[1] + mb * by * by);
+        o.s2[2] = (a.s2[2] + ma * az * az) + (b.s2[2] + mb * bz * bz);
+        o.s2[3] = (a.s2[3] + ma * ax * ay) + (b.s2[3] + mb * bx * by);
+        o.s2[4] = (a.s2[4] + ma * ax * az) + (b.s2[4] + mb * bx * bz);
+        o.s2[5] = (a.s2[5] + ma * ay * az) + (b.s2[5] + mb * by * bz);
+    }
+}
+
+// Moments, one subtree of up to K inputs per workgroup of K threads.  ent lists
+// a subtree's inputs (the leaves, or in later launches the subtree roots that
+// the launch before finished), then its inner nodes by height above them, as
+// (node, left, right, height) with left and right places in the list.  The
+// nodes pass their moments up through LDS, a barrier between heights.  One
+// launch per node height, with the children read back from memory, took 17
+// launches of 4 to 7 us at 10^5 bodies (leaf 4), 77 us more per evaluation than
+// the two launches now.
+template <bool Q2, int K>
+struct MomentLds {  // one array per field: neighbouring nodes lie in neighbouring banks
+    double d[Q2 ? 13 : 7][2 * K];
+    float f[6][2 * K];
+    __device__ void put(int e, const Moments<Q2> &m)
+    {
+        d[0][e] = m.M;
+        d[1][e] = m.sx;
+        d[2][e] = m.sy;
+        d[3][e] = m.sz;
+        if constexpr (Q2) {
+            d[4][e] = m.cx;
+            d[5][e] = m.cy;
+            d[6][e] = m.cz;
+            for (int k = 0; k < 6; ++k) d[7 + k][e] = m.s2[k];
+        }
+        for (int k = 0; k < 3; ++k) {
+            f[k][e] = m.lo[k];
+            f[3 + k][e] = m.hi[k];
+        }
+    }
+    __device__ Moments<Q2> get(int e) const
+    {
+        Moments<Q2> m;
+        m.M = d[0][e];
+        m.sx = d[1][e];
+        m.sy = d[2][e];
+        m.sz = d[3][e];
+        if constexpr (Q2) {
+            m.cx = d[4][e];
+            m.cy = d[5][e];
+            m.cz = d[6][e];
+            for (int k = 0; k < 6; ++k) m.s2[k] = d[7 + k][e];
+        }
+        for (int k = 0; k < 3; ++k) {
+            m.lo[k] = f[k][e];
+            m.hi[k] = f[3 + k][e];
+        }
+        return m;
+    }
+};
+
+template <bool Q2, int K, bool LEAVES>
+__global__ __launch_bounds__(K) void k_tree_moments(const float4 *__restrict__ pm, TreeDev T,
+                                                    const int4 *__restrict__ ent, const int2 *__restrict__ sub,
+                                                    int quad)
+{
+    __shared__ MomentLds<Q2, K> lds;
+    const int2 range = sub[blockIdx.x];  // first entry, entries
+    ent += range.x;
+    const int heights = ent[range.y - 1].w;  // the list is ordered by height
+    // this thread's two places in it
+    int4 mine[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int e = threadIdx.x + u * K;
+        mine[u] = e < range.y ? ent[e] : make_int4(0, 0, 0, -1);
+    }
+    for (int h = 0; h <= heights; ++h) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int4 d = mine[u];
+            if (d.w != h) continue;
+            Moments<Q2> m;
+            if (h > 0) {
+                merge_moments(lds.get(d.y), lds.get(d.z), m);
+                node_store(T, d.x, m, quad);
+            } else if (LEAVES) {
+                leaf_moments(pm, T.node[d.x], m);
+                node_store(T, d.x, m, quad);
+            } else {
+                const double4 a = T.sums[d.x], c = T.comd[d.x];
+                const float4 lo = T.lo[d.x], hi = T.hi[d.x];
+                m.M = a.x;
+                m.sx = a.y;
+                m.sy = a.z;
+                m.sz = a.w;
+                m.cx = c.x;
+                m.cy = c.y;
+                m.cz = c.z;
+                m.lo[0] = lo.x;
+                m.lo[1] = lo.y;
+                m.lo[2] = lo.z;
+                m.hi[0] = hi.x;
+                m.hi[1] = hi.y;
+                m.hi[2] = hi.z;
+                if constexpr (Q2) {
+                    const double4 p = T.s2a[d.x], q = T.s2b[d.x];
+                    m.s2[0] = p.x;
+                    m.s2[1] = p.y;
+                    m.s2[2] = p.z;
+                    m.s2[3] = p.w;
+                    m.s2[4] = q.x;
+                    m.s2[5] = q.y;
+                }
+            }
+            lds.put(threadIdx.x + u * K, m);
+        }
+        __syncthreads();
     }
 }
 
@@ -245,21 +370,6 @@ __global__ __launch_bounds__(256) void k_tree_pseudo(TreeDev T, int nn)
         q = q + 5.0 / (2.0 * kPseudo * a * a) * (3.0 * sSs - tr);
     }
     T.pp[t] = make_float4((float)(cd.x + a * s0), (float)(cd.y + a * s1), (float)(cd.z + a * s2), (float)q);
-}
-
-// Quadrupole records, one thread per node: Q = 3 S - trace(S) I in FP64,
-// rounded to FP32.
-__global__ __launch_bounds__(256) void k_tree_quad(TreeDev T, int nn)
-{
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nn) return;
-    const double4 A = T.s2a[c], B = T.s2b[c];
-    const double tr = (A.x + A.y) + A.z;
-    float4 *o = T.qr + (long)kQuadRec * c;
-    o[0] = T.rec[c];
-    o[1] = make_float4((float)(3.0 * A.x - tr), (float)(3.0 * A.y - tr), (float)(3.0 * A.z - tr),
-                       (float)(3.0 * A.w));
-    o[2] = make_float4((float)(3.0 * B.x), (float)(3.0 * B.y), 0.0f, 0.0f);
 }
 
 __device__ __forceinline__ unsigned lane_rank(unsigned long long mask)
@@ -779,18 +889,77 @@ void plan(HostTree &h, int n, int leaf)
     h.leaves.reserve(nl);
     build_rec(h, 0, n, leaf);
     groups_rec(h, 0);
-    // bucket the nodes by height (counting sort; leaves keep ORB order)
-    const int H = h.height[0];
-    h.height_off.assign(H + 2, 0);
-    for (int v : h.height) ++h.height_off[v + 1];
-    for (int k = 0; k <= H; ++k) h.height_off[k + 1] += h.height_off[k];
-    h.by_height.assign(h.node.size(), 0);
-    std::vector<int> pos(h.height_off.begin(), h.height_off.end() - 1);
-    for (size_t id = 0; id < h.node.size(); ++id) {
-        if (h.height[id] == 0) continue;
-        h.by_height[pos[h.height[id]]++] = (int)id;
+}
+
+// The moment kernels' subtrees: launch by launch, maximal subtrees of at most
+// `room` inputs, the inputs being the leaves first and then the roots of the
+// subtrees before, until the tree's root is one of them.
+constexpr int kMomLeaves = 128, kMomNodes = 256;
+
+void moment_plan(HostTree &h)
+{
+    const int nn = (int)h.node.size();
+    std::vector<char> input(nn, 0);
+    for (int id : h.leaves) input[id] = 1;
+    std::vector<int> count(nn), place(nn), rank(nn);
+    h.mom_ent.clear();
+    h.mom_sub.clear();
+    h.mom_off.assign(1, 0);
+    if (h.leaves.size() == 1) {  // the root is a leaf
+        h.mom_ent.push_back(make_int4(0, -1, -1, 0));
+        h.mom_sub.push_back(make_int2(0, 1));
+        h.mom_off.push_back(1);
+        return;
     }
-    for (size_t k = 0; k < h.leaves.size(); ++k) h.by_height[k] = h.leaves[k];
+    std::vector<int> stack, walk, inner;
+    for (int room = kMomLeaves; !input[0]; room = kMomNodes) {
+        // inputs below every node that is not below an input (children come after their parent)
+        for (int id = nn - 1; id >= 0; --id)
+            count[id] = input[id] ? 1 : (h.node[id].z < 0 ? 0 : std::min(room + 1, count[h.node[id].z]) +
+                                                                     std::min(room + 1, count[h.node[id].w]));
+        std::vector<int> roots;
+        stack.assign(1, 0);
+        while (!stack.empty()) {
+            const int id = stack.back();
+            stack.pop_back();
+            if (count[id] > room) {
+                stack.push_back(h.node[id].w);
+                stack.push_back(h.node[id].z);
+                continue;
+            }
+            roots.push_back(id);
+        }
+        const bool leaves = h.mom_off.size() == 1;
+        for (int r : roots) {
+            if (input[r] && !leaves) continue;  // finished already
+            const int first = (int)h.mom_ent.size();
+            inner.clear();
+            walk.assign(1, r);
+            while (!walk.empty()) {  // preorder
+                const int id = walk.back();
+                walk.pop_back();
+                if (input[id]) {
+                    place[id] = (int)h.mom_ent.size() - first;
+                    rank[id] = 0;
+                    h.mom_ent.push_back(make_int4(id, -1, -1, 0));
+                } else {
+                    inner.push_back(id);
+                    walk.push_back(h.node[id].w);
+                    walk.push_back(h.node[id].z);
+                }
+            }
+            for (size_t k = inner.size(); k-- > 0;)
+                rank[inner[k]] = 1 + std::max(rank[h.node[inner[k]].z], rank[h.node[inner[k]].w]);
+            std::stable_sort(inner.begin(), inner.end(), [&](int a, int b) { return rank[a] < rank[b]; });
+            for (int id : inner) {
+                place[id] = (int)h.mom_ent.size() - first;
+                h.mom_ent.push_back(make_int4(id, place[h.node[id].z], place[h.node[id].w], rank[id]));
+            }
+            h.mom_sub.push_back(make_int2(first, (int)h.mom_ent.size() - first));
+        }
+        h.mom_off.push_back((int)h.mom_sub.size());
+        for (int r : roots) input[r] = 1;
+    }
 }
 
 struct TreeCache {
@@ -825,10 +994,12 @@ int tree_prepare(int n, int leaf, hipStream_t s, TreeDev &out)
     }
     HostTree h;
     plan(h, n, leaf);
+    moment_plan(h);
     const size_t nn = h.node.size(), ng = h.groups.size();
     const size_t o_node = 0;
-    const size_t o_byh = o_node + align256(nn * sizeof(int4));
-    const size_t o_grp = o_byh + align256(nn * sizeof(int));
+    const size_t o_ment = o_node + align256(nn * sizeof(int4));
+    const size_t o_msub = o_ment + align256(h.mom_ent.size() * sizeof(int4));
+    const size_t o_grp = o_msub + align256(h.mom_sub.size() * sizeof(int2));
     const size_t o_sums = o_grp + align256(ng * sizeof(int));
     const size_t o_comd = o_sums + align256(nn * sizeof(double4));
     const size_t o_rec = o_comd + align256(nn * sizeof(double4));
@@ -857,7 +1028,8 @@ int tree_prepare(int n, int leaf, hipStream_t s, TreeDev &out)
     char *base = (char *)mem;
     TreeDev d;
     d.node = (const int4 *)(base + o_node);
-    d.by_height = (const int *)(base + o_byh);
+    d.mom_ent = (const int4 *)(base + o_ment);
+    d.mom_sub = (const int2 *)(base + o_msub);
     d.groups = (const int *)(base + o_grp);
     d.sums = (double4 *)(base + o_sums);
     d.comd = (double4 *)(base + o_comd);
@@ -876,7 +1048,11 @@ int tree_prepare(int n, int leaf, hipStream_t s, TreeDev &out)
     C.host = std::move(h);
     hipError_t e = hipMemcpyAsync(base + o_node, C.host.node.data(), nn * sizeof(int4), hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(base + o_byh, C.host.by_height.data(), nn * sizeof(int), hipMemcpyHostToDevice, s);
+        e = hipMemcpyAsync(base + o_ment, C.host.mom_ent.data(), C.host.mom_ent.size() * sizeof(int4),
+                           hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(base + o_msub, C.host.mom_sub.data(), C.host.mom_sub.size() * sizeof(int2),
+                           hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(base + o_grp, C.host.groups.data(), ng * sizeof(int), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -897,21 +1073,22 @@ int tree_prepare(int n, int leaf, hipStream_t s, TreeDev &out)
 template <bool Q2>
 hipError_t launch_moments_t(const float4 *pm, const TreeDev &d, const HostTree &h, int cells, hipStream_t s)
 {
-    const int nl = (int)h.leaves.size();
-    hipLaunchKernelGGL(k_tree_leaves<Q2>, dim3((nl + 255) / 256), dim3(256), 0, s, pm, d, nl);
-    hipError_t e = hipGetLastError();
-    for (size_t k = 1; e == hipSuccess && k + 1 < h.height_off.size(); ++k) {
-        const int first = h.height_off[k], count = h.height_off[k + 1] - first;
-        hipLaunchKernelGGL(k_tree_inner<Q2>, dim3((count + 255) / 256), dim3(256), 0, s, d, first, count);
+    const int quad = cells == kCellsQuad || cells == kCellsLocal;
+    hipError_t e = hipSuccess;
+    for (size_t k = 0; e == hipSuccess && k + 1 < h.mom_off.size(); ++k) {
+        const dim3 grid(h.mom_off[k + 1] - h.mom_off[k]);
+        const int2 *sub = d.mom_sub + h.mom_off[k];
+        if (k == 0)
+            hipLaunchKernelGGL((k_tree_moments<Q2, kMomLeaves, true>), grid, dim3(kMomLeaves), 0, s, pm, d, d.mom_ent,
+                               sub, quad);
+        else
+            hipLaunchKernelGGL((k_tree_moments<Q2, kMomNodes, false>), grid, dim3(kMomNodes), 0, s, pm, d, d.mom_ent,
+                               sub, quad);
         e = hipGetLastError();
     }
     const int nn = (int)h.node.size();
     if (Q2 && e == hipSuccess && cells == kCellsPseudo) {
         hipLaunchKernelGGL(k_tree_pseudo, dim3((nn * kPseudo + 255) / 256), dim3(256), 0, s, d, nn);
-        e = hipGetLastError();
-    }
-    if (Q2 && e == hipSuccess && (cells == kCellsQuad || cells == kCellsLocal)) {
-        hipLaunchKernelGGL(k_tree_quad, dim3((nn + 255) / 256), dim3(256), 0, s, d, nn);
         e = hipGetLastError();
     }
     return e;

@@ -18,7 +18,8 @@ constexpr int kCellsMono = 0, kCellsPseudo = 2, kCellsQuad = 3, kCellsLocal = 4;
 
 struct TreeDev {
     const int4 *node;    // begin, end, left, right (-1 for a leaf)
-    const int *by_height;  // node ids by height (0 = leaves, in ORB order), ascending
+    const int4 *mom_ent;   // the moment kernels' subtrees: (node, left, right, height), inputs first
+    const int2 *mom_sub;   // per subtree: first entry, entries
     const int *groups;     // group node ids in ORB order
     double4 *sums;       // M, Sx, Sy, Sz
     double4 *comd;       // com (FP64), diag2
@@ -35,8 +36,9 @@ struct TreeDev {
 struct HostTree {
     std::vector<int4> node;
     std::vector<int> leaves, groups, height;
-    std::vector<int> by_height;    // node ids ordered by height, leaves first in ORB order
-    std::vector<int> height_off;   // start of each height in by_height, plus the end
+    std::vector<int4> mom_ent;   // see TreeDev
+    std::vector<int2> mom_sub;
+    std::vector<int> mom_off;    // first subtree of each moment launch, plus the end
 };
 
 // Caller holds tree_mutex(): makes the tables for (n, leaf) current, computes

@@ -43,6 +43,33 @@ def test_moments_bitexact(orc, n, leaf):
     assert np.array_equal(box[:, 3:].astype(np.float64), want["hi"])
 
 
+# 127, 128, 129 and 256, 257 leaves (subtrees of at most 128 leaves), 128 * 256
+# leaves and one more (a third launch), and leaves of 1 and 64 bodies
+@pytest.mark.parametrize("n,leaf", [(508, 4), (512, 4), (513, 4), (1024, 4), (1025, 4), (131072, 4), (131073, 4),
+                                    (300, 1), (64 * 300 + 1, 64)])
+def test_moments_subtree_edges(orc, n, leaf):
+    """Moments and quadrupole records where the moment kernels' subtrees fill
+    up: the moments bit for bit, the records to the bar of the record tests."""
+    torch, nb = gpu()
+    pm, _ = ics.plummer(n, 320 + n % 89)
+    q, qh = _orb_input(torch, nb, pm, leaf)
+    mom, box = nb.tree_moments(q, leaf)
+    quad = nb.tree_quad(q, leaf)
+    torch.cuda.synchronize()
+    mom, box, quad = mom.cpu().numpy(), box.cpu().numpy(), quad.cpu().numpy()
+    want = orc.tree_moments(qh, leaf)
+    assert np.array_equal(mom[:, 0], want["mass"])
+    assert np.array_equal(mom[:, 1:4], want["com"])
+    assert np.array_equal(mom[:, 4], want["diag2"])
+    assert np.array_equal(box[:, :3].astype(np.float64), want["lo"])
+    assert np.array_equal(box[:, 3:].astype(np.float64), want["hi"])
+    assert np.array_equal(quad[:, 0, 3], want["mass"].astype(np.float32))
+    want_q = orc.tree_quad(widen32(qh), leaf)
+    got_q = np.c_[quad[:, 1, :], quad[:, 2, :2]].astype(np.float64)
+    scale = np.abs(want_q).max(axis=1, keepdims=True)
+    assert np.all(np.abs(got_q - want_q) <= 2.0 ** -22 * scale + 1e-300)
+
+
 def test_moments_zero_masses_and_repeat(orc):
     """Massless cells take the box centre; a second call on the same shape
     (counters reset by the first) gives the same bits."""
