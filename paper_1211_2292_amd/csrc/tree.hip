@@ -15,7 +15,7 @@
 //   box centre when M = 0.  Boxes are exact FP32 minima/maxima, and
 //   diag2 = sum over x, y, z of (hi - lo)^2 in FP64.
 // * groups: the targets are taken in groups, the maximal nodes of at most 64
-//   bodies (one wave each).
+//   bodies (one per lane).
 // * opening: cell c is accepted for group g iff c and g share no body and
 //   diag2_c < theta^2 * D2, D2 the squared distance from com_c to the box of g
 //   (per axis lo - com, com - hi or 0; summed x, y, z).  Every body of c lies
@@ -25,14 +25,16 @@
 // Kernels:
 // * k_tree_moments: whole subtrees per workgroup, bottom-up through LDS, two or
 //   three launches in all (see there).
-// * k_tree_walk: one wave per group.  The walk starts from the siblings of
-//   the group's ancestors (every cell disjoint from the group) and pops up to
-//   64 cells per step from a 512-entry stack in LDS, one cell per lane: the acceptance
-//   test is per cell, so the control flow of the wave stays uniform.
-//   Accepted cells go to an LDS batch of pseudo-body records that every lane
-//   sweeps with the same FP32 pair code as the direct sum (broadcast LDS
-//   reads); rejected leaves go to a batch of contiguous source ranges swept
-//   with scalar loads; the group's own bodies are one masked range.  A cell
+// * k_tree_walk: one or four waves per group.  The walk starts from the
+//   siblings of the group's ancestors (every cell disjoint from the group) and
+//   pops up to 64 cells per wave and step from a stack in LDS (512 entries per
+//   wave), one cell per lane: the acceptance test is per cell, so the control
+//   flow of the wave stays uniform.  Accepted cells go to an LDS batch of
+//   pseudo-body records that every lane sweeps with the same FP32 pair code as
+//   the direct sum (broadcast LDS reads); rejected leaves go to a batch of
+//   contiguous source ranges swept with scalar loads, or gathered into LDS
+//   first; the group's own bodies are one masked range.  Four waves share the
+//   stack and the batches and sweep a quarter of each.  A cell
 //   whose children would overflow the stack is summed body by body instead,
 //   which is exact.  In inspection mode the same walk writes the node ids of
 //   the accepted cells and of the rejected leaves instead of summing.
@@ -385,16 +387,17 @@ struct WalkOut {
 };
 
 // Sweeps the batched pseudo-body records in LDS (broadcast reads).
+template <int U>
 __device__ __forceinline__ void sweep_cells(const float4 *cb, int cnt, const Targets<float, 1> &T,
                                             float eps2, Sums<float, 1> &S)
 {
     int j = 0;
-    for (; j + kUnroll <= cnt; j += kUnroll) {
-        float4 b[kUnroll];
+    for (; j + U <= cnt; j += U) {
+        float4 b[U];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) b[u] = cb[j + u];
+        for (int u = 0; u < U; ++u) b[u] = cb[j + u];
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) pair_f32<1, false>(b[u], j + u, T, eps2, S);
+        for (int u = 0; u < U; ++u) pair_f32<1, false>(b[u], j + u, T, eps2, S);
     }
     for (; j < cnt; ++j) pair_f32<1, false>(cb[j], j, T, eps2, S);
 }
@@ -420,31 +423,93 @@ __device__ __forceinline__ void sweep_pseudo(const float4 *__restrict__ pp, cons
 __device__ __forceinline__ void sweep_quad(const float4 *qb, int cnt, const Targets<float, 1> &T, float eps2,
                                            Sums<float, 1> &S)
 {
+#pragma unroll 2
     for (int r = 0; r < cnt; ++r) {
         const float4 a = qb[kQuadRec * r], b = qb[kQuadRec * r + 1], d = qb[kQuadRec * r + 2];
         quad_f32(a, b, d, T, eps2, S);
     }
 }
 
-template <int MODE, bool INSPECT, int CELLS>
-// 7 waves per SIMD: 5 KB of LDS per wave and at most 72 VGPRs (measured
-// faster than 6 waves, and than 8 waves with register spills).  The local-
-// expansion walk keeps 20 expansion coefficients per lane and cannot reach 7;
-// asked for 5 it fits in 94 VGPRs without spills (left to itself the
-// allocator took 111, 4 waves).
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CELLS == kCellsLocal ? 5 : 7))) void k_tree_walk(const float4 *__restrict__ src, int n, TreeDev T,
-                                                  const float4 *__restrict__ cells, float eps2_in, double G,
-                                                  double theta2, WalkOut O, const int *__restrict__ order)
+// Sweeps the bodies of the near ranges [r, r1) of nbuf: the ranges' bodies are
+// numbered through, kNear of them at a time are gathered into LDS (first
+// their indices, then one load per lane), and the targets are summed against
+// the whole tile.  Each range by itself, read through the scalar cache, costs
+// a wait for its few bodies: with leaves of 4, three local-expansion forces
+// of 100000 bodies took 1860 us that way and take 1530 us this way, of 1000001
+// bodies 7053 and 6749 us (one wave per group).  From leaves of 16 on the
+// scalar loads amortise their wait and spare the LDS (quadrupole cells, 300001
+// bodies: 6730 against 6905 us; leaves of 8: 6007 against 5869 us).  The
+// monopole and pseudo-particle walks, which have no record buffer to lend, gain
+// 2% at leaves of 4 and lose 1% at 8 and 15% at 32, and keep the scalar loads.
+constexpr int kNear = 2 * kGroup;
+constexpr int kNearScalarLeaf = 16;
+__device__ __forceinline__ void wave_sync()
 {
-    __shared__ int stk[kStack];
-    __shared__ float4 cbuf[CELLS == kCellsMono ? kBuf : 1];    // monopole cells: the accepted records
-    __shared__ int cid[CELLS == kCellsPseudo ? kBuf : 1];      // pseudo-particle cells: the accepted ids
-    // quadrupole cells: the records of one step's accepted cells (swept every step)
-    __shared__ float4 qbuf[CELLS >= kCellsQuad ? kQuadRec * kGroup : 1];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void sweep_near(const float4 *__restrict__ src, const int2 *nbuf, int r, int r1, float4 *nb,
+                                           int lane, const Targets<float, 1> &T, float eps2, Sums<float, 1> &S)
+{
+    float *const idx = (float *)nb;
+    for (; r < r1; r += kGroup) {
+        const int2 a = r + lane < r1 ? nbuf[r + lane] : make_int2(0, 0);
+        const int len = a.y - a.x;
+        int off = len;  // where this lane's range begins among the batch's bodies
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int u = __shfl_up(off, o);
+            if (lane >= o) off += u;
+        }
+        const int total = __builtin_amdgcn_readlane(off, 63);
+        off -= len;
+        for (int w = 0; w < total; w += kNear) {
+            const int e = min(len, w + kNear - off);
+            for (int k = max(w - off, 0); k < e; ++k) idx[off + k - w] = __int_as_float(a.x + k);
+            wave_sync();
+            const int cnt = min(kNear, total - w);
+            const float4 p = src[lane < cnt ? __float_as_int(idx[lane]) : 0];
+            const float4 q = src[lane + kGroup < cnt ? __float_as_int(idx[lane + kGroup]) : 0];
+            wave_sync();
+            nb[lane] = p;
+            nb[lane + kGroup] = q;
+            wave_sync();
+            sweep_cells<kUnroll / 2>(nb, cnt, T, eps2, S);
+            wave_sync();
+        }
+    }
+}
+
+// One group's walk by W waves.  The waves pop the stack together, one cell per
+// thread, and share the lists of accepted cells and near ranges; each wave
+// sweeps its share of a list against all 64 targets (lane l of every wave is
+// target l), and the waves' sums are added at the end.
+//
+// 7 waves per SIMD: 5 KB of LDS per wave and at most 72 VGPRs (measured faster
+// than 6 waves, and than 8 waves with register spills).  The local-expansion
+// walk keeps 20 expansion coefficients per lane and cannot reach 7; alone in
+// its group a wave asked for 5 fits in 96 VGPRs without spills (left to itself
+// the allocator took 111, 4 waves), and the shared walk, which would spill
+// there, takes 4.
+template <int MODE, bool INSPECT, int CELLS, bool NEAR_LDS, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(CELLS == kCellsLocal ? (W > 1 ? 4 : 5) : 7))) void
+k_tree_walk(const float4 *__restrict__ src, int n, TreeDev T, const float4 *__restrict__ cells, float eps2_in,
+            double G, double theta2, WalkOut O, const int *__restrict__ order)
+{
+    constexpr bool QUAD = CELLS >= kCellsQuad;
+    static_assert(!INSPECT || W == 1, "inspection is one wave's");
+    static_assert(!NEAR_LDS || QUAD, "the near bodies go through the quadrupole records' buffer");
+    __shared__ int stk[W * kStack];
+    __shared__ float4 cbuf[CELLS == kCellsMono ? W * kBuf : 1];    // monopole cells: the accepted records
+    __shared__ int cid[CELLS == kCellsPseudo ? W * kBuf : 1];      // pseudo-particle cells: the accepted ids
+    // quadrupole cells: the records of one step's accepted cells (swept every step); near bodies between the steps
+    __shared__ float4 qbuf[QUAD ? W * kQuadRec * kGroup : W > 1 ? 2 * (W - 1) * kGroup : 1];
     // local expansions: the ids of cells waiting to be folded in
-    __shared__ int lid[CELLS == kCellsLocal ? kBuf : 1];
-    __shared__ int2 nbuf[kBuf];
-    const int lane = threadIdx.x;
+    __shared__ int lid[CELLS == kCellsLocal ? W * kBuf : 1];
+    __shared__ int2 nbuf[W * kBuf];
+    __shared__ int4 steps[W];  // this step's counts of each wave: accepted, near, opened, folded in
+    const int lane = W == 1 ? (int)threadIdx.x : (int)threadIdx.x & 63;
+    const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int g = order ? order[blockIdx.x] : (int)blockIdx.x;
     const int gnode = T.groups[g];
     const int4 gn = T.node[gnode];
@@ -470,6 +535,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CELLS == kCe
 #pragma unroll
     for (int c = 0; c < 4; ++c) R[c].zero();
     Sums<float, 1> S;
+    auto fold = [&]() {
+        R[0].fold(S.ax[0]);
+        R[1].fold(S.ay[0]);
+        R[2].fold(S.az[0]);
+        R[3].fold(S.ph[0]);
+    };
+    // this wave's share of a list
+    auto share = [&](int cnt, int w) { return W == 1 ? (w ? cnt : 0) : cnt * w / W; };
 
     // siblings of the ancestors, root first (the deepest ends on top)
     int top = 0;
@@ -477,7 +550,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CELLS == kCe
         const int4 nd = T.node[c];
         const int4 ln = T.node[nd.z];
         const bool left = gn.x < ln.y;
-        if (lane == 0) stk[top] = left ? nd.w : nd.z;
+        if (threadIdx.x == 0) stk[top] = left ? nd.w : nd.z;
         ++top;
         c = left ? nd.z : nd.w;
     }
@@ -485,61 +558,63 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CELLS == kCe
 
     auto flush_cells = [&]() {
         if constexpr (!INSPECT) {
+            const int b = share(nf, wave), cnt = share(nf, wave + 1) - b;
             S.zero();
             if constexpr (CELLS == kCellsPseudo) {
-                sweep_pseudo(cells, cid, nf, TT, eps2, S);
-            } else if constexpr (CELLS >= kCellsQuad) {
-                sweep_quad(qbuf, nf, TT, eps2, S);
+                sweep_pseudo(cells, cid + b, cnt, TT, eps2, S);
+            } else if constexpr (QUAD) {
+                sweep_quad(qbuf + kQuadRec * b, cnt, TT, eps2, S);
             } else {
                 static_assert(CELLS == kCellsMono, "unhandled cell model");
-                sweep_cells(cbuf, nf, TT, eps2, S);
+                sweep_cells<kUnroll>(cbuf + b, cnt, TT, eps2, S);
             }
-            R[0].fold(S.ax[0]);
-            R[1].fold(S.ay[0]);
-            R[2].fold(S.az[0]);
-            R[3].fold(S.ph[0]);
+            fold();
         }
         nf = 0;
     };
     auto flush_near = [&]() {
         if constexpr (!INSPECT) {
+            const int r1 = share(nr, wave + 1);
             S.zero();
-            for (int r = 0; r < nr;) {
-                const int2 a = nbuf[r];
-                int b = __builtin_amdgcn_readfirstlane(a.x);
-                int e = __builtin_amdgcn_readfirstlane(a.y);
-                ++r;
-                while (r < nr) {  // merge ranges that continue each other
-                    const int2 c2 = nbuf[r];
-                    const int nb = __builtin_amdgcn_readfirstlane(c2.x);
-                    if (nb != e) break;
-                    e = __builtin_amdgcn_readfirstlane(c2.y);
+            if constexpr (NEAR_LDS) {
+                float4 *const nb = qbuf + wave * kQuadRec * kGroup;
+                sweep_near(src, nbuf, share(nr, wave), r1, nb, lane, TT, eps2, S);
+            } else {
+                for (int r = share(nr, wave); r < r1;) {
+                    const int2 a = nbuf[r];
+                    int b = __builtin_amdgcn_readfirstlane(a.x);
+                    int e = __builtin_amdgcn_readfirstlane(a.y);
                     ++r;
+                    while (r < r1) {  // merge ranges that continue each other
+                        const int2 c2 = nbuf[r];
+                        const int nb = __builtin_amdgcn_readfirstlane(c2.x);
+                        if (nb != e) break;
+                        e = __builtin_amdgcn_readfirstlane(c2.y);
+                        ++r;
+                    }
+                    sweep_f32<1, false>(src, b, e, TT, eps2, S);
                 }
-                sweep_f32<1, false>(src, b, e, TT, eps2, S);
             }
-            R[0].fold(S.ax[0]);
-            R[1].fold(S.ay[0]);
-            R[2].fold(S.az[0]);
-            R[3].fold(S.ph[0]);
+            fold();
         }
         nr = 0;
     };
     auto flush_local = [&]() {
         if constexpr (CELLS == kCellsLocal && !INSPECT) {
-            for (int b = 0; b < nl; b += kGroup)
+            for (int b = wave * kGroup; b < nl; b += W * kGroup)
                 if (b + lane < nl) m2l_f32(cells + (long)kQuadRec * lid[b + lane], zgx, zgy, zgz, eps2, Lx);
         }
         nl = 0;
     };
 
+    __syncthreads();
     while (top > 0) {
-        const int k = min(kGroup, top);
+        const int k = min(W * kGroup, top);
         top -= k;
-        __syncthreads();
-        const bool act = lane < k;
-        const int c = act ? stk[top + lane] : 0;
-        __syncthreads();
+        if constexpr (W == 1) __syncthreads();
+        const bool act = (int)threadIdx.x < k;
+        const int c = act ? stk[top + threadIdx.x] : 0;
+        if constexpr (W == 1) __syncthreads();
         bool acc = false, nearr = false, open = false, loc = false;
         int4 nd = make_int4(0, 0, -1, -1);
         if (act) {
@@ -564,16 +639,52 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CELLS == kCe
                 }
             }
         }
-        // children that would not fit on the stack are summed body by body
-        const unsigned long long mo0 = __ballot(open);
-        if (open && top + 2 * (int)(lane_rank(mo0) + 1) > kStack) {
-            open = false;
-            nearr = true;
+        // where this wave's entries of each list begin, and the step's counts
+        const unsigned long long ma = __ballot(acc), mo0 = __ballot(open), ml = CELLS == kCellsLocal ? __ballot(loc) : 0ull;
+        unsigned long long mn = __ballot(nearr), mo = mo0;
+        int fa = nf, fn = nr, fl = nl, fo = top;
+        int ca, cn, co, cl;
+        if constexpr (W == 1) {
+            // children that would not fit on the stack are summed body by body
+            if (open && top + 2 * (int)(lane_rank(mo0) + 1) > kStack) {
+                open = false;
+                nearr = true;
+            }
+            mn = __ballot(nearr);
+            mo = __ballot(open);
+            ca = __popcll(ma);
+            cn = __popcll(mn);
+            co = __popcll(mo);
+            cl = __popcll(ml);
+        } else {
+            if (lane == 0) steps[wave] = make_int4(__popcll(ma), __popcll(mn), __popcll(mo0), __popcll(ml));
+            __syncthreads();
+            const int fit = (W * kStack - top) / 2;  // the same rule over the waves: the first cells are opened
+            ca = cn = co = cl = 0;
+            int before = 0;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                int4 q = steps[w];
+                const int o = min(q.z, max(fit - co, 0));
+                q.y += q.z - o;
+                q.z = o;
+                if (w == wave) before = co;
+                fa += w < wave ? q.x : 0;
+                fn += w < wave ? q.y : 0;
+                fl += w < wave ? q.w : 0;
+                ca += q.x;
+                cn += q.y;
+                co += q.z;
+                cl += q.w;
+            }
+            if (open && before + (int)lane_rank(mo0) >= fit) {
+                open = false;
+                nearr = true;
+            }
+            mn = __ballot(nearr);
+            mo = __ballot(open);
+            fo += 2 * before;
         }
-        const unsigned long long ma = __ballot(acc), mn = __ballot(nearr), mo = __ballot(open);
-        const int ca = __popcll(ma), cn = __popcll(mn), co = __popcll(mo);
-        const unsigned long long ml = CELLS == kCellsLocal ? __ballot(loc) : 0ull;
-        const int cl = __popcll(ml);
         if constexpr (INSPECT) {
             if (acc) {
                 const int q = tf + (int)lane_rank(ma);
@@ -585,26 +696,26 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CELLS == kCe
             }
         } else {
             if (acc) {
-                if constexpr (CELLS >= kCellsQuad) {
-                    const int slot = nf + (int)lane_rank(ma);
+                const int slot = fa + (int)lane_rank(ma);
+                if constexpr (QUAD) {
                     const float4 *r = cells + (long)kQuadRec * c;
                     qbuf[kQuadRec * slot] = r[0];
                     qbuf[kQuadRec * slot + 1] = r[1];
                     qbuf[kQuadRec * slot + 2] = r[2];
                 } else if constexpr (CELLS == kCellsPseudo) {
-                    cid[nf + (int)lane_rank(ma)] = c;
+                    cid[slot] = c;
                 } else {
                     static_assert(CELLS == kCellsMono, "unhandled cell model");
-                    cbuf[nf + (int)lane_rank(ma)] = T.rec[c];
+                    cbuf[slot] = T.rec[c];
                 }
             }
-            if (nearr) nbuf[nr + (int)lane_rank(mn)] = make_int2(nd.x, nd.y);
+            if (nearr) nbuf[fn + (int)lane_rank(mn)] = make_int2(nd.x, nd.y);
             if constexpr (CELLS == kCellsLocal) {
-                if (loc) lid[nl + (int)lane_rank(ml)] = c;
+                if (loc) lid[fl + (int)lane_rank(ml)] = c;
             }
         }
         if (open) {
-            const int q = top + 2 * (int)lane_rank(mo);
+            const int q = fo + 2 * (int)lane_rank(mo);
             stk[q] = nd.w;
             stk[q + 1] = nd.z;
         }
@@ -616,12 +727,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CELLS == kCe
         nl += cl;
         top += 2 * co;
         __syncthreads();
-        if (CELLS >= kCellsQuad ? nf > 0 : nf >= kGroup) flush_cells();
-        if (nr >= kGroup) flush_near();
-        if (nl >= kGroup) flush_local();
+        if (QUAD ? nf > 0 : nf >= W * kGroup) flush_cells();
+        if (nr >= W * kGroup) {
+            if constexpr (W > 1 && NEAR_LDS) __syncthreads();  // the records are swept: their buffer takes the bodies
+            flush_near();
+        }
+        if (nl >= W * kGroup) flush_local();
     }
     if (nf > 0) flush_cells();
     if (nl > 0) flush_local();
+    if constexpr (W > 1 && NEAR_LDS) __syncthreads();
     if (nr > 0) flush_near();
 
     if constexpr (INSPECT) {
@@ -633,7 +748,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CELLS == kCe
     } else {
         // the group's own bodies, without the self pair
         S.zero();
-        range_f32<1>(src, gn.x, gn.y, gn.x, gn.x + kGroup, TT, eps2, S);
+        const int s0 = gn.x + share(gn.y - gn.x, wave), s1 = gn.x + share(gn.y - gn.x, wave + 1);
+        range_f32<1>(src, s0, s1, gn.x, gn.x + kGroup, TT, eps2, S);
         if constexpr (CELLS == kCellsLocal) {
             // sum the local expansion over the wave, evaluate it at this body
 #pragma unroll
@@ -664,14 +780,26 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CELLS == kCe
             const float ytyy = __builtin_fmaf(yx, tx, __builtin_fmaf(yy, ty, yz * tz));
             S.ph[0] += c[0] + __builtin_fmaf(1.0f / 6.0f, ytyy, __builtin_fmaf(0.5f, yky, py));
         }
-        R[0].fold(S.ax[0]);
-        R[1].fold(S.ay[0]);
-        R[2].fold(S.az[0]);
-        R[3].fold(S.ph[0]);
-        if (i < gn.y) {
-            double r[4];
+        fold();
+        double r[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) r[c] = R[c].get();
+        for (int c = 0; c < 4; ++c) r[c] = R[c].get();
+        if constexpr (W > 1) {
+            double *const rb = (double *)qbuf;  // 4 sums per target of each wave but the first
+            __syncthreads();
+            if (wave > 0) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) rb[(4 * (wave - 1) + c) * kGroup + lane] = r[c];
+            }
+            __syncthreads();
+            if (wave > 0) return;
+#pragma unroll
+            for (int w = 0; w < W - 1; ++w) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) r[c] += rb[(4 * w + c) * kGroup + lane];
+            }
+        }
+        if (i < gn.y) {
             if constexpr (MODE == M_F32)
                 put_f32(O.acc_pot, i, r, (float)G);
             else
@@ -1110,7 +1238,7 @@ hipError_t launch_moments(const float4 *pm, const TreeDev &d, const HostTree &h,
                                : launch_moments_t<false>(pm, d, h, cells, s);
 }
 
-template <int MODE, bool INSPECT, int CELLS>
+template <int MODE, bool INSPECT, int CELLS, bool NEAR_LDS, int W>
 hipError_t launch_walk(const float4 *pm, int n, const TreeDev &d, int ngroups, float eps2, double G,
                        double theta2, const WalkOut &o, hipStream_t s)
 {
@@ -1126,9 +1254,46 @@ hipError_t launch_walk(const float4 *pm, int n, const TreeDev &d, int ngroups, f
         hipLaunchKernelGGL(k_group_order, dim3(1), dim3(kOrderThreads), 0, s, d, ngroups);
         order = d.order;
     }
-    hipLaunchKernelGGL((k_tree_walk<MODE, INSPECT, CELLS>), dim3(ngroups), dim3(64), 0, s, pm, n, d, recs, eps2,
-                       G, theta2, o, order);
+    hipLaunchKernelGGL((k_tree_walk<MODE, INSPECT, CELLS, NEAR_LDS, W>), dim3(ngroups), dim3(64 * W), 0, s, pm, n, d,
+                       recs, eps2, G, theta2, o, order);
     return hipGetLastError();
+}
+
+// Waves per group: four where the launch's time is that of its slowest groups,
+// one where the groups fill the chip several times over and the barriers only
+// cost.  Three forces with order and moments, one wave per group against four,
+// on Plummer spheres: local expansions 930 -> 552 us at 20001 bodies (512
+// groups), 1520 -> 1270 at 100000 (2048), 2310 -> 2157 at 200000 (4096; leaf
+// 16, theta 0.5: 6000 -> 4990), but 3228 -> 3621 at 400000 (8192); monopole
+// cells 1497 -> 1145 at 100000, 2478 -> 2146 at 200000, 6318 -> 6000 at 400000,
+// but 7514 -> 7601 at 800000 (16384).  Quadrupole and pseudo-particle cells, more
+// work per accepted cell, gained or were equal at every size up to 4 million
+// (quadrupole 3217 -> 2194 at 100000, 13498 -> 12618 at 1000001, 17.7 ms for
+// one force of 4 million either way) and have no one-wave form.  Two waves
+// were between one and four nearly everywhere, eight lost from 2048 groups on.
+constexpr int kWalkWaves = 4;
+constexpr int kWalkWideMono = 8192, kWalkWideLocal = 4096;
+
+template <int MODE, int CELLS, bool NEAR_LDS>
+hipError_t walk_waves(const float4 *pm, int n, const TreeDev &d, int ng, float eps2, double G, double th2,
+                      const WalkOut &o, hipStream_t s)
+{
+    if constexpr (CELLS == kCellsMono || CELLS == kCellsLocal) {
+        if (ng > (CELLS == kCellsMono ? kWalkWideMono : kWalkWideLocal))
+            return launch_walk<MODE, false, CELLS, NEAR_LDS, 1>(pm, n, d, ng, eps2, G, th2, o, s);
+    }
+    return launch_walk<MODE, false, CELLS, NEAR_LDS, kWalkWaves>(pm, n, d, ng, eps2, G, th2, o, s);
+}
+
+template <int MODE, int CELLS>
+hipError_t walk_near(const float4 *pm, int n, const TreeDev &d, int ng, int leaf, float eps2, double G, double th2,
+                     const WalkOut &o, hipStream_t s)
+{
+    if constexpr (CELLS >= kCellsQuad) {
+        if (leaf < kNearScalarLeaf)
+            return walk_waves<MODE, CELLS, true>(pm, n, d, ng, eps2, G, th2, o, s);
+    }
+    return walk_waves<MODE, CELLS, false>(pm, n, d, ng, eps2, G, th2, o, s);
 }
 
 }  // namespace
@@ -1181,20 +1346,20 @@ int tree_lists(const void *pm, int n, int leaf, double theta, int max_far, int m
     o.max_far = far_ids ? max_far : 0;
     o.max_near = near_ids ? max_near : 0;
     if (e == hipSuccess)
-        e = launch_walk<M_F32, true, kCellsMono>((const float4 *)pm, n, d, (int)g_tree.host.groups.size(),
+        e = launch_walk<M_F32, true, kCellsMono, false, 1>((const float4 *)pm, n, d, (int)g_tree.host.groups.size(),
                                                  0.0f, 1.0, theta * theta, o, s);
     return e == hipSuccess ? NBODY_OK : hip_fail(e, "tree lists");
 }
 
 namespace {
 template <int CELLS>
-hipError_t walk_prec(int prec, const float4 *pm, int n, const TreeDev &d, int ng, float eps2, double G, double th2,
-                     const WalkOut &o, hipStream_t s)
+hipError_t walk_prec(int prec, const float4 *pm, int n, const TreeDev &d, int ng, int leaf, float eps2, double G,
+                     double th2, const WalkOut &o, hipStream_t s)
 {
     switch (prec) {
-    case NBODY_F32: return launch_walk<M_F32, false, CELLS>(pm, n, d, ng, eps2, G, th2, o, s);
-    case NBODY_F32_KAHAN: return launch_walk<M_KAHAN, false, CELLS>(pm, n, d, ng, eps2, G, th2, o, s);
-    default: return launch_walk<M_F64ACC, false, CELLS>(pm, n, d, ng, eps2, G, th2, o, s);
+    case NBODY_F32: return walk_near<M_F32, CELLS>(pm, n, d, ng, leaf, eps2, G, th2, o, s);
+    case NBODY_F32_KAHAN: return walk_near<M_KAHAN, CELLS>(pm, n, d, ng, leaf, eps2, G, th2, o, s);
+    default: return walk_near<M_F64ACC, CELLS>(pm, n, d, ng, leaf, eps2, G, th2, o, s);
     }
 }
 }  // namespace
@@ -1212,7 +1377,7 @@ int tree_local_counts(const void *pm, int n, int leaf, double theta, int32_t *lo
     o.near_cnt = near_cnt;
     o.loc_cnt = loc_cnt;
     if (e == hipSuccess)
-        e = launch_walk<M_F32, true, kCellsLocal>((const float4 *)pm, n, d, (int)g_tree.host.groups.size(), 0.0f,
+        e = launch_walk<M_F32, true, kCellsLocal, false, 1>((const float4 *)pm, n, d, (int)g_tree.host.groups.size(), 0.0f,
                                                   1.0, theta * theta, o, s);
     return e == hipSuccess ? NBODY_OK : hip_fail(e, "tree local counts");
 }
@@ -1233,13 +1398,13 @@ int tree_accel(const void *pm, int n, int prec, double G, double eps, double the
     const double th2 = theta * theta;
     if (e == hipSuccess) {
         if (cells == kCellsPseudo)
-            e = walk_prec<kCellsPseudo>(prec, (const float4 *)pm, n, d, ng, eps2, G, th2, o, s);
+            e = walk_prec<kCellsPseudo>(prec, (const float4 *)pm, n, d, ng, leaf, eps2, G, th2, o, s);
         else if (cells == kCellsQuad)
-            e = walk_prec<kCellsQuad>(prec, (const float4 *)pm, n, d, ng, eps2, G, th2, o, s);
+            e = walk_prec<kCellsQuad>(prec, (const float4 *)pm, n, d, ng, leaf, eps2, G, th2, o, s);
         else if (cells == kCellsLocal)
-            e = walk_prec<kCellsLocal>(prec, (const float4 *)pm, n, d, ng, eps2, G, th2, o, s);
+            e = walk_prec<kCellsLocal>(prec, (const float4 *)pm, n, d, ng, leaf, eps2, G, th2, o, s);
         else
-            e = walk_prec<kCellsMono>(prec, (const float4 *)pm, n, d, ng, eps2, G, th2, o, s);
+            e = walk_prec<kCellsMono>(prec, (const float4 *)pm, n, d, ng, leaf, eps2, G, th2, o, s);
     }
     return e == hipSuccess ? NBODY_OK : hip_fail(e, "tree force");
 }

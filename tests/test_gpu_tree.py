@@ -245,6 +245,27 @@ def test_dispatch_order_changes_nothing(orc, n, ng, cells, ocells):
     assert rms_rel(got[tg, 3], p) < 1e-6
 
 
+@pytest.mark.parametrize("n,leaf,theta", [
+    (257, 3, 0.4), (20011, 15, 0.3), (20011, 16, 0.3), (100000, 4, 0.0), (262144, 4, 0.7), (262145, 4, 0.7),
+    (524288, 8, 0.7), (524289, 8, 0.7)])
+@pytest.mark.parametrize("cells,ocells", [("CELLS_MONOPOLE", 0), ("CELLS_PSEUDO", 2), ("CELLS_QUADRUPOLE", 3),
+                                          ("CELLS_LOCAL", 4)])
+def test_walk_shapes(orc, n, leaf, theta, cells, ocells):
+    """Both sides of the rules that choose the waves per group (4096 and 8192
+    groups) and how the near bodies are read (leaves of 16), and theta = 0 on
+    a tree deep enough that cells are summed for want of stack: each at the
+    tree-code bars against the oracle."""
+    torch, nb = gpu()
+    pm, _ = ics.plummer(n, 3100 + n)
+    q, qh = _orb_input(torch, nb, pm, leaf)
+    eps = 0.01
+    got = host(nb.tree_accel(q, eps, theta, leaf, prec=nb.F32_F64ACC, cells=getattr(nb, cells)))
+    tg = ics.sample_targets(n, 64, 5)
+    a, p = orc.tree_accel(widen32(qh), leaf, 64, theta, eps, targets=tg, cells=ocells)
+    assert rms_rel(got[tg, :3], a) <= 1e-6
+    assert rms_rel(got[tg, 3], p) <= 1e-6
+
+
 def test_repeat_and_shape_change_same_bits():
     """Cached tables: the same call twice gives the same bits, also after a
     call of another shape in between."""
