@@ -24,11 +24,11 @@
 // Device schedule:
 // * Traversal, top-down by node depth.  For a target node A the pairs (A, .)
 //   of the recursion are those inherited from its parent (the parent's
-//   pass-down list) closed under source splits: one wave per node pops up to
-//   64 pending sources per step from an LDS stack, one per lane, and
-//   classifies them (ballot ranks give every output a fixed position); at
-//   the deep depths one wave walks two sibling nodes, gathering each source
-//   once for both.  Each depth runs one walk that writes every node's lists into slots of a
+//   pass-down list) closed under source splits: the node's waves pop up to 64
+//   pending sources each per step from an LDS stack, one per lane, and
+//   classify them (ballot ranks give every output a fixed position); at the
+//   deep depths one wave walks two sibling nodes, gathering each source once
+//   for both.  Each depth runs one walk that writes every node's lists into slots of a
 //   per-depth capacity; when that layout would take more than its memory
 //   budget, each depth instead runs a count walk, a two-kernel scan (block
 //   sums, then offsets) and a fill walk into compact lists.  Writes are
@@ -64,7 +64,7 @@ namespace {
     } while (0)
 
 constexpr int kFmmStack = 64;     // bound on the tree height the traversal admits
-constexpr int kWalkStack = 2048;  // LDS stack entries per walking wave (64 per source depth + refill)
+constexpr int kWalkStack = 2048;  // most LDS stack entries per walking wave (64 per source depth + refill)
 
 // List kinds; per-node counts and offsets are stored [kind][nn].
 constexpr int kM2L = 0, kP2P = 1, kM2P = 2, kPass = 3, kKinds = 4;
@@ -103,22 +103,27 @@ __device__ __forceinline__ long cap_of(const FmmDev &F, int kind)
     return kind == kM2L ? F.cap_m2l : (kind == kP2P ? F.cap_p2p : (kind == kM2P ? F.cap_m2p : F.cap_pass));
 }
 
-__device__ __forceinline__ bool fmm_overlap(int4 a, int4 b) { return a.x < b.y && b.x < a.y; }
+__device__ __forceinline__ bool fmm_overlap(int4 a, int4 b) { return (a.x < b.y) & (b.x < a.y); }
 
 __device__ __forceinline__ unsigned fmm_rank(unsigned long long mask)
 {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
 }
 
+// One node's list as a walk writes it: where it begins and its room.  32-bit
+// counts, so that an entry is stored at a scalar base and a 32-bit offset.
+struct ListOut {
+    int *at;
+    int room;
+};
+
 // Bounds-checked store of one list entry: the entry's index in its list is
-// done + its rank among the lanes of mask, stored at base + index if the
-// index is below cap (the list's room); returns false when it does not fit.
-__device__ __forceinline__ bool put_entry(int *list, long base, long done, long cap, unsigned long long mask,
-                                          int value)
+// done + its rank among the lanes of mask; returns false when it does not fit.
+__device__ __forceinline__ bool put_entry(const ListOut &l, int done, unsigned long long mask, int value)
 {
-    const long q = done + (long)fmm_rank(mask);
-    if (q >= cap) return false;
-    list[base + q] = value;
+    const int q = done + (int)fmm_rank(mask);
+    if (q >= l.room) return false;
+    l.at[(unsigned)q] = value;
     return true;
 }
 
@@ -137,256 +142,238 @@ struct SlotDepth {
     int prev_pass;
 };
 
-// One wave per target node of one depth: the walk of its inherited
-// sources.  The pending sources sit on an LDS stack; each step pops up to 64
-// of them (one per lane) and classifies each: M2L, M2P, P2P, pass-down (to
-// both children of A) or split (both children of B pushed).  Ballot ranks
-// keep every output in a fixed order, so every pass produces the same lists.
+// Where the lists of node A, the t-th of its depth, begin (o) and go: the slots
+// of the one-pass layout, or the scanned offsets with the rest of the buffer
+// as room (offsets are global).  A count pass stores nothing.
 template <int WMODE>
-__global__ __launch_bounds__(64) void k_fmm_walk(FmmDev F, const int *__restrict__ ids, int first, int count,
-                                                 int parity, double theta2, SlotDepth sd)
+__device__ __forceinline__ void list_outs(const FmmDev &F, int A, int t, int parity, const SlotDepth &sd,
+                                          long (&o)[kKinds], ListOut (&out)[kKinds])
+{
+    int *const list[kKinds] = {F.m2l, F.p2p, F.m2p, parity ? F.pass1 : F.pass0};
+#pragma unroll
+    for (int q = 0; q < kKinds; ++q) {
+        o[q] = WMODE == kWalkSlot ? sd.base[q] + (long)t * sd.cap[q] : WMODE == kWalkFill ? F.off[q * F.nn + A] : 0;
+        const long room = WMODE == kWalkSlot ? sd.cap[q] : cap_of(F, q) - o[q];
+        out[q].at = list[q] + o[q];
+        out[q].room = (int)min(max(room, 0L), (long)INT32_MAX);
+    }
+}
+
+// Places the wait for a loaded value here.
+__device__ __forceinline__ void arrived(int &v) { asm volatile("" : "+v"(v)); }
+
+// What becomes of source B (node record nb, centre and squared diagonal cb) at
+// target A, by the definitions above.  Without branches on the lane, so that
+// every value's one wait lies before the list stores.
+struct Verdict {
+    bool m2l, m2p, p2p, pass, split;
+};
+
+__device__ __forceinline__ Verdict classify(bool act, const int4 na, const double4 ca, bool aleaf, const float4 lo,
+                                            const float4 hi, const int4 nb, const double4 cb, double theta2)
+{
+    Verdict v;
+    const bool apart = act & !fmm_overlap(na, nb), bleaf = nb.z < 0;
+    const double dx = ca.x - cb.x, dy = ca.y - cb.y, dz = ca.z - cb.z;
+    const double dist2 = (dx * dx + dy * dy) + dz * dz;
+    v.m2l = apart & (ca.w + cb.w < theta2 * dist2);
+    v.m2p = false;
+    if (aleaf) {
+        const double gx = box_gap(cb.x, lo.x, hi.x);
+        const double gy = box_gap(cb.y, lo.y, hi.y);
+        const double gz = box_gap(cb.z, lo.z, hi.z);
+        const double D2 = (gx * gx + gy * gy) + gz * gz;
+        v.m2p = apart & !v.m2l & (cb.w < theta2 * D2);
+    }
+    const bool rest = act & !v.m2l & !v.m2p;
+    v.p2p = rest & aleaf & bleaf;
+    v.pass = rest & !aleaf & (bleaf | (ca.w >= cb.w));
+    v.split = rest & !v.p2p & !v.pass;
+    return v;
+}
+
+// The list that the children of node P inherit: P's pass-down list in the
+// previous depth's buffer, cut where P's slot or its depth overflowed.  The
+// root (P < 0) starts from itself, the one node of its depth.
+template <int WMODE>
+__device__ __forceinline__ const int *inherited(const FmmDev &F, const int *ids, int P, int parity,
+                                                const SlotDepth &sd, int &nin)
+{
+    nin = 1;
+    if (P < 0) return ids;
+    nin = F.cnt[kPass * F.nn + P];
+    const long base = F.off[kPass * F.nn + P];
+    if (WMODE == kWalkSlot) nin = min(nin, sd.prev_pass);
+    if (base + nin > F.cap_pass) nin = (int)max(0L, F.cap_pass - base);
+    return (parity ? F.pass0 : F.pass1) + (nin > 0 ? base : 0L);
+}
+
+// W waves per target node of one depth: the walk of its inherited sources.
+// The pending sources sit on an LDS stack; each step pops up to 64 W of them
+// (one per thread) and classifies each: M2L, M2P, P2P, pass-down (to both
+// children of A) or split (both children of B pushed).  Ballot ranks, and the
+// counts of the waves before, keep every output in a fixed order, so every
+// pass produces the same lists.
+template <int WMODE, int W>
+__global__ __launch_bounds__(64 * W) void k_fmm_walk(FmmDev F, const int *__restrict__ ids, int first, int parity,
+                                                     double theta2, SlotDepth sd, int room)
 {
     constexpr bool FILL = WMODE != kWalkCount;
-    __shared__ int stk[kWalkStack];
-    const int lane = threadIdx.x;
+    extern __shared__ int stk[];
+    static_assert(W > 1, "one wave would need its own order of the stack's reads and writes");
+    __shared__ int steps[W][kKinds + 1];  // this step's counts of each wave: the lists and the splits
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
     const int t = blockIdx.x;
-    if (t >= count) return;
     const int A = ids[t];
     const int4 na = F.node[A];
     const double4 ca = F.comd[A];
     const bool aleaf = na.z < 0;
-    double bx0 = 0.0, by0 = 0.0, bz0 = 0.0, bx1 = 0.0, by1 = 0.0, bz1 = 0.0;  // A's box (M2P test)
-    if (aleaf) {
-        const float4 l = F.lo[A], h = F.hi[A];
-        bx0 = l.x;
-        by0 = l.y;
-        bz0 = l.z;
-        bx1 = h.x;
-        by1 = h.y;
-        bz1 = h.z;
-    }
+    const float4 blo = F.lo[A], bhi = F.hi[A];  // A's box (M2P test)
     const int nn = F.nn;
-    const int *in = nullptr;
-    int nin = 1;
-    if (A != 0) {
-        const int P = F.parent[A];
-        nin = F.cnt[kPass * nn + P];
-        const long base = F.off[kPass * nn + P];
-        if (WMODE == kWalkSlot) nin = min(nin, sd.prev_pass);  // the parent's slot overflowed
-        if (base + nin > F.cap_pass) nin = (int)max(0L, F.cap_pass - base);  // the parent's depth overflowed
-        in = (parity ? F.pass0 : F.pass1) + base;  // the previous depth's buffer
-    }
-    int *pass_out = parity ? F.pass1 : F.pass0;
-    long om = 0, op = 0, oc = 0, oq = 0;
-    // room of each list: the slot in the one-pass layout, else all of the buffer
-    long rm = F.cap_m2l, rp = F.cap_p2p, rc = F.cap_m2p, rq = F.cap_pass;
-    if (WMODE == kWalkSlot) {
-        om = sd.base[kM2L] + (long)t * sd.cap[kM2L];
-        op = sd.base[kP2P] + (long)t * sd.cap[kP2P];
-        oc = sd.base[kM2P] + (long)t * sd.cap[kM2P];
-        oq = sd.base[kPass] + (long)t * sd.cap[kPass];
-        rm = sd.cap[kM2L];
-        rp = sd.cap[kP2P];
-        rc = sd.cap[kM2P];
-        rq = sd.cap[kPass];
-    } else if (FILL) {
-        om = F.off[kM2L * nn + A];
-        op = F.off[kP2P * nn + A];
-        oc = F.off[kM2P * nn + A];
-        oq = F.off[kPass * nn + A];
-        rm -= om;  // offsets are global: the room is the rest of the buffer
-        rp -= op;
-        rc -= oc;
-        rq -= oq;
-    }
+    int nin;
+    const int *in = inherited<WMODE>(F, ids, A == 0 ? -1 : F.parent[A], parity, sd, nin);
+    long o[kKinds];
+    ListOut out[kKinds];
+    list_outs<WMODE>(F, A, t, parity, sd, o, out);
     int cm = 0, cp = 0, cc = 0, cq = 0, top = 0, next = 0;
     bool bad = false;
+    // Waits: the inherited entry that this thread pushes at the next refill is
+    // loaded with the step's sources, and every lane loads (the idle ones the
+    // root).  A load under a lane mask, or one that is used after the list stores, is
+    // waited for together with those stores.
+    int ahead = in[min(tid, max(nin - 1, 0))];
     for (;;) {
-        if (top < 64 && next < nin) {  // refill from the inherited list
-            const int k = min(64, nin - next);
-            if (lane < k) stk[top + lane] = in ? in[next + lane] : 0;
+        if (top < 64 * W && next < nin) {  // refill from the inherited list
+            const int k = min(64 * W, nin - next);
+            if (tid < k) stk[top + tid] = ahead;
             top += k;
             next += k;
         }
         if (top == 0) break;
-        const int k = min(64, top);
+        const int k = min(64 * W, top);
         top -= k;
         __syncthreads();
-        const bool act = lane < k;
-        int B = act ? stk[top + lane] : 0;
-        __syncthreads();
+        const bool act = tid < k;
+        int B = act ? stk[top + tid] : 0;
         if ((unsigned)B >= (unsigned)nn) B = 0;  // only after an overflow upstream
-        bool m2l = false, m2p = false, p2p = false, pass = false, split = false;
-        int4 nb = make_int4(0, 0, -1, -1);
-        if (act) {
-            nb = F.node[B];
-            const double4 cb = F.comd[B];
-            const bool apart = !fmm_overlap(na, nb);
-            if (apart) {
-                const double dx = ca.x - cb.x, dy = ca.y - cb.y, dz = ca.z - cb.z;
-                const double dist2 = (dx * dx + dy * dy) + dz * dz;
-                m2l = ca.w + cb.w < theta2 * dist2;
-            }
-            if (!m2l && aleaf && apart) {
-                const double gx = box_gap(cb.x, bx0, bx1);
-                const double gy = box_gap(cb.y, by0, by1);
-                const double gz = box_gap(cb.z, bz0, bz1);
-                const double D2 = (gx * gx + gy * gy) + gz * gz;
-                m2p = cb.w < theta2 * D2;
-            }
-            if (!m2l && !m2p) {
-                const bool bleaf = nb.z < 0;
-                if (aleaf && bleaf)
-                    p2p = true;
-                else if (bleaf || (!aleaf && ca.w >= cb.w))
-                    pass = true;
-                else
-                    split = true;
-            }
-        }
+        ahead = in[min(next + tid, max(nin - 1, 0))];
+        const int4 nb = F.node[B];
+        const double4 cb = F.comd[B];
+        const Verdict v = classify(act, na, ca, aleaf, blo, bhi, nb, cb, theta2);
+        arrived(ahead);
+        const bool m2l = v.m2l, m2p = v.m2p, p2p = v.p2p, pass = v.pass, split = v.split;
         const unsigned long long mm = __ballot(m2l), mc = __ballot(m2p), mp = __ballot(p2p), mq = __ballot(pass),
                                  ms = __ballot(split);
-        if (FILL) {
-            if (m2l && !put_entry(F.m2l, om, cm, rm, mm, B)) bad = true;
-            if (m2p && !put_entry(F.m2p, oc, cc, rc, mc, B)) bad = true;
-            if (p2p && !put_entry(F.p2p, op, cp, rp, mp, nb.x)) bad = true;  // a leaf as its first body
-            if (pass && !put_entry(pass_out, oq, cq, rq, mq, B)) bad = true;
+        // the step's counts, and how many of them lie in the waves before this one
+        int sum[kKinds + 1] = {(int)__popcll(mm), (int)__popcll(mp), (int)__popcll(mc), (int)__popcll(mq), (int)__popcll(ms)};
+        int before[kKinds + 1] = {0, 0, 0, 0, 0};
+        if (lane == 0)
+#pragma unroll
+            for (int q = 0; q <= kKinds; ++q) steps[wave][q] = sum[q];
+        __syncthreads();  // every wave has popped, too: the stack may be written
+#pragma unroll
+        for (int q = 0; q <= kKinds; ++q) {
+            sum[q] = 0;
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                if (w == wave) before[q] = sum[q];
+                sum[q] += steps[w][q];
+            }
         }
-        cm += __popcll(mm);
-        cc += __popcll(mc);
-        cp += __popcll(mp);
-        cq += __popcll(mq);
-        const int ns = __popcll(ms);
-        if (top + 2 * ns > kWalkStack) {  // cannot happen for trees the host admits
+        if (FILL) {
+            if (m2l && !put_entry(out[kM2L], cm + before[kM2L], mm, B)) bad = true;
+            if (m2p && !put_entry(out[kM2P], cc + before[kM2P], mc, B)) bad = true;
+            if (p2p && !put_entry(out[kP2P], cp + before[kP2P], mp, nb.x)) bad = true;  // a leaf as its first body
+            if (pass && !put_entry(out[kPass], cq + before[kPass], mq, B)) bad = true;
+        }
+        cm += sum[kM2L];
+        cp += sum[kP2P];
+        cc += sum[kM2P];
+        cq += sum[kPass];
+        const int ns = sum[kKinds];
+        if (top + 2 * ns > room) {  // cannot happen for trees the host admits
             bad = true;
             break;
         }
         if (split) {
-            const int q = top + 2 * (int)fmm_rank(ms);
+            const int q = top + 2 * (before[kKinds] + (int)fmm_rank(ms));
             stk[q] = nb.w;
             stk[q + 1] = nb.z;
         }
         top += 2 * ns;
         __syncthreads();
     }
-    if (WMODE != kWalkFill && lane == 0) {
+    if (WMODE != kWalkFill && tid == 0) {
         const int c4[kKinds] = {cm, cp, cc, cq};
-        const long o4[kKinds] = {om, op, oc, oq};
 #pragma unroll
         for (int q = 0; q < kKinds; ++q) {
             F.cnt[q * nn + A] = c4[q];
             if (WMODE == kWalkCount)
                 F.lcnt[q * nn + first + t] = c4[q];
             else
-                F.off[q * nn + A] = (int)o4[q];
+                F.off[q * nn + A] = (int)o[q];
         }
     }
     if (__ballot(bad) && lane == 0) atomicOr(&F.tot[0], 1ull);
 }
 
-// TPW target nodes per wave: positions TPW b .. TPW b + TPW - 1 of
-// one depth.  Below the root every depth holds whole sibling pairs, adjacent
-// in preorder, so targets 2j and 2j + 1 are the children of one parent and
-// inherit the same list; each distinct inherited list is loaded once.  The
-// stack holds the union of the targets' pending sources, each entry tagged
-// with the targets that still need it (bit k for target k, in the four high
-// bits of the entry; node ids stay below 2^28, which the host checks).  A
-// popped source is gathered once and classified for each of its targets by
-// the same tests as the one-target walk; it is split (children pushed,
-// tagged with the targets that split it) if any target splits it.  Each
-// target's lists are written at ballot ranks in pop order, so every pass
-// produces the same lists for a target: the same entries as the one-target
-// walk's, in another order.
+// Two target nodes per wave: positions 2 b and 2 b + 1 of one depth.  Below the
+// root every depth holds whole sibling pairs, adjacent in preorder, so these
+// are the children of one parent and inherit the same list.  The stack holds
+// the union of the targets' pending sources, each entry tagged with the
+// targets that still need it (bit k for target k, in the four high bits of the
+// entry; node ids stay below 2^28, which the host checks).  A popped source is
+// gathered once and classified for each of its targets by the same tests as in
+// the one-target walk; it is split (children pushed, tagged with the targets
+// that split it) if any target splits it.  Each target's lists are written at
+// ballot ranks in pop order, so every pass produces the same lists for a
+// target: the same entries as the one-target walk's, in another order.
 constexpr unsigned kTagShift = 28, kIdMask = (1u << kTagShift) - 1;
 
-template <int WMODE, int TPW>
-__global__ __launch_bounds__(64) void k_fmm_walk_multi(FmmDev F, const int *__restrict__ ids, int first, int count,
-                                                       int parity, double theta2, SlotDepth sd)
+template <int WMODE>
+__global__ __launch_bounds__(64) void k_fmm_walk_pair(FmmDev F, const int *__restrict__ ids, int first, int parity,
+                                                      double theta2, SlotDepth sd, int room)
 {
+    constexpr int TPW = 2;
     constexpr bool FILL = WMODE != kWalkCount;
-    __shared__ unsigned stk[kWalkStack];
+    extern __shared__ unsigned ustk[];
+    unsigned *const stk = ustk;
     const int lane = threadIdx.x;
     const int nn = F.nn;
-    int *pass_out = parity ? F.pass1 : F.pass0;
-    const int *pass_in = parity ? F.pass0 : F.pass1;  // the previous depth's buffer
-    int tpos[TPW], A[TPW], parent[TPW];
+    int tpos[TPW], A[TPW];
     int4 na[TPW];
     double4 ca[TPW];
-    bool aleaf[TPW], live[TPW];
-    double b0[TPW][3], b1[TPW][3];  // each target's box (M2P test)
-    long o[TPW][kKinds], room[TPW][kKinds];
+    bool aleaf[TPW];
+    float4 blo[TPW], bhi[TPW];  // each target's box (M2P test)
+    long o[TPW][kKinds];
+    ListOut out[TPW][kKinds];
     int c[TPW][kKinds];
-    // inherited lists: segment g is list seg_in[g] of seg_n[g] entries for the targets seg_tag[g]
-    const int *seg_in[TPW];
-    int seg_n[TPW];
-    unsigned seg_tag[TPW];
-    int nseg = 0;
 #pragma unroll
     for (int k = 0; k < TPW; ++k) {
         tpos[k] = TPW * blockIdx.x + k;
-        live[k] = tpos[k] < count;
-        A[k] = live[k] ? ids[tpos[k]] : ids[TPW * blockIdx.x];
+        A[k] = ids[tpos[k]];
         na[k] = F.node[A[k]];
         ca[k] = F.comd[A[k]];
         aleaf[k] = na[k].z < 0;
-        const float4 l = F.lo[A[k]], h = F.hi[A[k]];
-        b0[k][0] = l.x;
-        b0[k][1] = l.y;
-        b0[k][2] = l.z;
-        b1[k][0] = h.x;
-        b1[k][1] = h.y;
-        b1[k][2] = h.z;
-        parent[k] = A[k] == 0 ? -1 : F.parent[A[k]];
+        blo[k] = F.lo[A[k]];
+        bhi[k] = F.hi[A[k]];
+        list_outs<WMODE>(F, A[k], tpos[k], parity, sd, o[k], out[k]);
 #pragma unroll
-        for (int q = 0; q < kKinds; ++q) {
-            c[k][q] = 0;
-            if (WMODE == kWalkSlot) {
-                o[k][q] = sd.base[q] + (long)tpos[k] * sd.cap[q];
-                room[k][q] = sd.cap[q];
-            } else if (FILL) {
-                o[k][q] = F.off[q * nn + A[k]];
-                room[k][q] = cap_of(F, q) - o[k][q];  // offsets are global: the rest of the buffer
-            } else {
-                o[k][q] = 0;
-                room[k][q] = cap_of(F, q);
-            }
-        }
-        if (!live[k]) continue;
-        if (k > 0 && live[k - 1] && parent[k] >= 0 && parent[k] == parent[k - 1]) {
-            seg_tag[nseg - 1] |= 1u << k;  // the sibling's list serves both
-            continue;
-        }
-        if (A[k] == 0) {
-            seg_in[nseg] = nullptr;
-            seg_n[nseg] = 1;
-        } else {
-            int m = F.cnt[kPass * nn + parent[k]];
-            const long base = F.off[kPass * nn + parent[k]];
-            if (WMODE == kWalkSlot) m = min(m, sd.prev_pass);  // the parent's slot overflowed
-            if (base + m > F.cap_pass) m = (int)max(0L, F.cap_pass - base);  // the parent's depth overflowed
-            seg_in[nseg] = pass_in + base;
-            seg_n[nseg] = m;
-        }
-        seg_tag[nseg] = 1u << k;
-        ++nseg;
+        for (int q = 0; q < kKinds; ++q) c[k][q] = 0;
     }
-    int seg = 0, next = 0, top = 0;
+    int nin;
+    const int *in = inherited<WMODE>(F, ids, F.parent[A[0]], parity, sd, nin);
+    int next = 0, top = 0;
     bool bad = false;
+    int ahead = in[min(lane, max(nin - 1, 0))];  // loads and waits as in the one-target walk
     for (;;) {
-        while (top < 64 && seg < nseg) {  // refill
-            const int m = seg_n[seg];
-            const int take = min(64, m - next);
-            if (take > 0) {
-                if (lane < take)
-                    stk[top + lane] = (seg_in[seg] ? (unsigned)seg_in[seg][next + lane] : 0u) |
-                                      (seg_tag[seg] << kTagShift);
-                top += take;
-                next += take;
-            }
-            if (next >= m) {
-                ++seg;
-                next = 0;
-            }
+        if (top < 64 && next < nin) {  // refill
+            const int take = min(64, nin - next);
+            if (lane < take) stk[top + lane] = (unsigned)ahead | (((1u << TPW) - 1) << kTagShift);
+            top += take;
+            next += take;
         }
         if (top == 0) break;
         const int kpop = min(64, top);
@@ -398,47 +385,22 @@ __global__ __launch_bounds__(64) void k_fmm_walk_multi(FmmDev F, const int *__re
         int B = (int)(e & kIdMask);
         const unsigned tag = e >> kTagShift;
         if ((unsigned)B >= (unsigned)nn) B = 0;  // only after an overflow upstream
-        int4 nb = make_int4(0, 0, -1, -1);
-        double4 cb = make_double4(0.0, 0.0, 0.0, 0.0);
-        if (act) {
-            nb = F.node[B];
-            cb = F.comd[B];
-        }
+        ahead = in[min(next + lane, max(nin - 1, 0))];
+        const int4 nb = F.node[B];
+        const double4 cb = F.comd[B];
+        arrived(ahead);
         unsigned split_tag = 0;
 #pragma unroll
         for (int k = 0; k < TPW; ++k) {
-            bool m2l = false, m2p = false, p2p = false, pass = false, split = false;
-            if (act && (tag >> k & 1u)) {
-                const bool apart = !fmm_overlap(na[k], nb);
-                if (apart) {
-                    const double dx = ca[k].x - cb.x, dy = ca[k].y - cb.y, dz = ca[k].z - cb.z;
-                    const double dist2 = (dx * dx + dy * dy) + dz * dz;
-                    m2l = ca[k].w + cb.w < theta2 * dist2;
-                }
-                if (!m2l && aleaf[k] && apart) {
-                    const double gx = box_gap(cb.x, b0[k][0], b1[k][0]);
-                    const double gy = box_gap(cb.y, b0[k][1], b1[k][1]);
-                    const double gz = box_gap(cb.z, b0[k][2], b1[k][2]);
-                    const double D2 = (gx * gx + gy * gy) + gz * gz;
-                    m2p = cb.w < theta2 * D2;
-                }
-                if (!m2l && !m2p) {
-                    const bool bleaf = nb.z < 0;
-                    if (aleaf[k] && bleaf)
-                        p2p = true;
-                    else if (bleaf || (!aleaf[k] && ca[k].w >= cb.w))
-                        pass = true;
-                    else
-                        split = true;
-                }
-            }
+            const Verdict v = classify(act && (tag >> k & 1u), na[k], ca[k], aleaf[k], blo[k], bhi[k], nb, cb, theta2);
+            const bool m2l = v.m2l, m2p = v.m2p, p2p = v.p2p, pass = v.pass, split = v.split;
             const unsigned long long mm = __ballot(m2l), mc = __ballot(m2p), mp = __ballot(p2p),
                                      mq = __ballot(pass);
             if (FILL) {
-                if (m2l && !put_entry(F.m2l, o[k][kM2L], c[k][kM2L], room[k][kM2L], mm, B)) bad = true;
-                if (m2p && !put_entry(F.m2p, o[k][kM2P], c[k][kM2P], room[k][kM2P], mc, B)) bad = true;
-                if (p2p && !put_entry(F.p2p, o[k][kP2P], c[k][kP2P], room[k][kP2P], mp, nb.x)) bad = true;
-                if (pass && !put_entry(pass_out, o[k][kPass], c[k][kPass], room[k][kPass], mq, B)) bad = true;
+                if (m2l && !put_entry(out[k][kM2L], c[k][kM2L], mm, B)) bad = true;
+                if (m2p && !put_entry(out[k][kM2P], c[k][kM2P], mc, B)) bad = true;
+                if (p2p && !put_entry(out[k][kP2P], c[k][kP2P], mp, nb.x)) bad = true;
+                if (pass && !put_entry(out[k][kPass], c[k][kPass], mq, B)) bad = true;
             }
             c[k][kM2L] += __popcll(mm);
             c[k][kM2P] += __popcll(mc);
@@ -448,7 +410,7 @@ __global__ __launch_bounds__(64) void k_fmm_walk_multi(FmmDev F, const int *__re
         }
         const unsigned long long ms = __ballot(split_tag != 0);
         const int ns = __popcll(ms);
-        if (top + 2 * ns > kWalkStack) {  // cannot happen for trees the host admits
+        if (top + 2 * ns > room) {  // cannot happen for trees the host admits
             bad = true;
             break;
         }
@@ -463,7 +425,6 @@ __global__ __launch_bounds__(64) void k_fmm_walk_multi(FmmDev F, const int *__re
     if (WMODE != kWalkFill && lane == 0) {
 #pragma unroll
         for (int k = 0; k < TPW; ++k) {
-            if (!live[k]) continue;
 #pragma unroll
             for (int q = 0; q < kKinds; ++q) {
                 F.cnt[q * nn + A[k]] = c[k][q];
@@ -477,29 +438,31 @@ __global__ __launch_bounds__(64) void k_fmm_walk_multi(FmmDev F, const int *__re
     if (__ballot(bad) && lane == 0) atomicOr(&F.tot[0], 1ull);
 }
 
-// Target nodes per wave at a depth of `count` nodes: the deep depths, with
-// enough nodes to fill the chip more than once, walk 2 per wave (half the
-// waves, each source gathered once for both); the others 1, for
-// parallelism.  Measured at 2^20 (leaf 8, theta 0.5): the depths of 8192 to
-// 131072 nodes took 239-1019 us against 311-1141 us with one target per
-// wave, and 708-1299 us with 4 per wave from 32768 nodes on.
+// How the nodes of one depth are walked.  The deep depths, with enough nodes to
+// fill the chip more than once, walk 2 per wave (half the waves, each source
+// gathered once for both).  Measured at 2^20 (leaf 8, theta 0.5) with the walks
+// as they first were: the depths of 8192 to 131072 nodes took 239-1019 us
+// against 311-1141 us with one target per wave, and 708-1299 us with 4 per wave
+// from 32768 nodes on.  The depths above have fewer nodes than the chip has
+// room for waves, and a depth lasts as long as its longest walk, a chain of
+// steps: four waves per node take four steps' sources at once.  At 262144
+// bodies (leaf 8, theta 0.5) an FMM force took 2131 us with one wave per node,
+// 1952 us with four; eight gain 1% at up to 512 nodes and lose above.
 constexpr int kPairNodes = 8192;
-int walk_tpw(int count, int nn)
-{
-    if (nn > (int)kIdMask) return 1;
-    return count >= kPairNodes ? 2 : 1;
-}
+constexpr int kNodeWaves = 4;
 
 template <int WMODE>
-void launch_walk_depth(int tpw, const FmmDev &F, const int *ids, int first, int count, int parity, double theta2,
+void launch_walk_depth(const FmmDev &F, const int *ids, int first, int count, int stack, int parity, double theta2,
                        const SlotDepth &sd, hipStream_t s)
 {
-    if (tpw == 2)
-        hipLaunchKernelGGL((k_fmm_walk_multi<WMODE, 2>), dim3((count + 1) / 2), dim3(64), 0, s, F, ids, first, count,
-                           parity, theta2, sd);
+    // (below the root a depth holds whole sibling pairs)
+    if (count >= kPairNodes && count % 2 == 0 && F.nn <= (int)kIdMask)
+        hipLaunchKernelGGL(k_fmm_walk_pair<WMODE>, dim3(count / 2), dim3(64), stack * sizeof(int), s, F, ids, first,
+                           parity, theta2, sd, stack);
     else
-        hipLaunchKernelGGL(k_fmm_walk<WMODE>, dim3(count), dim3(64), 0, s, F, ids, first, count, parity, theta2,
-                           sd);
+        hipLaunchKernelGGL((k_fmm_walk<WMODE, kNodeWaves>), dim3(count), dim3(64 * kNodeWaves),
+                           kNodeWaves * stack * sizeof(int), s, F, ids, first, parity, theta2, sd,
+                           kNodeWaves * stack);
 }
 
 // Sum over the wave of four values (fixed butterfly).
@@ -852,6 +815,7 @@ __global__ void k_fmm_zero_tot(unsigned long long *tot, int count)
 // ---- host side -----------------------------------------------------------------
 struct FmmPlan {
     int n = 0, leaf = 0, dev = -1, nn = 0, depth = 0, max_level = 0;
+    int stack = 0;  // LDS stack entries that a walking wave needs at this height
     std::vector<int> parent, by_depth, depth_off;
     int *d_parent = nullptr, *d_by_depth = nullptr, *d_leaves = nullptr;
 };
@@ -919,6 +883,7 @@ int make_plan(const HostTree &h, int n, int leaf, int dev, hipStream_t s)
         set_error("tree height %d too large for the FMM traversal stack", h.height[0]);
         return NBODY_E_UNSUPPORTED;
     }
+    p.stack = 64 * (h.height[0] + 2);
     p.parent.assign(nn, -1);
     std::vector<int> dep(nn, 0);
     for (int a = 0; a < nn; ++a) {  // preorder: parents come first
@@ -1042,11 +1007,10 @@ hipError_t launch_traversal(const FmmDev &F, const FmmPlan &p, double theta2, hi
         const int first = p.depth_off[d], count = p.depth_off[d + 1] - first;
         const int *ids = p.d_by_depth + first;
         const int nblk = (count + kScanBlock - 1) / kScanBlock;
-        const int tpw = walk_tpw(count, F.nn);
-        launch_walk_depth<kWalkCount>(tpw, F, ids, first, count, d & 1, theta2, SlotDepth{}, s);
+        launch_walk_depth<kWalkCount>(F, ids, first, count, p.stack, d & 1, theta2, SlotDepth{}, s);
         hipLaunchKernelGGL(k_fmm_scan_part, dim3(nblk), dim3(256), 0, s, F, first, count);
         hipLaunchKernelGGL(k_fmm_scan_fin, dim3(nblk), dim3(256), 0, s, F, ids, first, count, d, nblk);
-        launch_walk_depth<kWalkFill>(tpw, F, ids, first, count, d & 1, theta2, SlotDepth{}, s);
+        launch_walk_depth<kWalkFill>(F, ids, first, count, p.stack, d & 1, theta2, SlotDepth{}, s);
         e = hipGetLastError();
     }
     return e;
@@ -1059,8 +1023,7 @@ hipError_t launch_traversal_slots(const FmmDev &F, const FmmPlan &p, double thet
     hipError_t e = hipGetLastError();
     for (int d = 0; d <= p.depth && e == hipSuccess; ++d) {
         const int first = p.depth_off[d], count = p.depth_off[d + 1] - first;
-        const int tpw = walk_tpw(count, F.nn);
-        launch_walk_depth<kWalkSlot>(tpw, F, p.d_by_depth + first, first, count, d & 1, theta2, g_slots.depth[d],
+        launch_walk_depth<kWalkSlot>(F, p.d_by_depth + first, first, count, p.stack, d & 1, theta2, g_slots.depth[d],
                                      s);
         e = hipGetLastError();
     }

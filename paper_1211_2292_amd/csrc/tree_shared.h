@@ -50,10 +50,12 @@ std::mutex &tree_mutex();
 
 namespace {
 
-// Distance along one axis from p to the interval [a, b] (0 inside).
+// Distance along one axis from p to the interval [a, b] (0 inside).  Outside,
+// exactly one of the differences is positive; the maximum is the same number
+// as the choice by comparisons, in half the instructions.
 __device__ __forceinline__ double box_gap(double p, double a, double b)
 {
-    return p < a ? a - p : (p > b ? p - b : 0.0);
+    return __builtin_fmax(__builtin_fmax(a - p, p - b), 0.0);
 }
 
 // One quadrupole cell against the lane's TPL targets: c = (com, M),

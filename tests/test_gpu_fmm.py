@@ -82,6 +82,24 @@ def test_lists_match_oracle_two_targets_per_wave(orc, n, leaf, theta, kind):
     assert rms_rel(out[tg, 3], p) < 1e-6
 
 
+@pytest.mark.parametrize("n,leaf,theta", [(4097, 1, 0.15), (9001, 1, 0.3), (65536, 8, 0.6), (65537, 8, 0.6)])
+def test_lists_of_deep_trees_and_small_depths(orc, n, leaf, theta):
+    """Leaves of one body (the tallest tree for n, most of it open at these
+    theta, so the walks' stacks fill), and a deepest depth of 8192 nodes or
+    just more, where the walks change from four waves per node to two nodes
+    per wave: the lists are the oracle's as sets."""
+    torch, nb = gpu()
+    pm, _ = ics.plummer(n, 830 + n)
+    q, qh = _orb_input(torch, nb, pm, leaf)
+    got = dict(zip(("m2l_cnt", "m2p_cnt", "p2p_cnt", "m2l", "m2p", "p2p"),
+                   (host(t).astype(np.int64) for t in nb.fmm_lists(q, theta, leaf))))
+    want = orc.fmm_lists(qh, leaf, theta)
+    for k in ("m2l", "m2p", "p2p"):
+        c = got[k + "_cnt"]
+        assert np.array_equal(c, want[k + "_cnt"]), k
+        assert np.array_equal(_per_node_sorted(got[k], c), _per_node_sorted(want[k], want[k + "_cnt"])), k
+
+
 @pytest.mark.parametrize("prec,tol_rms,tol_max", [("F32_F64ACC", 1e-6, 2e-5), ("F32_KAHAN", 1e-6, 2e-5),
                                                   ("F32", 2e-6, 1e-4)])
 @pytest.mark.parametrize("theta,leaf", [(0.0, 8), (0.5, 8), (0.7, 4), (0.6, 16)])
