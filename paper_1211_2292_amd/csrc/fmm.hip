@@ -79,7 +79,7 @@ constexpr int kScanBlock = 1024;  // positions per scan block (256 threads x 4)
 
 struct FmmDev {
     const int4 *node;
-    const double4 *comd;
+    const NodeRec *nrec;
     const float4 *lo, *hi;
     const float4 *qr;
     const int *parent;
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(64 * W) void k_fmm_walk(FmmDev F, const int *__rest
     const int t = blockIdx.x;
     const int A = ids[t];
     const int4 na = F.node[A];
-    const double4 ca = F.comd[A];
+    const double4 ca = F.nrec[A].cd;
     const bool aleaf = na.z < 0;
     const float4 blo = F.lo[A], bhi = F.hi[A];  // A's box (M2P test)
     const int nn = F.nn;
@@ -259,8 +259,8 @@ __global__ __launch_bounds__(64 * W) void k_fmm_walk(FmmDev F, const int *__rest
         int B = act ? stk[top + tid] : 0;
         if ((unsigned)B >= (unsigned)nn) B = 0;  // only after an overflow upstream
         ahead = in[min(next + tid, max(nin - 1, 0))];
-        const int4 nb = F.node[B];
-        const double4 cb = F.comd[B];
+        const int4 nb = F.nrec[B].nd;
+        const double4 cb = F.nrec[B].cd;
         const Verdict v = classify(act, na, ca, aleaf, blo, bhi, nb, cb, theta2);
         arrived(ahead);
         const bool m2l = v.m2l, m2p = v.m2p, p2p = v.p2p, pass = v.pass, split = v.split;
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(64) void k_fmm_walk_pair(FmmDev F, const int *__res
         tpos[k] = TPW * blockIdx.x + k;
         A[k] = ids[tpos[k]];
         na[k] = F.node[A[k]];
-        ca[k] = F.comd[A[k]];
+        ca[k] = F.nrec[A[k]].cd;
         aleaf[k] = na[k].z < 0;
         blo[k] = F.lo[A[k]];
         bhi[k] = F.hi[A[k]];
@@ -386,8 +386,8 @@ __global__ __launch_bounds__(64) void k_fmm_walk_pair(FmmDev F, const int *__res
         const unsigned tag = e >> kTagShift;
         if ((unsigned)B >= (unsigned)nn) B = 0;  // only after an overflow upstream
         ahead = in[min(next + lane, max(nin - 1, 0))];
-        const int4 nb = F.node[B];
-        const double4 cb = F.comd[B];
+        const int4 nb = F.nrec[B].nd;
+        const double4 cb = F.nrec[B].cd;
         arrived(ahead);
         unsigned split_tag = 0;
 #pragma unroll
@@ -573,7 +573,7 @@ __global__ __launch_bounds__(256) void k_fmm_m2l(FmmDev F, float eps2)
     if (A >= F.nn) return;
     const int c = F.cnt[kM2L * F.nn + A];
     const long o = F.off[kM2L * F.nn + A];
-    const double4 ca = F.comd[A];
+    const double4 ca = F.nrec[A].cd;
     const float zx = (float)ca.x, zy = (float)ca.y, zz = (float)ca.z;
     Local L;
 #pragma unroll
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(256) void k_fmm_l2l(FmmDev F, const int *__restrict
         return;
     }
     const double *c = F.loc + 20L * P;
-    const double4 ca = F.comd[A], cp = F.comd[P];
+    const double4 ca = F.nrec[A].cd, cp = F.nrec[P].cd;
     const double d[3] = {ca.x - cp.x, ca.y - cp.y, ca.z - cp.z};
     double kd[3], td[3][3], tdd[3];
     fmm_contract(c, d, kd, td, tdd);
@@ -771,7 +771,7 @@ __global__ __launch_bounds__(64) void k_fmm_leaf(const float4 *__restrict__ src,
     // the leaf's expansion at this body, in FP64
     const float4 pt = src[i];
     const double *c = F.loc + 20L * A;
-    const double4 ca = F.comd[A];
+    const double4 ca = F.nrec[A].cd;
     const double y[3] = {(double)pt.x - ca.x, (double)pt.y - ca.y, (double)pt.z - ca.z};
     double ky[3], ty[3][3], tyy[3];
     fmm_contract(c, y, ky, ty, tyy);
@@ -973,7 +973,7 @@ FmmDev dev_view(const TreeDev &d, const FmmPlan &p, const FmmBufs &b)
 {
     FmmDev F;
     F.node = d.node;
-    F.comd = d.comd;
+    F.nrec = d.nrec;
     F.lo = d.lo;
     F.hi = d.hi;
     F.qr = d.qr;

@@ -136,8 +136,8 @@ __device__ __forceinline__ void node_store(const TreeDev &T, int c, const Moment
     d2 = d2 + ez * ez;
     const float4 rec = make_float4((float)m.cx, (float)m.cy, (float)m.cz, (float)m.M);
     T.sums[c] = make_double4(m.M, m.sx, m.sy, m.sz);
-    T.comd[c] = make_double4(m.cx, m.cy, m.cz, d2);
-    T.rec[c] = rec;
+    T.nrec[c].cd = make_double4(m.cx, m.cy, m.cz, d2);
+    T.nrec[c].rec = rec;
     T.lo[c] = make_float4(m.lo[0], m.lo[1], m.lo[2], 0.0f);
     T.hi[c] = make_float4(m.hi[0], m.hi[1], m.hi[2], 0.0f);
     if constexpr (Q2) {
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(K) void k_tree_moments(const float4 *__restrict__ p
                 leaf_moments(pm, T.node[d.x], m);
                 node_store(T, d.x, m, quad);
             } else {
-                const double4 a = T.sums[d.x], c = T.comd[d.x];
+                const double4 a = T.sums[d.x], c = T.nrec[d.x].cd;
                 const float4 lo = T.lo[d.x], hi = T.hi[d.x];
                 m.M = a.x;
                 m.sx = a.y;
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(256) void k_tree_pseudo(TreeDev T, int nn)
         s1 = 0.0;
         s2 = v * inv;
     }
-    const double4 cd = T.comd[c];
+    const double4 cd = T.nrec[c].cd;
     const double M = T.sums[c].x;
     const double a = 0.5 * sqrt(cd.w);
     double q = M / kPseudo;
@@ -516,7 +516,7 @@ k_tree_walk(const float4 *__restrict__ src, int n, TreeDev T, const float4 *__re
     const float4 glo = T.lo[gnode], ghi = T.hi[gnode];
     const double ax = glo.x, ay = glo.y, az = glo.z, bx = ghi.x, by = ghi.y, bz = ghi.z;
     const float eps2 = lane_copy(eps2_in);
-    const double4 gcd = T.comd[gnode];  // the group's centre of mass and diag2
+    const double4 gcd = T.nrec[gnode].cd;  // the group's centre of mass and diag2
     const float zgx = (float)gcd.x, zgy = (float)gcd.y, zgz = (float)gcd.z;
     Local Lx;
 #pragma unroll
@@ -618,8 +618,8 @@ k_tree_walk(const float4 *__restrict__ src, int n, TreeDev T, const float4 *__re
         bool acc = false, nearr = false, open = false, loc = false;
         int4 nd = make_int4(0, 0, -1, -1);
         if (act) {
-            nd = T.node[c];
-            const double4 cd = T.comd[c];
+            nd = T.nrec[c].nd;
+            const double4 cd = T.nrec[c].cd;
             if constexpr (CELLS == kCellsLocal) {
                 const double ex = cd.x - gcd.x, ey = cd.y - gcd.y, ez = cd.z - gcd.z;
                 const double dz2 = (ex * ex + ey * ey) + ez * ez;
@@ -706,7 +706,7 @@ k_tree_walk(const float4 *__restrict__ src, int n, TreeDev T, const float4 *__re
                     cid[slot] = c;
                 } else {
                     static_assert(CELLS == kCellsMono, "unhandled cell model");
-                    cbuf[slot] = T.rec[c];
+                    cbuf[slot] = T.nrec[c].rec;
                 }
             }
             if (nearr) nbuf[fn + (int)lane_rank(mn)] = make_int2(nd.x, nd.y);
@@ -837,7 +837,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_bins(TreeDev T, int ng)
     __syncthreads();
     const int g = blockIdx.x * kOrderThreads + t;
     if (g < ng) {
-        const unsigned b = min(__float_as_uint((float)T.comd[T.groups[g]].w) >> 21, (unsigned)(kOrderBins - 1));
+        const unsigned b = min(__float_as_uint((float)T.nrec[T.groups[g]].cd.w) >> 21, (unsigned)(kOrderBins - 1));
         T.obin[g] = (unsigned short)b;
         atomicAdd(&lh[b], 1);
     }
@@ -934,11 +934,18 @@ __global__ __launch_bounds__(kOrderThreads) void k_group_order(TreeDev T, int ng
     }
 }
 
+// The node table's copy in the walk records.
+__global__ __launch_bounds__(256) void k_tree_nodes(TreeDev T, int nn)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < nn) T.nrec[i].nd = T.node[i];
+}
+
 __global__ void k_tree_export(TreeDev T, int nn, double *__restrict__ mom, float *__restrict__ box)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= nn) return;
-    const double4 s = T.sums[c], d = T.comd[c];
+    const double4 s = T.sums[c], d = T.nrec[c].cd;
     const float4 lo = T.lo[c], hi = T.hi[c];
     if (mom) {
         mom[5L * c + 0] = s.x;
@@ -1129,9 +1136,8 @@ int tree_prepare(int n, int leaf, hipStream_t s, TreeDev &out)
     const size_t o_msub = o_ment + align256(h.mom_ent.size() * sizeof(int4));
     const size_t o_grp = o_msub + align256(h.mom_sub.size() * sizeof(int2));
     const size_t o_sums = o_grp + align256(ng * sizeof(int));
-    const size_t o_comd = o_sums + align256(nn * sizeof(double4));
-    const size_t o_rec = o_comd + align256(nn * sizeof(double4));
-    const size_t o_lo = o_rec + align256(nn * sizeof(float4));
+    const size_t o_nrec = o_sums + align256(nn * sizeof(double4));
+    const size_t o_lo = o_nrec + align256(nn * sizeof(NodeRec));
     const size_t o_hi = o_lo + align256(nn * sizeof(float4));
     const size_t o_s2a = o_hi + align256(nn * sizeof(float4));
     const size_t o_s2b = o_s2a + align256(nn * sizeof(double4));
@@ -1160,8 +1166,7 @@ int tree_prepare(int n, int leaf, hipStream_t s, TreeDev &out)
     d.mom_sub = (const int2 *)(base + o_msub);
     d.groups = (const int *)(base + o_grp);
     d.sums = (double4 *)(base + o_sums);
-    d.comd = (double4 *)(base + o_comd);
-    d.rec = (float4 *)(base + o_rec);
+    d.nrec = (NodeRec *)(base + o_nrec);
     d.lo = (float4 *)(base + o_lo);
     d.hi = (float4 *)(base + o_hi);
     d.s2a = (double4 *)(base + o_s2a);
@@ -1183,6 +1188,10 @@ int tree_prepare(int n, int leaf, hipStream_t s, TreeDev &out)
                            hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(base + o_grp, C.host.groups.data(), ng * sizeof(int), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_tree_nodes, dim3((nn + 255) / 256), dim3(256), 0, s, d, (int)nn);
+        e = hipGetLastError();
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipFree(mem);
@@ -1242,7 +1251,7 @@ template <int MODE, bool INSPECT, int CELLS, bool NEAR_LDS, int W>
 hipError_t launch_walk(const float4 *pm, int n, const TreeDev &d, int ngroups, float eps2, double G,
                        double theta2, const WalkOut &o, hipStream_t s)
 {
-    const float4 *recs = CELLS == kCellsPseudo ? d.pp : (CELLS >= kCellsQuad ? d.qr : d.rec);
+    const float4 *recs = CELLS == kCellsPseudo ? d.pp : (CELLS >= kCellsQuad ? d.qr : nullptr);
     // the local-expansion force walk over many groups runs the largest boxes
     // first (unless NBODY_TREE_ORDER=0); the other walks and inspection keep
     // ORB order

@@ -16,14 +16,25 @@ namespace nbi {
 constexpr int kQuadRec = 3;  // float4 records per cell (quadrupole cells)
 constexpr int kCellsMono = 0, kCellsPseudo = 2, kCellsQuad = 3, kCellsLocal = 4;
 
+// What a walk reads of a visited node, in half a cache line.  A walk step gathers
+// 64 nodes and is bound by the lines it touches; with the centres, the
+// child links and the records in arrays of their own that was two lines per
+// node (three forces of 1000001 bodies with local expansions 6788 -> 6013 us, with
+// monopole cells 7500 -> 7000; an FMM force of 2^20 bodies 6380 -> 5877, of
+// 262144 bodies 1933 -> 1844).
+struct alignas(64) NodeRec {
+    double4 cd;  // com (FP64), diag2
+    int4 nd;     // begin, end, left, right (-1 for a leaf)
+    float4 rec;  // com (FP32), M (FP32): the pseudo-body record
+};
+
 struct TreeDev {
     const int4 *node;    // begin, end, left, right (-1 for a leaf)
     const int4 *mom_ent;   // the moment kernels' subtrees: (node, left, right, height), inputs first
     const int2 *mom_sub;   // per subtree: first entry, entries
     const int *groups;     // group node ids in ORB order
     double4 *sums;       // M, Sx, Sy, Sz
-    double4 *comd;       // com (FP64), diag2
-    float4 *rec;         // com (FP32), M (FP32): the pseudo-body record
+    NodeRec *nrec;
     float4 *lo, *hi;     // box
     double4 *s2a, *s2b;  // second moment about com: (xx, yy, zz, xy), (xz, yz, -, -)
     float4 *pp;          // pseudo-particle cells: kPseudo records (x, y, z, q) per node
