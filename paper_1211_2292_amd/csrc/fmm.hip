@@ -663,7 +663,14 @@ __global__ __launch_bounds__(256) void k_fmm_l2l(FmmDev F, const int *__restrict
 // size rounded up to a power of two) form NTG groups of TPL targets; the
 // LG = 64 / NTG lanes of a group hold its targets in registers and share its
 // sources out, one per lane at a time:
-// * P2P: up to 64 entries are read at once (a source leaf is stored as its
+// * P2P, leaves of more than 8 bodies (NTG > 1): through an LDS tile, which each of
+//   the NTG groups reads, and the loop of p2p_tile8.  Against the way of the
+//   smaller leaves, an FMM force of 300001 bodies (theta 0.5 and 0.6) takes 2119
+//   instead of 2268 us with leaves of 16, 2495 instead of 3012 with leaves of
+//   32; with leaves of 8, one group, where the tile's LDS traffic is the same per
+//   body but serves 8 targets, the two are equal (262144 bodies: 1836 and 1842
+//   us), and with leaves of 5 the tile loses 3%.
+// * P2P, smaller leaves: up to 64 entries are read at once (a source leaf is stored as its
 //   first body; every leaf holds `leaf` bodies except the last, which ends
 //   at n); their (entry, body) pairs are numbered e * 2^lb + body and lane v
 //   of a group takes v, v + LG, ... (the entry's first body read from the
@@ -673,15 +680,126 @@ __global__ __launch_bounds__(256) void k_fmm_l2l(FmmDev F, const int *__restrict
 // * Each lane's FP32 partial sums are folded by the precision mode over the
 //   group's lanes in lane order (through LDS); each target then adds its
 //   leaf's expansion in FP64 and is stored.
+// P2P of 8 targets in registers against the lane's records of an LDS tile: the
+// loop over `cnt` records, `step` bytes apart, of the pair code of pair_f32 (the
+// same operations, so the same bits), 4 targets at a time.  By hand for two
+// things that the compiler does not do: the reciprocal square roots of
+// 4 targets share one raised-priority stretch, and no FMA's accumulator lies in
+// the register bank (number mod 4) of one of its multiplicands, where it would
+// not issue together with another wave's (a third of the compiler's did).
+// Per target t, from v96 + 8 t: dx, dy, dz, r2 then rho, -, m rho, rho^2 then the
+// weight (-: free); S + 4 t holds the sums of az, ax, the potential and ay.
+#define NB_EACH4(INS) ".irp t,0,1,2,3\n" INS "\n.endr\n"
+#define NB_P2P_BATCH(S, X, Y, Z, Q)                                                  \
+    NB_EACH4("v_sub_f32 v[96+8*\\t], v[" Q "], v[" X "+\\t]")                        \
+    NB_EACH4("v_sub_f32 v[97+8*\\t], v[" Q "+1], v[" Y "+\\t]")                      \
+    NB_EACH4("v_sub_f32 v[98+8*\\t], v[" Q "+2], v[" Z "+\\t]")                      \
+    NB_EACH4("v_fma_f32 v[99+8*\\t], v[96+8*\\t], v[96+8*\\t], v[103]")              \
+    NB_EACH4("v_fmac_f32 v[99+8*\\t], v[97+8*\\t], v[97+8*\\t]")                     \
+    NB_EACH4("v_fmac_f32 v[99+8*\\t], v[98+8*\\t], v[98+8*\\t]")                     \
+    "s_setprio 1\n"                                                                  \
+    NB_EACH4("v_rsq_f32 v[99+8*\\t], v[99+8*\\t]")                                   \
+    "s_setprio 0\n"                                                                  \
+    NB_EACH4("v_mul_f32 v[102+8*\\t], v[99+8*\\t], v[99+8*\\t]")                     \
+    NB_EACH4("v_mul_f32 v[101+8*\\t], v[" Q "+3], v[99+8*\\t]")                      \
+    NB_EACH4("v_mul_f32 v[102+8*\\t], v[101+8*\\t], v[102+8*\\t]")                   \
+    NB_EACH4("v_fmac_f32 v[" S "+4*\\t+2], v[" Q "+3], v[99+8*\\t]")                 \
+    NB_EACH4("v_fmac_f32 v[" S "+4*\\t+1], v[102+8*\\t], v[96+8*\\t]")               \
+    NB_EACH4("v_fmac_f32 v[" S "+4*\\t+3], v[102+8*\\t], v[97+8*\\t]")               \
+    NB_EACH4("v_fmac_f32 v[" S "+4*\\t], v[102+8*\\t], v[98+8*\\t]")
+#define NB_P2P_STEP(Q, P)                                                            \
+    "s_waitcnt lgkmcnt(0)\n"                                                         \
+    "v_add_u32 %[addr], %[step], %[addr]\n"                                          \
+    "ds_read_b128 v[" P ":" P "+3], %[addr]\n"                                       \
+    NB_P2P_BATCH("32", "64", "72", "80", Q) NB_P2P_BATCH("48", "68", "76", "84", Q)
+
+constexpr int kTile = 512;  // bodies of a P2P tile
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ float wave_max(float v)
+{
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    return v;
+}
+
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// cnt even; reads one record beyond the last.
+__device__ __forceinline__ void p2p_tile8(const float4 *tile, int cnt, int step, Targets<float, 8> &T,
+                                          float eps2, Sums<float, 8> &S)
+{
+    f32x8 x, y, z;
+    f32x16 s0, s1;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        x[t] = T.x[t];
+        y[t] = T.y[t];
+        z[t] = T.z[t];
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        s0[4 * t] = S.az[t];
+        s0[4 * t + 1] = S.ax[t];
+        s0[4 * t + 2] = S.ph[t];
+        s0[4 * t + 3] = S.ay[t];
+        s1[4 * t] = S.az[t + 4];
+        s1[4 * t + 1] = S.ax[t + 4];
+        s1[4 * t + 2] = S.ph[t + 4];
+        s1[4 * t + 3] = S.ay[t + 4];
+    }
+    unsigned addr = (unsigned)(size_t)(__attribute__((address_space(3))) const float4 *)tile;
+    int turns = cnt / 2;
+    asm volatile(
+        "ds_read_b128 v[88:91], %[addr]\n"
+        ".Lp2p%=:\n"
+        NB_P2P_STEP("88", "92") NB_P2P_STEP("92", "88")
+        "s_sub_i32 %[turns], %[turns], 1\n"
+        "s_cmp_lg_u32 %[turns], 0\n"
+        "s_cbranch_scc1 .Lp2p%=\n"
+        "s_waitcnt lgkmcnt(0)\n"
+        : "+{v[32:47]}"(s0), "+{v[48:63]}"(s1), "+{v[64:71]}"(x), "+{v[72:79]}"(y), "+{v[80:87]}"(z),
+          [addr] "+v"(addr), [turns] "+s"(turns)  // (the targets pass through, so that one copy of them is live)
+        : "{v103}"(eps2), [step] "s"(step)
+        : "v88", "v89", "v90", "v91", "v92", "v93", "v94", "v95", "v96", "v97", "v98", "v99", "v101", "v102", "v104",
+          "v105", "v106", "v107", "v109", "v110", "v112", "v113", "v114", "v115", "v117", "v118", "v120", "v121",
+          "v122", "v123", "v125", "v126", "scc", "memory");
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        T.x[t] = x[t];
+        T.y[t] = y[t];
+        T.z[t] = z[t];
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        S.az[t] = s0[4 * t];
+        S.ax[t] = s0[4 * t + 1];
+        S.ph[t] = s0[4 * t + 2];
+        S.ay[t] = s0[4 * t + 3];
+        S.az[t + 4] = s1[4 * t];
+        S.ax[t + 4] = s1[4 * t + 1];
+        S.ph[t + 4] = s1[4 * t + 2];
+        S.ay[t + 4] = s1[4 * t + 3];
+    }
+}
+
 template <int MODE, int TPL, int NTG>
-__global__ __launch_bounds__(64) void k_fmm_leaf(const float4 *__restrict__ src, FmmDev F,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTG > 1 ? 4 : 1))) void k_fmm_leaf(const float4 *__restrict__ src, FmmDev F,
                                                  const int *__restrict__ leaves, int nleaves, float eps2_in,
                                                  double G, float4 *__restrict__ out, int n, int leaf, int lb)
 {
     constexpr int P = TPL * NTG;
     constexpr int LG = 64 / NTG;
+    constexpr bool TILE = NTG > 1;  // leaves of more than 8 bodies
     constexpr int UNR = TPL >= 8 ? 2 : (TPL >= 4 ? 4 : 8);  // source loads in flight per lane
-    __shared__ float red[64][4 * TPL + 1];
+    // the P2P tile with the record read beyond it, then the lanes' sums
+    __shared__ float4 tile[TILE ? kTile + 64 : 16 * (4 * TPL + 1)];
+    float(*const red)[4 * TPL + 1] = (float(*)[4 * TPL + 1]) tile;
+    static_assert(sizeof tile >= 64 * sizeof red[0], "the sums of 64 lanes");
     __shared__ double fin[P][4];
     const int w = blockIdx.x;
     if (w >= nleaves) return;
@@ -709,28 +827,67 @@ __global__ __launch_bounds__(64) void k_fmm_leaf(const float4 *__restrict__ src,
     const int cpc = (int)min((long)cp, max(0L, F.cap_p2p - op));
     const int bmask = (1 << lb) - 1;
     bool self = false;
-    for (int base = 0; base < cpc; base += 64) {
-        const int k = min(64, cpc - base);
-        const int mybeg = lane < k ? F.p2p[op + base + lane] : -1;
-        self = self || __ballot(mybeg == na.x) != 0ull;
-        const int npairs = k << lb;
-        for (int q0 = 0; q0 < npairs; q0 += LG * UNR) {
-            float4 sv[UNR];
-            int sj[UNR];
-            bool ok[UNR];
+    if constexpr (TILE) {
+        // Tiles of kTile bodies: the bodies of kTile >> lb entries, gathered 8 per
+        // lane.  Where an entry has no body (past the list's or the array's end, the
+        // leaf itself) lies a massless record away from every target.
+        float most = 0.5f;
 #pragma unroll
-            for (int r = 0; r < UNR; ++r) {
-                const int q = q0 + r * LG + v;
-                const int bg = __shfl(mybeg, (q >> lb) & 63);
-                const int body = q & bmask;
+        for (int t = 0; t < TPL; ++t) most = fmaxf(most, fabsf(T.x[t]));
+        most = wave_max(most);
+        const float far = most < 1e30f ? 2.0f * most : 1e30f;  // (from where differences would overflow)
+        const int per = kTile >> lb;
+        auto entries = [&](int base) { return lane < min(per, cpc - base) ? F.p2p[op + base + lane] : -1; };
+        int next = entries(0);
+        for (int base = 0; base < cpc; base += per) {
+            const int k = min(per, cpc - base);
+            const int ent = next;
+            self = self || __ballot(ent == na.x) != 0ull;
+            // (opaque: hoisted out of the loop, the 8 indices would spill)
+            int at = lane;
+            asm volatile("" : "+v"(at));
+            const int sub = at >> lb, body = at & bmask;
+            float4 b[kTile / 64];
+#pragma unroll
+            for (int u = 0; u < kTile / 64; ++u) {
+                const int bg = __shfl(ent, u * (64 >> lb) + sub);
                 const int len = ((unsigned)bg < (unsigned)n && bg != na.x) ? min(leaf, n - bg) : 0;
-                ok[r] = q < npairs && body < len;
-                sj[r] = bg + body;
-                sv[r] = src[ok[r] ? sj[r] : 0];
+                b[u] = src[body < len ? bg + body : 0];
+                if (body >= len) b[u] = make_float4(far, 0.0f, 0.0f, 0.0f);
             }
+            wave_sync();
 #pragma unroll
-            for (int r = 0; r < UNR; ++r)
-                if (ok[r]) pair_f32<TPL, false>(sv[r], sj[r], T, eps2, S);
+            for (int u = 0; u < kTile / 64; ++u) tile[u * 64 + lane] = b[u];
+            wave_sync();
+            next = entries(base + per);
+            // records of each lane's: an even number, as many as lie in the tile
+            const int cnt = ((k << lb) + 2 * LG - 1) / (2 * LG) * 2;
+            p2p_tile8(tile + v, cnt, LG * (int)sizeof(float4), T, eps2, S);
+        }
+    } else {
+        for (int base = 0; base < cpc; base += 64) {
+            const int k = min(64, cpc - base);
+            const int mybeg = lane < k ? F.p2p[op + base + lane] : -1;
+            self = self || __ballot(mybeg == na.x) != 0ull;
+            const int npairs = k << lb;
+            for (int q0 = 0; q0 < npairs; q0 += LG * UNR) {
+                float4 sv[UNR];
+                int sj[UNR];
+                bool ok[UNR];
+#pragma unroll
+                for (int r = 0; r < UNR; ++r) {
+                    const int q = q0 + r * LG + v;
+                    const int bg = __shfl(mybeg, (q >> lb) & 63);
+                    const int body = q & bmask;
+                    const int len = ((unsigned)bg < (unsigned)n && bg != na.x) ? min(leaf, n - bg) : 0;
+                    ok[r] = q < npairs && body < len;
+                    sj[r] = bg + body;
+                    sv[r] = src[ok[r] ? sj[r] : 0];
+                }
+#pragma unroll
+                for (int r = 0; r < UNR; ++r)
+                    if (ok[r]) pair_f32<TPL, false>(sv[r], sj[r], T, eps2, S);
+            }
         }
     }
     if (self) {  // the leaf's own bodies, without the self pair
@@ -748,6 +905,7 @@ __global__ __launch_bounds__(64) void k_fmm_leaf(const float4 *__restrict__ src,
         }
     }
     // fold the group's lanes in lane order
+    if constexpr (TILE) __syncthreads();
 #pragma unroll
     for (int t = 0; t < TPL; ++t) {
         red[lane][4 * t] = S.ax[t];

@@ -131,6 +131,24 @@ def test_edge_sizes(orc, n, leaf):
     assert rms_rel(got[:, 3], p) < 1e-6
 
 
+@pytest.mark.parametrize("n,leaf", [(9, 9), (33, 9), (1000, 9), (3001, 16), (2500, 17), (4097, 31), (3000, 33), (5003, 64)])
+@pytest.mark.parametrize("eps", [0.0, 0.01])
+def test_leaves_of_more_than_eight(orc, n, leaf, eps):
+    """Leaves of two to eight groups of targets, full and ragged, whose near
+    bodies go through tiles (the last one partly empty, and the leaf's own
+    entry left out of it): with no softening, where an empty record must not
+    meet a target, and with some massless bodies and one at the origin."""
+    torch, nb = gpu()
+    pm, _ = ics.plummer(n, 870 + n)
+    pm[::5, 3] = 0.0
+    pm[0, :3] = 0.0
+    q, qh = _orb_input(torch, nb, pm, leaf)
+    got = host(nb.fmm_accel(q, eps, 0.4, leaf, prec=nb.F32_F64ACC))
+    a, p = orc.fmm_accel(widen32(qh), leaf, 0.4, eps)
+    assert rms_rel(got[:, :3], a) < 1e-6
+    assert rms_rel(got[:, 3], p) < 1e-6
+
+
 def test_far_flung_leaf(orc):
     """A dense ball and 8 bodies strung far out along x: their leaf takes M2P
     cells rather than every leaf; lists and forces match the oracle."""
