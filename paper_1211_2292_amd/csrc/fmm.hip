@@ -36,7 +36,7 @@
 //   exact counts) and run again.
 // * M2L: one wave per node, one source cell per lane, the twenty
 //   coefficients summed over the wave in a fixed butterfly (FP32).
-// * L2L: one thread per node, depth by depth, in FP64.
+// * L2L: one thread per node, depth by depth, in FP64, in two launches.
 // * Leaves: one wave per leaf.  Each lane holds up to 8 of the leaf's
 //   targets in registers and takes one source body (P2P) or cell (M2P) at a
 //   time, so one load serves up to 8 pairs.  The lanes' FP32 partial sums are
@@ -75,6 +75,7 @@ constexpr int kRunStride = kFmmStack + 1;
 constexpr int kTotWords = 1 + kKinds * kRunStride;
 __host__ __device__ constexpr int tot_at(int kind, int d) { return 1 + kind * kRunStride + d; }
 
+constexpr int kL2lRoots = 256;    // see k_fmm_l2l
 constexpr int kScanBlock = 1024;  // positions per scan block (256 threads x 4)
 
 struct FmmDev {
@@ -565,37 +566,31 @@ __global__ __launch_bounds__(256) void k_fmm_scan_fin(FmmDev F, const int *__res
     }
 }
 
-// M2L: one wave per node.
-__global__ __launch_bounds__(256) void k_fmm_m2l(FmmDev F, float eps2)
+// M2L: one wave per node, and a workgroup per wave, since a node's list is what
+// it is.  The list is read a step ahead, and the coefficients are summed by
+// handing halves on instead of 20 butterflies of 6 shuffles (262144 bodies, 324
+// cells per node on average: 236 us with four waves per workgroup and the
+// butterflies, 222 us now; the gathers of the cells' records bound it).
+__global__ __launch_bounds__(64) void k_fmm_m2l(FmmDev F, float eps2)
 {
-    const int A = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (A >= F.nn) return;
-    const int c = F.cnt[kM2L * F.nn + A];
+    const int A = blockIdx.x;
+    const int lane = threadIdx.x;
     const long o = F.off[kM2L * F.nn + A];
+    const int c = (int)min((long)F.cnt[kM2L * F.nn + A], max(0L, F.cap_m2l - o));
     const double4 ca = F.nrec[A].cd;
     const float zx = (float)ca.x, zy = (float)ca.y, zz = (float)ca.z;
     Local L;
 #pragma unroll
     for (int k = 0; k < 20; ++k) L.c[k] = 0.0f;
+    const int *const list = F.m2l + o;
+    int next = lane < c ? list[lane] : -1;  // a step ahead
     for (int k = lane; k < c; k += 64) {
-        if (o + k >= F.cap_m2l) break;
-        const int B = F.m2l[o + k];
+        const int B = next;
+        next = k + 64 < c ? list[k + 64] : -1;
         if ((unsigned)B < (unsigned)F.nn) m2l_f32(F.qr + (long)kQuadRec * B, zx, zy, zz, eps2, L);
     }
-#pragma unroll
-    for (int k = 0; k < 20; ++k) {
-        float v = L.c[k];
-#pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s);
-        L.c[k] = v;
-    }
-    if (lane < 20) {
-        float v = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 20; ++k) v = lane == k ? L.c[k] : v;
-        F.own[20L * A + lane] = v;
-    }
+    const int q = wave_scatter20(L.c, lane);
+    if (q >= 0) F.own[20L * A + q] = L.c[0];
 }
 
 // Full symmetric K and T of the 20 coefficients (P0, p, K: xx yy zz xy xz yz,
@@ -626,13 +621,10 @@ __device__ __forceinline__ void fmm_contract(const double *c, const double d[3],
     }
 }
 
-// L2L, one thread per node of one depth: loc[A] = own[A] + the parent's
-// total re-expanded about com_A (the root takes its own sum).
-__global__ __launch_bounds__(256) void k_fmm_l2l(FmmDev F, const int *__restrict__ ids, int count)
+// L2L of one node: loc[A] = own[A] + the parent's total re-expanded about
+// com_A (the root takes its own sum).
+__device__ __forceinline__ void l2l_node(const FmmDev &F, int A)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= count) return;
-    const int A = ids[t];
     const int P = F.parent[A];
     double *out = F.loc + 20L * A;
     const float *own = F.own + 20L * A;
@@ -657,6 +649,23 @@ __global__ __launch_bounds__(256) void k_fmm_l2l(FmmDev F, const int *__restrict
     out[8] = (c[8] + td[0][2]) + (double)own[8];
     out[9] = (c[9] + td[1][2]) + (double)own[9];
     for (int k = 10; k < 20; ++k) out[k] = c[k] + (double)own[k];
+}
+
+// L2L, one thread per node, depth by depth.  Workgroup b takes the subtree of
+// the b-th node of its top depth: first[d][b] .. first[d][b + 1] are its
+// nodes' positions in the depth order at depth top + d.  One launch for the depths
+// of up to kL2lRoots nodes (one workgroup) and one for the depths below (a
+// workgroup per node of the last of those): a launch per depth took 103 us at
+// 262144 bodies (leaf 8, 16 depths), each a chain of loads and FP64 sums with
+// little else in flight; the two take 41 us.
+__global__ __launch_bounds__(256) void k_fmm_l2l(FmmDev F, const int *__restrict__ by_depth,
+                                                 const int *__restrict__ first, int roots, int depths)
+{
+    for (int d = 0; d < depths; ++d) {
+        const int p0 = first[(roots + 1) * d + blockIdx.x], p1 = first[(roots + 1) * d + blockIdx.x + 1];
+        for (int p = p0 + threadIdx.x; p < p1; p += blockDim.x) l2l_node(F, by_depth[p]);
+        __syncthreads();
+    }
 }
 
 // Leaves: one wave per leaf.  The leaf's P = TPL * NTG target slots (its
@@ -976,6 +985,10 @@ struct FmmPlan {
     int stack = 0;  // LDS stack entries that a walking wave needs at this height
     std::vector<int> parent, by_depth, depth_off;
     int *d_parent = nullptr, *d_by_depth = nullptr, *d_leaves = nullptr;
+    // L2L: the depth whose nodes are the second launch's subtrees, and for both
+    // launches the subtrees' positions (see k_fmm_l2l; the first launch's first)
+    int l2l_depth = 0, l2l_roots = 0;
+    int *d_l2l = nullptr;
 };
 
 struct FmmBufs {
@@ -1010,6 +1023,7 @@ void free_plan(FmmPlan &p)
     (void)hipFree(p.d_parent);
     (void)hipFree(p.d_by_depth);
     (void)hipFree(p.d_leaves);
+    (void)hipFree(p.d_l2l);
     p = FmmPlan();
 }
 
@@ -1062,10 +1076,27 @@ int make_plan(const HostTree &h, int n, int leaf, int dev, hipStream_t s)
     p.by_depth.assign(nn, 0);
     std::vector<int> pos(p.depth_off.begin(), p.depth_off.end() - 1);
     for (int a = 0; a < nn; ++a) p.by_depth[pos[dep[a]]++] = a;
+    // the L2L launches' tables: one subtree from the root down to the depth of kL2lRoots nodes, then that depth's
+    p.l2l_depth = 0;
+    while (p.l2l_depth < p.depth && p.depth_off[p.l2l_depth + 1] - p.depth_off[p.l2l_depth] < kL2lRoots) ++p.l2l_depth;
+    p.l2l_roots = p.depth_off[p.l2l_depth + 1] - p.depth_off[p.l2l_depth];
+    std::vector<int> l2l;
+    for (int k = 0; k <= p.l2l_depth; ++k) {
+        l2l.push_back(p.depth_off[k]);
+        l2l.push_back(p.depth_off[k + 1]);
+    }
+    for (int k = p.l2l_depth + 1; k <= p.depth; ++k) {
+        // the depth order is the preorder within a depth: each root's nodes follow one another
+        const auto b = p.by_depth.begin() + p.depth_off[k], e = p.by_depth.begin() + p.depth_off[k + 1];
+        for (int r = 0; r < p.l2l_roots; ++r)
+            l2l.push_back((int)(std::lower_bound(b, e, p.by_depth[p.depth_off[p.l2l_depth] + r]) - p.by_depth.begin()));
+        l2l.push_back(p.depth_off[k + 1]);
+    }
     const size_t nl = h.leaves.size();
     if (hipMalloc(&p.d_parent, nn * sizeof(int)) != hipSuccess ||
         hipMalloc(&p.d_by_depth, nn * sizeof(int)) != hipSuccess ||
-        hipMalloc(&p.d_leaves, nl * sizeof(int)) != hipSuccess) {
+        hipMalloc(&p.d_leaves, nl * sizeof(int)) != hipSuccess ||
+        hipMalloc(&p.d_l2l, l2l.size() * sizeof(int)) != hipSuccess) {
         free_plan(p);
         set_error("cannot allocate the FMM plan");
         return NBODY_E_NOMEM;
@@ -1075,6 +1106,8 @@ int make_plan(const HostTree &h, int n, int leaf, int dev, hipStream_t s)
         e = hipMemcpyAsync(p.d_by_depth, p.by_depth.data(), nn * sizeof(int), hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(p.d_leaves, h.leaves.data(), nl * sizeof(int), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(p.d_l2l, l2l.data(), l2l.size() * sizeof(int), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         free_plan(p);
@@ -1085,6 +1118,15 @@ int make_plan(const HostTree &h, int n, int leaf, int dev, hipStream_t s)
     p.dev = dev;
     p.nn = nn;
     return NBODY_OK;
+}
+
+hipError_t launch_l2l(const FmmDev &F, const FmmPlan &p, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_fmm_l2l, dim3(1), dim3(256), 0, s, F, p.d_by_depth, p.d_l2l, 1, p.l2l_depth + 1);
+    if (p.depth > p.l2l_depth)
+        hipLaunchKernelGGL(k_fmm_l2l, dim3(p.l2l_roots), dim3(256), 0, s, F, p.d_by_depth,
+                           p.d_l2l + 2 * (p.l2l_depth + 1), p.l2l_roots, p.depth - p.l2l_depth);
+    return hipGetLastError();
 }
 
 // Buffers for nn nodes (at most max_level on one depth) with at least the
@@ -1344,14 +1386,9 @@ int fmm_run(const void *pm, int n, int prec, double G, double eps, double theta,
         if (!tot[0]) {  // the lists fit: evaluate
             if (!out) return NBODY_OK;
             const float eps2 = (float)(eps * eps);
-            hipLaunchKernelGGL(k_fmm_m2l, dim3((nn + 3) / 4), dim3(256), 0, s, F, eps2);
+            hipLaunchKernelGGL(k_fmm_m2l, dim3(nn), dim3(64), 0, s, F, eps2);
             e = hipGetLastError();
-            for (int dd = 0; dd <= p.depth && e == hipSuccess; ++dd) {
-                const int first = p.depth_off[dd], count = p.depth_off[dd + 1] - first;
-                hipLaunchKernelGGL(k_fmm_l2l, dim3((count + 255) / 256), dim3(256), 0, s, F,
-                                   p.d_by_depth + first, count);
-                e = hipGetLastError();
-            }
+            if (e == hipSuccess) e = launch_l2l(F, p, s);
             if (e == hipSuccess) {
                 const float4 *x = (const float4 *)pm;
                 float4 *o = (float4 *)out;

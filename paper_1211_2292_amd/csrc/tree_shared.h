@@ -177,5 +177,35 @@ __device__ __forceinline__ void m2l_f32(const float4 *__restrict__ rec, float zx
                                              d3 * __builtin_fmaf(q1.w, uz, __builtin_fmaf(q2.x, uy, q2.y * ux))));
 }
 
+// Sums 20 values over the wave, each lane handing half of what it holds to its
+// partner at every step (22 shuffles where 20 butterflies take 120, the same
+// tree of sums).  Returns which total the lane is left with in c[0], or -1.
+__device__ __forceinline__ int wave_scatter20(float (&c)[20], int lane)
+{
+    int n = 20, at = 0;
+    int left = 20;  // totals among this lane's n places (the last may be padding)
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) {
+        const bool up = (lane & s) != 0;
+        if (n == 1) {
+            c[0] += __shfl_xor(c[0], s);
+            left = up ? 0 : left;
+            continue;
+        }
+        const int half = (n + 1) / 2;
+#pragma unroll
+        for (int k = 0; k < 10; ++k) {
+            if (k >= half) break;
+            const float hi = k + half < n ? c[k + half] : 0.0f;
+            const float got = __shfl_xor(up ? c[k] : hi, s);
+            c[k] = (up ? hi : c[k]) + got;
+        }
+        left = up ? left - half : min(left, half);
+        at += up ? half : 0;
+        n = half;
+    }
+    return left > 0 ? at : -1;
+}
+
 }  // namespace
 }  // namespace nbi
