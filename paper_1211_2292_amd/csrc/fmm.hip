@@ -95,6 +95,7 @@ struct FmmDev {
     long cap_m2l, cap_p2p, cap_m2p, cap_pass;
     long *bsum;               // [blocks][kKinds] scan block sums
     unsigned long long *tot;  // see tot_at
+    unsigned long long *flag; // host memory: the overflow flag as the evaluation found it
     float *own;               // [nn][20] own M2L sums
     double *loc;              // [nn][20] total expansions
 };
@@ -575,6 +576,9 @@ __global__ __launch_bounds__(64) void k_fmm_m2l(FmmDev F, float eps2)
 {
     const int A = blockIdx.x;
     const int lane = threadIdx.x;
+    const unsigned long long over = F.tot[0];
+    if (A == 0 && lane == 0) *F.flag = over;
+    if (over) return;
     const long o = F.off[kM2L * F.nn + A];
     const int c = (int)min((long)F.cnt[kM2L * F.nn + A], max(0L, F.cap_m2l - o));
     const double4 ca = F.nrec[A].cd;
@@ -661,6 +665,7 @@ __device__ __forceinline__ void l2l_node(const FmmDev &F, int A)
 __global__ __launch_bounds__(256) void k_fmm_l2l(FmmDev F, const int *__restrict__ by_depth,
                                                  const int *__restrict__ first, int roots, int depths)
 {
+    if (F.tot[0]) return;
     for (int d = 0; d < depths; ++d) {
         const int p0 = first[(roots + 1) * d + blockIdx.x], p1 = first[(roots + 1) * d + blockIdx.x + 1];
         for (int p = p0 + threadIdx.x; p < p1; p += blockDim.x) l2l_node(F, by_depth[p]);
@@ -811,7 +816,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTG > 1 ? 4 
     static_assert(sizeof tile >= 64 * sizeof red[0], "the sums of 64 lanes");
     __shared__ double fin[P][4];
     const int w = blockIdx.x;
-    if (w >= nleaves) return;
+    if (w >= nleaves || F.tot[0]) return;
     const int lane = threadIdx.x;
     const int g = lane / LG, v = lane % LG;
     const int A = leaves[w];
@@ -998,6 +1003,8 @@ struct FmmBufs {
     int *pass0 = nullptr, *pass1 = nullptr;
     long *bsum = nullptr;
     unsigned long long *tot = nullptr;
+    unsigned long long *flag = nullptr;  // pinned
+    hipEvent_t listed = nullptr;         // after the kernel that writes it
     float *own = nullptr;
     double *loc = nullptr;
 };
@@ -1037,6 +1044,8 @@ void free_bufs(FmmBufs &b)
     (void)hipFree(b.pass1);
     (void)hipFree(b.bsum);
     (void)hipFree(b.tot);
+    (void)hipHostFree(b.flag);
+    if (b.listed) (void)hipEventDestroy(b.listed);
     (void)hipFree(b.own);
     (void)hipFree(b.loc);
     b = FmmBufs();
@@ -1154,6 +1163,8 @@ int make_bufs(int nn, int max_level, int dev, const long (&want)[kKinds])
          hipMalloc(&b.pass1, (size_t)cap[kPass] * sizeof(int)) == hipSuccess &&
          hipMalloc(&b.bsum, (size_t)nb * kKinds * sizeof(long)) == hipSuccess &&
          hipMalloc(&b.tot, kTotWords * sizeof(unsigned long long)) == hipSuccess &&
+         hipHostMalloc(&b.flag, sizeof(unsigned long long)) == hipSuccess &&
+         hipEventCreateWithFlags(&b.listed, hipEventDisableTiming) == hipSuccess &&
          hipMalloc(&b.own, 20 * (size_t)nn * sizeof(float)) == hipSuccess &&
          hipMalloc(&b.loc, 20 * (size_t)nn * sizeof(double)) == hipSuccess;
     if (!ok) {
@@ -1193,6 +1204,7 @@ FmmDev dev_view(const TreeDev &d, const FmmPlan &p, const FmmBufs &b)
     F.cap_pass = b.cap[kPass];
     F.bsum = b.bsum;
     F.tot = b.tot;
+    F.flag = b.flag;
     F.own = b.own;
     F.loc = b.loc;
     return F;
@@ -1342,8 +1354,27 @@ void list_totals(const unsigned long long *tot, int depth, unsigned long long (&
     for (int q = 0; q < 3; ++q) out[q] = tot[tot_at(q, depth + 1)];
 }
 
-// Runs the traversal until the lists fit their buffers (one stream
-// synchronisation per attempt), then, with out != nullptr, the evaluation.
+// M2L, which tells the host whether the lists fit (g_bufs.listed), L2L and the
+// leaves; all of them only if the lists fit.
+hipError_t launch_evaluation(const FmmDev &F, const FmmPlan &p, const float4 *pm, int n, int prec, double G, double eps,
+                             int leaf, int nleaves, float4 *out, hipStream_t s)
+{
+    const float eps2 = (float)(eps * eps);
+    hipLaunchKernelGGL(k_fmm_m2l, dim3(p.nn), dim3(64), 0, s, F, eps2);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipEventRecord(g_bufs.listed, s);
+    if (e == hipSuccess) e = launch_l2l(F, p, s);
+    if (e != hipSuccess) return e;
+    switch (prec) {
+    case NBODY_F32: return launch_leaves_mode<M_F32>(pm, F, p, nleaves, n, leaf, eps2, G, out, s);
+    case NBODY_F32_KAHAN: return launch_leaves_mode<M_KAHAN>(pm, F, p, nleaves, n, leaf, eps2, G, out, s);
+    default: return launch_leaves_mode<M_F64ACC>(pm, F, p, nleaves, n, leaf, eps2, G, out, s);
+    }
+}
+
+// Runs the traversal until the lists fit their buffers, with out != nullptr each
+// time followed by the evaluation; the host waits until the lists are known to
+// fit, not for the evaluation.
 // Called with the tree and FMM locks held.
 int fmm_run(const void *pm, int n, int prec, double G, double eps, double theta, int leaf, void *out,
             hipStream_t s, TreeDev &d, const HostTree *&h)
@@ -1379,27 +1410,20 @@ int fmm_run(const void *pm, int n, int prec, double G, double eps, double theta,
         const FmmDev F = dev_view(d, p, g_bufs);
         hipError_t e = slots ? launch_traversal_slots(F, p, theta * theta, s) : launch_traversal(F, p, theta * theta, s);
         if (e != hipSuccess) return hip_fail(e, "FMM traversal");
+        if (out) {
+            // The evaluation follows without waiting for the host to see that the
+            // lists fit: where they did not, its kernels do nothing and the lists are made again.
+            e = launch_evaluation(F, p, (const float4 *)pm, n, prec, G, eps, leaf, nleaves, (float4 *)out, s);
+            if (e != hipSuccess) return hip_fail(e, "FMM kernels");
+            e = hipEventSynchronize(g_bufs.listed);
+            if (e != hipSuccess) return hip_fail(e, "FMM list check");
+            if (!*(volatile unsigned long long *)g_bufs.flag) return NBODY_OK;
+        }
         unsigned long long tot[kTotWords];
         e = hipMemcpyAsync(tot, g_bufs.tot, sizeof tot, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hip_fail(e, "FMM list check");
-        if (!tot[0]) {  // the lists fit: evaluate
-            if (!out) return NBODY_OK;
-            const float eps2 = (float)(eps * eps);
-            hipLaunchKernelGGL(k_fmm_m2l, dim3(nn), dim3(64), 0, s, F, eps2);
-            e = hipGetLastError();
-            if (e == hipSuccess) e = launch_l2l(F, p, s);
-            if (e == hipSuccess) {
-                const float4 *x = (const float4 *)pm;
-                float4 *o = (float4 *)out;
-                switch (prec) {
-                case NBODY_F32: e = launch_leaves_mode<M_F32>(x, F, p, nleaves, n, leaf, eps2, G, o, s); break;
-                case NBODY_F32_KAHAN: e = launch_leaves_mode<M_KAHAN>(x, F, p, nleaves, n, leaf, eps2, G, o, s); break;
-                default: e = launch_leaves_mode<M_F64ACC>(x, F, p, nleaves, n, leaf, eps2, G, o, s); break;
-                }
-            }
-            return e == hipSuccess ? NBODY_OK : hip_fail(e, "FMM kernels");
-        }
+        if (!tot[0]) return NBODY_OK;  // (inspection: the lists fit)
         if (slots) {  // resize the slots from the exact counts and run again
             std::vector<int> cnt(kKinds * (size_t)nn);
             e = hipMemcpyAsync(cnt.data(), g_bufs.cnt, cnt.size() * sizeof(int), hipMemcpyDeviceToHost, s);
