@@ -777,7 +777,7 @@ __device__ __forceinline__ void p2p_tile8(const float4 *tile, int cnt, int step,
         "s_cbranch_scc1 .Lp2p%=\n"
         "s_waitcnt lgkmcnt(0)\n"
         : "+{v[32:47]}"(s0), "+{v[48:63]}"(s1), "+{v[64:71]}"(x), "+{v[72:79]}"(y), "+{v[80:87]}"(z),
-          [addr] "+v"(addr), [turns] "+s"(turns)  // (the targets pass through, so that one copy of them is live)
+          [addr] "+&v"(addr), [turns] "+&s"(turns)  // (the targets pass through, so that one copy of them is live)
         : "{v103}"(eps2), [step] "s"(step)
         : "v88", "v89", "v90", "v91", "v92", "v93", "v94", "v95", "v96", "v97", "v98", "v99", "v101", "v102", "v104",
           "v105", "v106", "v107", "v109", "v110", "v112", "v113", "v114", "v115", "v117", "v118", "v120", "v121",

@@ -22,11 +22,10 @@
 // pass reads it whole), one pass that settles ties between equal coordinates
 // by index (k_orb_ties), and the partition (k_orb_partition), which also
 // accumulates each part's key box for the next level.  Phase B (k_orb_block)
-// finishes every remaining segment (at most max(kSmall, leaf) <=
-// kMaxBlockSeg bodies) inside one workgroup: the segment's keys are loaded
-// into LDS once, nodes above kWaveNode bodies are split by the workgroup,
-// smaller ones by one wave each, nodes of at most 64 bodies by ranking
-// inside the wave, and the final order is written.
+// finishes every remaining segment (at most kSmall bodies) inside one
+// workgroup: the segment's keys are loaded into LDS once, all nodes of a depth
+// are split together, nodes of at most 64 bodies are finished by one wave each,
+// and the final order is written.
 #include <algorithm>
 #include <cstring>
 #include <map>
@@ -37,10 +36,13 @@
 
 namespace nbi {
 
-constexpr int kSmall = 1024;        // phase A splits segments larger than this
-constexpr int kMaxBlockSeg = 4096;  // largest segment phase B accepts (and max leaf)
+// Phase A splits segments larger than this: as many as fit phase B's LDS.  A level
+// of phase A takes 40 us at 2^20 bodies, one of phase B 10.
+constexpr int kSmall = 4096;
+constexpr int kMaxBlockSeg = 4096;  // largest leaf
 constexpr int kChunk = 4096;        // elements per phase-A workgroup
 constexpr int kOrbBlock = 256;
+constexpr int kFinBlock = 1024;     // threads of a phase-B workgroup
 constexpr int kChunkPer = kChunk / kOrbBlock;  // elements per thread of a phase-A workgroup
 
 namespace {
@@ -167,32 +169,75 @@ __global__ __launch_bounds__(kOrbBlock) void k_orb_init(const int3 *__restrict__
     for (int j = threadIdx.x; j < kBins; j += kOrbBlock) hist[(size_t)s * kBins + j] = 0u;
 }
 
-__device__ __forceinline__ uint32_t wave_min(uint32_t v)
+// Cross-lane moves as operands (DPP): a step of a few clocks, where a shuffle is
+// a round trip to the LDS.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t v)
 {
-    for (int o = 32; o > 0; o >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, o));
-    return v;
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xf, 0xf, true);  // (every lane has a source)
 }
-__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppMirror = 0x140, kDppHalfMirror = 0x141;
+
+// v over the group of W lanes (aligned, a power of two), in every lane of it
+template <int W, typename OP>
+__device__ __forceinline__ uint32_t group_reduce(uint32_t v, OP op)
 {
-    for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o));
+    if constexpr (W >= 2) v = op(v, dpp<kDppXor1>(v));
+    if constexpr (W >= 4) v = op(v, dpp<kDppXor2>(v));
+    if constexpr (W >= 8) v = op(v, dpp<kDppHalfMirror>(v));
+    if constexpr (W >= 16) v = op(v, dpp<kDppMirror>(v));
+    if constexpr (W >= 32) {
+        const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        v = op(p[0], p[1]);
+    }
+    if constexpr (W >= 64) {
+        const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        v = op(p[0], p[1]);
+    }
     return v;
 }
 
-// Inclusive sum over the workgroup's threads: within each wave by shuffles,
-// then the totals of the waves before it (scratch: one entry per wave).
+__device__ __forceinline__ uint32_t wave_min(uint32_t v)
+{
+    return group_reduce<64>(v, [](uint32_t x, uint32_t y) { return min(x, y); });
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v)
+{
+    return group_reduce<64>(v, [](uint32_t x, uint32_t y) { return max(x, y); });
+}
+
+// v plus the v of the lane that CTRL names, in the rows of ROWS (others: v)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_add(uint32_t v)
+{
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+// Inclusive sum over the wave (ROW: over each row of 16 lanes).
+template <bool ROW = false>
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
+{
+    v = dpp_add<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    if constexpr (!ROW) {
+        v = dpp_add<0x142, 0xa>(v);  // lane 15 to the second row, lane 47 to the fourth
+        v = dpp_add<0x143, 0xc>(v);  // lane 31 to the upper two
+    }
+    return v;
+}
+
+// Inclusive sum over the workgroup's threads: within each wave, then the totals
+// of the waves before it (scratch: one entry per wave, at most 16).
 __device__ __forceinline__ uint32_t block_incl_scan_u32(uint32_t v, uint32_t *scratch)
 {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = (uint32_t)__shfl_up((int)v, o);
-        if (lane >= o) v += y;
-    }
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    v = wave_incl_scan(v);
     __syncthreads();
     if (lane == 63) scratch[w] = v;
     __syncthreads();
-    uint32_t before = 0;
-    for (int k = 0; k < w; ++k) before += scratch[k];
-    return v + before;
+    const uint32_t tot = wave_incl_scan<true>(lane < (int)(blockDim.x >> 6) ? scratch[lane & 15] : 0u);
+    return v + (w > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)tot, w - 1) : 0u);
 }
 
 // Hand-off between the workgroups of one launch, with no cache-wide fence (a
@@ -491,8 +536,15 @@ __global__ __launch_bounds__(kPassBlock) void k_orb_partition(const int3 *__rest
     const uint64_t kth = st[c.x].prefix;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
-    const uint32_t *ka = keys + (size_t)seg_axis(&st[c.x]) * n;
-    // this thread's bodies and their sides, loaded together
+    // all of the thread's loads together, ahead of the split axis
+    uint32_t kv[3][kPassPer];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int u = 0; u < kPassPer; ++u)
+            kv[a][u] = keys[(size_t)a * n + min(c.y + u * kPassBlock + (int)threadIdx.x, c.z - 1)];
+    const int axis = seg_axis(&st[c.x]);
+    // this thread's bodies and their sides
     int bod[kPassPer];
     uint32_t rank[kPassPer];
     bool lft[kPassPer];
@@ -501,7 +553,8 @@ __global__ __launch_bounds__(kPassBlock) void k_orb_partition(const int3 *__rest
         const int p = c.y + u * kPassBlock + threadIdx.x;
         const int q = min(p, c.z - 1);  // loads without a branch, masked below
         const int b = cur[q];
-        lft[u] = (((uint64_t)ka[q] << 32) | (uint32_t)b) <= kth;
+        const uint32_t ka = axis == 0 ? kv[0][u] : (axis == 1 ? kv[1][u] : kv[2][u]);
+        lft[u] = (((uint64_t)ka << 32) | (uint32_t)b) <= kth;
         bod[u] = p < c.z ? b : -1;
     }
     // rank inside the (step, wave) group by ballots, group totals in LDS
@@ -521,14 +574,7 @@ __global__ __launch_bounds__(kPassBlock) void k_orb_partition(const int3 *__rest
     if (w == 0) {
         const bool g = lane < kPassPer * kW;
         const uint32_t a = g ? cl[lane] : 0u, b = g ? cr[lane] : 0u;
-        uint32_t ia = a, ib = b;
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t ya = (uint32_t)__shfl_up((int)ia, o), yb = (uint32_t)__shfl_up((int)ib, o);
-            if (lane >= o) {
-                ia += ya;
-                ib += yb;
-            }
-        }
+        const uint32_t ia = wave_incl_scan(a), ib = wave_incl_scan(b);
         if (g) {
             cl[lane] = ia - a;
             cr[lane] = ib - b;
@@ -562,19 +608,18 @@ __global__ __launch_bounds__(kPassBlock) void k_orb_partition(const int3 *__rest
         dst[u] = bod[u] >= 0 && fits ? sg.x + (lft[u] ? 0 : sg.z) + (int)q : -1;
         if (dst[u] >= 0) cur_out[dst[u]] = bod[u];
     }
-    // one axis at a time: all of the thread's loads first, then the stores
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        uint32_t kv[kPassPer];
-#pragma unroll
-        for (int u = 0; u < kPassPer; ++u) kv[u] = keys[(size_t)a * n + min(c.y + u * kPassBlock + (int)threadIdx.x, c.z - 1)];
+        uint32_t *const out = keys_out + (size_t)a * n;
 #pragma unroll
         for (int u = 0; u < kPassPer; ++u) {
-            if (dst[u] < 0) continue;
-            keys_out[(size_t)a * n + dst[u]] = kv[u];
-            const int o = lft[u] ? 0 : 6;
-            bx[o + a] = min(bx[o + a], kv[u]);
-            bx[o + 3 + a] = max(bx[o + 3 + a], kv[u]);
+            const uint32_t v = kv[a][u];
+            const bool l = dst[u] >= 0 && lft[u], r = dst[u] >= 0 && !lft[u];
+            if (dst[u] >= 0) out[dst[u]] = v;
+            bx[a] = min(bx[a], l ? v : 0xFFFFFFFFu);
+            bx[3 + a] = max(bx[3 + a], l ? v : 0u);
+            bx[6 + a] = min(bx[6 + a], r ? v : 0xFFFFFFFFu);
+            bx[9 + a] = max(bx[9 + a], r ? v : 0u);
         }
     }
 #pragma unroll
@@ -600,24 +645,11 @@ __global__ __launch_bounds__(kPassBlock) void k_orb_partition(const int3 *__rest
 // holds it (phase A leaves them in the segment's order) and stay in their
 // slots; the recursion permutes slot numbers only.
 
-// Box of a node (min keys x,y,z then max keys x,y,z), over the whole
-// workgroup: two barriers for all six values.
-__device__ __forceinline__ void block_box(uint32_t *bb, uint32_t (*red)[6])
+__device__ __forceinline__ void wave_sync()
 {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int j = 0; j < 6; ++j) bb[j] = j < 3 ? wave_min(bb[j]) : wave_max(bb[j]);
-    __syncthreads();
-    if (lane == 0)
-#pragma unroll
-        for (int j = 0; j < 6; ++j) red[w][j] = bb[j];
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < 6; ++j) {
-        uint32_t v = red[0][j];
-        for (int k = 1; k < kOrbBlock / 64; ++k) v = j < 3 ? min(v, red[k][j]) : max(v, red[k][j]);
-        bb[j] = v;
-    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Finishes the recursion of a node of at most 64 bodies (positions
@@ -627,7 +659,7 @@ __device__ __forceinline__ void block_box(uint32_t *bb, uint32_t (*red)[6])
 // distinct), then each leaf is ordered by original index.
 constexpr int kWaveSeg = 64;
 
-__device__ void orb_wave(int32_t *pos, const uint32_t (*skey)[kSmall], const int32_t *gid,
+__device__ void orb_wave(uint16_t *pos, const uint32_t (*skey)[kSmall], const int32_t *gid,
                          uint32_t (*keys)[kWaveSeg], int32_t *wid, int lo, int m, int leaf, int lane)
 {
     const int s = lane < m ? pos[lo + lane] : 0;  // this lane's slot
@@ -699,397 +731,516 @@ __device__ void orb_wave(int32_t *pos, const uint32_t (*skey)[kSmall], const int
     if (lane < m)
 #pragma unroll 4
         for (int f = slo; f < slo + sm; ++f) r += wid[f] < b;
-    if (lane < m) pos[lo + slo + r] = s;
+    if (lane < m) pos[lo + slo + r] = (uint16_t)s;
 }
 
-__device__ __forceinline__ void wave_sync()
+
+// The same for a leaf size that is a power of two up to 32, in registers.  The
+// node's halves then have at most 32 bodies, theirs 16, and so on, so that at
+// every level the nodes are groups of W lanes with their bodies first: boxes
+// are reductions over the group and ranks counts over it, by cross-lane operands
+// instead of an LDS read per pair of lanes (64 nodes of a
+// 4096-body segment, four per wave, down to leaves of 4: 75 us by orb_wave, 20 so).
+// r += (oh, ol) of another lane < (mh, ml) of this one, one step per cross-lane control:
+// the borrow of the difference
+#define NB_RANK_STEP(CTRL)                                                                    \
+    "v_sub_co_u32_dpp %[t], vcc, %[ol], %[ml] " CTRL " row_mask:0xf bank_mask:0xf\n"          \
+    "v_subb_co_u32_dpp %[t], vcc, %[oh], %[mh], vcc " CTRL " row_mask:0xf bank_mask:0xf\n"    \
+    "v_addc_co_u32 %[r], vcc, 0, %[r], vcc\n"
+#define NB_RANK_OWN                                  \
+    "v_sub_co_u32 %[t], vcc, %[ol], %[ml]\n"         \
+    "v_subb_co_u32 %[t], vcc, %[oh], %[mh], vcc\n"   \
+    "v_addc_co_u32 %[r], vcc, 0, %[r], vcc\n"
+#define NB_RANK(STEPS)                                                                                      \
+    asm volatile("s_nop 1\n" STEPS                                                                          \
+                 : [r] "+&v"(r), [t] "=&v"(t)                                                               \
+                 : [oh] "v"(oh), [ol] "v"(ol), [mh] "v"(mh), [ml] "v"(ml)                                   \
+                 : "vcc")
+
+__device__ __forceinline__ void rank_row(uint32_t &r, uint32_t oh, uint32_t ol, uint32_t mh, uint32_t ml)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    uint32_t t;
+    NB_RANK(NB_RANK_OWN ".irp n,1,2,3,4,5,6,7,8,9,10,11,12,13,14,15\n" NB_RANK_STEP("row_ror:\\n") ".endr\n");
+}
+__device__ __forceinline__ void rank_quad(uint32_t &r, uint32_t oh, uint32_t ol, uint32_t mh, uint32_t ml)
+{
+    uint32_t t;
+    NB_RANK(NB_RANK_OWN NB_RANK_STEP("quad_perm:[1,0,3,2]") NB_RANK_STEP("quad_perm:[2,3,0,1]")
+                NB_RANK_STEP("quad_perm:[3,2,1,0]"));
+}
+__device__ __forceinline__ void rank_pair(uint32_t &r, uint32_t oh, uint32_t ol, uint32_t mh, uint32_t ml)
+{
+    uint32_t t;
+    NB_RANK(NB_RANK_STEP("quad_perm:[1,0,3,2]"));
 }
 
-// Nodes of at most kWaveNode bodies are split by one wave each, several
-// subtrees at once.
-constexpr int kWaveNode = 256;
-constexpr int kStack = 24;  // node stack entries (the recursion is at most 12 deep)
-
-// One wave finishes the subtree of node [lo0, lo0 + m0) of pos: the same
-// splits as the block-wide path (radix select of the k-th key with a
-// 256-bin histogram hw of the wave's own, ballot-ranked partition through
-// tmp), nodes of at most 64 bodies by orb_wave, leaves by rank.
-__device__ void wave_subtree(int32_t *pos, int32_t *tmp, uint32_t *akey, const uint32_t (*skey)[kSmall],
-                             const int32_t *gid, uint32_t *hw, uint32_t (*wk)[kWaveSeg], int32_t *wid, int2 *stk,
-                             int lo0, int m0, int leaf, int lane)
+// Rank of (h, l) among the group of W lanes; the pairs of a group are distinct.
+template <int W>
+__device__ __forceinline__ int group_rank(uint32_t h, uint32_t l)
 {
-    // node stack in LDS (stk: this wave's kStack entries); sp is uniform
-    int sp = 1;
-    if (lane == 0) stk[0] = make_int2(lo0, m0);
-    wave_sync();
-    while (sp > 0) {
-        --sp;
-        const int2 nd = stk[sp];
-        const int lo = nd.x, m = nd.y;
-        wave_sync();  // read before the pushes below overwrite the entry
-        if (m <= kWaveSeg) {
-            orb_wave(pos, skey, gid, wk, wid, lo, m, leaf, lane);
-            wave_sync();
-            continue;
-        }
-        if (m <= leaf) {
-            // leaf: ranks by original index over a contiguous copy
-            for (int e = lane; e < m; e += 64) akey[lo + e] = (uint32_t)gid[pos[lo + e]];
-            wave_sync();
-            for (int e = lane; e < m; e += 64) {
-                const uint32_t v = akey[lo + e];
-                int r = 0;
-#pragma unroll 4
-                for (int f = 0; f < m; ++f) r += akey[lo + f] < v;
-                tmp[lo + r] = pos[lo + e];
-            }
-            wave_sync();
-            for (int e = lane; e < m; e += 64) pos[lo + e] = tmp[lo + e];
-            wave_sync();
-            continue;
-        }
-        uint32_t bb[6] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0u, 0u, 0u};
-        for (int e = lane; e < m; e += 64) {
-            const int s = pos[lo + e];
+    uint32_t r = 0;
+    if constexpr (W == 2) {
+        rank_pair(r, h, l, h, l);
+    } else if constexpr (W == 4) {
+        rank_quad(r, h, l, h, l);
+    } else if constexpr (W == 8) {
+        rank_quad(r, h, l, h, l);
+        rank_quad(r, dpp<kDppHalfMirror>(h), dpp<kDppHalfMirror>(l), h, l);
+    } else if constexpr (W == 16) {
+        rank_row(r, h, l, h, l);
+    } else if constexpr (W == 32) {
+        const auto ph = __builtin_amdgcn_permlane16_swap(h, h, false, false);
+        const auto pl = __builtin_amdgcn_permlane16_swap(l, l, false, false);
+        rank_row(r, ph[0], pl[0], h, l);
+        rank_row(r, ph[1], pl[1], h, l);
+    } else {
+        const auto qh = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+        const auto ql = __builtin_amdgcn_permlane32_swap(l, l, false, false);
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const uint32_t v = skey[a][s];
-                bb[a] = min(bb[a], v);
-                bb[3 + a] = max(bb[3 + a], v);
-            }
+        for (int z = 0; z < 2; ++z) {
+            const auto ph = __builtin_amdgcn_permlane16_swap(qh[z], qh[z], false, false);
+            const auto pl = __builtin_amdgcn_permlane16_swap(ql[z], ql[z], false, false);
+            rank_row(r, ph[0], pl[0], h, l);
+            rank_row(r, ph[1], pl[1], h, l);
         }
-#pragma unroll
-        for (int j = 0; j < 6; ++j) bb[j] = j < 3 ? wave_min(bb[j]) : wave_max(bb[j]);
-        const int axis = pick_axis(bb);
-        const int L = (m + leaf - 1) / leaf;
-        const int k = min(m, leaf * ((L + 1) / 2));
-        for (int e = lane; e < m; e += 64) akey[lo + e] = skey[axis][pos[lo + e]];
-        wave_sync();
-        // radix select, 8 bits a round, with the single-key exit
-        uint64_t prefix = 0;
-        uint32_t kr = (uint32_t)k;
-        bool one = false;
-        for (int round = 0; round < 8; ++round) {
-            const int shift = 56 - 8 * round;
-            if (one) {
-                // the one key whose digits above `shift` are the prefix
-                uint64_t found = 0;
-                bool hit = false;
-                for (int e = lane; e < m; e += 64) {
-                    const uint64_t key = ((uint64_t)akey[lo + e] << 32) | (uint32_t)gid[pos[lo + e]];
-                    if ((key >> (shift + 8)) == prefix) {
-                        found = key;
-                        hit = true;
-                    }
-                }
-                const uint64_t who = __ballot(hit);
-                const int src = who ? __ffsll((long long)who) - 1 : 0;
-                prefix = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(found >> 32), src) << 32) |
-                         (uint32_t)__shfl((int)(uint32_t)found, src);
-                break;
-            }
-            for (int j = lane; j < 256; j += 64) hw[j] = 0u;
-            wave_sync();
-            for (int e = lane; e < m; e += 64) {
-                // the first four digits are the coordinate key's: no index needed
-                uint64_t key = (uint64_t)akey[lo + e] << 32;
-                if (round >= 4) key |= (uint32_t)gid[pos[lo + e]];
-                if (round == 0 || (key >> (shift + 8)) == prefix) atomicAdd(&hw[(key >> shift) & 0xFF], 1u);
-            }
-            wave_sync();
-            uint32_t c[4], tot = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                c[q] = hw[4 * lane + q];
-                tot += c[q];
-            }
-            uint32_t inc = tot;
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t y = (uint32_t)__shfl_up((int)inc, o);
-                if (lane >= o) inc += y;
-            }
-            const bool mine = inc >= kr && inc - tot < kr;
-            int bin = 0;
-            uint32_t nkr = 0, bc = 0;
-            if (mine) {
-                // the first of this lane's bins where the running count reaches kr
-                uint32_t acc = inc - tot, before = 0;
-                int jb = -1;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (jb < 0 && acc + c[j] >= kr) {
-                        jb = j;
-                        before = acc;
-                        bc = c[j];
-                    }
-                    acc += c[j];
-                }
-                bin = 4 * lane + jb;
-                nkr = kr - before;
-            }
-            const uint64_t who = __ballot(mine);
-            const int src = who ? __ffsll((long long)who) - 1 : 0;
-            bin = __shfl(bin, src);
-            kr = (uint32_t)__shfl((int)nkr, src);
-            one = __shfl((int)bc, src) == 1;
-            prefix = (prefix << 8) | (uint64_t)bin;
-            wave_sync();  // hw is cleared again by the next round
-        }
-        const uint64_t kth = prefix;
-        // partition, 64 entries at a time, in position order within each side
-        int dl = 0, dr = 0;
-        for (int e0 = 0; e0 < m; e0 += 64) {
-            const int e = e0 + lane;
-            const bool act = e < m;
-            const int s = act ? pos[lo + e] : 0;
-            // (key, index) <= kth; the index only decides between equal keys
-            const uint32_t hk = akey[lo + (act ? e : 0)], kh = (uint32_t)(kth >> 32);
-            const bool left = act && (hk < kh || (hk == kh && (uint32_t)gid[s] <= (uint32_t)kth));
-            const bool right = act && !left;
-            const unsigned long long bl = __ballot(left), br = __ballot(right);
-            const int rl = __builtin_amdgcn_mbcnt_hi((unsigned)(bl >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bl, 0u));
-            const int rr = __builtin_amdgcn_mbcnt_hi((unsigned)(br >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)br, 0u));
-            if (left && dl + rl < k) tmp[lo + dl + rl] = s;
-            if (right && dr + rr < m - k) tmp[lo + k + dr + rr] = s;
-            dl += __popcll(bl);
-            dr += __popcll(br);
-        }
-        wave_sync();
-        for (int e = lane; e < m; e += 64) pos[lo + e] = tmp[lo + e];
-        // right first so that the left child is processed next
-        if (lane == 0) {
-            stk[sp] = make_int2(lo + k, m - k);
-            stk[sp + 1] = make_int2(lo, k);
-        }
-        sp += 2;
-        wave_sync();
     }
+    return (int)r;
 }
 
-// Orders positions [lo, lo + m) of pos by original index (a leaf), through tmp.
-__device__ __forceinline__ void block_leaf(int32_t *pos, int32_t *tmp, uint32_t *val, const int32_t *gid, int lo,
-                                           int m)
+struct WaveBody {
+    uint32_t k[3];  // total-order keys
+    uint32_t id;    // original index (an empty lane: above every index, and its own)
+    uint32_t slot;
+};
+
+// One level: the group's node (its m bodies in the group's first lanes, at slo
+// of the whole node's positions) is split in two, whose bodies move to the
+// halves' first lanes.
+template <int W>
+__device__ __forceinline__ void wave_level(WaveBody &b, int &m, int &slo, int leaf_log, int lane)
 {
-    // ranks by original index over a contiguous copy (val)
-    for (int e = threadIdx.x; e < m; e += kOrbBlock) val[lo + e] = (uint32_t)gid[pos[lo + e]];
-    __syncthreads();
-    for (int e = threadIdx.x; e < m; e += kOrbBlock) {
-        const uint32_t v = val[lo + e];
-        int r = 0;
-#pragma unroll 4
-        for (int f = 0; f < m; ++f) r += val[lo + f] < v;
-        tmp[lo + r] = pos[lo + e];
+    const int leaf = 1 << leaf_log;
+    const int at = lane & (W - 1);
+    const bool body = at < m;
+    uint32_t bb[6];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        bb[a] = group_reduce<W>(body ? b.k[a] : 0xFFFFFFFFu, [](uint32_t x, uint32_t y) { return min(x, y); });
+        bb[3 + a] = group_reduce<W>(body ? b.k[a] : 0u, [](uint32_t x, uint32_t y) { return max(x, y); });
     }
-    __syncthreads();
-    for (int e = threadIdx.x; e < m; e += kOrbBlock) pos[lo + e] = tmp[lo + e];
-    __syncthreads();
+    const int axis = pick_axis(bb);
+    const uint32_t key = axis == 0 ? b.k[0] : (axis == 1 ? b.k[1] : b.k[2]);
+    const int r = group_rank<W>(body ? key : 0xFFFFFFFFu, b.id);
+    const bool split = m > leaf;
+    const int L = (m + leaf - 1) >> leaf_log;
+    const int k = min(m, ((L + 1) >> 1) << leaf_log);
+    // the empty lanes fill up the left half, then the right
+    const int q = !split ? at : r < k ? r : r < m ? W / 2 + r - k : r - m < W / 2 - k ? k + r - m : r;
+    const int dst = ((lane & ~(W - 1)) + q) * 4;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) b.k[a] = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)b.k[a]);
+    b.id = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)b.id);
+    b.slot = (uint32_t)__builtin_amdgcn_ds_permute(dst, (int)b.slot);
+    const bool right = (lane & (W / 2)) != 0;
+    slo += split && right ? k : 0;
+    m = split ? (right ? m - k : k) : (right ? 0 : m);
 }
 
-// segs: (start, size, which buffer pair holds it).  keys0/1: the three axes'
-// keys in the order of cur0/1 (axis a at a * n).
-__global__ __launch_bounds__(kOrbBlock) void k_orb_block(const int3 *__restrict__ segs,
+__device__ void orb_wave_pow2(uint16_t *pos, const uint32_t (*skey)[kSmall], const int32_t *gid, int lo, int m0,
+                              int leaf_log, int lane)
+{
+    WaveBody b;
+    b.slot = lane < m0 ? pos[lo + lane] : 0u;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) b.k[a] = skey[a][b.slot];
+    b.id = lane < m0 ? (uint32_t)gid[b.slot] : 0xFFFFFF00u | (uint32_t)lane;
+    int m = m0, slo = 0;
+    wave_level<64>(b, m, slo, leaf_log, lane);
+    if (leaf_log <= 4) wave_level<32>(b, m, slo, leaf_log, lane);
+    if (leaf_log <= 3) wave_level<16>(b, m, slo, leaf_log, lane);
+    if (leaf_log <= 2) wave_level<8>(b, m, slo, leaf_log, lane);
+    if (leaf_log <= 1) wave_level<4>(b, m, slo, leaf_log, lane);
+    if (leaf_log <= 0) wave_level<2>(b, m, slo, leaf_log, lane);
+    // leaves: ascending original index
+    int r = 0;
+    switch (leaf_log) {
+    case 5: r = group_rank<32>(0u, b.id); break;
+    case 4: r = group_rank<16>(0u, b.id); break;
+    case 3: r = group_rank<8>(0u, b.id); break;
+    case 2: r = group_rank<4>(0u, b.id); break;
+    case 1: r = group_rank<2>(0u, b.id); break;
+    default: break;
+    }
+    if ((lane & ((1 << leaf_log) - 1)) < m) pos[lo + slo + r] = (uint16_t)b.slot;
+}
+
+// Bins of a level's selection, shared by its nodes: node j of depth d has the
+// kFinBins >> d from j (kFinBins >> d) on.
+constexpr int kFinBins = 4096;
+constexpr int kFinDepth = 7;  // a node of depth 7 has at most 64 bodies, whatever the leaf size
+constexpr int kFinNodes = 1 << kFinDepth;
+constexpr int kFinPer = kSmall / kFinBlock;       // positions per thread
+constexpr int kBinPer = kFinBins / kFinBlock;     // bins per thread
+constexpr int kCand = 64;                         // keys that one wave ranks
+static_assert((kFinBins >> (kFinDepth - 1)) >= kBinPer, "a thread's bins belong to one node");
+
+// A node of the current depth.
+struct FinNode {
+    int lo, m, k;         // positions [lo, lo + m); the first k keys go left (0: not split)
+    uint32_t bb[6];       // key box
+    int axis;
+    int bits;             // the selection's window: 2^bits keys from `from` on
+    int krem;             // rank still to find inside it
+    int count;            // keys inside it
+    int base;             // keys counted in the bins before the node's
+    uint64_t from;
+    uint64_t kth;         // the k-th key
+    uint32_t cand;        // candidates gathered
+    uint32_t put[2];      // partition: entries placed left and right
+};
+
+// Bodies of a node of m that go left, 0 if it stays whole.  A leaf of more than
+// 64 bodies, which is to be ordered by index, is split along that.
+__device__ __forceinline__ int fin_split(int m, int leaf)
+{
+    if (m <= kWaveSeg) return 0;
+    const int unit = m <= leaf ? kWaveSeg : leaf;
+    return min(m, unit * (((m + unit - 1) / unit + 1) / 2));
+}
+
+__device__ __forceinline__ uint64_t body_key(uint32_t key, int32_t id) { return ((uint64_t)key << 32) | (uint32_t)id; }
+
+// Phase B.  segs: (start, size, which buffer pair holds it).  keys0/1: the
+// three axes' keys in the order of cur0/1 (axis a at a * n).
+//
+// All nodes of a depth are split together: the threads hold kFinPer positions
+// each, whatever node they belong to.  Per depth: the nodes' key boxes (LDS
+// atomics, one per wave where a wave lies in one node); a histogram of the
+// split axis' keys over each node's own range, in kFinBins bins shared out
+// among the nodes; the bin that holds the k-th key; the few keys in that bin,
+// ranked by one wave (a bin of more than kCand keys is divided again); the
+// partition of the slot numbers.  Until every node has at most 64 bodies, which
+// one wave per node finishes (orb_wave).  Leaves of more than 64 bodies are
+// split on by original index, which is the order their bodies end in.
+// A key is the coordinate's total-order key and the index below it, so the
+// keys are distinct and every selection ends.
+//
+// Bound by the latency of its LDS round trips and barriers, some ten per
+// depth, and by the VALU work of 16 waves on one CU.  At 2^20 bodies (leaf 4) it
+// takes 86 us for 256 segments of 4096; node by node, 1024 segments of 1024
+// took 139 us, after two more levels of phase A at 48 us each.
+__global__ __launch_bounds__(kFinBlock) void k_orb_block(const int3 *__restrict__ segs,
                                                          const uint32_t *__restrict__ keys0,
                                                          const uint32_t *__restrict__ keys1,
                                                          const int32_t *__restrict__ cur0,
                                                          const int32_t *__restrict__ cur1, int n, int leaf,
                                                          int32_t *__restrict__ perm)
 {
-    // one buffer: keys by slot (3 x kSmall), original index by slot, slots in
-    // the current order, partition target, the current node's keys along
-    // its split axis; a segment that is one leaf only needs its indices
-    __shared__ uint32_t lds[7 * kSmall];
-    static_assert(7 * kSmall >= kMaxBlockSeg, "a one-leaf segment's indices fit");
-    uint32_t (*skey)[kSmall] = reinterpret_cast<uint32_t (*)[kSmall]>(lds);
-    int32_t *gid = reinterpret_cast<int32_t *>(lds + 3 * kSmall);
-    int32_t *pos = reinterpret_cast<int32_t *>(lds + 4 * kSmall);
-    int32_t *tmp = reinterpret_cast<int32_t *>(lds + 5 * kSmall);
-    uint32_t *akey = lds + 6 * kSmall;
-    __shared__ uint32_t h[256];
-    __shared__ uint32_t red[kOrbBlock / 64];
-    __shared__ uint32_t red6[kOrbBlock / 64][6];
-    __shared__ uint32_t wl[kOrbBlock / 64], wr[kOrbBlock / 64];
-    __shared__ uint64_t kth_s;
-    __shared__ uint32_t krem_s, one_s;
-    constexpr int kMaxTask = 64;
-    __shared__ int2 task[kMaxTask];
-    __shared__ uint32_t hw[kOrbBlock / 64][256];
-    __shared__ uint32_t wkeys[kOrbBlock / 64][3][kWaveSeg];
-    __shared__ int32_t wgid[kOrbBlock / 64][kWaveSeg];
-    __shared__ int2 stk[kOrbBlock / 64 + 1][kStack];  // node stacks: the waves', then the block's
+    __shared__ uint32_t skey[3][kSmall];   // keys by slot
+    __shared__ int32_t gid[kSmall];        // original index by slot
+    __shared__ uint16_t posb[2][kSmall];   // slots in the current order, and the partition's target
+    __shared__ uint32_t hist[kFinBins];
+    __shared__ uint64_t cand[kFinNodes / 2][kCand];
+    __shared__ FinNode node[kFinNodes];
+    __shared__ uint32_t red[kFinBlock / 64];
+    __shared__ int again[2];  // a window is to be divided once more (by the parity of the turn)
     const int3 sg = segs[blockIdx.x];
     const int start = sg.x, size = sg.y;
     const int32_t *cur = sg.z ? cur1 : cur0;
     const uint32_t *keys = sg.z ? keys1 : keys0;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // the clamp only keeps a broken invariant (an unfilled slot) from turning
     // into out-of-bounds writes: every slot is filled
-    if (size > kSmall) {
-        // at most max(kSmall, leaf) bodies reach this kernel: a larger
-        // segment is one leaf, written in ascending original index (ranks;
-        // the indices are distinct)
-        int32_t *big = reinterpret_cast<int32_t *>(lds);
-        for (int e = threadIdx.x; e < size; e += kOrbBlock) big[e] = (int32_t)min((uint32_t)cur[start + e], (uint32_t)(n - 1));
-        __syncthreads();
-        for (int e = threadIdx.x; e < size; e += kOrbBlock) {
-            const int v = big[e];
-            int r = 0;
-            for (int f = 0; f < size; ++f) r += big[f] < v;
-            perm[start + r] = v;
-        }
-        return;
-    }
-    for (int e = threadIdx.x; e < size; e += kOrbBlock) {
+    for (int e = tid; e < size; e += kFinBlock) {
         gid[e] = (int32_t)min((uint32_t)cur[start + e], (uint32_t)(n - 1));
-        pos[e] = e;
+        posb[0][e] = (uint16_t)e;
 #pragma unroll
         for (int a = 0; a < 3; ++a) skey[a][e] = keys[(size_t)a * n + start + e];
     }
-    int2 *bstk = stk[kOrbBlock / 64];
-    if (threadIdx.x == 0) bstk[0] = make_int2(0, size);
-    __syncthreads();
-    int ntask = 0;  // same value in every thread: the loop below is uniform
-    int sp = 1;
-    while (sp > 0) {
-        --sp;
-        const int2 nd = bstk[sp];
-        const int lo = nd.x, m = nd.y;
-        __syncthreads();  // read before the pushes below overwrite the entry
-        if (m <= kWaveNode && ntask < kMaxTask) {
-            // its subtree is finished by one wave below, several at once
-            // (past the list's capacity the block-wide path takes them)
-            if (threadIdx.x == 0) task[ntask] = make_int2(lo, m);
-            ++ntask;
-            continue;
-        }
-        if (m <= leaf) {
-            block_leaf(pos, tmp, akey, gid, lo, m);
-            continue;
-        }
-        // bounding box and axis
-        uint32_t bb[6] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0u, 0u, 0u};
-        for (int e = threadIdx.x; e < m; e += kOrbBlock) {
-            const int s = pos[lo + e];
+    int lo0 = 0, m0 = size;  // thread j < 2^depth: node j
+    const int e0 = tid * kFinPer;  // this thread's positions
+    const int ne = max(0, min(kFinPer, size - e0));
+    int nid[kFinPer];  // the node of each
+#pragma unroll
+    for (int u = 0; u < kFinPer; ++u) nid[u] = 0;
+    uint16_t *pos = posb[0], *to = posb[1];
+    int depth = 0;
+    int most = size;  // bodies of the depth's largest node: the leftmost
+    for (;; ++depth) {
+        const int nn = 1 << depth, bins_log = 12 - depth;
+        __syncthreads();
+        if (tid == 0) again[0] = again[1] = 0;
+        if (tid < nn) {
+            FinNode &N = node[tid];
+            N.lo = lo0;
+            N.m = m0;
+            N.k = depth < kFinDepth ? fin_split(m0, leaf) : 0;
+            N.cand = 0u;
+            N.put[0] = N.put[1] = 0u;
+            N.count = kCand + 1;
+            N.kth = 0;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const uint32_t v = skey[a][s];
-                bb[a] = min(bb[a], v);
-                bb[3 + a] = max(bb[3 + a], v);
-            }
-        }
-        block_box(bb, red6);
-        const int axis = pick_axis(bb);
-        const int L = (m + leaf - 1) / leaf;
-        const int k = min(m, leaf * ((L + 1) / 2));
-        // the split axis's keys in node order, for the rounds and the partition
-        for (int e = threadIdx.x; e < m; e += kOrbBlock) akey[e] = skey[axis][pos[lo + e]];
-        // radix select of the k-th smallest key (total-order key, original
-        // index), 8 bits a round; once the bin holding it holds it alone, one
-        // pass reads it whole
-        if (threadIdx.x == 0) {
-            kth_s = 0;
-            krem_s = (uint32_t)k;
-            one_s = 0u;
-        }
-        for (int round = 0; round < 8; ++round) {
-            __syncthreads();
-            h[threadIdx.x] = 0u;
-            const uint64_t prefix = kth_s;
-            const uint32_t kr = krem_s;
-            const int shift = 56 - 8 * round;
-            if (one_s) {
-                // the one key whose digits above `shift` are the prefix
-                for (int e = threadIdx.x; e < m; e += kOrbBlock) {
-                    const uint64_t key = ((uint64_t)akey[e] << 32) | (uint32_t)gid[pos[lo + e]];
-                    if ((key >> (shift + 8)) == prefix) kth_s = key;
-                }
-                break;
-            }
-            __syncthreads();
-            for (int e = threadIdx.x; e < m; e += kOrbBlock) {
-                // the first four digits are the coordinate key's: no index needed
-                uint64_t key = (uint64_t)akey[e] << 32;
-                if (round >= 4) key |= (uint32_t)gid[pos[lo + e]];
-                if (round == 0 || (key >> (shift + 8)) == prefix) atomicAdd(&h[(key >> shift) & 0xFF], 1u);
-            }
-            __syncthreads();
-            // the bin holding rank kr (1-based): the one thread whose
-            // inclusive sum over the bins reaches kr first decides
-            const uint32_t hv = h[threadIdx.x];
-            const uint32_t inc = block_incl_scan_u32(hv, red);
-            if (inc >= kr && inc - hv < kr) {
-                kth_s = (prefix << 8) | (uint64_t)threadIdx.x;
-                krem_s = kr - (inc - hv);
-                one_s = hv == 1u;
+                N.bb[a] = 0xFFFFFFFFu;
+                N.bb[3 + a] = 0u;
             }
         }
         __syncthreads();
-        const uint64_t kth = kth_s;
-        // partition: keys <= the k-th key go left, in position order within
-        // each side (ballot ranks, then the waves before, then the chunks
-        // before); the order inside a side does not change the result
-        {
-            const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-            int dl = 0, dr = 0;  // entries placed by the chunks before
-            for (int e0 = 0; e0 < m; e0 += kOrbBlock) {
-                const int e = e0 + threadIdx.x;
-                const bool act = e < m;
-                const int s = act ? pos[lo + e] : 0;
-                // (key, index) <= kth; the index only decides between equal keys
-                const uint32_t hk = akey[act ? e : 0], kh = (uint32_t)(kth >> 32);
-                const bool left = act && (hk < kh || (hk == kh && (uint32_t)gid[s] <= (uint32_t)kth));
-                const bool right = act && !left;
-                const unsigned long long bl = __ballot(left), br = __ballot(right);
-                if (lane == 0) {
-                    wl[w] = (uint32_t)__popcll(bl);
-                    wr[w] = (uint32_t)__popcll(br);
+        if (most <= kWaveSeg || depth >= kFinDepth) break;
+        most = fin_split(most, leaf);
+        // the slots with their keys, and the nodes' boxes.  (A thread's positions lie
+        // in one node almost always: what they need of it is read again only
+        // where the node changes.)
+        int slot[kFinPer];
+        int32_t id[kFinPer];
+        uint32_t key[kFinPer][3];
+        const int first = __shfl(nid[0], 0);
+        const bool one = __all((ne == kFinPer) & (nid[0] == first) & (nid[kFinPer - 1] == first)) != 0;
+        bool split_u[kFinPer];
+        uint32_t bx[6] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0u, 0u, 0u};
+        auto box_out = [&](int j, bool split_j) {  // the box so far goes to node j, if that is split
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                if (split_j) {
+                    atomicMin(&node[j].bb[a], bx[a]);
+                    atomicMax(&node[j].bb[3 + a], bx[3 + a]);
                 }
-                __syncthreads();
-                int pl = 0, pr = 0, cl = 0, cr = 0;
-                for (int v = 0; v < kOrbBlock / 64; ++v) {
-                    if (v < w) {
-                        pl += (int)wl[v];
-                        pr += (int)wr[v];
+                bx[a] = 0xFFFFFFFFu;
+                bx[3 + a] = 0u;
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < kFinPer; ++u) {
+            if (u == 0 || nid[u] != nid[u - 1])
+                split_u[u] = node[nid[u]].k > 0;
+            else
+                split_u[u] = split_u[u - 1];
+            slot[u] = u < ne ? pos[e0 + u] : 0;
+            id[u] = gid[slot[u]];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) key[u][a] = skey[a][slot[u]];
+            if (u < ne)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    bx[a] = min(bx[a], key[u][a]);
+                    bx[3 + a] = max(bx[3 + a], key[u][a]);
+                }
+            if (!one && u < ne && (u + 1 >= ne || nid[u + 1 < kFinPer ? u + 1 : u] != nid[u]))
+                box_out(nid[u], split_u[u]);
+        }
+        if (one && split_u[0]) {
+#pragma unroll
+            for (int j = 0; j < 6; ++j) bx[j] = j < 3 ? wave_min(bx[j]) : wave_max(bx[j]);
+            if (lane == 0) box_out(first, true);
+        }
+        __syncthreads();
+        // the split axes and the first windows: from the smallest key's coordinate
+        // to the largest's, all indices
+        if (tid < nn && node[tid].k > 0) {
+            FinNode &N = node[tid];
+            N.krem = N.k;
+            if (N.m <= leaf) {  // by index
+                N.axis = 3;
+                N.from = 0;
+                N.bits = 32 - __clz(n);
+            } else {
+                N.axis = pick_axis(N.bb);
+                const uint32_t range = N.bb[3 + N.axis] - N.bb[N.axis];
+                N.from = (uint64_t)N.bb[N.axis] << 32;
+                N.bits = 64 - __clz((int)(range | 1u));  // (a range of 0 takes the indices' 32 bits and one)
+            }
+        }
+        uint64_t bk[kFinPer];  // the bodies' keys along their nodes' axes
+        int axis_u[kFinPer];
+        // divide the windows until every node's holds at most kCand keys
+        for (int turn = 0;; ++turn) {
+            const bool begin = turn == 0;
+#pragma unroll
+            for (int b = 0; b < kBinPer; ++b) hist[tid * kBinPer + b] = 0u;
+            __syncthreads();
+            if (tid == 0) again[(turn + 1) & 1] = 0;
+            {
+                uint64_t from = 0;
+                int bits = 0;
+                bool open = false;
+#pragma unroll
+                for (int u = 0; u < kFinPer; ++u) {
+                    if (u == 0 || nid[u] != nid[u - 1]) {
+                        const FinNode &N = node[nid[u]];
+                        open = split_u[u] && N.count > kCand;
+                        from = N.from;
+                        bits = N.bits;
+                        axis_u[u] = N.axis;
+                    } else {
+                        axis_u[u] = axis_u[u - 1];
                     }
-                    cl += (int)wl[v];
-                    cr += (int)wr[v];
+                    if (begin)
+                        bk[u] = body_key(axis_u[u] == 0   ? key[u][0]
+                                         : axis_u[u] == 1 ? key[u][1]
+                                         : axis_u[u] == 2 ? key[u][2]
+                                                          : 0u,
+                                         id[u]);
+                    const uint64_t rel = bk[u] - from;
+                    if (open && u < ne && (bits == 64 || (rel >> bits) == 0))
+                        atomicAdd(&hist[(nid[u] << bins_log) + (int)(rel >> max(bits - bins_log, 0))], 1u);
                 }
-                const int rl = __builtin_amdgcn_mbcnt_hi((unsigned)(bl >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bl, 0u));
-                const int rr = __builtin_amdgcn_mbcnt_hi((unsigned)(br >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)br, 0u));
-                if (left) {
-                    const int q = dl + pl + rl;
-                    if (q < k) tmp[lo + q] = s;
+            }
+            __syncthreads();
+            uint32_t c[kBinPer], sum = 0;
+#pragma unroll
+            for (int b = 0; b < kBinPer; ++b) {
+                c[b] = hist[tid * kBinPer + b];
+                sum += c[b];
+            }
+            const uint32_t inc = block_incl_scan_u32(sum, red);
+            const int j = (tid * kBinPer) >> bins_log;
+            const bool open = node[j].k > 0 && node[j].count > kCand;
+            if (open && ((tid * kBinPer) & ((1 << bins_log) - 1)) == 0) node[j].base = (int)(inc - sum);
+            const int krem = node[j].krem, bits = node[j].bits;
+            const uint64_t from = node[j].from;
+            __syncthreads();
+            if (open) {
+                int before = (int)(inc - sum) - node[j].base;
+                if (before < krem && before + (int)sum >= krem) {
+#pragma unroll
+                    for (int b = 0; b < kBinPer; ++b) {
+                        if (before < krem && before + (int)c[b] >= krem) {
+                            const int sh = max(bits - bins_log, 0);
+                            const int bin = tid * kBinPer + b - (j << bins_log);
+                            node[j].from = from + ((uint64_t)bin << sh);
+                            node[j].bits = sh;
+                            node[j].krem = krem - before;
+                            // (a window of one key holds one body)
+                            node[j].count = sh > 0 ? (int)c[b] : 1;
+                            if (sh > 0 && (int)c[b] > kCand) again[turn & 1] = 1;
+                        }
+                        before += (int)c[b];
+                    }
                 }
-                if (right) {
-                    const int q = dr + pr + rr;
-                    if (q < m - k) tmp[lo + k + q] = s;
+            }
+            __syncthreads();
+            if (!again[turn & 1]) break;
+        }
+        // the keys in the windows, ranked by a wave per node
+        {
+            uint64_t from = 0;
+            int bits = 0;
+#pragma unroll
+            for (int u = 0; u < kFinPer; ++u) {
+                if (u == 0 || nid[u] != nid[u - 1]) {
+                    from = node[nid[u]].from;
+                    bits = node[nid[u]].bits;
                 }
-                dl += cl;
-                dr += cr;
-                __syncthreads();  // wl, wr are reused by the next chunk
+                if (split_u[u] && u < ne && ((bk[u] - from) >> bits) == 0) {
+                    const uint32_t q = atomicAdd(&node[nid[u]].cand, 1u);
+                    if (q < (uint32_t)kCand) cand[nid[u]][q] = bk[u];
+                }
             }
         }
-        for (int e = threadIdx.x; e < m; e += kOrbBlock) pos[lo + e] = tmp[lo + e];
-        // right first so that the left child is processed next
-        if (threadIdx.x == 0) {
-            bstk[sp] = make_int2(lo + k, m - k);
-            bstk[sp + 1] = make_int2(lo, k);
-        }
-        sp += 2;
         __syncthreads();
-    }
-    __syncthreads();
-    {
-        const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        for (int t = w; t < ntask; t += kOrbBlock / 64) {
-            const int2 tk = task[t];
-            wave_subtree(pos, tmp, akey, skey, gid, hw[w], wkeys[w], wgid[w], stk[w], tk.x, tk.y, leaf, lane);
+        for (int j = wave; j < nn; j += kFinBlock / 64) {
+            FinNode &N = node[j];
+            const int cnt = min((int)N.cand, kCand);
+            if (N.k == 0 || cnt == 0) continue;
+            const uint64_t mine = cand[j][lane < cnt ? lane : 0];
+            int r = 1;
+#pragma unroll 8
+            for (int f = 0; f < cnt; ++f) r += cand[j][f] < mine;
+            if (lane < cnt && r == N.krem) N.kth = mine;
         }
+        __syncthreads();
+        // partition; the order inside a side does not change the result
+        bool left[kFinPer];
+        int nl = 0, nr = 0;
+        int lo_u = 0, k_u = 0, m_u = 0;
+        {
+            uint64_t kth = 0;
+#pragma unroll
+            for (int u = 0; u < kFinPer; ++u) {
+                if (u == 0 || nid[u] != nid[u - 1]) kth = node[nid[u]].kth;
+                left[u] = u < ne && split_u[u] && bk[u] <= kth;
+                nl += left[u];
+                nr += u < ne && !left[u];
+            }
+        }
+        lo_u = node[nid[0]].lo;
+        k_u = node[nid[0]].k;
+        m_u = node[nid[0]].m;
+        if (one && split_u[0]) {
+            // (left and right counts side by side: at most 64 kFinPer each)
+            uint32_t v = (uint32_t)nl | ((uint32_t)nr << 16);
+            const uint32_t mine = v;
+            v = wave_incl_scan(v);
+            uint32_t bl = 0, br = 0;
+            if (lane == 63) {
+                bl = atomicAdd(&node[first].put[0], v & 0xFFFFu);
+                br = atomicAdd(&node[first].put[1], v >> 16);
+            }
+            v -= mine;
+            int ql = __builtin_amdgcn_readlane((int)bl, 63) + (int)(v & 0xFFFFu);
+            int qr = k_u + __builtin_amdgcn_readlane((int)br, 63) + (int)(v >> 16);
+#pragma unroll
+            for (int u = 0; u < kFinPer; ++u) {
+                const int q = left[u] ? ql++ : qr++;
+                if (q < (left[u] ? k_u : m_u)) to[lo_u + q] = (uint16_t)slot[u];
+            }
+        } else {
+            int lo = lo_u, k = k_u, m = m_u;
+#pragma unroll
+            for (int u = 0; u < kFinPer; ++u) {
+                if (u > 0 && nid[u] != nid[u - 1]) {
+                    lo = node[nid[u]].lo;
+                    k = node[nid[u]].k;
+                    m = node[nid[u]].m;
+                }
+                if (u >= ne) continue;
+                if (!split_u[u]) {
+                    to[e0 + u] = (uint16_t)slot[u];
+                } else {
+                    const int q = left[u] ? (int)atomicAdd(&node[nid[u]].put[0], 1u)
+                                          : k + (int)atomicAdd(&node[nid[u]].put[1], 1u);
+                    if (q < (left[u] ? k : m)) to[lo + q] = (uint16_t)slot[u];
+                }
+            }
+        }
+        {
+            int lo = lo_u, k = k_u, was = nid[0];
+#pragma unroll
+            for (int u = 0; u < kFinPer; ++u) {
+                if (nid[u] != was) {
+                    was = nid[u];
+                    lo = node[was].lo;
+                    k = node[was].k;
+                }
+                nid[u] = 2 * nid[u] + (k > 0 && e0 + u >= lo + k);
+            }
+        }
+        // the next depth's nodes: 2 j and 2 j + 1 (an unsplit one stays the left)
+        if (tid < 2 * nn) {
+            const FinNode &N = node[tid / 2];
+            const int k = N.k > 0 ? N.k : N.m;
+            lo0 = N.lo + ((tid & 1) ? k : 0);
+            m0 = (tid & 1) ? N.m - k : k;
+        }
+        uint16_t *const t = pos;
+        pos = to;
+        to = t;
+    }
+    // (the nodes' table is the last depth's)
+    __shared__ uint32_t wkeys[kFinBlock / 64][3][kWaveSeg];
+    __shared__ int32_t wgid[kFinBlock / 64][kWaveSeg];
+    const int nn = 1 << depth;
+    for (int j = wave; j < nn; j += kFinBlock / 64) {
+        const int lo = node[j].lo, m = node[j].m;
+        if (m == 0) continue;
+        if (leaf <= 32 && (leaf & (leaf - 1)) == 0)
+            orb_wave_pow2(pos, skey, gid, lo, m, __builtin_ctz(leaf), lane);
+        else
+            orb_wave(pos, skey, gid, wkeys[wave], wgid[wave], lo, m, leaf, lane);
+        wave_sync();
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < size; e += kOrbBlock) perm[start + e] = gid[pos[e]];
+    for (int e = tid; e < size; e += kFinBlock) perm[start + e] = gid[pos[e]];
 }
 
 // ---- host side --------------------------------------------------------------
@@ -1261,7 +1412,7 @@ int orb_order(const void *pm, int prec, int n, int leaf, int32_t *perm, hipStrea
         e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "ORB level");
     }
-    hipLaunchKernelGGL(k_orb_block, dim3((unsigned)finals.size()), dim3(kOrbBlock), 0, s,
+    hipLaunchKernelGGL(k_orb_block, dim3((unsigned)finals.size()), dim3(kFinBlock), 0, s,
                        (const int3 *)(dtab + foff), kbuf[0], kbuf[1], cbuf[0], cbuf[1], n, leaf, perm);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "ORB leaves");

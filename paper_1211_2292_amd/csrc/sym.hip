@@ -232,7 +232,7 @@ __device__ __forceinline__ void sym_chunk_asm(const float4 *jp, SymTargets<TPL> 
     int cnt = 8;
     if constexpr (TPL == 4)
         asm volatile(NB_SYM_LOOP("0,1,2,3", "1,2,3", "16", "32", "48", "52", "56", "60", "64")
-                     : "+{v[32:47]}"(sum), "+{v[48:51]}"(js), [addr] "+v"(addr), [cnt] "+s"(cnt)
+                     : "+{v[32:47]}"(sum), "+{v[48:51]}"(js), [addr] "+&v"(addr), [cnt] "+&s"(cnt)
                      : "{v[16:31]}"(tg), "{v55}"(eps2)
                      : "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63", "v64", "v65", "v66", "v67", "v68",
                        "v69", "v70", "v71", "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v80", "v81",
@@ -240,7 +240,7 @@ __device__ __forceinline__ void sym_chunk_asm(const float4 *jp, SymTargets<TPL> 
                        "v95", "scc", "memory");
     else
         asm volatile(NB_SYM_LOOP("0,1", "1", "16", "24", "32", "36", "40", "44", "48")
-                     : "+{v[24:31]}"(sum), "+{v[32:35]}"(js), [addr] "+v"(addr), [cnt] "+s"(cnt)
+                     : "+{v[24:31]}"(sum), "+{v[32:35]}"(js), [addr] "+&v"(addr), [cnt] "+&s"(cnt)
                      : "{v[16:23]}"(tg), "{v39}"(eps2)
                      : "v40", "v41", "v42", "v43", "v44", "v45", "v46", "v47", "v48", "v49", "v50", "v51", "v52",
                        "v53", "v54", "v55", "v56", "v57", "v58", "v59", "v60", "v61", "v62", "v63", "scc", "memory");

@@ -29,6 +29,24 @@ def test_orb_bitexact_plummer(orc, n, leaf):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("leaf", [1, 2, 3, 4, 5, 8, 11, 16, 17, 31, 32, 33, 48, 63, 64, 65, 96, 129, 600, 1025, 2049, 4095])
+def test_orb_bitexact_segment_edges(orc, leaf):
+    """Segments around the sizes where the way of splitting changes: one
+    wave's 64 bodies, the workgroup's 4096 and their halves, full and ragged,
+    with leaf sizes that are and are not powers of two, below and above a
+    wave; with spread coordinates, and with few distinct ones (whole ranges
+    of equal keys, ordered by index)."""
+    torch, nb = gpu()
+    for n in (2, 63, 64, 65, 129, 257, 513, 1023, 2047, 2049, 4095, 4096, 4097, 8193):
+        pm, _ = ics.plummer(n, 2200 + n)
+        for coarse in (False, True):
+            if coarse:
+                pm[:, :3] = np.round(pm[:, :3])
+            want = orc.orb_order(pm, leaf)
+            got = _gpu_perm(torch, nb, pm.astype(np.float32), leaf, torch.float32)
+            assert np.array_equal(got, want), (n, coarse)
+
+
 def test_orb_f64_input_rounds_to_f32(orc):
     torch, nb = gpu()
     pm, _ = ics.uniform_ball(9000, 210)
