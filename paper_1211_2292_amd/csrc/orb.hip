@@ -9,18 +9,17 @@
 //   * the host computes the whole segment tree (sizes and left counts) once;
 //   * the device only decides which bodies go left, by finding the k-th
 //     smallest 64-bit key (total-order FP32 coordinate, original index) of
-//     each segment exactly, with a radix select;
+//     each segment exactly, by histograms and rank;
 //   * bodies may be partitioned in any order, because every later decision
 //     depends on set membership only and every leaf is finally sorted by
 //     original index.
 // Phase A handles segments larger than kSmall bodies, one level of the tree
 // per step, with multi-workgroup kernels over fixed-size chunks.  The three
 // axes' keys travel with the index array (two buffers, read and written in
-// turn), so every pass reads them coalesced.  A level is: four histogram
-// passes over the coordinate's 8-bit digits (k_orb_hist; the workgroup that
-// finishes a segment picks the bin, and once the bin holds a single key one
-// pass reads it whole), one pass that settles ties between equal coordinates
-// by index (k_orb_ties), and the partition (k_orb_partition), which also
+// turn), so every pass reads them coalesced.  A level is: two to four
+// histogram passes over the segment's own key range (k_orb_hist; the workgroup
+// that finishes a segment picks the bin), one pass that ranks the few keys of
+// the last bin (k_orb_pick), and the partition (k_orb_partition), which also
 // accumulates each part's key box for the next level.  Phase B (k_orb_block)
 // finishes every remaining segment (at most kSmall bodies) inside one
 // workgroup: the segment's keys are loaded into LDS once, all nodes of a depth
@@ -37,7 +36,7 @@
 namespace nbi {
 
 // Phase A splits segments larger than this: as many as fit phase B's LDS.  A level
-// of phase A takes 40 us at 2^20 bodies, one of phase B 10.
+// of phase A takes 33 us at 2^20 bodies, one of phase B 10.
 constexpr int kSmall = 4096;
 constexpr int kMaxBlockSeg = 4096;  // largest leaf
 constexpr int kChunk = 4096;        // elements per phase-A workgroup
@@ -86,46 +85,58 @@ __global__ __launch_bounds__(kOrbBlock) void k_orb_coords(const V *__restrict__ 
     cur[i] = i;
 }
 
-// Radix select over the 64-bit key (coordinate key in the high half, index
-// in the low half) in digits of kDigit bits, most significant first;
-// digit_shift(r) is the lowest bit of digit r.
+// Selection of a segment's k-th key (coordinate key in the high half, index in
+// the low half): a window of keys [from, from + 2^bits), at first from the
+// smallest coordinate to the largest, is divided into kBins bins, the bin that
+// holds the k-th key is the next window, and so on; once it holds at most
+// kPick keys, or after the last round, one pass gathers and ranks them.  A pass is
+// a chain of a few round trips to memory, whatever it counts, so what matters is
+// how many there are: four rounds over the coordinate's digits from the top, whose
+// first eight bits hardly tell a segment's bodies apart, and a pass for equal
+// coordinates took 27 us a level at 2^20 bodies; two rounds over the segment's own
+// range, two skipped ones and the pick take 22, without the skipped ones 17.
+// (kPick of 32 and 512: 3% and 7% slower.)
 constexpr int kDigit = 8;
 constexpr int kBins = 1 << kDigit;
-__host__ __device__ constexpr int digit_shift(int round)
-{
-    return 64 - kDigit * (round + 1) > 0 ? 64 - kDigit * (round + 1) : 0;
-}
-// bits above the digit of `round`: the prefix found before it
-__host__ __device__ constexpr int prefix_shift(int round)
-{
-    return round == 0 ? 64 : digit_shift(round - 1);
-}
-// The histogram, tie and partition passes run 512 threads per chunk: more
+constexpr int kRounds = 4;
+// The histogram, pick and partition passes run 512 threads per chunk: more
 // waves per CU to hide their latency, without more workgroups per segment.
 constexpr int kPassBlock = 512;
 constexpr int kPassPer = kChunk / kPassBlock;
+constexpr int kPick = 128;
+constexpr int kPickDigit = 10, kPickBins = 1 << kPickDigit;  // the pick's own rounds
+static_assert(kPickBins == 2 * kPassBlock, "two bins per thread");
+// Two rounds nearly always leave a few keys.  Where they don't (a dense cluster in
+// a wide box, few distinct coordinates), one workgroup takes the rest, which is
+// slow for many keys: levels of long segments take up to two rounds more, which
+// cost 2.5 us each where every segment is done.  (100000 bodies: 225 us for the
+// order with two rounds for short segments, 232 with three.)
+constexpr int kShortRounds = 2;
+constexpr int kLongSegment = 65536;
 static_assert(kBins <= kPassBlock, "one bin per thread");
-// The rounds over the coordinate's 32 bits run as histogram passes; the
-// index bits, which only matter between equal coordinates, are settled by
-// one pass over those bodies (k_orb_ties).
-constexpr int kCoordRounds = 32 / kDigit;
-static_assert(32 % kDigit == 0 && digit_shift(kCoordRounds - 1) == 32, "digits end at the coordinate");
+
+__device__ __forceinline__ uint64_t body_key(uint32_t key, int32_t id) { return ((uint64_t)key << 32) | (uint32_t)id; }
+
+struct Window {
+    uint64_t from;
+    int bits;
+    __device__ bool holds(uint64_t key) const { return bits == 64 || ((key - from) >> bits) == 0; }
+    // the bins of 2^shift keys
+    __device__ int shift() const { return max(bits - kDigit, 0); }
+    __device__ int bin(uint64_t key) const { return (int)((key - from) >> shift()); }
+    __device__ Window of_bin(int b) const { return {from + ((uint64_t)b << shift()), shift()}; }
+};
 
 // Per-segment state of one phase-A level.
-enum SegMode : int {
-    kSelect = 0,  // radix select: histogram the next digit inside the prefix
-    kFind = 1,    // one key holds the prefix: the next pass reads it whole
-    kDone = 2,    // the k-th key is known
-};
 struct SegState {
     uint32_t bb[6];    // min keys x,y,z then max keys x,y,z
-    int krem;          // rank still to find inside the current prefix
-    int mode;          // SegMode
-    uint64_t prefix;   // digits of the k-th key found so far
-    uint64_t full;     // the k-th key, written by the kFind pass
+    int krem;          // rank still to find inside the window
+    int pick;          // the window's keys are few enough to be ranked
+    Window win;        // from the second round on
+    uint64_t kth;      // the k-th key
     uint64_t placed;   // partition: bodies placed (high half) and placed left (low half)
     uint32_t arrived;  // workgroups of the current pass done with the segment
-    uint32_t ties;     // bodies whose coordinate equals the k-th key's (k_orb_ties)
+    uint32_t picked;   // bodies gathered (k_orb_pick)
 };
 
 __device__ __forceinline__ void init_state(SegState *st, int k)
@@ -136,12 +147,12 @@ __device__ __forceinline__ void init_state(SegState *st, int k)
         z.bb[3 + a] = 0u;
     }
     z.krem = k;
-    z.mode = kSelect;
-    z.prefix = 0;
-    z.full = 0;
+    z.pick = 0;
+    z.win = {0, 0};
+    z.kth = 0;
     z.placed = 0;
     z.arrived = 0;
-    z.ties = 0;
+    z.picked = 0;
     *st = z;
 }
 
@@ -333,14 +344,11 @@ __global__ __launch_bounds__(kOrbBlock) void k_orb_bbox(const int3 *__restrict__
     box_atomics(st[c.x].bb, tot);
 }
 
-// One pass of the radix select of every segment, for digit `round` of the
-// 64-bit key (total-order key along the segment's axis, original index).
-// kSelect: count the digit of the keys inside the prefix found so far; the
-// workgroup that finishes the segment picks the bin holding rank krem and
-// clears the counts.  If that bin holds a single key, the next pass (kFind)
-// only reads it whole.  keys: as for k_orb_bbox; cur: original index per
-// position.  The first pass also sets up the states of the next level
-// (st_next), which the partition fills in.
+// One round of every segment's selection: counts the window's keys by bin; the
+// workgroup that finishes the segment finds the bin with rank krem, makes it
+// the window and clears the counts.  keys: as for k_orb_bbox; cur: original
+// index per position.  The first round also sets up the states of the next
+// level (st_next), which the partition fills in.
 __global__ __launch_bounds__(kPassBlock) void k_orb_hist(const int3 *__restrict__ chunks,
                                                         const int3 *__restrict__ segs,
                                                         const uint32_t *__restrict__ keys, int n,
@@ -357,55 +365,36 @@ __global__ __launch_bounds__(kPassBlock) void k_orb_hist(const int3 *__restrict_
         for (int s = blockIdx.x; s < nseg_next; s += gridDim.x) init_state(&st_next[s], segs_next[s].z);
     const int3 c = chunks[blockIdx.x];
     // the state was written by earlier launches only
-    const int mode = st[c.x].mode;
-    if (mode == kDone) return;  // the whole segment returns: nobody arrives
-    const uint64_t prefix = st[c.x].prefix;
-    const int shift = digit_shift(round), pshift = prefix_shift(round);
-    const uint32_t dmask = (1u << (pshift - shift)) - 1u;
-    const uint32_t *ka = keys + (size_t)seg_axis(&st[c.x]) * n;
-    // the index (low 32 bits) matters once the digit reaches below bit 32, and
-    // to read the key whole
-    const bool need_idx = shift < 32 || mode == kFind;
+    if (st[c.x].pick) return;  // the whole segment returns: nobody arrives
+    const int axis = seg_axis(&st[c.x]);
+    const uint32_t *ka = keys + (size_t)axis * n;
+    Window win = st[c.x].win;
+    if (round == 0) {
+        const uint32_t lo = st[c.x].bb[axis], range = st[c.x].bb[3 + axis] - lo;
+        win.from = (uint64_t)lo << 32;
+        win.bits = 64 - __clz((int)(range | 1u));
+    }
+    // the index matters once the bins are narrower than a coordinate
+    const bool need_idx = win.shift() < 32;
     // positions past the chunk's end read its last element (no branch around
     // the loads, so they are all in flight together) and are masked below
     uint64_t key[kPassPer];
+#pragma unroll
+    for (int u = 0; u < kPassPer; ++u) {
+        const int p = min(c.y + u * kPassBlock + (int)threadIdx.x, c.z - 1);
+        key[u] = (uint64_t)ka[p] << 32;
+    }
     if (need_idx) {
 #pragma unroll
-        for (int u = 0; u < kPassPer; ++u) {
-            const int p = min(c.y + u * kPassBlock + (int)threadIdx.x, c.z - 1);
-            key[u] = ((uint64_t)ka[p] << 32) | (uint32_t)cur[p];
-        }
-    } else {
-#pragma unroll
-        for (int u = 0; u < kPassPer; ++u) {
-            const int p = min(c.y + u * kPassBlock + (int)threadIdx.x, c.z - 1);
-            key[u] = (uint64_t)ka[p] << 32;
-        }
-    }
-    // (round 0 has no prefix: a shift by 64 is not defined, so test it apart)
-    if (mode == kFind) {
-#pragma unroll
-        for (int u = 0; u < kPassPer; ++u) {
-            const int p = c.y + u * kPassBlock + threadIdx.x;
-            if (p < c.z && (round == 0 || (key[u] >> pshift) == prefix))
-                performed(__hip_atomic_exchange(&st[c.x].full, key[u], __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT));
-        }
-        if (!last_of_segment(st, c.x, segs, &last)) return;
-        if (threadIdx.x == 0) {
-            st[c.x].prefix = load_dev(&st[c.x].full);
-            st[c.x].mode = kDone;
-            store_dev(&st[c.x].arrived, 0u);
-        }
-        return;
+        for (int u = 0; u < kPassPer; ++u)
+            key[u] |= (uint32_t)cur[min(c.y + u * kPassBlock + (int)threadIdx.x, c.z - 1)];
     }
     if (threadIdx.x < kBins) h[threadIdx.x] = 0u;
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < kPassPer; ++u) {
         const int p = c.y + u * kPassBlock + threadIdx.x;
-        if (p < c.z && (round == 0 || (key[u] >> pshift) == prefix))
-            atomicAdd(&h[(uint32_t)(key[u] >> shift) & dmask], 1u);
+        if (p < c.z && win.holds(key[u])) atomicAdd(&h[win.bin(key[u])], 1u);
     }
     __syncthreads();
     uint32_t *hs = hist + (size_t)c.x * kBins;
@@ -422,93 +411,126 @@ __global__ __launch_bounds__(kPassBlock) void k_orb_hist(const int3 *__restrict_
     }
     const uint32_t inc = block_incl_scan_u32(cnt, red);
     const uint32_t krem = (uint32_t)st[c.x].krem;
+    __syncthreads();  // (read before the one thread below writes it)
     if (inc >= krem && inc - cnt < krem) {
-        st[c.x].prefix = (round == 0 ? 0ull : prefix << (pshift - shift)) | (uint64_t)threadIdx.x;
+        st[c.x].win = win.of_bin((int)threadIdx.x);
         st[c.x].krem = (int)(krem - (inc - cnt));
-        st[c.x].mode = (cnt == 1u && round < kCoordRounds - 1) ? kFind : kSelect;
+        st[c.x].pick = cnt <= (uint32_t)kPick;
     }
     if (threadIdx.x == 0) store_dev(&st[c.x].arrived, 0u);
 }
 
-// After the coordinate rounds: the k-th key's coordinate c is known, and its
-// rank krem among the bodies with coordinate c.  Their original indices are
-// gathered into cand (at the segment's own positions), and the workgroup that
-// finishes the segment selects the krem-th smallest of them (radix select
-// over the 32-bit index; a single body needs none).
-__global__ __launch_bounds__(kPassBlock) void k_orb_ties(const int3 *__restrict__ chunks,
+// After the rounds: the window's bodies (their keys) are gathered into cand, at the segment's own places, and the workgroup that finishes the
+// segment finds the k-th key among theirs: by rank, after further rounds of
+// its own where they are more than kPick (equal coordinates, mostly).
+__global__ __launch_bounds__(kPassBlock) void k_orb_pick(const int3 *__restrict__ chunks,
                                                         const int3 *__restrict__ segs,
                                                         const uint32_t *__restrict__ keys, int n,
                                                         const int32_t *__restrict__ cur,
                                                         SegState *__restrict__ st,
-                                                        uint32_t *__restrict__ cand)
+                                                        uint64_t *__restrict__ cand)
 {
-    __shared__ uint32_t h[256];
+    __shared__ uint32_t h[kPickBins];
     __shared__ uint32_t red[kPassBlock / 64];
-    __shared__ uint32_t sel_s, krem_s;
+    __shared__ uint64_t few[kPick];
+    __shared__ uint32_t nfew, bin_s, krem_s, count_s;
     __shared__ int last;
     const int3 c = chunks[blockIdx.x];
-    if (st[c.x].mode == kDone) return;  // the whole segment returns: nobody arrives
-    const uint32_t coord = (uint32_t)st[c.x].prefix;  // the prefix is the coordinate key here
     const int3 sg = segs[c.x];
+    const Window win = st[c.x].win;
     const uint32_t *ka = keys + (size_t)seg_axis(&st[c.x]) * n;
-    const int lane = threadIdx.x & 63;
     uint32_t kv[kPassPer];
 #pragma unroll
     for (int u = 0; u < kPassPer; ++u) kv[u] = ka[min(c.y + u * kPassBlock + (int)threadIdx.x, c.z - 1)];
+    // a body whose coordinate the window reaches; its index decides only where
+    // the window is narrower than a coordinate
+    uint32_t hits = 0;
 #pragma unroll
     for (int u = 0; u < kPassPer; ++u) {
         const int p = c.y + u * kPassBlock + threadIdx.x;
-        const bool hit = p < c.z && kv[u] == coord;
-        const uint64_t mk = __ballot(hit);
-        if (!mk) continue;
-        // one slot run per wave and step
-        uint32_t base = 0;
-        if (lane == __ffsll((long long)mk) - 1) base = atomicAdd(&st[c.x].ties, (uint32_t)__popcll(mk));
-        base = (uint32_t)__shfl((int)base, __ffsll((long long)mk) - 1);
-        if (hit) {
-            const uint32_t q = base + (uint32_t)__popcll(mk & ((1ull << lane) - 1ull));
-            if (q < (uint32_t)sg.y)
-                performed(__hip_atomic_exchange(&cand[sg.x + q], (uint32_t)cur[p], __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT));
-        }
+        bool hit = p < c.z && kv[u] >= (uint32_t)(win.from >> 32) &&
+                   (win.bits >= 32 ? win.holds((uint64_t)kv[u] << 32) : kv[u] == (uint32_t)(win.from >> 32));
+        if (hit && win.bits < 32) hit = win.holds(body_key(kv[u], cur[p]));
+        hits |= hit ? 1u << u : 0u;
+    }
+    // one run of slots per workgroup, and one wait for all of a thread's entries
+    const uint32_t mine = (uint32_t)__popc(hits), upto = block_incl_scan_u32(mine, red);
+    if (threadIdx.x == kPassBlock - 1) bin_s = upto ? atomicAdd(&st[c.x].picked, upto) : 0u;
+    __syncthreads();
+    if (hits) {
+        uint32_t q = bin_s + upto - mine;
+        unsigned long long was = 0;
+#pragma unroll
+        for (int u = 0; u < kPassPer; ++u)
+            if (hits >> u & 1u) {
+                if (q < (uint32_t)sg.y)
+                    was |= __hip_atomic_exchange((unsigned long long *)&cand[sg.x + q],
+                                                 body_key(kv[u], cur[c.y + u * kPassBlock + threadIdx.x]),
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                ++q;
+            }
+        performed(was);
     }
     if (!last_of_segment(st, c.x, segs, &last)) return;
-    const uint32_t T = min(load_dev(&st[c.x].ties), (uint32_t)sg.y);
-    const uint32_t *cs = cand + sg.x;
-    uint32_t sel = 0;
-    if (T == 1u) {
-        sel = load_dev(&cs[0]);
-    } else {
-        if (threadIdx.x == 0) {
-            sel_s = 0u;
-            krem_s = (uint32_t)st[c.x].krem;
+    const uint32_t T = min(load_dev(&st[c.x].picked), (uint32_t)sg.y);
+    uint64_t from = win.from;
+    int bits = win.bits;  // (below 64 after a round)
+    // every candidate in the window, several loads in flight
+    auto each = [&](auto &&use) {
+        constexpr int kAhead = 8;
+        for (uint32_t i0 = threadIdx.x; i0 < T; i0 += kAhead * kPassBlock) {
+            uint64_t k[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) k[u] = load_dev(&cand[sg.x + min(i0 + u * kPassBlock, T - 1)]);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+                if (i0 + u * kPassBlock < T && ((k[u] - from) >> bits) == 0) use(k[u]);
         }
-        for (int round = 0; round < 4; ++round) {
-            __syncthreads();
-            if (threadIdx.x < 256) h[threadIdx.x] = 0u;
-            const uint32_t prefix = sel_s, kr = krem_s;
-            const int shift = 24 - 8 * round;
-            __syncthreads();
-            for (uint32_t i = threadIdx.x; i < T; i += kPassBlock) {
-                const uint32_t v = load_dev(&cs[i]);
-                if (round == 0 || (v >> (shift + 8)) == prefix) atomicAdd(&h[(v >> shift) & 0xFFu], 1u);
-            }
-            __syncthreads();
-            const uint32_t hv = threadIdx.x < 256 ? h[threadIdx.x] : 0u;
-            const uint32_t inc = block_incl_scan_u32(hv, red);
-            if (inc >= kr && inc - hv < kr) {
-                sel_s = (prefix << 8) | (uint32_t)threadIdx.x;
-                krem_s = kr - (inc - hv);
-            }
+    };
+    uint32_t krem = (uint32_t)st[c.x].krem, count = T;
+    while (count > (uint32_t)kPick && bits > 0) {
+        const int sh = max(bits - kPickDigit, 0);
+        h[threadIdx.x] = 0u;
+        h[threadIdx.x + kPassBlock] = 0u;
+        if (threadIdx.x == 0) {
+            bin_s = 0u;
+            krem_s = krem;
+            count_s = 0u;
         }
         __syncthreads();
-        sel = sel_s;
+        each([&](uint64_t k) { atomicAdd(&h[(k - from) >> sh], 1u); });
+        __syncthreads();
+        const uint32_t c0 = h[2 * threadIdx.x], c1 = h[2 * threadIdx.x + 1];
+        const uint32_t to = block_incl_scan_u32(c0 + c1, red), before = to - c0 - c1;
+        if (before < krem && to >= krem) {
+            const bool second = before + c0 < krem;
+            bin_s = 2 * threadIdx.x + second;
+            krem_s = krem - before - (second ? c0 : 0u);
+            count_s = second ? c1 : c0;
+        }
+        __syncthreads();
+        from += (uint64_t)bin_s << sh;
+        bits = sh;
+        krem = krem_s;
+        count = count_s;
+        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        st[c.x].prefix = ((uint64_t)coord << 32) | sel;
-        st[c.x].mode = kDone;
-        store_dev(&st[c.x].arrived, 0u);
+    if (threadIdx.x == 0) nfew = 0u;
+    __syncthreads();
+    each([&](uint64_t k) {
+        const uint32_t q = atomicAdd(&nfew, 1u);
+        if (q < (uint32_t)kPick) few[q] = k;
+    });
+    __syncthreads();
+    const uint32_t m = min(nfew, (uint32_t)kPick);
+    if (threadIdx.x < m) {
+        const uint64_t mine = few[threadIdx.x];
+        uint32_t r = 1;
+#pragma unroll 8
+        for (uint32_t f = 0; f < m; ++f) r += few[f] < mine;
+        if (r == krem) st[c.x].kth = mine;
     }
+    if (threadIdx.x == 0) store_dev(&st[c.x].arrived, 0u);
 }
 
 // Keys <= the k-th key go left.  Each workgroup takes one run of slots per
@@ -533,7 +555,7 @@ __global__ __launch_bounds__(kPassBlock) void k_orb_partition(const int3 *__rest
     __shared__ uint32_t box[kW][12];
     __shared__ uint32_t tot[12];
     const int3 c = chunks[blockIdx.x];
-    const uint64_t kth = st[c.x].prefix;
+    const uint64_t kth = st[c.x].kth;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const uint64_t below = (1ull << lane) - 1ull;
     // all of the thread's loads together, ahead of the split axis
@@ -907,8 +929,6 @@ __device__ __forceinline__ int fin_split(int m, int leaf)
     const int unit = m <= leaf ? kWaveSeg : leaf;
     return min(m, unit * (((m + unit - 1) / unit + 1) / 2));
 }
-
-__device__ __forceinline__ uint64_t body_key(uint32_t key, int32_t id) { return ((uint64_t)key << 32) | (uint32_t)id; }
 
 // Phase B.  segs: (start, size, which buffer pair holds it).  keys0/1: the
 // three axes' keys in the order of cur0/1 (axis a at a * n).
@@ -1328,8 +1348,8 @@ int orb_order(const void *pm, int prec, int n, int leaf, int32_t *perm, hipStrea
     const size_t foff = put(finals.data(), finals.size() * sizeof(int3));
     const size_t nbytes = (size_t)n * 4;
     // two buffers of the three axes' keys in the current order (each level
-    // reads one and writes the other), then the tie pass's candidates
-    uint32_t *kmem = (uint32_t *)scratch(kSlotOrb0, 7 * nbytes);
+    // reads one and writes the other), then the pick pass's candidates
+    uint32_t *kmem = (uint32_t *)scratch(kSlotOrb0, 8 * nbytes);
     // original index per position, same two-buffer scheme as the keys
     int32_t *cbuf[2] = {(int32_t *)scratch(kSlotOrb1, nbytes), (int32_t *)scratch(kSlotOrb2, nbytes)};
     char *dtab = (char *)scratch(kSlotOrb3, tab.size() + 16);
@@ -1342,7 +1362,7 @@ int orb_order(const void *pm, int prec, int n, int leaf, int32_t *perm, hipStrea
         return NBODY_E_NOMEM;
     }
     uint32_t *kbuf[2] = {kmem, kmem + 3 * (size_t)n};
-    uint32_t *cand = kmem + 6 * (size_t)n;  // tied bodies' indices (k_orb_ties)
+    uint64_t *cand = (uint64_t *)(kmem + 6 * (size_t)n);  // the keys of a window's bodies (k_orb_pick)
     SegState *st[2] = {(SegState *)state, (SegState *)(state + stbytes)};
     uint32_t *hist = (uint32_t *)(state + 2 * stbytes);
     {
@@ -1402,10 +1422,13 @@ int orb_order(const void *pm, int prec, int n, int leaf, int32_t *perm, hipStrea
             hipLaunchKernelGGL(k_orb_init, dim3((unsigned)maxseg), dim3(kOrbBlock), 0, s, segs, nseg, st[i], hist);
             hipLaunchKernelGGL(k_orb_bbox, dim3(nch), dim3(kOrbBlock), 0, s, chunks, kbuf[i], n, st[i]);
         }
-        for (int r = 0; r < kCoordRounds; ++r)
+        int longest = 0;
+        for (const int3 &sg : levels[l].segs) longest = std::max(longest, sg.y);
+        const int rounds = longest > kLongSegment ? kRounds : kShortRounds;
+        for (int r = 0; r < rounds; ++r)
             hipLaunchKernelGGL(k_orb_hist, dim3(nch), dim3(kPassBlock), 0, s, chunks, segs, kbuf[i], n, cbuf[i],
                                st[i], hist, r, segs_next, nseg_next, st[o]);
-        hipLaunchKernelGGL(k_orb_ties, dim3(nch), dim3(kPassBlock), 0, s, chunks, segs, kbuf[i], n, cbuf[i], st[i],
+        hipLaunchKernelGGL(k_orb_pick, dim3(nch), dim3(kPassBlock), 0, s, chunks, segs, kbuf[i], n, cbuf[i], st[i],
                            cand);
         hipLaunchKernelGGL(k_orb_partition, dim3(nch), dim3(kPassBlock), 0, s, chunks, segs, kids, kbuf[i], kbuf[o],
                            n, cbuf[i], cbuf[o], st[i], st[o]);

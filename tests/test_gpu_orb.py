@@ -47,6 +47,36 @@ def test_orb_bitexact_segment_edges(orc, leaf):
             assert np.array_equal(got, want), (n, coarse)
 
 
+@pytest.mark.parametrize("kind", ["grid", "cluster", "plane", "equal", "wide"])
+@pytest.mark.parametrize("n", [70001, 140001])
+def test_orb_bitexact_selection_windows(orc, kind, n):
+    """Where the windows of the multi-workgroup selection do not close on a few
+    keys: few distinct coordinates, a cluster that fills a small part of the
+    box's range, one constant axis, all bodies at one point, and coordinates
+    over the FP32 range; below and above the segment size that takes a round
+    more."""
+    torch, nb = gpu()
+    g = ics.rng(2300 + n)
+    pos = np.zeros((n, 4))
+    x = g.normal(size=(n, 3))
+    if kind == "grid":
+        x = np.floor(4 * x)
+    elif kind == "cluster":
+        x = 1000.0 + 1e-3 * x
+        x[:5] = [[-1e6, 0, 0], [1e6, 1, 0], [0, -1e6, 0], [0, 1e6, 0], [0, 0, 1e6]]
+    elif kind == "plane":
+        x[:, 0] = 0.0
+        x[:, 1] = np.round(x[:, 1], 2)
+    elif kind == "equal":
+        x[:] = 0.25
+    else:
+        x = x * 10.0 ** g.uniform(-30, 30, size=(n, 1))
+    pos[:, :3] = x
+    p32 = pos.astype(np.float32)
+    want = orc.orb_order(p32.astype(np.float64), 8)
+    assert np.array_equal(_gpu_perm(torch, nb, p32, 8, torch.float32), want)
+
+
 def test_orb_f64_input_rounds_to_f32(orc):
     torch, nb = gpu()
     pm, _ = ics.uniform_ball(9000, 210)
