@@ -315,6 +315,16 @@ static Tune default_tune(int kernel, int prec, int64_t n, int64_t ntarg, int64_t
     const int64_t waves = (ntarg + 63) / 64;
     int js = 1;
     while (js < 32 && waves * js < 65536 && n / (js * 2) >= min_sources) js *= 2;
+    // A share of the targets (at most half) leaves the chip part empty with 32
+    // splits: up to 256 while there are fewer than four rounds of waves and the
+    // records fit the 64 MiB that nbody_accel_noalloc has (so that both calls run
+    // the same shape).  25003 of 200000: 1318 us with 32, 1240 with 64; 3000 of
+    // 100001: 140 with 32, 100 with 128; 6251 of 400000: 952 with 32, 648 with 256.
+    // All targets gain nothing (16384: 82.1 with 32, 85.0 with 64).
+    if (kernel == 0 && js == 32 && 2 * ntarg <= n)
+        while (js < 256 && waves * js < 32768 && n / (js * 2) >= min_sources &&
+               ntarg * js * 2 * (int64_t)sizeof(double4) <= (int64_t)kStaticScratchBytes)
+            js *= 2;
     // A multiple of 8 splits gives each XCD its own source segments, read
     // from its own L2 (the force kernels' workgroup mapping).  At 2^20
     // sources, 8 splits of 2 MiB fit that 4 MiB cache: the bytes fetched past

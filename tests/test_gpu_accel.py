@@ -358,6 +358,36 @@ def test_small_problem_kernel_edges(orc, mode, n, tb, tc):
     assert rms_rel(out[k, :3], acc) <= bar and rms_rel(out[k, 3], pot) <= bar
 
 
+@pytest.mark.parametrize("n,tb,tc", [(16385, 16000, 385), (30001, 29501, 500), (65536, 1, 64), (100001, 40000, 12000),
+                                     (120000, 0, 60000), (120000, 0, 60001), (400000, 393749, 6251)])
+@pytest.mark.parametrize("mode", ["F32_KAHAN", "F32", "F64"])
+def test_share_of_the_targets(orc, mode, n, tb, tc):
+    """A share of the targets takes more source splits the smaller it is: up to
+    256, with up to half of the targets, while the records fit the scratch of
+    the call that allocates nothing, which gives the same bits."""
+    import ctypes
+    torch, nb = gpu()
+    dt = torch.float64 if mode == "F64" else torch.float32
+    prec = getattr(nb, mode)
+    pm, _ = ics.plummer(n, 5100 + n % 997)
+    src = pm if mode == "F64" else widen32(pm)
+    p = to_dev(torch, src, dt)
+    outs = []
+    for call in (nb.lib().nbody_accel, nb.lib().nbody_accel_noalloc):
+        out = torch.full((tc, 4), float("nan"), dtype=dt, device=p.device)
+        rc = call(ctypes.c_void_p(p.data_ptr()), n, prec, 1.0, 0.01, ctypes.c_void_p(out.data_ptr()), tb, tc,
+                  ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(*outs)
+    k = ics.sample_targets(tc, min(tc, 300), n)
+    acc, pot = orc.accel(src, 0.01, targets=tb + k)
+    got = outs[0].cpu().numpy().astype(np.float64)[k]
+    bar = {"F64": 1e-12, "F32": 1e-4, "F32_KAHAN": 2e-6}[mode]
+    assert rms_rel(got[:, :3], acc) <= bar and rms_rel(got[:, 3], pot) <= bar
+
+
 # 44 blocks of 512 is the smallest count the pairwise kernels take: full, one
 # body in the last block, one short of full, an odd count; the same around the
 # first size with blocks of 1024; and a size whose sums take two launches (the
