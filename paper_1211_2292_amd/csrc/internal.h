@@ -187,6 +187,13 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 //   close: v += h a          (closing kick of the previous step)
 //   energy partials of (v, phi) after the closing kick, if epart != nullptr
 //   open:  v += h a; x += dt v  (opening kick and drift of the next step)
+// The small-problem force of all bodies fused with the step: acc receives the
+// force, then the kick and drift; the positions go to `to` (drifted or, without
+// a drift, copied; null: nowhere).  epart: two sums per workgroup, slice_blocks(n).
+constexpr int kEnergyRow = 16;  // bodies of a workgroup of it
+int slice_blocks(int n);
+hipError_t launch_slice_step(int prec, const void *pm, int n, double G, double eps, void *acc, void *vel, void *to,
+                             double h, double dt, bool close, bool open, double *epart, hipStream_t s);
 hipError_t launch_step(int prec, void *pm, void *vel, const void *acc, int n, double h, double dt,
                        bool close, bool open, double *epart, int *eblocks, hipStream_t s);
 int step_blocks(int n);
@@ -197,7 +204,8 @@ hipError_t launch_reduce_step(int prec, RecordKind kind, const void *partial, in
                               void *acc, int n, double h, double dt, bool close, bool open,
                               double *epart, int *eblocks, hipStream_t s);
 // Energies of `states` states whose partials follow one another, nblocks each.
-hipError_t launch_energy_final(const double *epart, int nblocks, int states, double *out, hipStream_t s);
+// parts: sums per state, of a step kernel's workgroups or (rows) of kEnergyRow bodies each.
+hipError_t launch_energy_final(const double *epart, int parts, bool rows, int states, double *out, hipStream_t s);
 hipError_t launch_permute(const void *src, void *dst, const int32_t *perm, int n, int rec_bytes,
                           bool inverse, hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes, hipStream_t s);

@@ -145,5 +145,34 @@ __device__ __forceinline__ void put_f32(float4 *out, long k, const double (&r)[4
     out[k] = make_float4(G * (float)r[0], G * (float)r[1], G * (float)r[2], -G * (float)r[3]);
 }
 
+// ---- leapfrog step of one body -----------------------------------------------------
+// close: v += h a;  energies (1/2 m |v|^2, 1/2 m phi) in FP64;
+// open: v += h a; x += dt v.
+template <typename V, typename S>
+__device__ __forceinline__ void step_body(V &x, V &vel, const V a, S h, S dt, int close, int open, bool energy,
+                                          double &ek, double &eu)
+{
+    V v = vel;
+    if (close) {
+        v.x = v.x + h * a.x;
+        v.y = v.y + h * a.y;
+        v.z = v.z + h * a.z;
+    }
+    if (energy) {
+        const double vx = v.x, vy = v.y, vz = v.z, m = x.w;
+        ek = 0.5 * m * ((vx * vx + vy * vy) + vz * vz);
+        eu = 0.5 * m * (double)a.w;
+    }
+    if (open) {
+        v.x = v.x + h * a.x;
+        v.y = v.y + h * a.y;
+        v.z = v.z + h * a.z;
+        x.x = x.x + dt * v.x;
+        x.y = x.y + dt * v.y;
+        x.z = x.z + dt * v.z;
+    }
+    if (close || open) vel = v;
+}
+
 }  // namespace
 }  // namespace nbi

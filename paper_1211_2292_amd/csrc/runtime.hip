@@ -489,15 +489,24 @@ static int batched_force(int prec, const void *pm, const BatchPlan &p, double G,
 // ---------------------------------------------------------------------------
 struct StepBuffers {
     double *epart = nullptr;  // energy block partials of kEnergySteps states
-    void *partial = nullptr;  // split scratch of the force kernel
+    void *partial = nullptr;  // split scratch of the force kernel (fused small problems: the second positions)
     bool sweep = false;       // partial holds the sweep's records only
 };
 
 // States whose energy partials wait for one final launch (a launch per step
 // took 3.5 of 24 us at 4096 FP64 bodies).
 constexpr int kEnergySteps = 64;
-static size_t energy_bytes(int nb, int nsteps)
+// Small problems whose step follows the force in its launch, with the positions
+// in two buffers.  Fewer bodies than this run the two launches, which need no
+// scratch of the library's.
+constexpr int kFusedMin = 512;
+static bool step_fused(const Tune &t, const BatchPlan *plan, int64_t n)
 {
+    return !plan && t.path == kPathSlice && n >= kFusedMin;
+}
+static size_t energy_bytes(int n, int nsteps)
+{
+    const int nb = std::max(step_blocks(n), slice_blocks(n));
     return sizeof(double) * 2 * (size_t)nb * (size_t)std::min(kEnergySteps, nsteps + 1);
 }
 
@@ -509,14 +518,21 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
     Tune bt = lookup_tune(1, prec, n);
     double *ep = energy ? buf.epart : nullptr;
     int eb = 0;
+    bool eb_rows = false;  // eb counts rows (fused steps)
     int waiting = 0;  // states whose partials are in buf.epart, the last one state `seen` - 1
     int seen = 0;
+    // the positions as they are: in pm, or in the second buffer of fused steps
+    void *x = pm, *other = nullptr;
+    {
+        const Tune t = lookup_tune(0, prec, n);
+        if (step_fused(t, plan, n)) other = buf.partial ? buf.partial : scratch(kSlotPartial, rec_bytes(prec) * n);
+    }
     auto energies = [&](bool last) -> int {
         if (!energy) return NBODY_OK;
         ++waiting;
         ++seen;
         if (waiting == kEnergySteps || last) {
-            NB_TRY(launch_energy_final(buf.epart, eb, waiting, energy + 2 * (seen - waiting), s), "energy kernel");
+            NB_TRY(launch_energy_final(buf.epart, eb, eb_rows, waiting, energy + 2 * (seen - waiting), s), "energy kernel");
             waiting = 0;
         }
         ep = buf.epart + 2 * (size_t)eb * waiting;
@@ -526,6 +542,14 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
     // A direct force with a source split leaves its per-split records in
     // scratch and the step pass reduces them itself (one launch fewer).
     auto eval_step = [&](bool step, bool close, bool open) -> int {
+        if (other && step) {
+            void *const to = open ? (x == pm ? other : pm) : (x == pm ? nullptr : pm);
+            NB_TRY(launch_slice_step(prec, x, n, G, eps, acc, vel, to, h, dt, close, open, ep, s), "force + step kernel");
+            eb = slice_blocks(n);
+            eb_rows = true;
+            if (to) x = to;
+            return NBODY_OK;
+        }
         if (!plan) {
             Tune t = lookup_tune(0, prec, n);
             if (buf.sweep) t.path = kPathSweep;
@@ -546,6 +570,7 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
         return NBODY_OK;
     };
     auto step_only = [&](bool close, bool open) -> int {
+        eb_rows = false;
         NB_TRY(launch_step(prec, pm, vel, acc, n, h, dt, close, open, ep, &eb, s), "step kernel");
         return NBODY_OK;
     };
@@ -558,7 +583,8 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
     }
     if (!have_acc) NB_CHECK(eval_step(true, false, true));
     else NB_CHECK(step_only(false, true));
-    NB_CHECK(energies(false));
+    // (a first state from the step kernel alone has other blocks than fused ones)
+    NB_CHECK(energies(have_acc && other));
     for (int k = 0; k < nsteps; ++k) {
         const bool last = (k == nsteps - 1);
         NB_CHECK(eval_step(true, true, !last));
@@ -804,7 +830,7 @@ int nbody_energy(const void *pos_mass, const void *vel, const void *acc_pot, int
     NB_TRY(launch_step(prec, const_cast<void *>(pos_mass), const_cast<void *>(vel), acc_pot, (int)n,
                        0.0, 0.0, false, false, ep, nullptr, s),
            "energy kernel");
-    NB_TRY(launch_energy_final(ep, nb, 1, energy_out, s), "energy kernel");
+    NB_TRY(launch_energy_final(ep, nb, false, 1, energy_out, s), "energy kernel");
     return NBODY_OK;
 }
 
@@ -847,11 +873,10 @@ int nbody_leapfrog_kdk(void *pos_mass, void *vel, void *acc_pot, int64_t n,
     }
     hipStream_t s = (hipStream_t)stream;
     double *en = want_energy ? energy_out : nullptr;
-    const int nb = step_blocks((int)n);
     if (!(flags & NBODY_GRAPH)) {
         StepBuffers buf;
         if (en) {
-            buf.epart = (double *)scratch(kSlotEnergy, energy_bytes(nb, nsteps));
+            buf.epart = (double *)scratch(kSlotEnergy, energy_bytes((int)n, nsteps));
             if (!buf.epart) {
                 set_error("cannot allocate energy scratch");
                 return NBODY_E_NOMEM;
@@ -896,6 +921,7 @@ int nbody_leapfrog_kdk(void *pos_mass, void *vel, void *acc_pot, int64_t n,
         } undo{e};
         Tune t = lookup_tune(0, prec, n);
         size_t pb = plan ? 0 : accel_partial_bytes(prec, (int)n, t);
+        if (step_fused(t, plan, n)) pb = rec_bytes(prec) * (size_t)n;
         StepBuffers buf;
         if (pb && t.path == kPathSym && hipMalloc(&e.partial, pb) != hipSuccess) {
             (void)hipGetLastError();
@@ -905,7 +931,7 @@ int nbody_leapfrog_kdk(void *pos_mass, void *vel, void *acc_pot, int64_t n,
             pb = accel_partial_bytes(prec, (int)n, t);
         }
         if (pb && !e.partial) NB_TRY(hipMalloc(&e.partial, pb), "graph scratch");
-        if (en) NB_TRY(hipMalloc((void **)&e.epart, energy_bytes(nb, nsteps)), "graph scratch");
+        if (en) NB_TRY(hipMalloc((void **)&e.epart, energy_bytes((int)n, nsteps)), "graph scratch");
         hipStream_t cs;
         {
             std::lock_guard<std::mutex> lk(g_mu);

@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "pair.h"
 
 namespace nbi {
 namespace {
@@ -22,10 +23,21 @@ __device__ __forceinline__ void block_sum2(double &a, double &b, int slot, bool 
         sb[slot] = b;
     }
     __syncthreads();
-    for (int w = kBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-            sa[threadIdx.x] += sa[threadIdx.x + w];
-            sb[threadIdx.x] += sb[threadIdx.x + w];
+    // rows of kEnergyRow first, then the rows: the fused small-problem step
+    // leaves its rows' sums, and both give the same bits
+    const int t = threadIdx.x, row = t % kEnergyRow;
+#pragma unroll
+    for (int w = kEnergyRow / 2; w > 0; w >>= 1) {
+        if (t < kBlock && row < w) {
+            sa[t] += sa[t + w];
+            sb[t] += sb[t + w];
+        }
+        __syncthreads();
+    }
+    for (int w = kBlock / 2; w >= kEnergyRow; w >>= 1) {
+        if (t < w && row == 0) {
+            sa[t] += sa[t + w];
+            sb[t] += sb[t + w];
         }
         __syncthreads();
     }
@@ -33,35 +45,14 @@ __device__ __forceinline__ void block_sum2(double &a, double &b, int slot, bool 
     b = sb[0];
 }
 
-// close: v += h a;  energy partials (1/2 m |v|^2, 1/2 m phi) in FP64;
-// open: v += h a; x += dt v.
 template <typename V, typename S>
 __device__ __forceinline__ void step_one(V *__restrict__ pm, V *__restrict__ vel, int i, const V a,
                                          S h, S dt, int close, int open, bool energy, double &ek,
                                          double &eu)
 {
     V x = pm[i];
-    V v = vel[i];
-    if (close) {
-        v.x = v.x + h * a.x;
-        v.y = v.y + h * a.y;
-        v.z = v.z + h * a.z;
-    }
-    if (energy) {
-        const double vx = v.x, vy = v.y, vz = v.z, m = x.w;
-        ek = 0.5 * m * ((vx * vx + vy * vy) + vz * vz);
-        eu = 0.5 * m * (double)a.w;
-    }
-    if (open) {
-        v.x = v.x + h * a.x;
-        v.y = v.y + h * a.y;
-        v.z = v.z + h * a.z;
-        x.x = x.x + dt * v.x;
-        x.y = x.y + dt * v.y;
-        x.z = x.z + dt * v.z;
-        pm[i] = x;
-    }
-    if (close || open) vel[i] = v;
+    step_body(x, vel[i], a, h, dt, close, open, energy, ek, eu);
+    if (open) pm[i] = x;
 }
 
 template <typename V, typename S>
@@ -122,16 +113,34 @@ __global__ __launch_bounds__(kReduceThreads) void k_reduce_step(const P *__restr
 }
 
 // One workgroup per state: each lane sums a strided subset of the block
-// partials in order, then a fixed-order tree.
+// partials in order, then a fixed-order tree.  With ROWS a state's `parts` are
+// row sums, of which a block has kBlock / kEnergyRow.
+template <bool ROWS>
 __global__ __launch_bounds__(kBlock) void k_energy_final(const double *__restrict__ epart,
-                                                         int nblocks, double *__restrict__ out)
+                                                         int parts, double *__restrict__ out)
 {
     double a = 0.0, b = 0.0;
-    epart += 2 * (size_t)nblocks * blockIdx.x;
+    epart += 2 * (size_t)parts * blockIdx.x;
     out += 2 * blockIdx.x;
-    for (int k = threadIdx.x; k < nblocks; k += kBlock) {
-        a += epart[2 * k];
-        b += epart[2 * k + 1];
+    constexpr int R = ROWS ? kBlock / kEnergyRow : 1;
+    for (int k = threadIdx.x; k * R < parts; k += kBlock) {
+        double x[R], y[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const int p = k * R + j;
+            x[j] = p < parts ? epart[2 * p] : 0.0;
+            y[j] = p < parts ? epart[2 * p + 1] : 0.0;
+        }
+#pragma unroll
+        for (int w = R / 2; w > 0; w >>= 1)
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                if (j < w) {
+                    x[j] += x[j + w];
+                    y[j] += y[j + w];
+                }
+        a += x[0];
+        b += y[0];
     }
     block_sum2(a, b, threadIdx.x, true);
     if (threadIdx.x == 0) {
@@ -226,9 +235,12 @@ hipError_t launch_reduce_step(int prec, RecordKind kind, const void *partial, in
     return hipGetLastError();
 }
 
-hipError_t launch_energy_final(const double *epart, int nblocks, int states, double *out, hipStream_t s)
+hipError_t launch_energy_final(const double *epart, int parts, bool rows, int states, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_energy_final, dim3(states), dim3(kBlock), 0, s, epart, nblocks, out);
+    if (rows)
+        hipLaunchKernelGGL(k_energy_final<true>, dim3(states), dim3(kBlock), 0, s, epart, parts, out);
+    else
+        hipLaunchKernelGGL(k_energy_final<false>, dim3(states), dim3(kBlock), 0, s, epart, parts, out);
     return hipGetLastError();
 }
 

@@ -1539,7 +1539,7 @@ int tree_leapfrog(void *pm, void *vel, void *acc, int32_t *order, int n, int pre
         if (rc != NBODY_OK) return rc;
     }
     hipError_t e = launch_step(prec, pm, vel, acc, n, h, dt, false, nsteps > 0, ep, &eb, s);
-    if (e == hipSuccess && energy) e = launch_energy_final(ep, eb, 1, energy, s);
+    if (e == hipSuccess && energy) e = launch_energy_final(ep, eb, false, 1, energy, s);
     if (e != hipSuccess) return hip_fail(e, "tree leapfrog step");
     for (int k = 0; k < nsteps; ++k) {
         if (reorder_every > 0 && (k + 1) % reorder_every == 0) {
@@ -1550,7 +1550,7 @@ int tree_leapfrog(void *pm, void *vel, void *acc, int32_t *order, int n, int pre
         if (rc != NBODY_OK) return rc;
         const bool last = (k == nsteps - 1);
         e = launch_step(prec, pm, vel, acc, n, h, dt, true, !last, ep, &eb, s);
-        if (e == hipSuccess && energy) e = launch_energy_final(ep, eb, 1, energy + 2 * (k + 1), s);
+        if (e == hipSuccess && energy) e = launch_energy_final(ep, eb, false, 1, energy + 2 * (k + 1), s);
         if (e != hipSuccess) return hip_fail(e, "tree leapfrog step");
     }
     return NBODY_OK;

@@ -119,3 +119,40 @@ def test_energies_of_many_steps(steps):
     torch.cuda.synchronize()
     assert torch.equal(p1, p2) and torch.equal(v1, v2)
     assert torch.equal(en, torch.stack(ref))
+
+
+@pytest.mark.parametrize("mode,n", [("F32_KAHAN", 511), ("F32_KAHAN", 512), ("F32", 513), ("F32_F64ACC", 8192),
+                                    ("F64", 527), ("F64", 4096)])
+@pytest.mark.parametrize("steps", [1, 2, 5])
+def test_fused_small_steps(mode, n, steps):
+    """Small problems step in the force's launch, the positions going back and
+    forth between two buffers: odd and even counts of steps, from a given and
+    from a computed force, equal force and kick_drift by hand bit for bit, and
+    so do energies and graph replays with other work in between."""
+    torch, nb = gpu()
+    prec, eps, dt = getattr(nb, mode), 0.01, 1e-3
+    dtype = torch.float64 if mode == "F64" else torch.float32
+    pm, v = ics.plummer(n, 67)
+    p0, v0 = to_dev(torch, pm, dtype), to_dev(torch, v, dtype)
+    ph, vh = p0.clone(), v0.clone()
+    ah = nb.accel(ph, eps, prec=prec)
+    a0 = ah.clone()
+    en = [nb.energy(ph, vh, ah)]
+    for k in range(steps):
+        nb.kick_drift(ph, vh, ah, dt / 2, dt, close=False, open=True, prec=prec)
+        ah = nb.accel(ph, eps, prec=prec)
+        nb.kick_drift(ph, vh, ah, dt / 2, dt, close=True, open=False, prec=prec)
+        en.append(nb.energy(ph, vh, ah))
+    for given in (False, True):
+        for graph in (False, True):
+            pg, vg = p0.clone(), v0.clone()
+            ag = a0.clone()
+            for rep in range(3 if graph else 1):
+                pg.copy_(p0)
+                vg.copy_(v0)
+                ag.copy_(a0 if given else torch.zeros_like(a0))
+                got = nb.leapfrog_kdk(pg, vg, ag, eps, dt, steps, prec=prec, acc_valid=given, graph=graph, energy=True)
+                nb.accel(p0, 2 * eps, prec=prec)
+                torch.cuda.synchronize()
+                assert torch.equal(pg, ph) and torch.equal(vg, vh) and torch.equal(ag, ah)
+                assert torch.equal(got, torch.stack(en))
