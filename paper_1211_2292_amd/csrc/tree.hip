@@ -39,7 +39,7 @@
 //   which is exact.  In inspection mode the same walk writes the node ids of
 //   the accepted cells and of the rejected leaves instead of summing.
 // * k_order_bins, k_group_order: the order in which the local-expansion walk
-//   takes its groups when there are many (largest boxes first; see there).
+//   takes its groups (largest boxes first, from 1025 groups on; see there).
 //
 // Order 2 (pseudo-particle multipoles: Makino, J. Comput. Phys. 151, 1999,
 // the paper's reference [20], which Section VI cites for the O(N) fast
@@ -819,12 +819,19 @@ k_tree_walk(const float4 *__restrict__ src, int n, TreeDev T, const float4 *__re
 // L2 locality favours.  k_order_bins puts each group's diag2 in one of 1024
 // bins by its FP32 bit pattern (exponent and two mantissa bits);
 // k_group_order, one workgroup, takes the bins from the top down until they
-// hold 1/16 of the groups and writes a stable partition of the group
-// indices: those groups, then the others, each in ORB order.  Only the order
-// in which the workgroups run changes, never what a group computes.
+// hold 1/16 of the groups (1/5 of fewer than 8192) and writes a stable
+// partition of the group indices: those groups, then the others, each in ORB
+// order.  Only the order in which the workgroups run changes, never what a
+// group computes.  Few groups, leaf sizes below 16: 100000 bodies (2048
+// groups, four waves each), 5 steps, 1749 -> 1590 us (1/3 of the groups first
+// 1642, 1/8 1651); 2 steps with 247060 bodies (4356 groups, one wave each)
+// 2419 -> 2199 us; 0.998 to 1.10x over 1828 to 5189 groups, theta 0.5 to 1.
+// The two launches, 11 us per walk, are in these times.  Leaves of 16 and more lose 1%: their
+// walks are longer and more alike.
 constexpr int kOrderThreads = 1024;
 constexpr int kOrderBins = 1024;
-constexpr int kOrderMinGroups = 8192;  // fewer groups run in about one round
+constexpr int kOrderMinGroups = 8192;
+constexpr int kOrderFewGroups = 1024;  // up to here all groups run at once, four waves each
 
 // One thread per group; each workgroup also writes the histogram of its
 // kOrderThreads groups' bins (a row of kOrderBins counts).
@@ -876,7 +883,7 @@ __device__ __forceinline__ int block_incl_sum(int *sc, int v, int *total = nullp
 constexpr int kOrderPer = 16;
 constexpr int kOrderChunk = kOrderPer * kOrderThreads;
 
-__global__ __launch_bounds__(kOrderThreads) void k_group_order(TreeDev T, int ng)
+__global__ __launch_bounds__(kOrderThreads) void k_group_order(TreeDev T, int ng, int part)
 {
     static_assert(kOrderBins == kOrderThreads, "one bin per thread");
     __shared__ int hist[kOrderBins];
@@ -896,7 +903,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_group_order(TreeDev T, int ng
     if (t == 0) cut = 0;
     __syncthreads();
     // groups in bins >= kOrderBins - 1 - t, counted from the top bin down
-    const int want = max(1, ng / 16);
+    const int want = max(1, ng / part);
     const int h = hist[kOrderBins - 1 - t];
     const int top = block_incl_sum(sc, h);
     if (top >= want && top - h < want) {
@@ -1252,15 +1259,17 @@ hipError_t launch_walk(const float4 *pm, int n, const TreeDev &d, int ngroups, f
                        double theta2, const WalkOut &o, hipStream_t s)
 {
     const float4 *recs = CELLS == kCellsPseudo ? d.pp : (CELLS >= kCellsQuad ? d.qr : nullptr);
-    // the local-expansion force walk over many groups runs the largest boxes
-    // first (unless NBODY_TREE_ORDER=0); the other walks and inspection keep
+    // the local-expansion force walk over many groups (with small leaves, over
+    // more than run at once) runs the largest boxes first (unless NBODY_TREE_ORDER=0); the other walks and inspection keep
     // ORB order
     const int *order = nullptr;
     const char *env = getenv("NBODY_TREE_ORDER");
-    if (!INSPECT && CELLS == kCellsLocal && ngroups >= kOrderMinGroups && !(env && env[0] == '0')) {
+    if (!INSPECT && CELLS == kCellsLocal && (ngroups >= kOrderMinGroups || (NEAR_LDS && ngroups > kOrderFewGroups)) &&
+        !(env && env[0] == '0')) {
         hipLaunchKernelGGL(k_order_bins, dim3((ngroups + kOrderThreads - 1) / kOrderThreads), dim3(kOrderThreads), 0,
                            s, d, ngroups);
-        hipLaunchKernelGGL(k_group_order, dim3(1), dim3(kOrderThreads), 0, s, d, ngroups);
+        hipLaunchKernelGGL(k_group_order, dim3(1), dim3(kOrderThreads), 0, s, d, ngroups,
+                           ngroups >= kOrderMinGroups ? 16 : 5);
         order = d.order;
     }
     hipLaunchKernelGGL((k_tree_walk<MODE, INSPECT, CELLS, NEAR_LDS, W>), dim3(ngroups), dim3(64 * W), 0, s, pm, n, d,

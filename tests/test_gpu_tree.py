@@ -245,6 +245,28 @@ def test_dispatch_order_changes_nothing(orc, n, ng, cells, ocells):
     assert rms_rel(got[tg, 3], p) < 1e-6
 
 
+@pytest.mark.parametrize("n,leaf", [(65536, 4), (65537, 4), (100000, 8), (262144, 15)])
+def test_dispatch_order_of_few_groups(n, leaf):
+    """1024 (ORB order), 1025, 2048 and 5189 groups (one wave each): the walk
+    that runs large boxes first gives the bits of ORB order, every record written."""
+    import os
+    torch, nb = gpu()
+    pm, _ = ics.plummer(n, 781)
+    q, _ = _orb_input(torch, nb, pm, leaf)
+    outs = []
+    for env in (None, "0"):
+        out = torch.full_like(q, float("nan"))
+        if env:
+            os.environ["NBODY_TREE_ORDER"] = env
+        try:
+            nb.tree_accel(q, 0.01, 0.7, leaf, prec=nb.F32_KAHAN, out=out, cells=nb.CELLS_LOCAL)
+        finally:
+            os.environ.pop("NBODY_TREE_ORDER", None)
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(outs[0]).all()) and torch.equal(*outs)
+
+
 @pytest.mark.parametrize("n,leaf,theta", [
     (257, 3, 0.4), (20011, 15, 0.3), (20011, 16, 0.3), (100000, 4, 0.0), (262144, 4, 0.7), (262145, 4, 0.7),
     (524288, 8, 0.7), (524289, 8, 0.7)])
