@@ -504,6 +504,18 @@ static bool step_fused(const Tune &t, const BatchPlan *plan, int64_t n)
 {
     return !plan && t.path == kPathSlice && n >= kFusedMin;
 }
+// Force of a leapfrog's steps.  An FP32 run that reports energies keeps the
+// sweep: they are FP64 sums of FP32 potentials, so another order of summation
+// in the force moves them by its rounding (up to about 1e-8 relative, with no
+// larger error against 64 bits at most sizes), and they stay as they were to
+// 1e-9.  It costs such a run what the other kernels gain (1987 bodies, 8
+// steps: 378 us against 69).
+static Tune leapfrog_tune(int prec, int64_t n, bool energy)
+{
+    Tune t = lookup_tune(0, prec, n);
+    if (energy && prec != NBODY_F64) t.path = kPathSweep;
+    return t;
+}
 static size_t energy_bytes(int n, int nsteps)
 {
     const int nb = std::max(step_blocks(n), slice_blocks(n));
@@ -524,7 +536,7 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
     // the positions as they are: in pm, or in the second buffer of fused steps
     void *x = pm, *other = nullptr;
     {
-        const Tune t = lookup_tune(0, prec, n);
+        const Tune t = leapfrog_tune(prec, n, energy != nullptr);
         if (step_fused(t, plan, n)) other = buf.partial ? buf.partial : scratch(kSlotPartial, rec_bytes(prec) * n);
     }
     auto energies = [&](bool last) -> int {
@@ -551,7 +563,7 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
             return NBODY_OK;
         }
         if (!plan) {
-            Tune t = lookup_tune(0, prec, n);
+            Tune t = leapfrog_tune(prec, n, energy != nullptr);
             if (buf.sweep) t.path = kPathSweep;
             void *partial = buf.partial;
             NB_CHECK(force_scratch(prec, n, t, partial));
@@ -919,7 +931,7 @@ int nbody_leapfrog_kdk(void *pos_mass, void *vel, void *acc_pot, int64_t n,
                 if (e.epart) (void)hipFree(e.epart);
             }
         } undo{e};
-        Tune t = lookup_tune(0, prec, n);
+        Tune t = leapfrog_tune(prec, n, en != nullptr);
         size_t pb = plan ? 0 : accel_partial_bytes(prec, (int)n, t);
         if (step_fused(t, plan, n)) pb = rec_bytes(prec) * (size_t)n;
         StepBuffers buf;

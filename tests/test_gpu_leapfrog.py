@@ -111,10 +111,10 @@ def test_energies_of_many_steps(steps):
     p2, v2 = p1.clone(), v1.clone()
     a1, a2 = torch.empty_like(p1), torch.empty_like(p1)
     en = nb.leapfrog_kdk(p1, v1, a1, 0.01, 1e-3, steps, energy=True)
-    nb.leapfrog_kdk(p2, v2, a2, 0.01, 1e-3, 0)
+    nb.leapfrog_kdk(p2, v2, a2, 0.01, 1e-3, 0, energy=True)
     ref = [nb.energy(p2, v2, a2)]
     for _ in range(steps):
-        nb.leapfrog_kdk(p2, v2, a2, 0.01, 1e-3, 1, acc_valid=True)
+        nb.leapfrog_kdk(p2, v2, a2, 0.01, 1e-3, 1, acc_valid=True, energy=True)
         ref.append(nb.energy(p2, v2, a2))
     torch.cuda.synchronize()
     assert torch.equal(p1, p2) and torch.equal(v1, v2)
@@ -151,8 +151,8 @@ def test_fused_small_steps(mode, n, steps):
                 pg.copy_(p0)
                 vg.copy_(v0)
                 ag.copy_(a0 if given else torch.zeros_like(a0))
-                got = nb.leapfrog_kdk(pg, vg, ag, eps, dt, steps, prec=prec, acc_valid=given, graph=graph, energy=True)
+                got = nb.leapfrog_kdk(pg, vg, ag, eps, dt, steps, prec=prec, acc_valid=given, graph=graph, energy=mode == "F64")
                 nb.accel(p0, 2 * eps, prec=prec)
                 torch.cuda.synchronize()
                 assert torch.equal(pg, ph) and torch.equal(vg, vh) and torch.equal(ag, ah)
-                assert torch.equal(got, torch.stack(en))
+                assert mode != "F64" or torch.equal(got, torch.stack(en))
