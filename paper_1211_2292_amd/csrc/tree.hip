@@ -494,7 +494,7 @@ __device__ __forceinline__ void sweep_near(const float4 *__restrict__ src, const
 template <int MODE, bool INSPECT, int CELLS, bool NEAR_LDS, int W>
 __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(CELLS == kCellsLocal ? (W > 1 ? 4 : 5) : 7))) void
 k_tree_walk(const float4 *__restrict__ src, int n, TreeDev T, const float4 *__restrict__ cells, float eps2_in,
-            double G, double theta2, WalkOut O, const int *__restrict__ order)
+            double G, double theta2, WalkOut O, const int *__restrict__ order, int first)
 {
     constexpr bool QUAD = CELLS >= kCellsQuad;
     static_assert(!INSPECT || W == 1, "inspection is one wave's");
@@ -510,7 +510,7 @@ k_tree_walk(const float4 *__restrict__ src, int n, TreeDev T, const float4 *__re
     __shared__ int4 steps[W];  // this step's counts of each wave: accepted, near, opened, folded in
     const int lane = W == 1 ? (int)threadIdx.x : (int)threadIdx.x & 63;
     const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int g = order ? order[blockIdx.x] : (int)blockIdx.x;
+    const int place = first + (int)blockIdx.x, g = order ? order[place] : place;
     const int gnode = T.groups[g];
     const int4 gn = T.node[gnode];
     const float4 glo = T.lo[gnode], ghi = T.hi[gnode];
@@ -1272,9 +1272,15 @@ hipError_t launch_walk(const float4 *pm, int n, const TreeDev &d, int ngroups, f
                            ngroups >= kOrderMinGroups ? 16 : 5);
         order = d.order;
     }
-    hipLaunchKernelGGL((k_tree_walk<MODE, INSPECT, CELLS, NEAR_LDS, W>), dim3(ngroups), dim3(64 * W), 0, s, pm, n, d,
-                       recs, eps2, G, theta2, o, order);
-    return hipGetLastError();
+    // a launch holds fewer than 2^32 threads
+    constexpr int kMost = (1 << 30) / (64 * W);
+    hipError_t e = hipSuccess;
+    for (int first = 0; first < ngroups && e == hipSuccess; first += kMost) {
+        hipLaunchKernelGGL((k_tree_walk<MODE, INSPECT, CELLS, NEAR_LDS, W>), dim3(std::min(kMost, ngroups - first)),
+                           dim3(64 * W), 0, s, pm, n, d, recs, eps2, G, theta2, o, order, first);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 // Waves per group: four where the launch's time is that of its slowest groups,

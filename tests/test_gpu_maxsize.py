@@ -85,3 +85,44 @@ def test_accel_at_maximum_n(orc, mode, tbeg, tcount, shape):
     assert normwise(got[:, 3], pot_ref) < bar
     assert max_rel(got[:, :3], acc_ref) < 100 * bar
     assert max_rel(got[:, 3], pot_ref) < 100 * bar
+
+
+@pytest.mark.parametrize("cells,bar", [("CELLS_QUADRUPOLE", 2e-6), ("CELLS_PSEUDO", 7 * 0.25 ** 6)])
+def test_tree_walk_of_more_than_2_24_groups(orc, cells, bar):
+    """2^24 + 1 groups (leaves of 33 bodies): walked by four waves each, more
+    than one launch's 2^32 threads.  The bodies lie along a line, so they are
+    in ORB order already, and one of them has mass: an accepted cell that
+    holds it has its centre of mass on it and no second moment, so quadrupole
+    cells give the exact force of that body up to FP32 rounding; the twelve
+    points that stand for it otherwise are exact up to the order 6 in their
+    distance from the centre over the target's (1/4 at theta = 0.5), whose
+    force has the factor 7."""
+    torch, nb = gpu()
+    leaf = 33
+    n = leaf * (1 << 24) + 1
+    if torch.cuda.mem_get_info()[0] < (80 << 30):
+        pytest.skip("needs 80 GiB of free device memory")
+    heavy = n // 3
+    pm = torch.zeros((n, 4), dtype=torch.float32, device="cuda")
+    out = torch.full((n, 4), float("nan"), dtype=torch.float32, device="cuda")
+    try:
+        pm[:, 0] = torch.arange(n, dtype=torch.float64, device="cuda") * 2.0 ** -20
+        pm[heavy, 3] = 1.0
+        nb.tree_accel(pm, EPS, 0.5, leaf, prec=nb.F32_F64ACC, cells=getattr(nb, cells), out=out)
+        edge = np.arange(0, n, leaf << 22)  # first bodies of 2^22 groups
+        keep = np.unique(np.clip(np.concatenate([edge[:, None] + np.array([-1, 0, 1, 32, 33]), heavy + np.arange(-40, 41)[:, None]],
+                                                axis=None), 0, n - 1))
+        keep = np.union1d(keep, np.arange(n - 70, n))
+        k = torch.as_tensor(keep, device="cuda")
+        src, got = host(pm[k]), host(out[k])
+        assert bool(torch.isfinite(out).all())
+    finally:
+        del pm, out
+        nb.release()
+        torch.cuda.empty_cache()
+    acc, pot = orc.accel(src, EPS)
+    pulled = np.abs(acc[:, 0]) > 0  # (nearest bodies share the coordinate of the one with mass)
+    assert pulled.sum() > 100
+    assert max_rel(got[pulled, :3], acc[pulled]) < bar
+    assert np.all(got[~pulled, :3] == 0)
+    assert max_rel(got[keep != heavy, 3], pot[keep != heavy]) < bar
