@@ -227,7 +227,7 @@ __device__ __forceinline__ void merge_moments(const Moments<Q2> &a, const Moment
 // Moments, one subtree of up to K inputs per workgroup of K threads.  ent lists
 // a subtree's inputs (the leaves, or in later launches the subtree roots that
 // the launch before finished), then its inner nodes by height above them, as
-// (node, left, right, height) with left and right places in the list.  The
+// (node - root, left, right, height) with left and right places in the list.  The
 // nodes pass their moments up through LDS, a barrier between heights.  One
 // launch per node height, with the children read back from memory, took 17
 // launches of 4 to 7 us at 10^5 bodies (leaf 4), 77 us more per evaluation than
@@ -276,19 +276,20 @@ struct MomentLds {  // one array per field: neighbouring nodes lie in neighbouri
 
 template <bool Q2, int K, bool LEAVES>
 __global__ __launch_bounds__(K) void k_tree_moments(const float4 *__restrict__ pm, TreeDev T,
-                                                    const int4 *__restrict__ ent, const int2 *__restrict__ sub,
+                                                    const int4 *__restrict__ ent, const int4 *__restrict__ sub,
                                                     int quad)
 {
     __shared__ MomentLds<Q2, K> lds;
-    const int2 range = sub[blockIdx.x];  // first entry, entries
-    ent += range.x;
-    const int heights = ent[range.y - 1].w;  // the list is ordered by height
+    const int4 range = sub[blockIdx.x];  // root, first entry, entries
+    ent += range.y;
+    const int heights = ent[range.z - 1].w;  // the list is ordered by height
     // this thread's two places in it
     int4 mine[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int e = threadIdx.x + u * K;
-        mine[u] = e < range.y ? ent[e] : make_int4(0, 0, 0, -1);
+        mine[u] = e < range.z ? ent[e] : make_int4(0, 0, 0, -1);
+        mine[u].x += range.x;
     }
     for (int h = 0; h <= heights; ++h) {
 #pragma unroll
@@ -1035,72 +1036,77 @@ void plan(HostTree &h, int n, int leaf)
 
 // The moment kernels' subtrees: launch by launch, maximal subtrees of at most
 // `room` inputs, the inputs being the leaves first and then the roots of the
-// subtrees before, until the tree's root is one of them.
+// subtrees before, until the tree's root is one of them.  A node's subtree
+// depends on its size only, at most two sizes per level, and its nodes are
+// numbered from it on, so one list per size serves all its subtrees: the plan
+// takes a step per subtree, not per node.  (First force of a new n with 2^20
+// bodies, leaf 4: 10.3 ms with a list per subtree and its upload, 3.7 so.)
 constexpr int kMomLeaves = 128, kMomNodes = 256;
 
-void moment_plan(HostTree &h)
+void moment_plan(HostTree &h, int leaf)
 {
-    const int nn = (int)h.node.size();
-    std::vector<char> input(nn, 0);
-    for (int id : h.leaves) input[id] = 1;
-    std::vector<int> count(nn), place(nn), rank(nn);
     h.mom_ent.clear();
     h.mom_sub.clear();
     h.mom_off.assign(1, 0);
-    if (h.leaves.size() == 1) {  // the root is a leaf
-        h.mom_ent.push_back(make_int4(0, -1, -1, 0));
-        h.mom_sub.push_back(make_int2(0, 1));
-        h.mom_off.push_back(1);
-        return;
-    }
-    std::vector<int> stack, walk, inner;
-    for (int room = kMomLeaves; !input[0]; room = kMomNodes) {
-        // inputs below every node that is not below an input (children come after their parent)
-        for (int id = nn - 1; id >= 0; --id)
-            count[id] = input[id] ? 1 : (h.node[id].z < 0 ? 0 : std::min(room + 1, count[h.node[id].z]) +
-                                                                     std::min(room + 1, count[h.node[id].w]));
-        std::vector<int> roots;
-        stack.assign(1, 0);
+    auto size_of = [&](int id) { return h.node[id].y - h.node[id].x; };
+    std::map<int, int> before;  // inputs of a node by its size, in the launch before
+    int room_before = 0;        // (its room; 0: the first launch, whose inputs are the leaves)
+    for (int room = kMomLeaves;; room = kMomNodes) {
+        auto is_input = [&](int id) { return room_before ? before.at(size_of(id)) <= room_before : h.node[id].z < 0; };
+        std::map<int, int> count;
+        auto inputs = [&](auto &&self, int id) -> int {
+            const auto it = count.find(size_of(id));
+            if (it != count.end()) return it->second;
+            const int c = is_input(id) ? 1 : self(self, h.node[id].z) + self(self, h.node[id].w);
+            return count[size_of(id)] = c;
+        };
+        std::map<int, int2> lists;  // by the root's size: first entry, entries
+        auto list_of = [&](int root) -> int2 {
+            const auto it = lists.find(size_of(root));
+            if (it != lists.end()) return it->second;
+            const int first = (int)h.mom_ent.size();
+            // inner nodes in preorder: node, left, right, height (a child: its place in the list, or ~ its index here)
+            std::vector<int4> inner;
+            auto collect = [&](auto &&self, int id) -> int2 {
+                if (is_input(id)) {
+                    h.mom_ent.push_back(make_int4(id - root, -1, -1, 0));
+                    return make_int2((int)h.mom_ent.size() - 1 - first, 0);
+                }
+                const size_t k = inner.size();
+                inner.emplace_back();
+                const int2 l = self(self, h.node[id].z), r = self(self, h.node[id].w);
+                inner[k] = make_int4(id - root, l.x, r.x, 1 + std::max(l.y, r.y));
+                return make_int2(~(int)k, inner[k].w);
+            };
+            collect(collect, root);
+            std::vector<int> order(inner.size()), place(inner.size());
+            for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
+            std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return inner[a].w < inner[b].w; });
+            for (int k : order) {
+                int4 e = inner[k];
+                place[k] = (int)h.mom_ent.size() - first;
+                if (e.y < 0) e.y = place[~e.y];
+                if (e.z < 0) e.z = place[~e.z];
+                h.mom_ent.push_back(e);
+            }
+            return lists[size_of(root)] = make_int2(first, (int)h.mom_ent.size() - first);
+        };
+        std::vector<int> stack(1, 0);
         while (!stack.empty()) {
             const int id = stack.back();
             stack.pop_back();
-            if (count[id] > room) {
+            if (inputs(inputs, id) > room) {
                 stack.push_back(h.node[id].w);
                 stack.push_back(h.node[id].z);
-                continue;
+            } else if (!room_before || !is_input(id)) {  // (a subtree finished already stays an input)
+                const int2 l = list_of(id);
+                h.mom_sub.push_back(make_int4(id, l.x, l.y, 0));
             }
-            roots.push_back(id);
-        }
-        const bool leaves = h.mom_off.size() == 1;
-        for (int r : roots) {
-            if (input[r] && !leaves) continue;  // finished already
-            const int first = (int)h.mom_ent.size();
-            inner.clear();
-            walk.assign(1, r);
-            while (!walk.empty()) {  // preorder
-                const int id = walk.back();
-                walk.pop_back();
-                if (input[id]) {
-                    place[id] = (int)h.mom_ent.size() - first;
-                    rank[id] = 0;
-                    h.mom_ent.push_back(make_int4(id, -1, -1, 0));
-                } else {
-                    inner.push_back(id);
-                    walk.push_back(h.node[id].w);
-                    walk.push_back(h.node[id].z);
-                }
-            }
-            for (size_t k = inner.size(); k-- > 0;)
-                rank[inner[k]] = 1 + std::max(rank[h.node[inner[k]].z], rank[h.node[inner[k]].w]);
-            std::stable_sort(inner.begin(), inner.end(), [&](int a, int b) { return rank[a] < rank[b]; });
-            for (int id : inner) {
-                place[id] = (int)h.mom_ent.size() - first;
-                h.mom_ent.push_back(make_int4(id, place[h.node[id].z], place[h.node[id].w], rank[id]));
-            }
-            h.mom_sub.push_back(make_int2(first, (int)h.mom_ent.size() - first));
         }
         h.mom_off.push_back((int)h.mom_sub.size());
-        for (int r : roots) input[r] = 1;
+        if (count[size_of(0)] <= room) return;
+        before.swap(count);
+        room_before = room;
     }
 }
 
@@ -1136,12 +1142,12 @@ int tree_prepare(int n, int leaf, hipStream_t s, TreeDev &out)
     }
     HostTree h;
     plan(h, n, leaf);
-    moment_plan(h);
+    moment_plan(h, leaf);
     const size_t nn = h.node.size(), ng = h.groups.size();
     const size_t o_node = 0;
     const size_t o_ment = o_node + align256(nn * sizeof(int4));
     const size_t o_msub = o_ment + align256(h.mom_ent.size() * sizeof(int4));
-    const size_t o_grp = o_msub + align256(h.mom_sub.size() * sizeof(int2));
+    const size_t o_grp = o_msub + align256(h.mom_sub.size() * sizeof(int4));
     const size_t o_sums = o_grp + align256(ng * sizeof(int));
     const size_t o_nrec = o_sums + align256(nn * sizeof(double4));
     const size_t o_lo = o_nrec + align256(nn * sizeof(NodeRec));
@@ -1170,7 +1176,7 @@ int tree_prepare(int n, int leaf, hipStream_t s, TreeDev &out)
     TreeDev d;
     d.node = (const int4 *)(base + o_node);
     d.mom_ent = (const int4 *)(base + o_ment);
-    d.mom_sub = (const int2 *)(base + o_msub);
+    d.mom_sub = (const int4 *)(base + o_msub);
     d.groups = (const int *)(base + o_grp);
     d.sums = (double4 *)(base + o_sums);
     d.nrec = (NodeRec *)(base + o_nrec);
@@ -1191,7 +1197,7 @@ int tree_prepare(int n, int leaf, hipStream_t s, TreeDev &out)
         e = hipMemcpyAsync(base + o_ment, C.host.mom_ent.data(), C.host.mom_ent.size() * sizeof(int4),
                            hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(base + o_msub, C.host.mom_sub.data(), C.host.mom_sub.size() * sizeof(int2),
+        e = hipMemcpyAsync(base + o_msub, C.host.mom_sub.data(), C.host.mom_sub.size() * sizeof(int4),
                            hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(base + o_grp, C.host.groups.data(), ng * sizeof(int), hipMemcpyHostToDevice, s);
@@ -1221,7 +1227,7 @@ hipError_t launch_moments_t(const float4 *pm, const TreeDev &d, const HostTree &
     hipError_t e = hipSuccess;
     for (size_t k = 0; e == hipSuccess && k + 1 < h.mom_off.size(); ++k) {
         const dim3 grid(h.mom_off[k + 1] - h.mom_off[k]);
-        const int2 *sub = d.mom_sub + h.mom_off[k];
+        const int4 *sub = d.mom_sub + h.mom_off[k];
         if (k == 0)
             hipLaunchKernelGGL((k_tree_moments<Q2, kMomLeaves, true>), grid, dim3(kMomLeaves), 0, s, pm, d, d.mom_ent,
                                sub, quad);

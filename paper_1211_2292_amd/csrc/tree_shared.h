@@ -30,8 +30,8 @@ struct alignas(64) NodeRec {
 
 struct TreeDev {
     const int4 *node;    // begin, end, left, right (-1 for a leaf)
-    const int4 *mom_ent;   // the moment kernels' subtrees: (node, left, right, height), inputs first
-    const int2 *mom_sub;   // per subtree: first entry, entries
+    const int4 *mom_ent;   // the moment kernels' lists of a subtree's nodes: (node - root, left, right, height), inputs first
+    const int4 *mom_sub;   // per subtree: root, first entry of its list, entries
     const int *groups;     // group node ids in ORB order
     double4 *sums;       // M, Sx, Sy, Sz
     NodeRec *nrec;
@@ -48,7 +48,7 @@ struct HostTree {
     std::vector<int4> node;
     std::vector<int> leaves, groups, height;
     std::vector<int4> mom_ent;   // see TreeDev
-    std::vector<int2> mom_sub;
+    std::vector<int4> mom_sub;
     std::vector<int> mom_off;    // first subtree of each moment launch, plus the end
 };
 

@@ -43,6 +43,26 @@ def test_moments_bitexact(orc, n, leaf):
     assert np.array_equal(box[:, 3:].astype(np.float64), want["hi"])
 
 
+@pytest.mark.parametrize("n,leaf", [(70001, 5), (300007, 3), (40000, 1), (99991, 7), (2000003, 31)])
+def test_moments_of_subtrees_of_two_sizes(orc, n, leaf):
+    """Sizes whose subtrees differ by one leaf, so that a moment launch works
+    through several lists of nodes: the moments bit for bit, after a call of
+    another shape."""
+    torch, nb = gpu()
+    pm, _ = ics.plummer(n, 340 + n % 97)
+    q, qh = _orb_input(torch, nb, pm, leaf)
+    nb.tree_moments(q[:1000].contiguous(), leaf)
+    mom, box = nb.tree_moments(q, leaf)
+    torch.cuda.synchronize()
+    mom, box = mom.cpu().numpy(), box.cpu().numpy()
+    want = orc.tree_moments(qh, leaf)
+    assert np.array_equal(mom[:, 0], want["mass"])
+    assert np.array_equal(mom[:, 1:4], want["com"])
+    assert np.array_equal(mom[:, 4], want["diag2"])
+    assert np.array_equal(box[:, :3].astype(np.float64), want["lo"])
+    assert np.array_equal(box[:, 3:].astype(np.float64), want["hi"])
+
+
 # 127, 128, 129 and 256, 257 leaves (subtrees of at most 128 leaves), 128 * 256
 # leaves and one more (a third launch), and leaves of 1 and 64 bodies
 @pytest.mark.parametrize("n,leaf", [(508, 4), (512, 4), (513, 4), (1024, 4), (1025, 4), (131072, 4), (131073, 4),
