@@ -533,11 +533,19 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
     bool eb_rows = false;  // eb counts rows (fused steps)
     int waiting = 0;  // states whose partials are in buf.epart, the last one state `seen` - 1
     int seen = 0;
+    const bool have_acc = (flags & NBODY_ACC_VALID) != 0;
     // the positions as they are: in pm, or in the second buffer of fused steps
     void *x = pm, *other = nullptr;
-    {
-        const Tune t = leapfrog_tune(prec, n, energy != nullptr);
-        if (step_fused(t, plan, n)) other = buf.partial ? buf.partial : scratch(kSlotPartial, rec_bytes(prec) * n);
+    // one force kernel, and its scratch, for all steps of the call
+    Tune t;
+    void *partial = buf.partial;
+    if (!plan && (nsteps > 0 || !have_acc)) {
+        t = leapfrog_tune(prec, n, energy != nullptr);
+        if (buf.sweep) t.path = kPathSweep;
+        if (step_fused(t, plan, n))
+            other = partial ? partial : scratch(kSlotPartial, rec_bytes(prec) * n);
+        else
+            NB_CHECK(force_scratch(prec, n, t, partial));
     }
     auto energies = [&](bool last) -> int {
         if (!energy) return NBODY_OK;
@@ -563,10 +571,6 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
             return NBODY_OK;
         }
         if (!plan) {
-            Tune t = leapfrog_tune(prec, n, energy != nullptr);
-            if (buf.sweep) t.path = kPathSweep;
-            void *partial = buf.partial;
-            NB_CHECK(force_scratch(prec, n, t, partial));
             if (const int records = accel_partial_records(n, t); records && step) {
                 NB_TRY(launch_accel(prec, pm, n, G, eps, acc, 0, n, t, partial, s, false), "force kernel");
                 NB_TRY(launch_reduce_step(prec, accel_record_kind(prec, n, t), partial, records, G, pm, vel, acc, n, h, dt, close, open,
@@ -586,7 +590,6 @@ static int leapfrog_enqueue(void *pm, void *vel, void *acc, int n, const BatchPl
         NB_TRY(launch_step(prec, pm, vel, acc, n, h, dt, close, open, ep, &eb, s), "step kernel");
         return NBODY_OK;
     };
-    const bool have_acc = (flags & NBODY_ACC_VALID) != 0;
     if (nsteps == 0) {
         // a(x_0) and, on request, the energies at t_0
         if (!have_acc) NB_CHECK(eval_step(energy != nullptr, false, false));

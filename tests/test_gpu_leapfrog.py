@@ -156,3 +156,51 @@ def test_fused_small_steps(mode, n, steps):
                 torch.cuda.synchronize()
                 assert torch.equal(pg, ph) and torch.equal(vg, vh) and torch.equal(ag, ah)
                 assert mode != "F64" or torch.equal(got, torch.stack(en))
+
+
+def test_pairwise_records_do_not_fit():
+    """Where the pairwise kernels' records (1000 MiB for 2^18 bodies) cannot be
+    had, a force, a run and a captured run take the split sweep (128 MiB):
+    the bits of the sweep's pinned shape.  The rest of the device's memory is
+    held by another tensor meanwhile; afterwards the pairwise kernels run."""
+    torch, nb = gpu()
+    n, eps, dt, prec = 1 << 18, 0.01, 1e-3, nb.F32_KAHAN
+    pm, v = ics.plummer(n, 71)
+    p0, v0 = to_dev(torch, pm, torch.float32), to_dev(torch, v, torch.float32)
+    pe, ve, ae = p0.clone(), v0.clone(), torch.empty_like(p0)
+    pr, vr, ar = p0.clone(), v0.clone(), torch.empty_like(p0)
+    out = torch.empty_like(p0)
+    nb.set_tuning(0, prec, *nb.get_tuning(0, prec, n))
+    try:
+        force = nb.accel(p0, eps, prec=prec)
+        nb.leapfrog_kdk(pr, vr, ar, eps, dt, 3, prec=prec)
+    finally:
+        nb.set_tuning(0, prec)
+    torch.cuda.synchronize()
+    nb.release()
+    torch.cuda.empty_cache()
+    held = []
+    for _ in range(4):  # (memory just freed may be counted late)
+        free = torch.cuda.mem_get_info()[0]
+        if free > (900 << 20):
+            held.append(torch.empty(free - (700 << 20), dtype=torch.uint8, device="cuda"))
+    try:
+        print("free MiB", torch.cuda.mem_get_info()[0] >> 20, flush=True)
+        assert torch.cuda.mem_get_info()[0] < (1000 << 20)
+        nb.accel(p0, eps, prec=prec, out=out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, force)
+        for graph in (False, True, True):
+            pe.copy_(p0)
+            ve.copy_(v0)
+            nb.leapfrog_kdk(pe, ve, ae, eps, dt, 3, prec=prec, graph=graph)
+            torch.cuda.synchronize()
+            assert torch.equal(pe, pr) and torch.equal(ve, vr) and torch.equal(ae, ar), graph
+    finally:
+        del held
+        nb.release()
+        torch.cuda.empty_cache()
+    again = nb.accel(p0, eps, prec=prec)
+    torch.cuda.synchronize()
+    assert not torch.equal(again, force)  # the pairwise kernels' order of summation
+    nb.release()
