@@ -223,6 +223,31 @@ print(json.dumps(out))
         assert e <= 1e-5 and ep <= 1e-5
 
 
+def _fresh(code, cache):
+    """The JSON that `code` prints, run in a process of its own."""
+    r = subprocess.run([sys.executable, "-c", code % ROOT], env=dict(os.environ, NBODY_TUNE_CACHE=str(cache)),
+                       capture_output=True, text=True, timeout=240)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return json.loads(r.stdout.strip().splitlines()[-1])
+
+
+@pytest.mark.parametrize("n", [1000, 3000])
+def test_autotuned_vjp_is_not_slower(tmp_path, n):
+    """The untuned shape is one of nbody_autotune's candidates: at sizes where
+    it beats every other one by far (512 bodies 18 us against 47), it is what
+    the tuner returns, or one with half its source splits."""
+    code = r'''
+import sys, json
+sys.path.insert(0, %%r)
+import paper_1211_2292_amd as nb
+before = nb.get_tuning(2, nb.F32_KAHAN, %d)
+nb.autotune(2, nb.F32_KAHAN, %d)
+print(json.dumps([before, nb.get_tuning(2, nb.F32_KAHAN, %d)]))
+''' % (n, n, n)
+    before, after = _fresh(code, tmp_path / "tune.json")
+    assert after[1] >= before[1] // 2, (before, after)
+
+
 def test_release_and_reuse():
     torch, nb = gpu()
     pm, v = ics.plummer(3000, 77)
