@@ -286,6 +286,8 @@ constexpr int64_t kVjpMinSources = 64;
 // 4.8e-7 to 3.3e-7, mbar 3.2e-7 to 2.3e-7).
 constexpr int kVjpTile = 128;
 
+constexpr int kTunedSplits = 32;  // most source splits of a pinned or tuned shape
+
 // Kernels of a call whose shape is not pinned.
 static int default_path(int kernel, int prec, int64_t n, int64_t ntarg)
 {
@@ -356,7 +358,9 @@ static Tune lookup_tune(int kernel, int prec, int64_t n, int64_t ntarg = -1, boo
     if (ntarg < 0) ntarg = n;
     const Tune d = untuned(kernel, prec, n, ntarg);
     auto it = g_tuned.find(TuneKey(kernel, prec, log2ceil(n)));
-    if (it == g_tuned.end()) return d;
+    // a tuned shape was measured with all bodies as targets: a share of them
+    // that takes more splits than the tuner tries keeps the shape made for it
+    if (it == g_tuned.end() || d.jsplit > kTunedSplits) return d;
     Tune t = it->second;  // a measured shape of the sweep, for the calls that run it
     t.path = d.path;
     return t;
@@ -1745,7 +1749,7 @@ extern "C" int nbody_autotune(int32_t kernel, int32_t prec, int64_t n, const int
         if ((prec == NBODY_F64 || kernel == 2) && tp == 4) continue;
         for (int jt : jts) {
             if (kernel == 0 || kernel == 2) {
-                for (int js = 1; js <= 32; js *= 2) {
+                for (int js = 1; js <= kTunedSplits; js *= 2) {
                     if (js > 1 && n / js < 512) break;
                     const int64_t waves = (n + 64 * tp - 1) / (64 * tp);
                     if (waves * js > 65536 && js > 1) break;

@@ -248,6 +248,31 @@ print(json.dumps([before, nb.get_tuning(2, nb.F32_KAHAN, %d)]))
     assert after[1] >= before[1] // 2, (before, after)
 
 
+def test_tuned_entry_leaves_a_small_share_its_splits(tmp_path):
+    """An entry of the tuning file was measured with all bodies as targets.  A
+    share of the targets that the library gives more than 32 source splits
+    keeps them (bit for bit the untuned result); one that it does not, and the
+    same share with the shape pinned, run the entry's shape."""
+    code = r'''
+import sys, json
+sys.path.insert(0, %r)
+import torch, ics, numpy as np
+import paper_1211_2292_amd as nb
+n = 100001
+p = torch.as_tensor(ics.plummer(n, 2300)[0].astype(np.float32), device="cuda")
+few = nb.accel(p, 0.01, target_begin=500, target_count=3000)
+many = nb.accel(p, 0.01, target_begin=0, target_count=60001)
+print(json.dumps([nb.get_tuning(0, nb.F32_KAHAN, n), few.cpu().numpy().tobytes().hex(), many.cpu().numpy().tobytes().hex()[:4096]]))
+'''
+    plain, tuned = tmp_path / "none.json", tmp_path / "tune.json"
+    tuned.write_text('{\n  "0,2,17": [2, 4, 1024, 0]\n}\n')
+    shape0, few0, many0 = _fresh(code, plain)
+    shape1, few1, many1 = _fresh(code, tuned)
+    assert shape1 == [2, 4, 1024, 0] != shape0
+    assert few0 == few1
+    assert many0 != many1
+
+
 def test_release_and_reuse():
     torch, nb = gpu()
     pm, v = ics.plummer(3000, 77)
