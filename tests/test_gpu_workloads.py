@@ -231,6 +231,39 @@ def _fresh(code, cache):
     return json.loads(r.stdout.strip().splitlines()[-1])
 
 
+def test_autotuned_shape_itself_is_accurate(tmp_path):
+    """nbody_accel runs another kernel than the tuned sweep at 4096, 8192 and
+    65536 bodies; pinned, the shape that nbody_autotune chose there runs, and
+    meets the force bar of the compensated modes."""
+    code = r'''
+import sys, json
+sys.path.insert(0, %r)
+import numpy as np, torch, ics, oracle
+import paper_1211_2292_amd as nb
+out = []
+for mode in ("F32_KAHAN", "F32_F64ACC"):
+    prec = getattr(nb, mode)
+    for n in (4096, 8192, 65536):
+        nb.autotune(0, prec, n)
+        pm = ics.plummer(n, 2200 + n)[0].astype(np.float32)
+        p = torch.as_tensor(pm, device="cuda")
+        free = nb.accel(p, 0.01, prec=prec)
+        nb.set_tuning(0, prec, *nb.get_tuning(0, prec, n))
+        a = nb.accel(p, 0.01, prec=prec)
+        nb.set_tuning(0, prec)
+        tg = ics.sample_targets(n, 1024, 2201 + n)
+        acc, pot = oracle.accel(pm.astype(np.float64), 0.01, targets=tg)
+        g = a.cpu().numpy()[tg]
+        e = float(np.sqrt(np.mean((np.linalg.norm(g[:, :3] - acc, axis=1) / np.linalg.norm(acc, axis=1)) ** 2)))
+        ep = float(np.sqrt(np.mean(((g[:, 3] - pot) / pot) ** 2)))
+        out.append([bool(torch.equal(free, a)), e, ep])
+print(json.dumps(out))
+'''
+    for same, e, ep in _fresh(code, tmp_path / "tune.json"):
+        assert not same  # the sweep ran, not the kernel of the unpinned call
+        assert e <= 1e-5 and ep <= 1e-5
+
+
 @pytest.mark.parametrize("n", [1000, 3000])
 def test_autotuned_vjp_is_not_slower(tmp_path, n):
     """The untuned shape is one of nbody_autotune's candidates: at sizes where
