@@ -281,6 +281,10 @@ constexpr int64_t kSymMin = 44 * 512, kSymMax = int64_t(1) << 24;
 // bodies 1441 / 994 / 876 us).  The fixed-point leapfrog keeps 256: its states
 // depend on the shape bit for bit.
 constexpr int64_t kVjpMinSources = 64;
+// Bodies from which FP32 splits them at all: the second launch, which adds the
+// splits, takes 2 us (one split against two: 128 bodies 16.2 / 19.1 us, 160 16.0
+// / 18.2, 192 18.8 / 18.2; FP64 128 bodies 20.7 / 18.4).
+constexpr int64_t kVjpSplitF32 = 192;
 // Sources per FP32 partial sum of that sweep.  Tiles of 128 instead of 512 cost
 // under 1% and cut the errors by a third (10007 bodies, against FP64: xbar
 // 4.8e-7 to 3.3e-7, mbar 3.2e-7 to 2.3e-7).
@@ -345,6 +349,7 @@ static Tune untuned(int kernel, int prec, int64_t n, int64_t ntarg)
     if (kernel != 2) return default_tune(kernel, prec, n, ntarg);
     Tune t = default_tune(kernel, prec, n, ntarg, kVjpMinSources);
     t.jtile = kVjpTile;
+    if (prec != NBODY_F64 && n < kVjpSplitF32) t.jsplit = 1;
     return t;
 }
 

@@ -289,3 +289,16 @@ def test_bench_refuses_more_than_one_gpu():
     assert r.returncode == 2
     msg = json.loads(r.stdout.strip().splitlines()[-1])
     assert "one GPU" in msg["error"]
+
+
+def test_default_vjp_splits_of_few_bodies():
+    """Without a pin or a tuned entry, FP32 modes split the sources of the
+    force + VJP sweep from 192 bodies on (below, the launch that adds the
+    splits costs more than it saves), FP64 from 128 on; 64 sources per split
+    from there."""
+    import paper_1211_2292_amd as nb
+    if os.environ.get("NBODY_TUNE_CACHE"):
+        pytest.skip("a tuning cache may hold a measured shape")
+    for prec in (nb.F32, nb.F32_KAHAN, nb.F32_F64ACC):
+        assert [nb.get_tuning(2, prec, n)[1] for n in (1, 127, 128, 191, 192, 255, 256, 1024)] == [1, 1, 1, 1, 2, 2, 4, 16]
+    assert [nb.get_tuning(2, nb.F64, n)[1] for n in (1, 127, 128, 191, 256)] == [1, 1, 2, 2, 4]
