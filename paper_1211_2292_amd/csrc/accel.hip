@@ -468,7 +468,7 @@ struct SliceStep {
     typename SliceRec<T>::V *vel, *to;
     T h, dt;
     int close, open;
-    double *epart;  // per workgroup: kinetic and potential energy, or null
+    double *epart;  // FP64: per workgroup, kinetic and potential energy, or null (FP32 runs with energies take the sweep)
 };
 
 template <typename T, int MODE, bool STEP>
@@ -480,6 +480,7 @@ __global__ __launch_bounds__(kSliceThreads) void k_accel_slice(const typename Sl
     using V = typename SliceRec<T>::V;
     constexpr int C = SliceRec<T>::kChunk;
     static_assert(C % kSlices == 0 && sizeof(V) * C >= sizeof(double) * 4 * kSliceThreads, "the sums reuse the chunk");
+    constexpr bool ENERGY = STEP && sizeof(T) == 8;
     __shared__ V buf[C];
     const int tid = threadIdx.x, tg = tid % kSliceT, sl = tid / kSliceT;
     const int t0 = tbeg + blockIdx.x * kSliceT, i = t0 + tg;
@@ -549,11 +550,12 @@ __global__ __launch_bounds__(kSliceThreads) void k_accel_slice(const typename Sl
             put(out, i - tbeg, r, G);
         if constexpr (STEP) {
             V x = src[i];
-            step_body<V, T>(x, step.vel[i], out[i], step.h, step.dt, step.close, step.open, step.epart != nullptr, ek, eu);
+            step_body<V, T>(x, step.vel[i], out[i], step.h, step.dt, step.close, step.open,
+                            ENERGY && step.epart != nullptr, ek, eu);
             if (step.to) step.to[i] = x;
         }
     }
-    if constexpr (STEP) {
+    if constexpr (ENERGY) {
         if (!step.epart) return;
         static_assert(kSliceT == kEnergyRow, "the workgroup's bodies are a row");
 #pragma unroll

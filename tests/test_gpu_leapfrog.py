@@ -121,6 +121,30 @@ def test_energies_of_many_steps(steps):
     assert torch.equal(en, torch.stack(ref))
 
 
+@pytest.mark.parametrize("n", [527, 4096, 4097])
+@pytest.mark.parametrize("steps", [62, 63, 64, 130])
+@pytest.mark.parametrize("given", [False, True])
+def test_energies_of_many_fused_steps(n, steps, given):
+    """The same for FP64 runs whose step is fused with the force (up to 4096
+    bodies), which leave rows' sums: from a computed force and from a given
+    one, whose first state comes from the step kernel and is reduced by
+    itself, before, at and past the 64 states of one reduction."""
+    torch, nb = gpu()
+    pm, v = ics.plummer(n, 59)
+    p1, v1 = to_dev(torch, pm, torch.float64), to_dev(torch, v, torch.float64)
+    p2, v2 = p1.clone(), v1.clone()
+    a2 = nb.accel(p2, 0.01)
+    a1 = a2.clone() if given else torch.empty_like(p1)
+    en = nb.leapfrog_kdk(p1, v1, a1, 0.01, 1e-3, steps, energy=True, acc_valid=given)
+    ref = [nb.energy(p2, v2, a2)]
+    for _ in range(steps):
+        nb.leapfrog_kdk(p2, v2, a2, 0.01, 1e-3, 1, acc_valid=True)
+        ref.append(nb.energy(p2, v2, a2))
+    torch.cuda.synchronize()
+    assert torch.equal(p1, p2) and torch.equal(v1, v2) and torch.equal(a1, a2)
+    assert torch.equal(en, torch.stack(ref))
+
+
 @pytest.mark.parametrize("mode,n", [("F32_KAHAN", 511), ("F32_KAHAN", 512), ("F32", 513), ("F32_F64ACC", 8192),
                                     ("F64", 527), ("F64", 4096)])
 @pytest.mark.parametrize("steps", [1, 2, 5])
