@@ -86,7 +86,8 @@ enum {
 /* Flags of nbody_leapfrog_kdk. */
 #define NBODY_ACC_VALID 0x1u /* acc_pot already holds a(x) at the input state */
 #define NBODY_GRAPH 0x2u     /* capture the step loop in a HIP graph, reuse it */
-#define NBODY_ENERGY 0x4u    /* write FP64 energies to energy_out             */
+#define NBODY_ENERGY 0x4u    /* write FP64 energies to energy_out (in FP32 modes
+                                with the sweep's forces: see nbody_leapfrog_kdk) */
 
 /*
  * Orthogonal Recursive Bisection order (Section IV.B: divide space into
@@ -193,7 +194,16 @@ int nbody_accel_vjp(const void *pos_mass, const void *acc_pot_cot, int64_t n, in
  * nondecreasing; forces act only within a system.
  * NBODY_ENERGY: energy_out (device, double[(nsteps+1)*2]) receives
  * (K, U) = (1/2 sum m|v|^2, 1/2 sum m phi) in FP64 after each step, entry 0
- * at the input state (one system only).
+ * at the input state (one system only).  The energies are FP64 sums of the
+ * forces' potentials, and in the FP32 modes another order of summation in the
+ * force moves them by up to about 1e-8.  So that they stay comparable, an FP32
+ * run of one system with NBODY_ENERGY takes its forces from the split sweep at
+ * every size, one without from the kernels that nbody_accel chooses: where
+ * those are others (up to 8192 bodies, and from 22528 to 2^24), the two runs'
+ * states differ by the rounding of the forces.  With a pinned shape
+ * (nbody_set_tuning), in FP64, and for batches (offsets_host) the flag changes
+ * no bit of the state.  nbody_energy after a run without the flag gives the
+ * energies of that run's own trajectory.
  * NBODY_GRAPH: the whole step loop is captured once into a HIP graph keyed by
  * (pointers, sizes, scalars, flags) and replayed on later identical calls.
  */
@@ -204,7 +214,8 @@ int nbody_leapfrog_kdk(void *pos_mass, void *vel, void *acc_pot, int64_t n,
 
 /*
  * The elementwise half of one leapfrog step, for callers that drive the loop
- * themselves (nbody_leapfrog_kdk is nbody_accel plus this):
+ * themselves (nbody_leapfrog_kdk is nbody_accel plus this, bit for bit but for
+ * FP32 runs with NBODY_ENERGY, see there):
  *   close != 0: v += h a             (closing kick with a = acc_pot)
  *   open  != 0: v += h a; x += dt v  (opening kick and drift)
  * Both may be set (closing kick of one step, then opening kick and drift of

@@ -236,7 +236,10 @@ def _offsets(offsets):
 def leapfrog_kdk(pos_mass, vel, acc_pot, eps, dt, nsteps, G=1.0, prec=None, offsets=None,
                  acc_valid=False, graph=False, energy=False, energy_out=None):
     """nsteps of KDK leapfrog in place; returns the (nsteps+1, 2) FP64 energy
-    tensor when energy=True (``energy_out`` if given), else None."""
+    tensor when energy=True (``energy_out`` if given), else None.  In the FP32
+    modes energy=True takes the forces from the split sweep, whose rounding may
+    differ from that of a run without it (see nbody.h); ``energy`` after a run
+    without it does not."""
     pm = _rec(pos_mass, "pos_mass")
     v = _rec(vel, "vel", pm.dtype)
     a = _rec(acc_pot, "acc_pot", pm.dtype)

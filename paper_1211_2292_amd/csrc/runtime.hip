@@ -523,7 +523,8 @@ static bool step_fused(const Tune &t, const BatchPlan *plan, int64_t n)
 // in the force moves them by its rounding (up to about 1e-8 relative, with no
 // larger error against 64 bits at most sizes), and they stay as they were to
 // 1e-9.  It costs such a run what the other kernels gain (1987 bodies, 8
-// steps: 275 us against 69).
+// steps: 275 us against 69), and its states differ from those of a run without
+// energies by the forces' rounding (nbody.h says so at nbody_leapfrog_kdk).
 static Tune leapfrog_tune(int prec, int64_t n, bool energy)
 {
     Tune t = lookup_tune(0, prec, n);

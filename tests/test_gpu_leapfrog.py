@@ -182,6 +182,45 @@ def test_fused_small_steps(mode, n, steps):
                 assert mode != "F64" or torch.equal(got, torch.stack(en))
 
 
+@pytest.mark.parametrize("mode", ["F32", "F32_KAHAN", "F32_F64ACC", "F64"])
+@pytest.mark.parametrize("n", [300, 1987, 8192, 10007, 30001])
+def test_runs_with_and_without_energies(mode, n):
+    """What NBODY_ENERGY may change: nothing in FP64 or with a pinned shape;
+    otherwise in FP32 the rounding of the forces, where the unpinned force is
+    not the sweep (10007 bodies: it is, and nothing changes).  Bars for four
+    steps: each force is within 2e-6 (RMS, as for single forces), four of them
+    times dt move velocities of order 1 by under 1e-8, so what remains is a
+    few roundings of the FP32 state, 4 x 2^-24; potentials, under 2e-7 each
+    (a few 2^-24), bound the potential energy, and velocities the kinetic."""
+    torch, nb = gpu()
+    prec = getattr(nb, mode)
+    dtype = torch.float64 if mode == "F64" else torch.float32
+    pm, v = ics.plummer(n, 73)
+    p0, v0 = to_dev(torch, pm, dtype), to_dev(torch, v, dtype)
+
+    def run(energy):
+        p, w, a = p0.clone(), v0.clone(), torch.empty_like(p0)
+        en = nb.leapfrog_kdk(p, w, a, 0.01, 1e-3, 4, prec=prec, energy=energy)
+        return p, w, a, (en[-1] if energy else nb.energy(p, w, a))
+
+    nb.set_tuning(0, prec, *nb.get_tuning(0, prec, n))
+    try:
+        x, y = run(True), run(False)
+    finally:
+        nb.set_tuning(0, prec)
+    torch.cuda.synchronize()
+    assert all(torch.equal(b, c) for b, c in zip(x, y))
+    x, y = run(True), run(False)
+    torch.cuda.synchronize()
+    if mode == "F64" or n == 10007:
+        assert all(torch.equal(b, c) for b, c in zip(x, y))
+        return
+    far = [float((b.double() - c.double()).norm() / c.double().norm()) for b, c in zip(x, y)]
+    assert not torch.equal(x[2], y[2])  # (the two kernels did run)
+    assert far[0] <= 2.0 ** -22 and far[1] <= 2.0 ** -22 and far[2] <= 2 * 2e-6, far
+    assert float(((x[3] - y[3]) / y[3]).abs().max()) <= 4e-7
+
+
 def test_pairwise_records_do_not_fit():
     """Where the pairwise kernels' records (1000 MiB for 2^18 bodies) cannot be
     had, a force, a run and a captured run take the split sweep (128 MiB):
