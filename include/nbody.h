@@ -34,8 +34,9 @@
  *   synchronises the device except nbody_autotune(), nbody_release(), a
  *   tree call for a new (n, leaf) (it uploads the node table),
  *   nbody_janus_adjoint (its mass check), nbody_orb_order when
- *   NBODY_CHECK_INPUTS is set, and the FMM calls (one stream
- *   synchronisation each, to check their list buffers).
+ *   NBODY_CHECK_INPUTS is set, and the FMM calls (each waits until its lists
+ *   are known to fit their buffers; the evaluation that follows is not waited
+ *   for).
  * - Library scratch is one buffer per purpose and device, shared by all
  *   streams.  A call that needs more than any earlier one allocates a larger
  *   buffer (a power of two in size) and does not wait: the one it replaces
@@ -102,7 +103,7 @@ enum {
  *   FP32 first.  The result is a pure function of the input (bit-exact).
  * pos_mass: n records (float4 or double4 by prec).  perm_out: int32[n],
  * perm_out[p] = original index of the body at position p.  Uses library
- * scratch of about 36 bytes per body.  Non-finite coordinates make the order
+ * scratch of about 40 bytes per body.  Non-finite coordinates make the order
  * unspecified; with the environment variable NBODY_CHECK_INPUTS set (to
  * anything but "0") the call first checks every record, synchronises the
  * stream, and refuses non-finite coordinates or masses with NBODY_E_INVAL
@@ -129,13 +130,18 @@ int nbody_permute(const void *src, void *dst, const int32_t *perm, int64_t n,
  * target_begin + target_count) against all n sources.
  * acc_pot_out: target_count records, entry t for target target_begin + t;
  * it must not overlap pos_mass.  Deterministic: the same inputs and tuning
- * give bitwise the same output.
- * Unless a shape is pinned (nbody_set_tuning), all of 22528 to 2^24 bodies as
- * targets in an FP32 mode evaluate every unordered pair once and add the sums
- * across tiles in FP64 in every mode; this takes up to 1 GiB of library
- * scratch (where that cannot be allocated, the split sweep runs instead), and
- * the record of a target then differs from its record in a call for fewer
- * targets within the mode's error bound, not bit for bit.
+ * give bitwise the same output, as long as the scratch below can be had.
+ * Unless a shape is pinned (nbody_set_tuning), two ranges run other kernels
+ * than the split sweep:
+ *   - Up to 8192 bodies in an FP32 mode and 4096 in FP64: one launch without
+ *     scratch, whose sums of at most 32 FP32 terms are added in FP64.
+ *   - All of 22528 to 2^24 bodies as targets in an FP32 mode: every unordered
+ *     pair is evaluated once and the sums are added across tiles in FP64 in
+ *     every mode.  This takes up to 1 GiB of library scratch; where that
+ *     cannot be allocated, the split sweep runs instead.  The record of a
+ *     target then differs from its record in a call for fewer targets (one
+ *     GPU's share of them, for instance) within the mode's error bound, not
+ *     bit for bit.
  */
 int nbody_accel(const void *pos_mass, int64_t n, int32_t prec, double G, double eps,
                 void *acc_pot_out, int64_t target_begin, int64_t target_count, void *stream);
@@ -146,9 +152,10 @@ int nbody_accel(const void *pos_mass, int64_t n, int32_t prec, double G, double 
  * arguments and validation as nbody_accel; it calls no hipMalloc, hipFree or
  * other allocating routine.  When the kernel shape splits the source range
  * (jsplit > 1) the per-split partial records (jsplit * target_count records
- * of 32 bytes; 16 in NBODY_F32) go to a file-scope device array of
- * NBODY_NOALLOC_SCRATCH bytes (64 MiB) that each GPU the library runs on
- * holds until the process ends.
+ * of 32 bytes; 16 in NBODY_F32), or the records of the kernels that evaluate
+ * every pair once, go to a file-scope device array of NBODY_NOALLOC_SCRATCH
+ * bytes (64 MiB) that each GPU the library runs on holds until the process
+ * ends.
  *   - If the partials of nbody_accel's shape fit, the same shape runs and the
  *     result equals nbody_accel's bit for bit.
  *   - If they do not fit and the shape was chosen by the library (default or
@@ -206,6 +213,10 @@ int nbody_accel_vjp(const void *pos_mass, const void *acc_pot_cot, int64_t n, in
  * energies of that run's own trajectory.
  * NBODY_GRAPH: the whole step loop is captured once into a HIP graph keyed by
  * (pointers, sizes, scalars, flags) and replayed on later identical calls.
+ * Each captured graph holds scratch of its own until nbody_release(): what
+ * one force of nbody_accel takes (up to 1 GiB from 22528 bodies on; where that
+ * cannot be allocated, the graph holds the split sweep).  A call without it
+ * decides once, before its first step.
  */
 int nbody_leapfrog_kdk(void *pos_mass, void *vel, void *acc_pot, int64_t n,
                        const int64_t *offsets_host, int32_t nsys, int32_t prec, double G,
@@ -313,11 +324,12 @@ int nbody_trajectory_adjoint(const void *ckpt, int64_t n, int32_t prec, double G
  * definitions.
  * 1 <= leaf <= NBODY_TREE_GROUP.  The first call for a new (n, leaf)
  * uploads the node table and synchronizes the stream; later calls are
- * asynchronous.  The tree tables are library scratch (about 430 bytes per
+ * asynchronous.  The tree tables are library scratch (about 450 bytes per
  * node) shared by all tree calls on a device: overlapping calls race.
  * With group local expansions (NBODY_CELLS_LOCAL) and 8192 groups or more,
  * the groups whose boxes are among the largest 1/16 (by a histogram of
  * diag2) are walked first, since their walks cost several times the mean;
+ * with leaf < 16 so are the largest 1/5 of 1025 to 8191 groups;
  * the environment variable NBODY_TREE_ORDER=0 keeps ORB order.  The results
  * do not depend on the order.
  *
@@ -450,7 +462,7 @@ int nbody_tree_leapfrog(void *pos_mass, void *vel, void *acc_pot, int32_t *order
  *              prec.
  * theta = 0 gives no M2L or M2P entry: the direct sum, at a P2P cost of
  * (n/leaf)^2 leaf pairs.  List buffers are library-owned and grow as needed;
- * each call synchronises its stream once to check them.  The traversal
+ * each call waits for its stream once to check them.  The traversal
  * writes each node's lists in one pass into slots sized for the largest
  * node of its depth (about five times the entries); when that would take
  * more than an eighth of the device's memory (or more than the environment
@@ -513,15 +525,24 @@ int nbody_janus_adjoint(void *state, const void *pos_mass, int64_t n, double G, 
  * JSON file named by the environment variable NBODY_TUNE_CACHE, if set).
  * The candidates are (tpl, jsplit, jtile) with variant 0; every candidate
  * performs the same arithmetic per pair, so tuning changes where partial sums
- * are folded, never the accuracy class of the result.
+ * are folded, never the accuracy class of the result; the untuned shape is one
+ * of them.  For kernel 0 they are shapes of the split sweep with all bodies as
+ * targets: calls that nbody_accel serves with another kernel (see there) keep
+ * that one, and a share of the targets that takes more than 32 splits untuned
+ * keeps those.  FP32 runs with NBODY_ENERGY, the calls for other shares and
+ * the remaining sizes run the recorded shape.
  * nbody_set_tuning pins a shape for later calls: tpl (targets per lane:
  * 1, 2, 4), jsplit (independent source ranges per target, 1..32, reduced in
  * fixed order; kernel 1 takes 1), jtile (sources per partial sum, multiple
  * of 8), variant (FP32 force kernel only, apart from 0: 0 = source records
  * through scalar loads; 1 = staged in LDS, jtile a multiple of 256, identical
  * results to 0, never chosen by nbody_autotune); kernel and prec as above;
- * tpl = jsplit = jtile = -1 clears it.
- * nbody_get_tuning reports the shape the library would use.
+ * tpl = jsplit = jtile = -1 clears it.  A pinned shape of kernel 0 runs the
+ * sweep in every call, whatever the size.
+ * nbody_get_tuning reports the shape in which the library would run the sweep
+ * with all bodies as targets.  At the sizes where nbody_accel runs another
+ * kernel unpinned (see there) it is the shape of the calls that still take the
+ * sweep, and pinning it switches the others to the sweep as well.
  */
 int nbody_autotune(int32_t kernel, int32_t prec, int64_t n, const int64_t *offsets_host,
                    int32_t nsys, void *stream);

@@ -664,7 +664,9 @@ def set_tuning(kernel, prec, tpl=-1, jsplit=-1, jtile=-1, variant=0):
 
 
 def get_tuning(kernel, prec, n):
-    """(tpl, jsplit, jtile, variant) the library would use for size n."""
+    """(tpl, jsplit, jtile, variant) in which the library would run the sweep for
+    size n with all bodies as targets (the unpinned force takes other kernels at
+    some sizes, see nbody.h)."""
     a, b, c, d = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
     _check(lib().nbody_get_tuning(int(kernel), int(prec), int(n), ctypes.byref(a), ctypes.byref(b),
                                   ctypes.byref(c), ctypes.byref(d)))
