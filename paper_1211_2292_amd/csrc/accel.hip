@@ -17,16 +17,20 @@
 //   count.  The library is built with contraction off and every fused
 //   multiply-add is written out, so the same arithmetic is emitted in every
 //   kernel that shares these routines (batched results equal standalone ones
-//   bit for bit).
+//   of the sweep in the same shape bit for bit).
 // * Sources are processed in tiles of `jtile`; the FP32 partial sum of a tile
 //   is folded into the running per-target sum by the precision mode (plain
 //   FP32, Kahan-compensated FP32, or FP64).
 // * The self pair is removed exactly: only the sub-range of sources that
 //   overlaps the wave's own targets runs the masked variant (one compare and
 //   one select per pair); every other source range runs unmasked.
-// * Small problems split the source range over gridDim.y workgroup rows; the
-//   per-split records go to scratch and are reduced in split order by a
-//   second kernel, so the result never depends on scheduling.
+// * Where the targets alone are too few waves to fill the chip, the source
+//   range is split over gridDim.y workgroup rows; the per-split records go to
+//   scratch and are reduced in split order by a second kernel, so the result
+//   never depends on scheduling.
+// * Unless a shape is pinned, small problems run k_accel_slice instead (one
+//   launch, no scratch), and the force on all of many bodies the kernels of
+//   sym.hip.
 #include <mutex>
 
 #include "internal.h"
@@ -599,11 +603,11 @@ __global__ __launch_bounds__(kBlock) void k_split_reduce_f32(const float4 *__res
 // FP64) tile sums in LDS, and fold them in tile order into running sums kept
 // one component per wave.  The sums are those of k_accel_f32 with one split
 // over the same tiles, folded in the same order, so each system's result
-// equals its standalone evaluation bit for bit; but the longest system no
-// longer takes one wave's time for all its sources, which had bound batches
-// whose units all fit the chip at once: 128 systems of 256 to 8192 bodies ran
-// 655 us with one wave per 64 targets, 361 us now (the pairs
-// alone need about 290 at the force kernel's rate).  The workgroup that
+// equals bit for bit its standalone evaluation with this shape pinned; but the
+// longest system no longer takes one wave's time for all its sources, which
+// had bound batches whose units all fit the chip at once: 128 systems of 256
+// to 8192 bodies ran 655 us with one wave per 64 targets, 361 us now (the
+// pairs alone need about 290 at the force kernel's rate).  The workgroup that
 // finishes last returns both counters to zero, which keeps repeated launches
 // and graph replays self-contained.
 template <int TPL, bool SEQ>

@@ -673,27 +673,6 @@ __global__ __launch_bounds__(256) void k_fmm_l2l(FmmDev F, const int *__restrict
     }
 }
 
-// Leaves: one wave per leaf.  The leaf's P = TPL * NTG target slots (its
-// size rounded up to a power of two) form NTG groups of TPL targets; the
-// LG = 64 / NTG lanes of a group hold its targets in registers and share its
-// sources out, one per lane at a time:
-// * P2P, leaves of more than 8 bodies (NTG > 1): through an LDS tile, which each of
-//   the NTG groups reads, and the loop of p2p_tile8.  Against the way of the
-//   smaller leaves, an FMM force of 300001 bodies (theta 0.5 and 0.6) takes 2119
-//   instead of 2268 us with leaves of 16, 2495 instead of 3012 with leaves of
-//   32; with leaves of 8, one group, where the tile's LDS traffic is the same per
-//   body but serves 8 targets, the two are equal (262144 bodies: 1836 and 1842
-//   us), and with leaves of 5 the tile loses 3%.
-// * P2P, smaller leaves: up to 64 entries are read at once (a source leaf is stored as its
-//   first body; every leaf holds `leaf` bodies except the last, which ends
-//   at n); their (entry, body) pairs are numbered e * 2^lb + body and lane v
-//   of a group takes v, v + LG, ... (the entry's first body read from the
-//   lane that loaded it).  The leaf's own entry is swept apart with the self
-//   pair masked.
-// * M2P: lane v takes cells v, v + LG, ... as quadrupole cells.
-// * Each lane's FP32 partial sums are folded by the precision mode over the
-//   group's lanes in lane order (through LDS); each target then adds its
-//   leaf's expansion in FP64 and is stored.
 // P2P of 8 targets in registers against the lane's records of an LDS tile: the
 // loop over `cnt` records, `step` bytes apart, of the pair code of pair_f32 (the
 // same operations, so the same bits), 4 targets at a time.  By hand for two
@@ -728,20 +707,12 @@ __global__ __launch_bounds__(256) void k_fmm_l2l(FmmDev F, const int *__restrict
     NB_P2P_BATCH("32", "64", "72", "80", Q) NB_P2P_BATCH("48", "68", "76", "84", Q)
 
 constexpr int kTile = 512;  // bodies of a P2P tile
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 __device__ __forceinline__ float wave_max(float v)
 {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
     return v;
 }
-
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // cnt even; reads one record beyond the last.
 __device__ __forceinline__ void p2p_tile8(const float4 *tile, int cnt, int step, Targets<float, 8> &T,
@@ -801,6 +772,27 @@ __device__ __forceinline__ void p2p_tile8(const float4 *tile, int cnt, int step,
     }
 }
 
+// Leaves: one wave per leaf.  The leaf's P = TPL * NTG target slots (its
+// size rounded up to a power of two) form NTG groups of TPL targets; the
+// LG = 64 / NTG lanes of a group hold its targets in registers and share its
+// sources out, one per lane at a time:
+// * P2P, leaves of more than 8 bodies (NTG > 1): through an LDS tile, which each of
+//   the NTG groups reads, and the loop of p2p_tile8.  Against the way of the
+//   smaller leaves, an FMM force of 300001 bodies (theta 0.5 and 0.6) takes 2119
+//   instead of 2268 us with leaves of 16, 2495 instead of 3012 with leaves of
+//   32; with leaves of 8, one group, where the tile's LDS traffic is the same per
+//   body but serves 8 targets, the two are equal (262144 bodies: 1836 and 1842
+//   us), and with leaves of 5 the tile loses 3%.
+// * P2P, smaller leaves: up to 64 entries are read at once (a source leaf is stored as its
+//   first body; every leaf holds `leaf` bodies except the last, which ends
+//   at n); their (entry, body) pairs are numbered e * 2^lb + body and lane v
+//   of a group takes v, v + LG, ... (the entry's first body read from the
+//   lane that loaded it).  The leaf's own entry is swept apart with the self
+//   pair masked.
+// * M2P: lane v takes cells v, v + LG, ... as quadrupole cells.
+// * Each lane's FP32 partial sums are folded by the precision mode over the
+//   group's lanes in lane order (through LDS); each target then adds its
+//   leaf's expansion in FP64 and is stored.
 template <int MODE, int TPL, int NTG>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTG > 1 ? 4 : 1))) void k_fmm_leaf(const float4 *__restrict__ src, FmmDev F,
                                                  const int *__restrict__ leaves, int nleaves, float eps2_in,

@@ -12,8 +12,9 @@ namespace nbi {
 
 // Kernel shape of the force sweep.
 //   tpl    targets held per lane (1, 2 or 4): a wave owns 64*tpl targets
-//   jsplit number of independent source ranges per target (1..32); each
-//          range is a separate workgroup row, reduced in fixed order after
+//   jsplit number of independent source ranges per target (pinned and tuned
+//          shapes 1..32, the library's own up to 256); each range is a
+//          separate workgroup row, reduced in fixed order after
 //   jtile  sources per partial sum (multiple of 8); the partials are folded
 //          into the running sum by the precision mode
 //   variant 0: sources through scalar loads (SGPR operands);
@@ -76,6 +77,20 @@ __device__ __forceinline__ double rsq_f64(double q)
     const double e = __builtin_fma(-q, y * y, 1.0);
     return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
 }
+
+// Orders the wave's LDS accesses around this point (the lanes of a wave run
+// together, so a barrier is not needed between them).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Register tuples of the hand-scheduled loops.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 bool tune_valid(const Tune &t);
 
@@ -158,12 +173,13 @@ hipError_t launch_sym(const void *pm, int n, double eps, void *slots, hipStream_
 constexpr size_t kStaticScratchBytes = NBODY_NOALLOC_SCRATCH;
 void *static_split_scratch();
 
-// Batched force over a work list of (system, first target) units sorted
-// longest first.  Waves that share each 64 tpl targets of a system of n bodies:
-// 4, or as many as it has source tiles (a power of two); a unit of 4 waves
-// then holds 256 tpl / batch_split targets.
+// Waves of a batched unit that share each 64 tpl targets of a system of n
+// bodies: 4, or as many as it has source tiles (a power of two); a unit of 4
+// waves then holds 256 tpl / batch_split targets.
 __host__ __device__ inline int batch_split(int64_t n, int jtile) { return n > 3 * (int64_t)jtile ? 4 : (n > jtile ? 2 : 1); }
-// units: int2[nunits] = (system, target offset within the system); offsets: int64 device copy [nsys+1]; counter: one zeroed uint32
+// Batched force over a work list of (system, first target) units sorted
+// longest first.  units: int2[nunits] = (system, target offset within the
+// system); offsets: int64 device copy [nsys+1]; counter: one zeroed uint32
 // pair, left zeroed again by the kernel on exit.
 hipError_t launch_batched(int prec, const void *pm, const int64_t *offsets, const int2 *units,
                           int nunits, double G, const float *eps_sys, double eps, void *out,
@@ -183,17 +199,18 @@ size_t vjp_partial_bytes(int n, const Tune &t);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 
 // ---- elementwise steps (step.hip) ------------------------------------------
-// One pass between two force evaluations:
-//   close: v += h a          (closing kick of the previous step)
-//   energy partials of (v, phi) after the closing kick, if epart != nullptr
-//   open:  v += h a; x += dt v  (opening kick and drift of the next step)
-// The small-problem force of all bodies fused with the step: acc receives the
-// force, then the kick and drift; the positions go to `to` (drifted or, without
-// a drift, copied; null: nowhere).  epart: two sums per workgroup, slice_blocks(n).
+// The small-problem force of all bodies (accel.hip) fused with the step below:
+// acc receives the force, then the kick and drift; the positions go to `to`
+// (drifted or, without a drift, copied; null: nowhere).  epart (FP64 only): two
+// sums per workgroup, slice_blocks(n) of them.
 constexpr int kEnergyRow = 16;  // bodies of a workgroup of it
 int slice_blocks(int n);
 hipError_t launch_slice_step(int prec, const void *pm, int n, double G, double eps, void *acc, void *vel, void *to,
                              double h, double dt, bool close, bool open, double *epart, hipStream_t s);
+// One pass between two force evaluations:
+//   close: v += h a          (closing kick of the previous step)
+//   energy partials of (v, phi) after the closing kick, if epart != nullptr
+//   open:  v += h a; x += dt v  (opening kick and drift of the next step)
 hipError_t launch_step(int prec, void *pm, void *vel, const void *acc, int n, double h, double dt,
                        bool close, bool open, double *epart, int *eblocks, hipStream_t s);
 int step_blocks(int n);
@@ -203,8 +220,8 @@ int step_blocks(int n);
 hipError_t launch_reduce_step(int prec, RecordKind kind, const void *partial, int js, double G, void *pm, void *vel,
                               void *acc, int n, double h, double dt, bool close, bool open,
                               double *epart, int *eblocks, hipStream_t s);
-// Energies of `states` states whose partials follow one another, nblocks each.
-// parts: sums per state, of a step kernel's workgroups or (rows) of kEnergyRow bodies each.
+// Energies of `states` states whose partials follow one another.  parts: sums
+// per state, of a step kernel's workgroups or (rows) of kEnergyRow bodies each.
 hipError_t launch_energy_final(const double *epart, int parts, bool rows, int states, double *out, hipStream_t s);
 hipError_t launch_permute(const void *src, void *dst, const int32_t *perm, int n, int rec_bytes,
                           bool inverse, hipStream_t s);

@@ -667,13 +667,6 @@ __global__ __launch_bounds__(kPassBlock) void k_orb_partition(const int3 *__rest
 // holds it (phase A leaves them in the segment's order) and stay in their
 // slots; the recursion permutes slot numbers only.
 
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Finishes the recursion of a node of at most 64 bodies (positions
 // [lo, lo + m) of pos) with one wave, one position per lane, every node of a
 // level split at once.  keys: per-wave LDS of 3 x 64 total-order keys.  The
@@ -698,9 +691,7 @@ __device__ void orb_wave(uint16_t *pos, const uint32_t (*skey)[kSmall], const in
     for (;;) {
         const bool split = lane < m && sm > leaf;
         if (!__any(split)) break;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_sync();
         int to = at;
         int k = sm;
         if (split) {
@@ -726,9 +717,7 @@ __device__ void orb_wave(uint16_t *pos, const uint32_t (*skey)[kSmall], const in
             const int L = (sm + leaf - 1) / leaf;
             k = min(sm, leaf * ((L + 1) / 2));
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_sync();
         if (lane < m) {
             keys[0][to] = kx;
             keys[1][to] = ky;
@@ -745,9 +734,7 @@ __device__ void orb_wave(uint16_t *pos, const uint32_t (*skey)[kSmall], const in
             }
         }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     // leaves: ascending original index
     int r = 0;
     if (lane < m)

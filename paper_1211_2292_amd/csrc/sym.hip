@@ -208,10 +208,6 @@ __device__ __forceinline__ void sym_chunk(const float4 *jp, int j0, int n, int s
     "s_waitcnt lgkmcnt(0)\n"                                                                                      \
     "s_nop 1\n"
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 template <int TPL>
 __device__ __forceinline__ void sym_chunk_asm(const float4 *jp, SymTargets<TPL> &T, float eps2, float (&s)[4])
 {

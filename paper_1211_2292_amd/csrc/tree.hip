@@ -444,11 +444,6 @@ __device__ __forceinline__ void sweep_quad(const float4 *qb, int cnt, const Targ
 // 2% at leaves of 4 and lose 1% at 8 and 15% at 32, and keep the scalar loads.
 constexpr int kNear = 2 * kGroup;
 constexpr int kNearScalarLeaf = 16;
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 __device__ __forceinline__ void sweep_near(const float4 *__restrict__ src, const int2 *nbuf, int r, int r1, float4 *nb,
                                            int lane, const Targets<float, 1> &T, float eps2, Sums<float, 1> &S)
 {
