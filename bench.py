@@ -45,8 +45,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_FP32_TFLOPS = 157.3   # MI355X FP32 vector peak (AMD), packed FP32 counted
 FLOP_PER_PAIR = 20
-VARIANTS = {0: "scalar-load sources", 1: "LDS sources"}
-VARIANT_KERNELS = {0: "k_accel_f32", 1: "k_accel_lds_f32"}
+PAIRWISE = (22528, 1 << 24)  # all of so many bodies in an FP32 mode: every unordered pair once (nbody_accel in nbody.h)
 FLOP_PER_QUAD_CELL = 54   # one quadrupole cell against one target, counted like the pair's 20
 FLOP_PER_M2L = 313        # one cell folded into a group's third-order local expansion (m2l_f32)
 
@@ -215,9 +214,9 @@ def main():
     pairs = float(n) * float(n)
     value = pairs / (ms_per_step * 1e-3) / 1e9
     achieved = FLOP_PER_PAIR * pairs / (kern_avg * 1e-3) / 1e12
-    tune = nb.get_tuning(0, prec, n)
+    kernel = force_kernel(nb, prec, n)
     log(f"[bench] {ms_per_step:.2f} ms/step, force kernel {kern_avg:.2f} ms, {value:.1f} Gint/s, "
-        f"{achieved:.2f} TFLOP/s ({100 * achieved / PEAK_FP32_TFLOPS:.1f}% of FP32 peak), tune {tune}")
+        f"{achieved:.2f} TFLOP/s ({100 * achieved / PEAK_FP32_TFLOPS:.1f}% of FP32 peak), {kernel}")
 
     result = {
         "metric": "G-interactions/s and % FP32 peak at N=1M; fwd+adjoint step time vs plain fwd",
@@ -235,8 +234,7 @@ def main():
         "config": {"workload": "colliding Plummer pair, N=1048576, mass ratio 1:3, eps=0.005, "
                                "dt=5e-4, leapfrog KDK, NBODY_F32_F64ACC",
                    "n": n, "eps": eps, "dt": dt, "precision": "F32_F64ACC",
-                   "kernel_shape": {"tpl": tune[0], "jsplit": tune[1], "jtile": tune[2],
-                                    "variant": VARIANTS.get(tune[3], str(tune[3]))}},
+                   "kernel": kernel},
         "pct_fp32_peak": round(100 * achieved / PEAK_FP32_TFLOPS, 2),
         "wall_s_timed": round(wall, 3),
         "orb": {"leaf": 256, "order_ms": round(orb_ms, 3), "first_call_ms": round(orb_first_ms, 3),
@@ -246,9 +244,11 @@ def main():
                         "steps": args.steps + args.warmup + 1},
         "roofline": {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4),
-                     "traffic": measured_traffic(tune, n),
-                     "kernel": VARIANT_KERNELS.get(tune[3], "k_accel_f32") + f"<{tune[0]}, F64ACC>",
+                     "traffic": measured_traffic(kernel, n),
+                     "kernel": kernel,
                      "flop_per_pair": FLOP_PER_PAIR,
+                     "flop_counted": "per ordered pair, by the usual count (the pairwise kernel evaluates each "
+                                     "unordered pair once)",
                      "avg_launch_ms": round(kern_avg, 4),
                      "launch_ms_std": round(float(np.std(kern_ms)), 4),
                      "launch_ms_min_max": [round(float(np.min(kern_ms)), 4), round(float(np.max(kern_ms)), 4)]},
@@ -266,28 +266,36 @@ def main():
     print(json.dumps(result), flush=True)
 
 
+def force_kernel(nb, prec, n):
+    """The kernel of an unpinned FP32 force on all n bodies."""
+    if PAIRWISE[0] <= n <= PAIRWISE[1]:
+        return "k_sym<4>" if n >= 73728 else "k_sym<2>"
+    tpl, jsplit, jtile, _ = nb.get_tuning(0, prec, n)
+    return f"k_accel_f32<{tpl}, F64ACC>, {jsplit} splits, tiles of {jtile}"
+
+
 def force_source_sha1():
     """SHA-1 of the sources the force kernel is compiled from."""
     import hashlib
     h = hashlib.sha1()
-    for f in ("accel.hip", "pair.h", "internal.h"):
+    for f in ("sym.hip", "accel.hip", "pair.h", "internal.h"):
         with open(os.path.join(ROOT, "paper_1211_2292_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
 
 
-def measured_traffic(tune, n):
-    """HBM bytes per force launch from the committed rocprofv3 counter
-    summary, if it was taken on the kernel shape in use now and on the same
-    kernel sources; else None."""
-    path = os.path.join(ROOT, "profiles", "k_accel_f32_collide1m_pmc.md")
+def measured_traffic(kernel, n):
+    """Bytes that the force kernels of one evaluation move past L2, from the
+    committed rocprofv3 counter summary, if it was taken on the kernel in use
+    now and on the same kernel sources; else None."""
+    path = os.path.join(ROOT, "profiles", "k_sym_collide1m_pmc.md")
     try:
         sha = force_source_sha1()
         for line in open(path):
             if line.startswith("traffic_record:"):
                 rec = json.loads(line.split(":", 1)[1])
-                if rec["shape"] == list(tune) and rec["n"] == n and rec.get("src_sha1") == sha:
-                    return rec["bytes_per_launch"]
+                if rec["kernel"] == kernel and rec["n"] == n and rec.get("src_sha1") == sha:
+                    return rec["bytes_per_force"]
     except (OSError, ValueError, KeyError):
         pass
     return None
