@@ -271,8 +271,10 @@ constexpr int64_t kSliceMaxF32 = 8192, kSliceMaxF64 = 4096;
 // (sym.hip).  Its tiles have to fill 256 CUs evenly: with 46 blocks of 512
 // bodies (23457) it takes 148 us against 160 for the split sweep, with 51 169 /
 // 186, but with 40 122 / 116.  40001 bodies 356 / 420 us, 65536 885 / 1085, 2^18
-// 13.3 / 16.7 ms, 2^20 207.5 / 256.6 ms.  Above kSymMax its sums no longer fit
-// kSymScratch.
+// 13.3 / 16.7 ms, 2^20 213 / 263 ms, 2^21 874 / 1049 ms, 2^22 3.36 / 4.18 s, 2^23
+// 13.3 / 16.9 s, 2^24 53.4 / 71.2 s, although the records of 2^24 bodies leave
+// room for one tile per block and launch (8193 launches).  Above kSymMax not
+// even two records per body fit kSymScratch.
 constexpr int64_t kSymMin = 44 * 512, kSymMax = int64_t(1) << 24;
 
 // Sources per split that the force + VJP sweep keeps: a few thousand bodies

@@ -440,3 +440,22 @@ def test_pairwise_kernel_leapfrog_and_graph(n):
         junk = nb.accel(p0, eps, prec=prec).sum()
         assert torch.equal(pg, pe) and torch.equal(vg, ve) and torch.equal(ag, ae), rep
         del junk
+
+
+@pytest.mark.parametrize("mode", MODES32)
+@pytest.mark.parametrize("n,tb,tc", [(22529, 0, 22529), (23457, 0, 23457), (73729, 0, 73729), (30001, 29501, 500),
+                                     (100001, 40000, 3000), (4097, 0, 4097)])
+def test_fp32_errors_are_a_few_roundings(orc, mode, n, tb, tc):
+    """The pairwise kernels, shares of the targets and the small-problem kernel
+    at a bar near what FP32 allows, unequal masses: sums of a few hundred FP32
+    terms whose own errors are a few 2^-24 and of either sign, so 8 x 2^-24 of
+    the result (RMS) in every mode."""
+    torch, nb = gpu()
+    pm, _ = ics.plummer(n, 5300 + n % 991)
+    pm[:, 3] *= np.linspace(0.5, 1.5, n)
+    src = widen32(pm)
+    out = _run(nb, torch, src, 0.01, mode, torch.float32, target_begin=tb, target_count=tc)
+    k = ics.sample_targets(tc, min(tc, 400), n)
+    acc, pot = orc.accel(src, 0.01, targets=tb + k)
+    bar = 8 * 2.0 ** -24
+    assert rms_rel(out[k, :3], acc) <= bar and rms_rel(out[k, 3], pot) <= bar
