@@ -55,14 +55,21 @@ __device__ __forceinline__ float lane_copy(float x)
 // without, 13.2 with; in the force kernel at 2^20 bodies 301 against 256 ms.
 // Kernels bound by the latency of their loads (the tree walk's quadrupole
 // sweep) lose a few percent by it and use the plain instruction.
-__device__ __forceinline__ float rsq_prio(float q)
+template <int N>
+__device__ __forceinline__ void rsq_prio(float (&q)[N])
 {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(1);
-    const float r = __builtin_amdgcn_rsqf(q);
+#pragma unroll
+    for (int k = 0; k < N; ++k) q[k] = __builtin_amdgcn_rsqf(q[k]);
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
-    return r;
+}
+__device__ __forceinline__ float rsq_prio(float q)
+{
+    float one[1] = {q};
+    rsq_prio(one);
+    return one[0];
 }
 
 // 1/sqrt(q) in FP64 from the hardware estimate (relative error 2^-24) and one
