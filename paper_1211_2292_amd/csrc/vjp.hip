@@ -30,8 +30,14 @@ namespace nbi {
 namespace {
 
 // Sources per unrolled step.  Measured with the reciprocal square root at
-// raised priority: 1, 2, 4, 8 take 106, 99, 96, 90 us for 10007 bodies.
-constexpr int kVjpUnroll = 8;
+// raised priority: 1, 2, 4, 8 take 106, 99, 96, 90 us for 10007 bodies.  FP64 with
+// two targets per lane (a pinned shape; its registers leave no room for more):
+// 2, 4, 8 take 294, 253, 334 us there.
+template <typename T, int TPL>
+constexpr int vjp_unroll()
+{
+    return sizeof(T) == 8 && TPL == 2 ? 4 : 8;
+}
 
 // eps^2 is kept in a vector register in FP32 (see lane_copy); FP64 keeps the
 // compiler's choice.
@@ -116,16 +122,17 @@ __device__ __forceinline__ void vsweep(const V *__restrict__ pm, const V *__rest
                                        int j1, const VTgt<T, TPL> &K, T eps2,
                                        VAcc<T, TPL> &S)
 {
+    constexpr int U = vjp_unroll<T, TPL>();
     int j = j0;
-    for (; j + kVjpUnroll <= j1; j += kVjpUnroll) {
-        V p[kVjpUnroll], c[kVjpUnroll];
+    for (; j + U <= j1; j += U) {
+        V p[U], c[U];
 #pragma unroll
-        for (int u = 0; u < kVjpUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             p[u] = pm[j + u];
             c[u] = cot[j + u];
         }
 #pragma unroll
-        for (int u = 0; u < kVjpUnroll; ++u) vpair<T, V, TPL, PHI, MASK>(p[u], c[u], j + u, K, eps2, S);
+        for (int u = 0; u < U; ++u) vpair<T, V, TPL, PHI, MASK>(p[u], c[u], j + u, K, eps2, S);
     }
     for (; j < j1; ++j) vpair<T, V, TPL, PHI, MASK>(pm[j], cot[j], j, K, eps2, S);
 }
@@ -316,16 +323,17 @@ template <typename T, typename V, int TPL, bool MASK>
 __device__ __forceinline__ void ssweep(const V *__restrict__ pm, const V *__restrict__ cot, int j0,
                                        int j1, const VTgt<T, TPL> &K, T eps2, SAcc<T, TPL> &S)
 {
+    constexpr int U = vjp_unroll<T, TPL>();
     int j = j0;
-    for (; j + kVjpUnroll <= j1; j += kVjpUnroll) {
-        V p[kVjpUnroll], c[kVjpUnroll];
+    for (; j + U <= j1; j += U) {
+        V p[U], c[U];
 #pragma unroll
-        for (int u = 0; u < kVjpUnroll; ++u) {
+        for (int u = 0; u < U; ++u) {
             p[u] = pm[j + u];
             c[u] = cot[j + u];
         }
 #pragma unroll
-        for (int u = 0; u < kVjpUnroll; ++u) spair<T, V, TPL, MASK>(p[u], c[u], j + u, K, eps2, S);
+        for (int u = 0; u < U; ++u) spair<T, V, TPL, MASK>(p[u], c[u], j + u, K, eps2, S);
     }
     for (; j < j1; ++j) spair<T, V, TPL, MASK>(pm[j], cot[j], j, K, eps2, S);
 }
