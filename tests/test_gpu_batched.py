@@ -198,3 +198,39 @@ def test_batched_tile_sharing_edges(mode, tpl, jtile):
     finally:
         nb.set_tuning(0, prec)
         nb.set_tuning(1, prec)
+
+
+@pytest.mark.parametrize("nsys", [1, 2047, 2048, 2049, 5003])
+def test_batched_units_and_workgroups(nsys):
+    """Around as many units as workgroups (2048 on 256 CUs, where a unit is one
+    small system here): each workgroup starts with a unit of its own and takes
+    more only if there are more.  Every record is written, call after call, in
+    eager calls and in replays of a captured one, and sampled systems equal
+    their standalone evaluation in the same shape bit for bit."""
+    torch, nb = gpu()
+    g = ics.rng(2400 + nsys)
+    sizes = g.integers(1, 71, nsys)
+    pm, _, off = _batch([int(s) for s in sizes], 94)
+    p = to_dev(torch, pm, torch.float32)
+    first = nb.batched_accel(p, off, 0.01)
+    out = torch.full_like(p, float("nan"))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        nb.batched_accel(p, off, 0.01, out=out)
+    for rep in range(4):
+        out.fill_(float("nan"))
+        if rep % 2:
+            graph.replay()
+        else:
+            nb.batched_accel(p, off, 0.01, out=out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, first), rep
+    nb.set_tuning(0, nb.F32_KAHAN, 1, 1, 512)
+    try:
+        for s in set([0, nsys - 1]) | set(int(k) for k in g.integers(0, nsys, 20)):
+            ref = nb.accel(p[off[s]:off[s + 1]].contiguous(), 0.01)
+            torch.cuda.synchronize()
+            assert torch.equal(first[off[s]:off[s + 1]], ref), s
+    finally:
+        nb.set_tuning(0, nb.F32_KAHAN)
