@@ -33,9 +33,9 @@
 // at the rates measured in isolation (1.75 instructions per clock and CU, 2.1
 // clocks per v_rsq_f32, 1.1 per DPP move) take 56 clocks for 512 interactions
 // of a wave.  By the counters it issues 1.45 instructions per clock and CU at
-// 2.25 GHz.  The force on 2^20 bodies takes 207 to 219 ms, which differs by the
-// GPU, 5.0 to 5.3e12 interactions per second; the one-sided sweep with 8 source
-// splits takes 257 to 263 on the same ones.  The reciprocal square roots
+// 2.25 GHz.  The force on 2^20 bodies takes 207 to 235 ms, which differs by the
+// GPU, 4.7 to 5.3e12 interactions per second; where it takes 213 the one-sided
+// sweep with 8 source splits takes 263.  The reciprocal square roots
 // and the DPP moves, which issue alone, stand together at raised wave priority
 // (see rsq_prio).  4 targets per lane and 4 waves per SIMD (128 VGPRs, 40 KB of
 // LDS) measured best for many tiles, 2 targets and 6 waves for few (kSymWide).
