@@ -892,12 +892,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTG > 1 ? 4 
                 }
 #pragma unroll
                 for (int r = 0; r < UNR; ++r)
-                    if (ok[r]) pair_f32<TPL, false>(sv[r], sj[r], T, eps2, S);
+                    if (ok[r]) pair_f32<TPL, false, 1>(sv[r], sj[r], T, eps2, S);
             }
         }
     }
     if (self) {  // the leaf's own bodies, without the self pair
-        for (int q = v; q < na.y - na.x; q += LG) pair_f32<TPL, true>(src[na.x + q], na.x + q, T, eps2, S);
+        for (int q = v; q < na.y - na.x; q += LG) pair_f32<TPL, true, 1>(src[na.x + q], na.x + q, T, eps2, S);
     }
     // M2P
     const int cc = F.cnt[kM2P * nn + A];
